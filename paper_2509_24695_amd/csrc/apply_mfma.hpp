@@ -389,19 +389,20 @@ constexpr int kApplyStateLdsBytes = ApplyOperands<64, true>::kSharedBytes;
 template <bool HILO, int WAVES, int DEPTH, int ROPE, bool S_LDS = false, bool DEN_VALU = false>
 __global__ __launch_bounds__(64 * WAVES, 1) void apply_mfma_d64(
     const uint16_t *__restrict__ Q, uint16_t *__restrict__ O, RopeArg rope, TokStrides st, int H,
-    int /* d: always 64; keeps the argument list of the d = 112/128 kernel */, int t0, int t1, int C, const float *__restrict__ S, const float *__restrict__ z, float eps)
+    int /* d: always 64; keeps the argument list of the d = 112/128 kernel */, int t0, int t1, int C, const float *__restrict__ S, const float *__restrict__ z, float eps, int order)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = blockIdx.x, bh = blockIdx.y;
+    const WgRole role(C, order);
+    const int c = role.c, bh = role.bh;
     const int b = bh / H, h = bh % H;
     const uint16_t *Qh = Q + b * st.b + h * st.h;
     uint16_t *Oh = O + b * st.b + h * st.h;
     const int n_tiles = (t1 - t0 + kApplyTile - 1) / kApplyTile;
 
     ApplyStream<DEPTH, ROPE> stream(Qh, Oh, rope, lds + apply_lds_bytes<WAVES, ROPE>(), st.n, t1, lane,
-                                    TileWalk(t0, WAVES * c + wave, WAVES * C, n_tiles, bh));
+                                    TileWalk(t0, WAVES * c + wave, WAVES * C, n_tiles, role.phase(b, order)));
     Rope3dFill tabs;
     if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
     apply_prefetch<0, DEPTH>(stream);   // in flight while S is fetched

@@ -85,23 +85,14 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00020000);
 }
 
-// Tokens are read once and outputs written once, so with SV_STREAM_NT both are
-// marked non-temporal.
-#ifndef SV_STREAM_NT
-#define SV_STREAM_NT 1
-#endif
-#ifndef SV_STORE_NT
-#define SV_STORE_NT SV_STREAM_NT
-#endif
-__device__ __forceinline__ u32x4 load_stream16(rsrc_t r, uint32_t off) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, SV_STREAM_NT ? 2 : 0);
+// Tokens are read once and outputs written once, so both are marked non-temporal (NT) - except where the cache
+// lines of a row are shared with the neighbouring heads of a [B][N][H][d] tensor (see shares_lines in
+// sv_linattn.hip): there the neighbours' accesses have to meet in the L2.
+template <bool NT = true> __device__ __forceinline__ u32x4 load_stream16(rsrc_t r, uint32_t off) {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, NT ? 2 : 0);
 }
-// Token bytes that one wave reads (STREAM) or that a second wave reads again soon after.
-template <bool STREAM> __device__ __forceinline__ u32x4 load_tokens16(rsrc_t r, uint32_t off) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, STREAM && SV_STREAM_NT ? 2 : 0);
-}
-__device__ __forceinline__ void store_stream16(rsrc_t r, uint32_t off, u32x4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, SV_STORE_NT ? 2 : 0);
+template <bool NT = true> __device__ __forceinline__ void store_stream16(rsrc_t r, uint32_t off, u32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, NT ? 2 : 0);
 }
 // Cached 16-byte load (rotation table: shared by all heads, worth keeping in L2).
 __device__ __forceinline__ f32x4 load_cached16(rsrc_t r, uint32_t off) {
@@ -118,6 +109,19 @@ template <> struct Elem<float> {
 template <> struct Elem<uint16_t> {   // bf16 bit patterns
     static __device__ __forceinline__ float load(const uint16_t *p) { return bf16_bits_to_f32(*p); }
     static __device__ __forceinline__ void store(uint16_t *p, float x) { *p = f32_to_bf16_bits(x); }
+};
+
+// How a grid's workgroups are dealt to (chunk, head) and the heads' walks staggered (kernel argument `order`):
+constexpr int kOrderChunkMajor = 1;   // chunk_major_role instead of (blockIdx.x, blockIdx.y)
+constexpr int kOrderLockstep = 2;     // all heads of a batch walk in phase: they read pieces of the same cache lines
+constexpr int kDies = 8;              // MI355X: accelerator dies (XCDs), one L2 each; workgroup ids go round them
+struct WgRole {
+    int c, bh;
+    __device__ __forceinline__ WgRole(int C, int order) : c(blockIdx.x), bh(blockIdx.y) {
+        if (order & kOrderChunkMajor) chunk_major_role((int)(blockIdx.y * gridDim.x + blockIdx.x), C, (int)gridDim.y, kDies, c, bh);
+    }
+    // phase key of the walk (see TileWalk)
+    __device__ __forceinline__ int phase(int b, int order) const { return order & kOrderLockstep ? 5 * b : bh; }
 };
 
 // Tiles of a token range are dealt to chunks as evenly as integers allow:

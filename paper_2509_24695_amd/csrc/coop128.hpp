@@ -36,7 +36,7 @@ constexpr int kCoopTile = 32 * kCoopRow;         // one 32-token tile in LDS
 
 // One wave's share of the workgroup's K/V stream: rows 8*wave .. +8 of every tile
 // (16 lanes of 16 bytes per row, 4 rows per load instruction), DEPTH tiles in flight.
-template <int DEPTH, int ROPE>
+template <int DEPTH, int ROPE, bool NT>
 struct CoopStateStream {
     static constexpr int NLD = 2;
     rsrc_t rK, rV;
@@ -60,15 +60,15 @@ struct CoopStateStream {
         const uint32_t base = valid ? walk.offset<32>(i, row_bytes) : kOutOfRange;
 #pragma unroll
         for (int j = 0; j < NLD; ++j) {
-            k[s][j] = load_stream16(rK, base + lane_off + (uint32_t)j * 4u * row_bytes);
-            v[s][j] = load_stream16(rV, base + lane_off + (uint32_t)j * 4u * row_bytes);
+            k[s][j] = load_stream16<NT>(rK, base + lane_off + (uint32_t)j * 4u * row_bytes);
+            v[s][j] = load_stream16<NT>(rV, base + lane_off + (uint32_t)j * 4u * row_bytes);
         }
         rot.request(s, i < walk.count, walk.token<32>(i));
     }
 };
 
-template <int DEPTH, int ROPE>
-__device__ __forceinline__ void coop_state_prefetch(CoopStateStream<DEPTH, ROPE> &st)
+template <int DEPTH, int ROPE, bool NT>
+__device__ __forceinline__ void coop_state_prefetch(CoopStateStream<DEPTH, ROPE, NT> &st)
 {
 #pragma unroll
     for (int s = 0; s < DEPTH; ++s) {
@@ -90,8 +90,8 @@ template <int ROPE> __host__ __device__ constexpr int coop_state_lds_bytes() { r
 // i+1 (ReLU, rotation) into the other buffer; the barrier at the end of the step
 // says both that tile i+1 is complete and that everybody is done reading tile i,
 // whose buffer the next step overwrites.
-template <int DEPTH, int ROPE>
-__device__ __forceinline__ void state_accumulate_coop(CoopStateStream<DEPTH, ROPE> &st, unsigned char *lds, int wave,
+template <int DEPTH, int ROPE, bool NT>
+__device__ __forceinline__ void state_accumulate_coop(CoopStateStream<DEPTH, ROPE, NT> &st, unsigned char *lds, int wave,
                                                       int lane, int kb, int vb, StateAcc &acc)
 {
     static_assert(DEPTH % 2 == 0, "stage parity selects the LDS buffer");
@@ -166,7 +166,7 @@ __device__ __forceinline__ void state_accumulate_coop(CoopStateStream<DEPTH, ROP
 //   WAVES = 4, NB = 1   one tile, 8 rows per wave, few enough registers for two waves per SIMD (in use)
 //   WAVES = 4, NB = 2   a pair of tiles per step, 16 rows per wave
 //   WAVES = 2, NB = 2   one tile, 16 rows per wave
-template <int DEPTH, int ROPE, int WAVES, int NB>
+template <int DEPTH, int ROPE, int WAVES, int NB, bool NT>
 struct CoopApplyStream {
     static constexpr int STEP = 8 * WAVES * NB;   // tokens per workgroup step
     static constexpr int ROWS = STEP / WAVES;     // rows per wave
@@ -191,13 +191,13 @@ struct CoopApplyStream {
     {
         const uint32_t base = valid ? walk.offset<STEP>(i, row_bytes) : kOutOfRange;
 #pragma unroll
-        for (int j = 0; j < NLD; ++j) q[s][j] = load_stream16(rQ, base + lane_off + (uint32_t)j * 4u * row_bytes);
+        for (int j = 0; j < NLD; ++j) q[s][j] = load_stream16<NT>(rQ, base + lane_off + (uint32_t)j * 4u * row_bytes);
         rot.request(s, i < walk.count, walk.token<STEP>(i));
     }
 };
 
-template <int FROM, int TO, int DEPTH, int ROPE, int WAVES, int NB>
-__device__ __forceinline__ void coop_apply_prefetch(CoopApplyStream<DEPTH, ROPE, WAVES, NB> &st)
+template <int FROM, int TO, int DEPTH, int ROPE, int WAVES, int NB, bool NT>
+__device__ __forceinline__ void coop_apply_prefetch(CoopApplyStream<DEPTH, ROPE, WAVES, NB, NT> &st)
 {
 #pragma unroll
     for (int s = FROM; s < TO; ++s) {
@@ -219,8 +219,8 @@ template <int WAVES, int NB> __host__ __device__ constexpr int coop_apply_lds_by
 // the vector ALU (a lane holds eight features of the row and the matching eight of z, `zr`; 16
 // lanes share a row) and leaves it in LDS beside the tile.  The products are exact in fp32, the
 // unrotated phi(Q) is at hand there even with ROPE, and the matrix core is left with the numerator.
-template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB>
-__device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WAVES, NB> &st, unsigned char *lds,
+template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB, bool NT>
+__device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WAVES, NB, NT> &st, unsigned char *lds,
                                                  int wave, int lane, const ApplyOperands<128, HILO, NB, false> &A,
                                                  const float (&zr)[8], float eps)
 {
@@ -312,7 +312,7 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
             }
 #pragma unroll
             for (int j = 0; j < NLD; ++j)
-                store_stream16(st.rO, out_off + st.lane_off + (uint32_t)j * 4u * st.row_bytes, o[j]);
+                store_stream16<NT>(st.rO, out_off + st.lane_off + (uint32_t)j * 4u * st.row_bytes, o[j]);
         }
     };
     // first round apart: the loop is entered in its own steady state of outstanding loads and stores
@@ -332,16 +332,17 @@ __host__ __device__ constexpr int state_d128_lds_bytes() {
 // State reduction for d = 112 or 128.  grid = (C, B*H), block = 256; workgroup c
 // owns tiles c + C*i of the T = ceil((t1-t0)/32) tiles.  FINALIZE and ROPE as in
 // state_mfma_d64; partial states and S are d x d with row length d.
-template <int DEPTH, bool FINALIZE, int ROPE>
+template <int DEPTH, bool FINALIZE, int ROPE, bool NT>
 __global__ __launch_bounds__(256, 1) void state_mfma_d128(
     const uint16_t *__restrict__ K, const uint16_t *__restrict__ V, RopeArg rope, TokStrides st,
     int H, int d, int t0, int t1, int C, const float *S_in, const float *z_in, float *S_out, float *z_out,
-    void *__restrict__ ws, unsigned long long epoch, uint32_t spin_limit)
+    void *__restrict__ ws, unsigned long long epoch, uint32_t spin_limit, int order)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = blockIdx.x, bh = blockIdx.y, BH = gridDim.y;
+    const WgRole role(C, order);
+    const int c = role.c, bh = role.bh, BH = gridDim.y;
     const int b = bh / H, h = bh % H;
     const int elems = d * d + d;
     const uint16_t *Kh = K + b * st.b + h * st.h;
@@ -352,8 +353,8 @@ __global__ __launch_bounds__(256, 1) void state_mfma_d128(
 
     StateAcc acc;
     acc.clear();
-    CoopStateStream<DEPTH, ROPE> stream(Kh, Vh, rope, lds + state_d128_lds_bytes<ROPE>(), st.n, t1, d, wave, lane,
-                                        TileWalk(t0, c, C, n_tiles, bh));
+    CoopStateStream<DEPTH, ROPE, NT> stream(Kh, Vh, rope, lds + state_d128_lds_bytes<ROPE>(), st.n, t1, d, wave, lane,
+                                        TileWalk(t0, c, C, n_tiles, role.phase(b, order)));
     Rope3dFill tabs;
     if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
     coop_state_prefetch(stream);
@@ -383,23 +384,24 @@ __global__ __launch_bounds__(256, 1) void state_mfma_d128(
 // With NB = 1 a wave keeps one 128 x 32 panel of S and fits in half a SIMD's registers: two
 // workgroups (eight waves) share a compute unit, and while one wave waits at a barrier or works on
 // the vector ALU (ReLU, rotation, scaling) the other wave of its SIMD feeds the matrix core.
-template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB>
+template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB, bool NT>
 __global__ __launch_bounds__(64 * WAVES, NB == 1 ? 2 : 1) void apply_mfma_d128(
     const uint16_t *__restrict__ Q, uint16_t *__restrict__ O, RopeArg rope, TokStrides st, int H,
-    int d, int t0, int t1, int C, const float *__restrict__ S, const float *__restrict__ z, float eps)
+    int d, int t0, int t1, int C, const float *__restrict__ S, const float *__restrict__ z, float eps, int order)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = blockIdx.x, bh = blockIdx.y;
+    const WgRole role(C, order);
+    const int c = role.c, bh = role.bh;
     const int b = bh / H, h = bh % H;
     const uint16_t *Qh = Q + b * st.b + h * st.h;
     uint16_t *Oh = O + b * st.b + h * st.h;
     constexpr int STEP = 8 * WAVES * NB;
     const int n_steps = (t1 - t0 + STEP - 1) / STEP;
 
-    CoopApplyStream<DEPTH, ROPE, WAVES, NB> stream(Qh, Oh, rope, lds + coop_apply_lds_bytes<WAVES, NB>(), st.n, t1,
-                                                   d, wave, lane, TileWalk(t0, c, C, n_steps, bh));
+    CoopApplyStream<DEPTH, ROPE, WAVES, NB, NT> stream(Qh, Oh, rope, lds + coop_apply_lds_bytes<WAVES, NB>(), st.n, t1,
+                                                   d, wave, lane, TileWalk(t0, c, C, n_steps, role.phase(b, order)));
     Rope3dFill tabs;
     if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
     coop_apply_prefetch<0, DEPTH>(stream);   // in flight while S is fetched

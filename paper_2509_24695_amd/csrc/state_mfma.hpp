@@ -532,7 +532,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void state_mfma_d64(
     const uint16_t *__restrict__ K, const uint16_t *__restrict__ V, RopeArg rope, TokStrides st,
     int H, int /* d: always 64; keeps the argument list of the d = 112/128 kernel */, int t0, int t1,
     int C, const float *S_in, const float *z_in, float *S_out, float *z_out, void *__restrict__ ws,
-    unsigned long long epoch, uint32_t spin_limit)
+    unsigned long long epoch, uint32_t spin_limit, int order)
 {
     constexpr int THREADS = 64 * WAVES;
     constexpr int kTileBytes = TILE * kRowBytes;
@@ -540,7 +540,8 @@ __global__ __launch_bounds__(64 * WAVES, 1) void state_mfma_d64(
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = blockIdx.x, bh = blockIdx.y, BH = gridDim.y;
+    const WgRole role(C, order);
+    const int c = role.c, bh = role.bh, BH = gridDim.y;
     const int b = bh / H, h = bh % H;
     const uint16_t *Kh = K + b * st.b + h * st.h;
     const uint16_t *Vh = V + b * st.b + h * st.h;
@@ -552,7 +553,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void state_mfma_d64(
     acc.clear();
     const unsigned char *lds_tab = lds + state_lds_bytes<TILE, WAVES>();
     StateStream<TILE, DEPTH, ROPE> stream(Kh, Vh, rope, lds_tab, st.n, t1, lane,
-                                          TileWalk(t0, WAVES * c + wave, WAVES * C, n_tiles, bh));
+                                          TileWalk(t0, WAVES * c + wave, WAVES * C, n_tiles, role.phase(b, order)));
     unsigned char *tileK = lds + wave * 2 * kTileBytes;
     Rope3dFill tabs;
     if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel

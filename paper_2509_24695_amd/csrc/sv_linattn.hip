@@ -43,7 +43,7 @@ constexpr bool kApplyHiLo = true;
 // 75 600 tokens; the one-launch block step 0.5-1 us per block slower with the vector ALU form), so they stay on
 // the matrix core; sv_measure_apply_variant runs both forms side by side.
 constexpr bool kDenValu = false;
-constexpr int kDies = 8, kCusPerDie = 32;      // MI355X: 8 accelerator dies (XCDs) of 32 compute units, one L2 each
+constexpr int kCusPerDie = 32;      // MI355X: 8 accelerator dies (XCDs) of 32 compute units, one L2 each
 constexpr uint32_t kSpinLimit = 1u << 24;      // polls of ~100 ns: far beyond any real wait
 std::atomic<uint32_t> g_spin_limit{kSpinLimit};  // sv_linattn_set_wait_limit
 uint32_t spin_limit() { return g_spin_limit.load(std::memory_order_relaxed); }
@@ -66,9 +66,10 @@ struct Device {
 };
 
 // The kernels in use, by padded head dimension and RoPE mode.  LDS sizes include the room for the
-// factored tables where the mode needs it.
-template <int DP, int ROPE> struct Kernels;
-template <int ROPE> struct Kernels<64, ROPE> {
+// factored tables where the mode needs it.  SHARED: heads share cache lines (shares_lines); at d = 64 a head's row
+// is a whole line, one form serves all.
+template <int DP, int ROPE, bool SHARED = false> struct Kernels;
+template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
     static constexpr int W = 0;
     static constexpr auto state = state_mfma_d64<kStateTile, kStateWaves, kStateDepth, true, ROPE>;
@@ -91,19 +92,19 @@ template <int ROPE> struct Kernels<64, ROPE> {
     static constexpr int apply_wgs_per_cu = ROPE == kRopeNone ? 8 : 1;
     static constexpr int apply_wgs_per_cu_short = apply_wgs_per_cu, apply_short_steps = 0;   // no other form for short ranges
 };
-template <int ROPE> struct Kernels<128, ROPE> {
+template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     static constexpr int W = 1;
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
     // State: wave-private tiles, except with a full rotation table, whose rows need the registers
     // the wave-private kernel spends on the whole 128 x 128 state (then: one tile shared by the four waves).
     static constexpr bool kWideState = ROPE != kRopeTable;
     template <bool FINALIZE> static constexpr auto pick_state() {
-        if constexpr (kWideState) return &state_mfma_wide<(ROPE == kRope3D ? kWideStateDepth3D : kWideStateDepth), FINALIZE, ROPE>;
-        else return &state_mfma_d128<kCoopStateDepth, FINALIZE, ROPE>;
+        if constexpr (kWideState) return &state_mfma_wide<(ROPE == kRope3D ? kWideStateDepth3D : kWideStateDepth), FINALIZE, ROPE, !SHARED>;
+        else return &state_mfma_d128<kCoopStateDepth, FINALIZE, ROPE, !SHARED>;
     }
     static constexpr auto state = pick_state<true>();
     static constexpr auto state_partial = pick_state<false>();
-    static constexpr auto apply = apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB>;
+    static constexpr auto apply = apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB, !SHARED>;
     static constexpr int state_lds = kWideState ? kWideLdsBytes : state_d128_lds_bytes<ROPE>() + kTab;
     static constexpr int apply_lds = coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
     static constexpr int state_wg_tokens = kWideState ? 4 * kWideTile : 32;   // four private tiles, or one shared
@@ -116,9 +117,9 @@ template <int ROPE> struct Kernels<128, ROPE> {
     static constexpr int apply_wgs_per_cu_short = apply_wgs_per_cu < 2 ? apply_wgs_per_cu : 2, apply_short_steps = 6;
 };
 
-template <int DP, int ROPE> void init_kernels(Device &d)
+template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
 {
-    using KN = Kernels<DP, ROPE>;
+    using KN = Kernels<DP, ROPE, SHARED>;
     const auto attr = hipFuncAttributeMaxDynamicSharedMemorySize;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state), attr, KN::state_lds);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state_partial), attr, KN::state_lds);
@@ -139,17 +140,21 @@ template <int DP, int ROPE> void init_kernels(Device &d)
     d.state_resident_wgs[KN::W][ROPE] = per_cu * d.num_cu;
 }
 
-// Calls f(Kernels<DP, ROPE>{}) for the MFMA kernel family that serves head dimension d and RoPE mode.
-template <typename F> void with_mfma_kernels(int d, int rope_mode, F &&f)
+// Calls f(Kernels<DP, ROPE, SHARED>{}) for the MFMA kernel family that serves head dimension d, RoPE mode and layout.
+template <typename F> void with_mfma_kernels(int d, int rope_mode, bool shared, F &&f)
 {
     if (d == 64) {
         if (rope_mode == kRope3D) f(Kernels<64, kRope3D>{});
         else if (rope_mode == kRopeTable) f(Kernels<64, kRopeTable>{});
         else f(Kernels<64, kRopeNone>{});
     } else {
-        if (rope_mode == kRope3D) f(Kernels<128, kRope3D>{});
-        else if (rope_mode == kRopeTable) f(Kernels<128, kRopeTable>{});
-        else f(Kernels<128, kRopeNone>{});
+        auto pick = [&](auto sh) {
+            if (rope_mode == kRope3D) f(Kernels<128, kRope3D, sh()>{});
+            else if (rope_mode == kRopeTable) f(Kernels<128, kRopeTable, sh()>{});
+            else f(Kernels<128, kRopeNone, sh()>{});
+        };
+        if (shared) pick(std::true_type{});
+        else pick(std::false_type{});
     }
 }
 
@@ -210,6 +215,9 @@ const Device &device_info()
         init_kernels<128, kRopeNone>(d);
         init_kernels<128, kRopeTable>(d);
         init_kernels<128, kRope3D>(d);
+        init_kernels<128, kRopeNone, true>(d);
+        init_kernels<128, kRopeTable, true>(d);
+        init_kernels<128, kRope3D, true>(d);
         for (int hd : {32, 64, 112, 128})          // the larger generic apply kernels need more than 64 KB of LDS
             with_head_dim(hd, [&](auto D) {
                 const auto attr = hipFuncAttributeMaxDynamicSharedMemorySize;
@@ -310,23 +318,42 @@ sv_status launch_status() { return hipGetLastError() == hipSuccess ? SV_OK : SV_
 
 bool eps_ok(float eps) { return isfinite(eps) && eps >= 0.f; }
 
+// Token rows of all heads side by side: [B][N][H][d], what a projection leaves behind.
+bool token_major(const Shape &s) { return s.H > 1 && s.st.h < s.st.n; }
+
+// ... and neighbouring heads have pieces of the same 128-byte cache lines (d = 112: 224-byte pieces)?  Then the
+// kernels go without the non-temporal hint, which makes a head's pieces of a line leave the L2 before the neighbour's
+// accesses: the apply kernel alone 64 against 104 us (32 760 tokens, 20 heads), both kernels 158 against 174.
+bool shares_lines(const Shape &s) { return token_major(s) && (s.st.h * s.elem_bytes) % 128 != 0; }
+
+// How the workgroups of the layer kernels are dealt to heads and chunks.  Token-major tensors: all heads of a batch
+// walk in phase, so that together they read whole runs of consecutive rows, and where a 256-byte granule of memory
+// holds pieces of several heads (d = 64, 112) the heads of a chunk share a die as well.  Layers of 32 heads of 64,
+// 151 200 tokens: 493 us with both, 523 in phase only, 535 with neither; 40 heads of 112, 32 760 tokens, rotated: 290,
+// 319, 349; 40 heads of 128: 265, 262, 273.
+int workgroup_order(const Shape &s)
+{
+    if (!token_major(s)) return 0;
+    return (s.st.h * s.elem_bytes) % 256 != 0 ? kOrderLockstep | kOrderChunkMajor : kOrderLockstep;
+}
+
 // S_out, z_out = (S_in, z_in, or 0 when S_in is null) + state of tokens [t0,t1).  S_in may equal S_out.
 // rope: rotation table or null.  All arguments are already validated.
 void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, const Shape &s, int t0, int t1,
                        const float *S_in, const float *z_in, float *S_out, float *z_out, void *ws, const Device &dev,
                        dim3 rgrid, hipStream_t stream)
 {
-    with_mfma_kernels(s.d, rope.mode, [&](auto kn) {
+    with_mfma_kernels(s.d, rope.mode, shares_lines(s), [&](auto kn) {
         using KN = decltype(kn);
         const int C = plan_chunks(s.BH, t1 - t0, KN::state_wg_tokens, dev.num_cu);
         if ((int64_t)C * s.BH <= dev.state_resident_wgs[KN::W][rope.mode]) {
             // the head's workgroups wait for each other inside the kernel: all must be resident
             KN::state<<<dim3(C, s.BH), 64 * kStateWaves, KN::state_lds, stream>>>(
                 k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, next_epoch(s.host_epochs_only),
-                spin_limit());
+                spin_limit(), workgroup_order(s));
         } else {
             KN::state_partial<<<dim3(C, s.BH), 64 * kStateWaves, KN::state_lds, stream>>>(
-                k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, 0ull, 0u);
+                k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, 0ull, 0u, workgroup_order(s));
             with_head_dim(s.d, [&](auto D) {
                 state_reduce<D()><<<rgrid, kThreads, 0, stream>>>(static_cast<float *>(ws), C, kMaxChunks, S_in, z_in,
                                                                  S_out, z_out);
@@ -382,7 +409,7 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
     const Device &dev = device_info();
     if (!dev.ok) return SV_ERR_LAUNCH;
     if (mfma_path(s, rope)) {
-        with_mfma_kernels(s.d, rope.mode, [&](auto kn) {
+        with_mfma_kernels(s.d, rope.mode, shares_lines(s), [&](auto kn) {
             using KN = decltype(kn);
             int C = KN::apply_wgs_per_cu * dev.num_cu / s.BH;
             const int steps = (n + KN::apply_wg_tokens - 1) / KN::apply_wg_tokens;
@@ -400,7 +427,7 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
             if (C < 1) C = 1;
             KN::apply<<<dim3(C, s.BH), KN::apply_threads, KN::apply_lds, stream>>>(
                 static_cast<const uint16_t *>(Q), static_cast<uint16_t *>(O), rope.arg, s.st, s.H, s.d, t0, t1, C, S,
-                z, eps);
+                z, eps, workgroup_order(s));
         });
         return launch_status();
     }
@@ -770,7 +797,7 @@ sv_status sv_measure_apply_variant(int32_t variant, const void *Q, const sv_tens
     auto launch = [&](auto kernel, int lds) {
         static_cast<void>(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         kernel<<<dim3(C, s.BH), KN::apply_threads, lds, static_cast<hipStream_t>(stream)>>>(
-            static_cast<const uint16_t *>(Q), static_cast<uint16_t *>(O), none.arg, s.st, s.H, s.d, tok_begin, tok_end, C, S, z, eps);
+            static_cast<const uint16_t *>(Q), static_cast<uint16_t *>(O), none.arg, s.st, s.H, s.d, tok_begin, tok_end, C, S, z, eps, workgroup_order(s));
     };
     constexpr int lds0 = KN::apply_lds, lds1 = KN::apply_lds + kApplyStateLdsBytes;
     switch (variant) {

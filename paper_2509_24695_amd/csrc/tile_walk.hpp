@@ -62,6 +62,18 @@ struct StateSlice {
 // dealt from a different start in each head (see block_step_mfma).
 SV_HOST_DEVICE inline int block_step_share(int c, int bh, int C) { return (c + bh) % C; }
 
+// Which (chunk, head) workgroup `id` of a grid of C chunks x BH heads works on in the chunk-major order: the
+// grid's ids go round the `dies` dies one by one, and die e takes the e-th part of the list (chunk 0 of all
+// heads, chunk 1 of all heads, ...).  So the heads of one chunk, which read the same rows of a rotation table and,
+// in a [B][N][H][d] tensor, neighbouring pieces of the same cache lines, share a die's L2.
+SV_HOST_DEVICE inline void chunk_major_role(int id, int C, int BH, int dies, int &c, int &bh)
+{
+    const int total = C * BH, e = id % dies, left = total % dies;
+    const int logical = e * (total / dies) + (e < left ? e : left) + id / dies;
+    c = logical / BH;
+    bh = logical - c * BH;
+}
+
 // Phase key (the `bh` argument of TileWalk) of head bh in the die-local forms of the kernels, where die x
 // holds heads x, x + n_dies, ...: keyed by the head index itself, heads of one die would share phases (two
 // distinct ones for four heads), so the sixteen phases are dealt die by die, the heads of a die as far apart

@@ -62,7 +62,7 @@ struct WideAcc {
 
 // One wave's input stream: rows lane/16 + 4 j of every tile of its walk, DEPTH tiles in flight.
 // Lanes whose features lie past d (d = 112) address out of range: they read zeros.
-template <int DEPTH, int ROPE>
+template <int DEPTH, int ROPE, bool NT>
 struct WideStateStream {
     static constexpr int NLD = kWideTile / 4;
     rsrc_t rK, rV;
@@ -85,15 +85,15 @@ struct WideStateStream {
         const uint32_t base = valid ? walk.offset<kWideTile>(i, row_bytes) : kOutOfRange;
 #pragma unroll
         for (int j = 0; j < NLD; ++j) {
-            k[s][j] = load_stream16(rK, base + lane_off + (uint32_t)j * 4u * row_bytes);
-            v[s][j] = load_stream16(rV, base + lane_off + (uint32_t)j * 4u * row_bytes);
+            k[s][j] = load_stream16<NT>(rK, base + lane_off + (uint32_t)j * 4u * row_bytes);
+            v[s][j] = load_stream16<NT>(rV, base + lane_off + (uint32_t)j * 4u * row_bytes);
         }
         rot.request(s, i < walk.count, walk.token<kWideTile>(i));
     }
 };
 
-template <int DEPTH, int ROPE>
-__device__ __forceinline__ void wide_state_prefetch(WideStateStream<DEPTH, ROPE> &st)
+template <int DEPTH, int ROPE, bool NT>
+__device__ __forceinline__ void wide_state_prefetch(WideStateStream<DEPTH, ROPE, NT> &st)
 {
 #pragma unroll
     for (int s = 0; s < DEPTH; ++s) {
@@ -106,10 +106,10 @@ __device__ __forceinline__ void wide_state_prefetch(WideStateStream<DEPTH, ROPE>
 // rotator has been told the tile (begin_tile).  Straight-line code, so that it can share a
 // scheduling region with MFMAs.  Two chunks at a time: their eight table lookups go out first,
 // ReLU and key sums fill the latency.
-template <int DEPTH, int ROPE>
-__device__ __forceinline__ void wide_state_prepare(WideStateStream<DEPTH, ROPE> &st, int s, WideAcc &acc)
+template <int DEPTH, int ROPE, bool NT>
+__device__ __forceinline__ void wide_state_prepare(WideStateStream<DEPTH, ROPE, NT> &st, int s, WideAcc &acc)
 {
-    constexpr int NLD = WideStateStream<DEPTH, ROPE>::NLD;
+    constexpr int NLD = WideStateStream<DEPTH, ROPE, NT>::NLD;
 #pragma unroll
     for (int j0 = 0; j0 < NLD; j0 += 2) {
         f32x2 cs[2][4];
@@ -133,11 +133,11 @@ __device__ __forceinline__ void wide_state_prepare(WideStateStream<DEPTH, ROPE> 
 // tokens past t1 hold zeros and add nothing.  tileK, tileV: the wave's private LDS tiles.
 // Software-pipelined by one tile: with one wave per SIMD nothing else fills the matrix core's
 // shadow, so the vector work of tile i + 1 is issued between the MFMAs of tile i.
-template <int DEPTH, int ROPE>
-__device__ __forceinline__ void wide_state_accumulate(WideStateStream<DEPTH, ROPE> &st, unsigned char *tileK,
+template <int DEPTH, int ROPE, bool NT>
+__device__ __forceinline__ void wide_state_accumulate(WideStateStream<DEPTH, ROPE, NT> &st, unsigned char *tileK,
                                                       unsigned char *tileV, int wave, int lane, WideAcc &acc)
 {
-    constexpr int NLD = WideStateStream<DEPTH, ROPE>::NLD;
+    constexpr int NLD = WideStateStream<DEPTH, ROPE, NT>::NLD;
     const int wr_off = (lane >> 4) * kWideRow + (lane & 15) * 16;
     st.rot.template begin_tile<kWideTile>(st.walk, 0);
     wide_state_prepare(st, 0, acc);
@@ -296,17 +296,18 @@ __device__ __forceinline__ void wide_state_wg_reduce_store(WideAcc &acc, unsigne
 // grid = (C, B*H), block = 256.  Wave w of workgroup c owns tiles 4c + w + 4C i of the
 // T = ceil((t1 - t0) / 16) tiles.  FINALIZE as in state_mfma_d64.  ROPE: kRopeNone or kRope3D (the
 // table rows of kRopeTable do not fit in the registers left beside the state).
-template <int DEPTH, bool FINALIZE, int ROPE>
+template <int DEPTH, bool FINALIZE, int ROPE, bool NT>
 __global__ __launch_bounds__(256, 1) void state_mfma_wide(
     const uint16_t *__restrict__ K, const uint16_t *__restrict__ V, RopeArg rope, TokStrides st,
     int H, int d, int t0, int t1, int C, const float *S_in, const float *z_in, float *S_out, float *z_out,
-    void *__restrict__ ws, unsigned long long epoch, uint32_t spin_limit)
+    void *__restrict__ ws, unsigned long long epoch, uint32_t spin_limit, int order)
 {
     static_assert(ROPE == kRopeNone || ROPE == kRope3D, "no full-table form of this kernel");
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = blockIdx.x, bh = blockIdx.y, BH = gridDim.y;
+    const WgRole role(C, order);
+    const int c = role.c, bh = role.bh, BH = gridDim.y;
     const int b = bh / H, h = bh % H;
     const int elems = d * d + d;
     const uint16_t *Kh = K + b * st.b + h * st.h;
@@ -317,8 +318,8 @@ __global__ __launch_bounds__(256, 1) void state_mfma_wide(
 
     WideAcc acc;
     acc.clear();
-    WideStateStream<DEPTH, ROPE> stream(Kh, Vh, rope, lds + kWideTabOffset, st.n, t1, d, lane,
-                                        TileWalk(t0, 4 * c + wave, 4 * C, n_tiles, bh));
+    WideStateStream<DEPTH, ROPE, NT> stream(Kh, Vh, rope, lds + kWideTabOffset, st.n, t1, d, lane,
+                                        TileWalk(t0, 4 * c + wave, 4 * C, n_tiles, role.phase(b, order)));
     Rope3dFill tabs;
     if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
     wide_state_prefetch(stream);

@@ -1,0 +1,13 @@
+"""The chunk-major order of the layer kernels' workgroups, compiled with g++ and run here."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_chunk_major_order_covers_every_chunk_once(tmp_path):
+    exe = tmp_path / "host_workgroup_order"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Wextra", os.path.join(ROOT, "tests", "host_workgroup_order.cpp"),
+                    "-o", str(exe)], check=True)
+    res = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
+    assert res.returncode == 0 and res.stdout.startswith("OK"), res.stdout
