@@ -1,0 +1,444 @@
+// State reduction and apply in fp32 arithmetic on the matrix cores (v_mfma_f32_16x16x4_f32): the fp32 mode at every head
+// dimension, and bf16 at d = 32.
+//
+//   S[k][v] (+)= sum_j phi(K[j][k]) V[j][v],  z[k] (+)= sum_j phi(K[j][k])          (Sec. 3.2, brackets)
+//   O[i][v] = (sum_k phi(Q[i][k]) S[k][v]) / (sum_k phi(Q[i][k]) z[k] + eps)        (Sec. 3.2, right-hand form)
+//
+// Bound by HBM: 4 d flops per byte of fp32 tokens, the fp32 matrix rate allows about 20 times what the streams
+// need at d = 32 and 5 times at d = 128.  One MFMA takes a 16 x 4 and a 4 x 16 operand, one element per lane (row or
+// column lane % 16, contraction index lane / 16), which is what lets both kernels go without LDS:
+//
+//   state   the contraction runs over tokens: lane (m, g) loads VEC consecutive features VEC*m .. of token g of
+//           a group of four with one 4- to 16-byte load (16 lanes make a row), and element e of that vector IS
+//           the operand of feature block e, whose 16 features are e, VEC + e, 2 VEC + e, ...
+//   apply   the contraction runs over features: lane (n, g) holds chunks of 4 consecutive features of a token, chunk j
+//           from feature(j, g) on, and element q is the operand of the step that contracts the features
+//           feature(j, 0) + q .. feature(j, 3) + q; the state is kept in registers in the matching order.  Output block b holds features NB*n + b, so that a
+//           lane ends up with NB consecutive features of a token and stores them as they are.
+//
+// Measured (both kernels of a layer, before: plain FMAs out of LDS): fp32, 32 heads of 64, 4 680 tokens 120 -> 46.5 us;
+// bf16, 128 heads of 32, 4 096 tokens 130 -> 42 us; fp32, 2 heads of 32, 1 024 tokens 17.7 -> 14.3 us (two launches for three).
+// What is left above the streams' time is the start of a kernel and the chain by which a head's workgroups agree.
+//
+// d <= 64: a wave holds the whole state and works alone on its tiles.  d = 112, 128: the waves of a workgroup
+// share the tiles, in the state kernel as 64 x 64 quadrants (each half row is loaded by two waves, the second out
+// of the caches), in the apply kernel as 32 output features each.
+#pragma once
+
+#include "rope.hpp"
+#include "state_mfma.hpp"
+
+namespace sv {
+
+// W 32-bit words from / to a buffer resource, non-temporal.
+template <int W> struct Words { uint32_t w[W]; };
+template <int W> __device__ __forceinline__ Words<W> load_words(rsrc_t r, uint32_t off)
+{
+    Words<W> x;
+    if constexpr (W == 4) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 2);
+        x.w[0] = v.x; x.w[1] = v.y; x.w[2] = v.z; x.w[3] = v.w;
+    } else if constexpr (W == 2) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 2);
+        x.w[0] = v[0]; x.w[1] = v[1];
+    } else {
+        x.w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 2);
+    }
+    return x;
+}
+template <int W> __device__ __forceinline__ void store_words(rsrc_t r, uint32_t off, const Words<W> &x)
+{
+    if constexpr (W == 4) {
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{x.w[0], x.w[1], x.w[2], x.w[3]}, r, off, 0, 2);
+    } else if constexpr (W == 2) {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{x.w[0], x.w[1]}, r, off, 0, 2);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b32(x.w[0], r, off, 0, 2);
+    }
+}
+// N values of type T as fp32, from and to the words that hold them.
+template <typename T, int N> constexpr int kWords = N * (int)sizeof(T) / 4;
+template <typename T, int N> __device__ __forceinline__ void widen(const Words<kWords<T, N>> &x, float (&f)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if constexpr (sizeof(T) == 4) f[i] = __uint_as_float(x.w[i]);
+        else f[i] = i & 1 ? bf16_hi(x.w[i / 2]) : bf16_lo(x.w[i / 2]);
+    }
+}
+template <typename T, int N> __device__ __forceinline__ Words<kWords<T, N>> narrow(const float (&f)[N])
+{
+    Words<kWords<T, N>> x;
+#pragma unroll
+    for (int i = 0; i < kWords<T, N>; ++i) {
+        if constexpr (sizeof(T) == 4) x.w[i] = __float_as_uint(f[i]);
+        else x.w[i] = pack_bf16x2(f[2 * i], f[2 * i + 1]);
+    }
+    return x;
+}
+
+// Position of token `tok` in the factored tables' grid.  Quotients by a product with the rounded reciprocal: exact
+// for fewer than 2^20 tokens, which the host checks ((x + 0.5) / n is 0.5 / n away from an integer).
+struct GridPos {
+    int f, r, c;
+    __device__ __forceinline__ GridPos(const Rope3D &R, int tok, float inv_rc, float inv_cols)
+    {
+        const int rc = R.rows * R.cols;
+        f = (int)(((float)tok + 0.5f) * inv_rc);
+        const int rem = tok - f * rc;
+        r = (int)(((float)rem + 0.5f) * inv_cols);
+        c = rem - r * R.cols;
+        f = f < R.frames ? f : R.frames - 1;      // tokens past the last: any valid entry, their features are zero
+    }
+};
+// (cos, sin) of feature pair p at that position, from the tables in LDS.
+__device__ __forceinline__ f32x2 rope3d_entry_lds(const unsigned char *tab, const Rope3D &R, const GridPos &g, int p)
+{
+    const int nt = R.frames * R.n_t, nh = R.rows * R.n_h;
+    int e = g.f * R.n_t + p;
+    if (p >= R.n_t) e = nt + g.r * R.n_h + (p - R.n_t);
+    if (p >= R.n_t + R.n_h) e = nt + nh + g.c * R.n_w + (p - R.n_t - R.n_h);
+    return reinterpret_cast<const f32x2 *>(tab)[e];
+}
+// Turns the N / 2 feature pairs in f by the entries in cs.
+template <int N> __device__ __forceinline__ void rotate_pairs(float (&f)[N], const f32x2 (&cs)[N / 2])
+{
+#pragma unroll
+    for (int p = 0; p < N / 2; ++p) {
+        const float a = f[2 * p], b = f[2 * p + 1];
+        f[2 * p] = a * cs[p].x - b * cs[p].y;
+        f[2 * p + 1] = a * cs[p].y + b * cs[p].x;
+    }
+}
+
+// ---- state ----------------------------------------------------------------------------------------------------
+
+template <typename T, int D> struct StateF32 {
+    static constexpr bool kSplit = D > 64;                 // quadrants instead of whole states
+    static constexpr int F = kSplit ? 64 : D;              // features of a wave's part, on both axes
+    static constexpr int VEC = F / 16, W = kWords<T, VEC>;
+    static constexpr int U = 16 / VEC;                     // groups of four tokens per tile: 16 tokens, 32 at d = 32
+    static constexpr int TILE = 4 * U;
+    static constexpr int DEPTH = 3;                        // tiles in flight per wave
+    static constexpr int kSlot = F * F + F;                // a wave's part in LDS: state, then key sums
+    static constexpr int kWgTokens = kSplit ? TILE : 4 * TILE;
+    template <int ROPE> static constexpr int lds_bytes() {
+        constexpr int slots = 4 * kSlot * 4, tab = ROPE == kRope3D ? kRope3dLdsBytes : 0;   // tables, then slots
+        return (slots > tab ? slots : tab) + kEpochLdsBytes;
+    }
+};
+
+// grid = (C, B*H), block = 256; arguments, FINALIZE and the workspace as in state_mfma_d64.
+template <typename T, int D, bool FINALIZE, int ROPE>
+__global__ __launch_bounds__(kThreads, 1) void state_f32(
+    const T *__restrict__ K, const T *__restrict__ V, RopeArg rope, TokStrides st, int H, int t0, int t1, int C,
+    const float *S_in, const float *z_in, float *S_out, float *z_out, void *__restrict__ ws, unsigned long long epoch,
+    uint32_t spin_limit, int order)
+{
+    using P = StateF32<T, D>;
+    constexpr int VEC = P::VEC, W = P::W, U = P::U, TILE = P::TILE, DEPTH = P::DEPTH, F = P::F, E = (int)sizeof(T);
+    constexpr int elems = D * D + D;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 15, g = lane >> 4;
+    const WgRole role(C, order);
+    const int c = role.c, bh = role.bh, BH = gridDim.y;
+    const int b = bh / H, h = bh % H;
+    EpochSource es;
+    if (FINALIZE) es.begin(ws, BH, elems, epoch, bh, c, C);
+
+    const int kb = P::kSplit ? wave & 1 : 0, vb = P::kSplit ? wave >> 1 : 0;
+    const int n_tiles = (t1 - t0 + TILE - 1) / TILE;
+    const TileWalk walk(t0, P::kSplit ? c : 4 * c + wave, P::kSplit ? C : 4 * C, n_tiles, role.phase(b, order));
+    const uint32_t row_bytes = (uint32_t)st.n * E;
+    const rsrc_t rK = make_rsrc(K + b * st.b + h * st.h, (uint32_t)t1 * row_bytes);
+    const rsrc_t rV = make_rsrc(V + b * st.b + h * st.h, (uint32_t)t1 * row_bytes);
+    const int fk = F * kb + VEC * m, fv = F * vb + VEC * m;         // the lane's first features
+    const uint32_t offK = fk < D ? (uint32_t)g * row_bytes + (uint32_t)fk * E : kOutOfRange;
+    const uint32_t offV = fv < D ? (uint32_t)g * row_bytes + (uint32_t)fv * E : kOutOfRange;
+    const rsrc_t rT = make_rsrc(rope.table, ROPE == kRopeTable ? (uint32_t)t1 * (uint32_t)(D * 4) : 0u);
+    const uint32_t offT = fk < D ? (uint32_t)g * (uint32_t)(D * 4) + (uint32_t)fk * 4u : kOutOfRange;
+
+    Words<W> kw[DEPTH][U], vw[DEPTH][U];
+    Words<ROPE == kRopeTable ? VEC : 1> tw[DEPTH][U];
+    // Requests the wave's i-th tile into stage s; past the share every address is out of range and reads zeros.
+    auto request = [&](int s, int i) __attribute__((always_inline)) {
+        const uint32_t base = walk.offset<TILE>(i, row_bytes);
+        const uint32_t bk = fk < D ? base : 0u, bv = fv < D ? base : 0u;      // kOutOfRange once, not twice
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            kw[s][u] = load_words<W>(rK, offK + bk + (uint32_t)(4 * u) * row_bytes);
+            vw[s][u] = load_words<W>(rV, offV + bv + (uint32_t)(4 * u) * row_bytes);
+        }
+        if constexpr (ROPE == kRopeTable) {
+            const uint32_t bt = fk < D ? walk.offset<TILE>(i, (uint32_t)(D * 4)) : 0u;
+#pragma unroll
+            for (int u = 0; u < U; ++u) tw[s][u] = load_words<VEC>(rT, offT + bt + (uint32_t)(4 * u) * (uint32_t)(D * 4));
+        }
+    };
+
+    Rope3dFill tabs;
+    if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s) request(s, s);
+    if (ROPE == kRope3D) {
+        rope3d_lds_fill_end(lds, rope.r3, tabs);
+        wg_barrier();
+    }
+    const float inv_rc = ROPE == kRope3D ? 1.0f / (float)(rope.r3.rows * rope.r3.cols) : 0.f;
+    const float inv_cols = ROPE == kRope3D ? 1.0f / (float)rope.r3.cols : 0.f;
+
+    f32x4 acc[VEC][VEC] = {};
+    float zs[VEC] = {};
+    for (int i0 = 0; i0 < walk.count; i0 += DEPTH) {
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) {
+            if (i0 + s >= walk.count) break;     // short shares: the rest of the round would be code and no work
+            __builtin_amdgcn_sched_barrier(0);   // stages stay in program order
+            float kf[U][VEC], vf[U][VEC];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                widen<T, VEC>(kw[s][u], kf[u]);
+                widen<T, VEC>(vw[s][u], vf[u]);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    kf[u][e] = fmaxf(kf[u][e], 0.f);
+                    zs[e] += kf[u][e];                      // the key sum is never rotated
+                }
+                if constexpr (ROPE != kRopeNone) {
+                    f32x2 cs[VEC / 2];
+                    if constexpr (ROPE == kRopeTable) {
+#pragma unroll
+                        for (int p = 0; p < VEC / 2; ++p)
+                            cs[p] = f32x2{__uint_as_float(tw[s][u].w[2 * p]), __uint_as_float(tw[s][u].w[2 * p + 1])};
+                    } else {
+                        const GridPos pos(rope.r3, walk.token<TILE>(i0 + s) + 4 * u + g, inv_rc, inv_cols);
+#pragma unroll
+                        for (int p = 0; p < VEC / 2; ++p) {
+                            const int pair = fk / 2 + p;
+                            cs[p] = rope3d_entry_lds(lds, rope.r3, pos, pair < D / 2 ? pair : D / 2 - 1);
+                        }
+                    }
+                    rotate_pairs<VEC>(kf[u], cs);
+                }
+            }
+            request(s, i0 + s + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i)
+#pragma unroll
+                    for (int j = 0; j < VEC; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][i], vf[u][j], acc[i][j], 0, 0, 0);
+        }
+    }
+
+    // The wave's part in [k][v] order in its LDS slot: element r of block (i, j) is key feature VEC (4 g + r) + i, value
+    // feature VEC m + j, so a lane's blocks j make VEC consecutive floats.
+    float *slots = reinterpret_cast<float *>(lds), *mine = slots + wave * P::kSlot;
+    wg_barrier();                                   // everybody is done with the tables
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float *row = mine + (VEC * (4 * g + r) + i) * F + VEC * m;
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) row[j] = acc[i][j][r];
+        }
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        float x = zs[e];
+        x += __shfl_xor(x, 16);
+        x += __shfl_xor(x, 32);
+        if (lane < 16) mine[F * F + VEC * m + e] = x;
+    }
+    wg_barrier();
+    float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems, *out = partials + (size_t)c * elems;
+    if constexpr (P::kSplit) {
+        constexpr int s_units = D * D / 2, units = s_units + D / 2;
+        for (int u = tid; u < units; u += kThreads) {
+            const float *src;
+            if (u < s_units) {
+                const int k = (2 * u) / D, v = 2 * u - k * D;
+                src = slots + ((k >> 6) + 2 * (v >> 6)) * P::kSlot + (k & 63) * 64 + (v & 63);
+            } else {
+                const int k = 2 * (u - s_units);
+                src = slots + (k >> 6) * P::kSlot + F * F + (k & 63);
+            }
+            store_coherent(out + 2 * u, *reinterpret_cast<const f32x2 *>(src));
+        }
+    } else {
+        constexpr int units = P::kSlot / 2;
+        for (int u = tid; u < units; u += kThreads) {
+            f32x2 x[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) x[w] = *reinterpret_cast<const f32x2 *>(slots + w * P::kSlot + 2 * u);
+            store_coherent(out + 2 * u, (x[0] + x[2]) + (x[1] + x[3]));
+        }
+    }
+    if (FINALIZE) {
+        epoch = es.resolve(reinterpret_cast<unsigned long long *>(lds + P::template lds_bytes<ROPE>() - kEpochLdsBytes));
+        const float *Sc = S_in ? S_in + (size_t)bh * D * D : nullptr, *zc = z_in + (size_t)bh * D;
+        const StateSlice sl(c, C, D);
+        f32x2 carry[3];
+        state_slice_carry<kThreads>(sl, Sc, zc, tid, carry);
+        if (!state_publish_and_wait(ws, BH, elems, bh, c, C, 0, epoch, spin_limit, lane))
+            return;                                 // timed out: this wave leaves its part of S, z as it was
+        state_finalize_slice<kThreads, false>(partials, sl, C, Sc, zc, S_out + (size_t)bh * D * D, z_out + (size_t)bh * D,
+                                              tid, carry);
+    }
+}
+
+// ---- apply ----------------------------------------------------------------------------------------------------
+
+template <int D> struct ApplyF32 {
+    static constexpr bool kSplit = D > 64;                  // 32 output features per wave, the waves share the tiles
+    static constexpr int NB = D == 64 ? 4 : 2;              // blocks of 16 output features per wave
+    static constexpr int NJ = D / 16;
+    static constexpr int TILE = 16;
+    // tiles in flight per wave; the rotation of wide heads leaves registers for one
+    // first of the four features that lane (n, g) holds in chunk j: whole 64-byte runs of a row per load
+    template <typename T> static __device__ __forceinline__ int feature(int j, int g) {
+        return sizeof(T) == 2 ? 8 * g + 4 * j : 16 * j + 4 * g;
+    }
+    template <int ROPE> static constexpr int kDepth = ROPE != kRopeNone && D > 64 ? 1 : 2;
+    static constexpr int kWgTokens = kSplit ? TILE : 4 * TILE;
+};
+
+// grid = (C, B*H), block = 256; dynamic LDS: kRope3dLdsBytes with kRope3D.
+template <typename T, int D, int ROPE>
+__global__ __launch_bounds__(kThreads, 2) void apply_f32(
+    const T *__restrict__ Q, T *__restrict__ O, RopeArg rope, TokStrides st, int H, int t0, int t1, int C,
+    const float *__restrict__ S, const float *__restrict__ z, float eps, int order)
+{
+    using P = ApplyF32<D>;
+    constexpr int NB = P::NB, NJ = P::NJ, TILE = P::TILE, DEPTH = P::template kDepth<ROPE>, E = (int)sizeof(T);
+    // a lane's features of a token come in NL loads of LC chunks (16 bytes)
+    constexpr int LC = E == 2 ? 2 : 1, NL = NJ / LC;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, g = lane >> 4;
+    const WgRole role(C, order);
+    const int c = role.c, bh = role.bh;
+    const int b = bh / H, h = bh % H;
+    const int n_tiles = (t1 - t0 + TILE - 1) / TILE;
+    const TileWalk walk(t0, P::kSplit ? c : 4 * c + wave, P::kSplit ? C : 4 * C, n_tiles, role.phase(b, order));
+    const uint32_t row_bytes = (uint32_t)st.n * E;
+    const rsrc_t rQ = make_rsrc(Q + b * st.b + h * st.h, (uint32_t)t1 * row_bytes);
+    const rsrc_t rO = make_rsrc(O + b * st.b + h * st.h, (uint32_t)t1 * row_bytes);
+    const rsrc_t rT = make_rsrc(rope.table, ROPE == kRopeTable ? (uint32_t)t1 * (uint32_t)(D * 4) : 0u);
+    // MFMA row i is token 4 (i % 4) + i / 4 of the tile: element r of an accumulator in lane group g is then token 4 r + g,
+    // and a store instruction writes four consecutive rows
+    const int tok = 4 * (n & 3) + (n >> 2);
+    const uint32_t offQ = (uint32_t)tok * row_bytes + (uint32_t)(P::template feature<T>(0, g) * E);
+    const uint32_t offT = (uint32_t)tok * (uint32_t)(D * 4) + (uint32_t)(P::template feature<T>(0, g) * 4);
+    const int f_out = (P::kSplit ? 32 * wave : 0) + NB * n;               // the lane's first output feature
+    const uint32_t offO = (uint32_t)g * row_bytes + (uint32_t)(f_out * E);
+
+    Words<4> qw[DEPTH][NL];
+    Words<ROPE == kRopeTable ? 4 : 1> tw[DEPTH][NJ];
+    auto request = [&](int s, int i) __attribute__((always_inline)) {
+        const uint32_t base = walk.offset<TILE>(i, row_bytes) + offQ;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) qw[s][l] = load_words<4>(rQ, base + (uint32_t)(64 * l));
+        if constexpr (ROPE == kRopeTable) {
+            const uint32_t bt = walk.offset<TILE>(i, (uint32_t)(D * 4)) + offT;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) tw[s][j] = load_words<4>(rT, bt + (uint32_t)((E == 2 ? 16 : 64) * j));
+        }
+    };
+    Rope3dFill tabs;
+    if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s) request(s, s);
+    if (ROPE == kRope3D) {
+        rope3d_lds_fill_end(lds, rope.r3, tabs);
+        wg_barrier();
+    }
+    const float inv_rc = ROPE == kRope3D ? 1.0f / (float)(rope.r3.rows * rope.r3.cols) : 0.f;
+    const float inv_cols = ROPE == kRope3D ? 1.0f / (float)rope.r3.cols : 0.f;
+
+    // the state and the key sums, in the order in which the contraction meets the features
+    float sr[NJ][4][NB], zr[NJ][4];
+    const float *Sh = S + (size_t)bh * D * D, *zh = z + (size_t)bh * D;
+    const bool exists = f_out < D;                                      // NB divides D: all of a lane's features or none
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = P::template feature<T>(j, g) + q;
+            zr[j][q] = zh[k];
+            typedef float vec __attribute__((ext_vector_type(NB)));
+            const vec x = *reinterpret_cast<const vec *>(Sh + k * D + (exists ? f_out : 0));
+#pragma unroll
+            for (int e = 0; e < NB; ++e) sr[j][q][e] = x[e];            // columns that do not exist are never stored
+        }
+
+    for (int i0 = 0; i0 < walk.count; i0 += DEPTH) {
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) {
+            const int i = i0 + s;
+            if (i >= walk.count) break;
+            __builtin_amdgcn_sched_barrier(0);
+            float qf[NJ][4], den = 0.f;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                if constexpr (E == 2) {
+                    const Words<2> half = {{qw[s][0].w[2 * j], qw[s][0].w[2 * j + 1]}};
+                    widen<T, 4>(half, qf[j]);
+                } else {
+                    widen<T, 4>(qw[s][j], qf[j]);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    qf[j][q] = fmaxf(qf[j][q], 0.f);
+                    den = fmaf(qf[j][q], zr[j][q], den);                // the denominator takes the plain features
+                }
+            }
+            if constexpr (ROPE == kRopeTable) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    const f32x2 cs[2] = {{__uint_as_float(tw[s][j].w[0]), __uint_as_float(tw[s][j].w[1])},
+                                         {__uint_as_float(tw[s][j].w[2]), __uint_as_float(tw[s][j].w[3])}};
+                    rotate_pairs<4>(qf[j], cs);
+                }
+            } else if constexpr (ROPE == kRope3D) {
+                const GridPos pos(rope.r3, walk.token<TILE>(i) + tok, inv_rc, inv_cols);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    const f32x2 cs[2] = {rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2),
+                                         rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2 + 1)};
+                    rotate_pairs<4>(qf[j], cs);
+                }
+            }
+            request(s, i + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+            den += __shfl_xor(den, 16);
+            den += __shfl_xor(den, 32);                                 // that of MFMA row n, in all its lanes
+            f32x4 acc[NB] = {};
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int e = 0; e < NB; ++e)
+                        acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[j][q], sr[j][q][e], acc[e], 0, 0, 0);
+            // element r of block e: MFMA row 4 g + r, token 4 r + g, feature f_out + e
+            const uint32_t out = exists ? walk.offset<TILE>(i, row_bytes) + offO : kOutOfRange;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float dd = __shfl(den, 4 * g + r) + eps;
+                float o[NB];
+#pragma unroll
+                for (int e = 0; e < NB; ++e) o[e] = acc[e][r] / dd;
+                store_words(rO, out + (uint32_t)(4 * r) * row_bytes, narrow<T, NB>(o));
+            }
+        }
+    }
+}
+
+}  // namespace sv

@@ -1,9 +1,8 @@
 // Plain fp32-arithmetic kernels for every supported (dtype, d) pair, and the
 // fixed-order partial-state reduction used by all paths.
 //
-// These serve the fp32 validation mode (results within 1e-5 of a float64
-// evaluation) and the bf16 shapes that have no MFMA kernel.  D is the head
-// dimension: 32, 64, 112 or 128.  Products are fp32
+// These serve what the matrix-core kernels do not address: heads that span 2 GiB and more, and factored rotation
+// tables larger than the LDS set aside for them.  D is the head dimension: 32, 64, 112 or 128.  Products are fp32
 // FMAs in token order inside a chunk; chunks are combined by state_reduce.
 #pragma once
 

@@ -15,6 +15,7 @@
 #include "block_step_fused.hpp"
 #include "coop128.hpp"
 #include "common.hpp"
+#include "f32_mfma.hpp"
 #include "generic_kernels.hpp"
 #include "state_mfma.hpp"
 #include "wide_state.hpp"
@@ -38,6 +39,10 @@ constexpr int kCoopStateDepth = 4;            // 32-token tiles of the shared-ti
 constexpr int kFusedStateDepth[3] = {2, 2, 2};   // one-launch block step (d = 64), by RoPE mode
 constexpr int kFusedApplyDepth[3] = {6, 2, 6};   // Q tiles held in registers across the in-kernel waits
 constexpr bool kApplyHiLo = true;
+// Workgroups per compute unit of the fp32-arithmetic apply kernel.  Every wave starts by fetching its part of the state,
+// so few and long ones win (d = 64, 4 680 tokens: 46.5 us for the layer with two, 52.8 with four, 57.8 with eight); at
+// d = 32 the state is small and more waves cover the loads (44.8, 42.1, 41.7 us).
+constexpr int f32_apply_wgs_per_cu(int d) { return d == 32 ? 4 : 2; }
 // d = 64: the denominators phi(Q_i).z ride through the matrix core as two more operand rows (false) or are taken on
 // the vector ALU with a wavefront-level reduction (true).  Measured level (within 1 % either way at 32 760 and
 // 75 600 tokens; the one-launch block step 0.5-1 us per block slower with the vector ALU form), so they stay on
@@ -62,6 +67,7 @@ struct Device {
     // how many workgroups fit on the device at once, [DP = 128][RoPE mode]
     int state_resident_wgs[2][3] = {{0, 0, 0}, {0, 0, 0}};   // state kernel with in-kernel finalize
     int fused_resident_wgs[3] = {0, 0, 0};                   // one-launch block step (d = 64), by RoPE mode
+    int f32_resident_wgs[5][3] = {};                         // fp32-arithmetic state kernel, [KernelsF32::kIndex][RoPE mode]
     bool ok = false;
 };
 
@@ -116,6 +122,31 @@ template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     // ranges of fewer than apply_short_steps steps per workgroup: two per compute unit (see enqueue_apply)
     static constexpr int apply_wgs_per_cu_short = apply_wgs_per_cu < 2 ? apply_wgs_per_cu : 2, apply_short_steps = 6;
 };
+
+// The kernels with fp32 arithmetic: fp32 tokens at every d, bf16 at d = 32.
+template <typename T_, int D_, int ROPE_> struct KernelsF32 {
+    using T = T_;
+    static constexpr int D = D_, ROPE = ROPE_;
+    static constexpr int kIndex = sizeof(T) == 2 ? 4 : D == 32 ? 0 : D == 64 ? 1 : D == 112 ? 2 : 3;
+    static constexpr auto state = state_f32<T, D, true, ROPE>;
+    static constexpr auto state_partial = state_f32<T, D, false, ROPE>;
+    static constexpr auto apply = apply_f32<T, D, ROPE>;
+    static constexpr int state_lds = StateF32<T, D>::template lds_bytes<ROPE>();
+    static constexpr int apply_lds = ROPE == kRope3D ? kRope3dLdsBytes : 0;
+    static constexpr int state_wg_tokens = StateF32<T, D>::kWgTokens, apply_wg_tokens = ApplyF32<D>::kWgTokens;
+};
+template <typename T, int D, int ROPE> void init_f32_kernels(Device &d)
+{
+    using KN = KernelsF32<T, D, ROPE>;
+    const auto attr = hipFuncAttributeMaxDynamicSharedMemorySize;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state), attr, KN::state_lds);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state_partial), attr, KN::state_lds);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(KN::state), kThreads,
+                                                     KN::state_lds) != hipSuccess)
+        per_cu = 0;
+    d.f32_resident_wgs[KN::kIndex][ROPE] = per_cu * d.num_cu;
+}
 
 template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
 {
@@ -218,6 +249,15 @@ const Device &device_info()
         init_kernels<128, kRopeNone, true>(d);
         init_kernels<128, kRopeTable, true>(d);
         init_kernels<128, kRope3D, true>(d);
+        for (int hd : {32, 64, 112, 128})
+            with_head_dim(hd, [&](auto D) {
+                init_f32_kernels<float, D(), kRopeNone>(d);
+                init_f32_kernels<float, D(), kRopeTable>(d);
+                init_f32_kernels<float, D(), kRope3D>(d);
+            });
+        init_f32_kernels<uint16_t, 32, kRopeNone>(d);
+        init_f32_kernels<uint16_t, 32, kRopeTable>(d);
+        init_f32_kernels<uint16_t, 32, kRope3D>(d);
         for (int hd : {32, 64, 112, 128})          // the larger generic apply kernels need more than 64 KB of LDS
             with_head_dim(hd, [&](auto D) {
                 const auto attr = hipFuncAttributeMaxDynamicSharedMemorySize;
@@ -292,19 +332,47 @@ sv_status check_desc(const sv_tensor_desc *t, Shape *s)
     return SV_OK;
 }
 
-// The MFMA kernels address a head's tokens (and the rotation table) with 32-bit byte offsets.
-bool mfma_path(const Shape &s, const Rope &rope)
+// The matrix-core kernels address a head's tokens (and the rotation table) with 32-bit byte offsets: what a head spans, and
+// what one tile spans (rows past the end are reached by address before they are dropped), stays below 2 GiB.
+bool offsets_fit(const Shape &s, const Rope &rope)
 {
     constexpr int64_t kLimit = int64_t(1) << 31;
-    if (!s.bf16 || s.d < 64 || (int64_t)s.N * s.st.n * 2 >= kLimit) return false;
-    if (rope.mode == kRopeTable && (int64_t)s.N * s.d * 4 >= kLimit) return false;
-    if (rope.mode == kRope3D) {            // the three tables must fit the LDS set aside for them
-        const Rope3D &r = rope.arg.r3;
-        if ((int64_t)rope3d_entries(r.frames, r.rows, r.cols, r.n_t, r.n_h, r.n_w) * 8 > kRope3dLdsBytes) return false;
-        // positions are carried in 24-bit multiplies and fp32 reciprocals there
-        if (r.frames >= (1 << 20) || r.rows >= (1 << 20) || r.cols >= (1 << 20)) return false;
-    }
-    return true;
+    const int64_t rows = s.N > 64 ? s.N : 64;
+    if (s.st.n >= kLimit / (rows * s.elem_bytes)) return false;
+    return !(rope.mode == kRopeTable && (int64_t)s.N * s.d * 4 >= kLimit);
+}
+
+// Do the factored tables fit the LDS set aside for them, and the positions the arithmetic?
+bool rope3d_fits(const Rope &rope)
+{
+    if (rope.mode != kRope3D) return true;
+    const Rope3D &r = rope.arg.r3;
+    if ((int64_t)rope3d_entries(r.frames, r.rows, r.cols, r.n_t, r.n_h, r.n_w) * 8 > kRope3dLdsBytes) return false;
+    // positions are carried in 24-bit multiplies and fp32 reciprocals there
+    return r.frames < (1 << 20) && r.rows < (1 << 20) && r.cols < (1 << 20);
+}
+
+// bf16, d >= 64: bf16 products on the matrix cores.
+bool mfma_path(const Shape &s, const Rope &rope) { return s.bf16 && s.d >= 64 && offsets_fit(s, rope) && rope3d_fits(rope); }
+
+// fp32 tokens, and bf16 at d = 32: fp32 products on the matrix cores.  What neither path takes (heads of 2 GiB and
+// more, factored tables of more than 32 KB) runs on the plain kernels of generic_kernels.hpp.
+bool f32_path(const Shape &s, const Rope &rope)
+{
+    return (!s.bf16 || s.d == 32) && offsets_fit(s, rope) && rope3d_fits(rope) && (rope.mode != kRope3D || s.N < (1 << 20));
+}
+
+// Calls f(KernelsF32<T, D, ROPE>{}) for a shape of f32_path.
+template <typename F> void with_f32_kernels(const Shape &s, int rope_mode, F &&f)
+{
+    auto pick = [&](auto t, auto D) {
+        using T = decltype(t);
+        if (rope_mode == kRope3D) f(KernelsF32<T, D(), kRope3D>{});
+        else if (rope_mode == kRopeTable) f(KernelsF32<T, D(), kRopeTable>{});
+        else f(KernelsF32<T, D(), kRopeNone>{});
+    };
+    if (s.bf16) pick(uint16_t{}, std::integral_constant<int, 32>{});
+    else with_head_dim(s.d, [&](auto D) { pick(float{}, D); });
 }
 
 sv_status check_range(const Shape &s, int32_t t0, int32_t t1)
@@ -384,7 +452,22 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
                           z_in, S_out, z_out, ws, dev, rgrid, stream);
         return launch_status();
     }
-    // fp32 validation mode, bf16 d = 32 and oversized heads: plain-FMA partials, then the fixed-order reduction
+    if (f32_path(s, rope)) {
+        with_f32_kernels(s, rope.mode, [&](auto kn) {
+            using KN = decltype(kn);
+            using T = typename KN::T;
+            const int C = plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
+            const bool resident = (int64_t)C * s.BH <= dev.f32_resident_wgs[KN::kIndex][rope.mode];
+            const auto kernel = resident ? KN::state : KN::state_partial;
+            kernel<<<dim3(C, s.BH), kThreads, KN::state_lds, stream>>>(
+                static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, t0, t1, C, S_in, z_in, S_out,
+                z_out, ws, resident ? next_epoch(s.host_epochs_only) : 0ull, spin_limit(), workgroup_order(s));
+            if (!resident)
+                state_reduce<KN::D><<<rgrid, kThreads, 0, stream>>>(wsf, C, kMaxChunks, S_in, z_in, S_out, z_out);
+        });
+        return launch_status();
+    }
+    // oversized heads and tables: plain-FMA partials, then the fixed-order reduction
     const int C = plan_chunks(s.BH, n, 32, 2 * dev.num_cu);
     const dim3 grid(C, s.BH);
     with_head_dim(s.d, [&](auto D) {
@@ -428,6 +511,20 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
             KN::apply<<<dim3(C, s.BH), KN::apply_threads, KN::apply_lds, stream>>>(
                 static_cast<const uint16_t *>(Q), static_cast<uint16_t *>(O), rope.arg, s.st, s.H, s.d, t0, t1, C, S,
                 z, eps, workgroup_order(s));
+        });
+        return launch_status();
+    }
+    if (f32_path(s, rope)) {
+        with_f32_kernels(s, rope.mode, [&](auto kn) {
+            using KN = decltype(kn);
+            using T = typename KN::T;
+            int C = f32_apply_wgs_per_cu(KN::D) * dev.num_cu / s.BH;
+            const int steps = (n + KN::apply_wg_tokens - 1) / KN::apply_wg_tokens;
+            if (C > steps) C = steps;
+            if (C < 1) C = 1;
+            KN::apply<<<dim3(C, s.BH), kThreads, KN::apply_lds, stream>>>(
+                static_cast<const T *>(Q), static_cast<T *>(O), rope.arg, s.st, s.H, t0, t1, C, S, z, eps,
+                workgroup_order(s));
         });
         return launch_status();
     }
