@@ -35,7 +35,11 @@ __host__ __device__ constexpr int block_step_lds_bytes() {
 // ROPE: keys and queries are rotated after the ReLU in the numerator path (table row = token of the block).
 // LOCAL: grid = (C * B*H) with B*H a multiple of n_dies; all workgroups of a head run on one die and
 // exchange their partial states and the new state through that die's L2 (see store_coherent).
-template <int TILE, int WAVES, int DEPTH_S, bool HILO, int DEPTH_A, int ROPE, bool LOCAL = false, bool DEN_VALU = false>
+// FEW: at most four workgroups per head (64 heads and more on 256 compute units); a workgroup alone neither publishes nor
+// waits, and the slices that one wave folds are long.  As a form of its own it leaves the other's code as short as it
+// was (both in one kernel: 0.6 % slower at eight per head).  Two blocks of 1 560 tokens, 160 heads: 83.0 -> 67.6 us, 96
+// heads 53.7 -> 49.9.
+template <int TILE, int WAVES, int DEPTH_S, bool HILO, int DEPTH_A, int ROPE, bool FEW, bool LOCAL = false, bool DEN_VALU = false>
 __global__ __launch_bounds__(64 * WAVES, 1) void block_step_mfma(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
     uint16_t *__restrict__ O, RopeArg rope, TokStrides st, int H, int N, int C,
@@ -72,6 +76,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void block_step_mfma(
     const float *Sc = S_in + (size_t)bh * d * d, *zc = z_in + (size_t)bh * d;
     float *Sh = S_out + (size_t)bh * d * d, *zh = z_out + (size_t)bh * d;
     float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems;
+    const HeadState hs{Sc, zc, Sh, zh};
     EpochSource es;
     es.begin(ws, BH, elems, epoch, bh, c, C);
     // kRope3D: the tables sit behind everything else in LDS and live through both phases
@@ -105,7 +110,8 @@ __global__ __launch_bounds__(64 * WAVES, 1) void block_step_mfma(
         }
         state_accumulate(kvstream, tileK, tileK + kTileBytes, lane, acc);
         state_wg_reduce_store<WAVES, ROPE != kRopeNone, LOCAL>(acc, reinterpret_cast<float *>(lds), wave, lane,
-                                           partials + (size_t)share * elems);   // slot = share: the fold adds the shares in tile order
+                                           partials + (size_t)share * elems,    // slot = share: the fold adds the shares in tile order
+                                           FEW && C == 1, hs);
     }
     // ---- the head agrees on its new state ------------------------------------------------------
     // Wave 0 alone waits for the head's partials, folds this workgroup's slice into S, z, publishes
@@ -114,43 +120,57 @@ __global__ __launch_bounds__(64 * WAVES, 1) void block_step_mfma(
     // complete in order, so the chain's wave keeps its own queue empty, and one wave per workgroup
     // polling is a quarter of the flag traffic.  The carried values of the slice are fetched before
     // the wait; they do not depend on the other workgroups.
-    epoch = es.resolve(reinterpret_cast<unsigned long long *>(epoch_lds));
-    int *agreed = reinterpret_cast<int *>(epoch_lds + 8);          // did both waits end in time?
-    const StateSlice sl(c, C, d);
-    f32x2 carry[5] = {};
-    if (wave == 0) state_slice_carry<kWave>(sl, Sc, zc, lane, carry);
-    if (LOCAL) {
+    if (FEW && C == 1) {
+        // the head is this workgroup's alone: its state is stored, and read back below
+        apply_prefetch<kEarly, DEPTH_A>(qstream);
         coherent_stores_done();
         wg_barrier();
-        if (threadIdx.x == 0) flag_publish<true>(ws_flags(ws, BH, elems, bh, 0) + c, flag_with_die(epoch, my_die));
     } else {
-        state_publish(ws, BH, elems, bh, c, 0, epoch);
-    }
-    if (wave != 0) {
-        apply_prefetch<kEarly, DEPTH_A>(qstream);
-    } else {
-        bool same_die = true;
-        bool ok = LOCAL ? flags_wait_all_local(ws_flags(ws, BH, elems, bh, 0), C, epoch, spin_limit, lane, my_die, &same_die)
-                        : state_wait(ws, BH, elems, bh, C, 0, epoch, spin_limit, lane);
-        ok = ok && same_die;
-        if (ok) {
-            state_finalize_slice<kWave, true, 5, 8, LOCAL>(partials, sl, C, Sc, zc, Sh, zh, lane, carry);
+        epoch = es.resolve(reinterpret_cast<unsigned long long *>(epoch_lds));
+        int *agreed = reinterpret_cast<int *>(epoch_lds + 8);          // did both waits end in time?
+        const StateSlice sl(c, C, d);
+        f32x2 carry[5] = {};
+        if (!FEW && wave == 0) hs.carried<kWave>(d, sl.lo, lane, carry);
+        if (LOCAL) {
             coherent_stores_done();
-            if (lane == 0) {
-                if (LOCAL) flag_publish<true>(ws_flags(ws, BH, elems, bh, 1) + c, flag_with_die(epoch, my_die));
-                else flag_publish(ws_flags(ws, BH, elems, bh, 1) + c, epoch);
-            }
-            ok = LOCAL ? flags_wait_all_local(ws_flags(ws, BH, elems, bh, 1), C, epoch, spin_limit, lane, my_die, &same_die)
-                       : state_wait(ws, BH, elems, bh, C, 1, epoch, spin_limit, lane);
+            wg_barrier();
+            if (threadIdx.x == 0) flag_publish<true>(ws_flags(ws, BH, elems, bh, 0) + c, flag_with_die(epoch, my_die));
+        } else {
+            state_publish(ws, BH, elems, bh, c, 0, epoch);
         }
-        if (LOCAL && !ok && lane == 0)
-            __hip_atomic_store(ws_error(ws, BH, elems), kWsTimeoutMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (lane == 0) *agreed = ok;
+        if (wave != 0) {
+            apply_prefetch<kEarly, DEPTH_A>(qstream);
+        } else {
+            bool same_die = true;
+            auto wait = [&](int phase) __attribute__((always_inline)) {
+                return LOCAL ? flags_wait_all_local(ws_flags(ws, BH, elems, bh, phase), C, epoch, spin_limit, lane, my_die, &same_die)
+                             : state_wait(ws, BH, elems, bh, C, phase, epoch, spin_limit, lane);
+            };
+            bool ok = wait(0) && same_die;
+            if (ok) {
+                if constexpr (!FEW) {
+                    state_finalize_slice<kWave, true, 5, 8, false, LOCAL>(partials, sl, C, d, hs, lane, carry);
+                } else {
+                    f32x2 first[17];                       // 17 units per lane: one or two rounds for two to four workgroups
+                    hs.carried<kWave>(d, sl.lo, lane, first);
+                    state_finalize_slice<kWave, true, 17, 4, true, LOCAL>(partials, sl, C, d, hs, lane, first);
+                }
+                coherent_stores_done();
+                if (lane == 0) {
+                    if (LOCAL) flag_publish<true>(ws_flags(ws, BH, elems, bh, 1) + c, flag_with_die(epoch, my_die));
+                    else flag_publish(ws_flags(ws, BH, elems, bh, 1) + c, epoch);
+                }
+                ok = wait(1) && same_die;
+            }
+            if (LOCAL && !ok && lane == 0)
+                __hip_atomic_store(ws_error(ws, BH, elems), kWsTimeoutMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == 0) *agreed = ok;
+        }
+        wg_barrier();
+        // A wait that ran out (recorded in the workspace): nothing more is stored, neither this workgroup's
+        // slice of S, z (if the first wait failed) nor any row of O_b.
+        if (!*agreed) return;
     }
-    wg_barrier();
-    // A wait that ran out (recorded in the workspace): nothing more is stored, neither this workgroup's
-    // slice of S, z (if the first wait failed) nor any row of O_b.
-    if (!*agreed) return;
 
     // ---- apply the updated state to this workgroup's share of Q_b --------------------------------
     ApplyOperands<64, HILO> A;
@@ -159,7 +179,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void block_step_mfma(
     A.template load_shared<true>(Sh, zh, wave, lane, lds);   // through LDS that the state phase has left and the apply phase not yet taken
     float zf[4][8];
     if (DEN_VALU) load_key_sums<true>(zh, lane, zf);
-    if (wave == 0) apply_prefetch<kEarly, DEPTH_A>(qstream);
+    if (wave == 0 && !(FEW && C == 1)) apply_prefetch<kEarly, DEPTH_A>(qstream);
     apply_tiles<HILO, DEPTH_A, ROPE, false, DEN_VALU>(qstream, lds + wave * apply_wave_lds_bytes<ROPE>(), lane, A, eps, nullptr, zf);
 }
 

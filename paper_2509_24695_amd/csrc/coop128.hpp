@@ -365,17 +365,12 @@ __global__ __launch_bounds__(256, 1) void state_mfma_d128(
     state_accumulate_coop(stream, lds, wave, lane, wave & 1, wave >> 1, acc);
 
     float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems;
-    state_wg_quadrant_store(acc, reinterpret_cast<float *>(lds), wave, lane, d, partials + (size_t)c * elems);
-    if (FINALIZE) {
+    const HeadState hs{S_in ? S_in + (size_t)bh * d * d : nullptr, z_in + (size_t)bh * d, S_out + (size_t)bh * d * d,
+                       z_out + (size_t)bh * d};
+    state_wg_quadrant_store(acc, reinterpret_cast<float *>(lds), wave, lane, d, partials + (size_t)c * elems, FINALIZE && C == 1, hs);
+    if (FINALIZE && C > 1) {
         epoch = es.resolve(reinterpret_cast<unsigned long long *>(lds + state_d128_lds_bytes<ROPE>() - kEpochLdsBytes));
-        const float *Sc = S_in ? S_in + (size_t)bh * d * d : nullptr, *zc = z_in + (size_t)bh * d;
-        const StateSlice sl(c, C, d);
-        f32x2 carry[3];
-        state_slice_carry<256>(sl, Sc, zc, (int)threadIdx.x, carry);
-        if (!state_publish_and_wait(ws, BH, elems, bh, c, C, 0, epoch, spin_limit, lane))
-            return;                                     // timed out: this wave leaves its part of S, z as it was
-        state_finalize_slice<256, false>(partials, sl, C, Sc, zc, S_out + (size_t)bh * d * d, z_out + (size_t)bh * d,
-                                         (int)threadIdx.x, carry);
+        state_agree<256>(ws, BH, elems, bh, c, C, d, epoch, spin_limit, lane, partials, hs);
     }
 }
 

@@ -257,38 +257,29 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
     }
     wg_barrier();
     float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems, *out = partials + (size_t)c * elems;
-    if constexpr (P::kSplit) {
-        constexpr int s_units = D * D / 2, units = s_units + D / 2;
-        for (int u = tid; u < units; u += kThreads) {
-            const float *src;
-            if (u < s_units) {
-                const int k = (2 * u) / D, v = 2 * u - k * D;
-                src = slots + ((k >> 6) + 2 * (v >> 6)) * P::kSlot + (k & 63) * 64 + (v & 63);
-            } else {
-                const int k = 2 * (u - s_units);
-                src = slots + (k >> 6) * P::kSlot + F * F + (k & 63);
-            }
-            store_coherent(out + 2 * u, *reinterpret_cast<const f32x2 *>(src));
-        }
-    } else {
-        constexpr int units = P::kSlot / 2;
-        for (int u = tid; u < units; u += kThreads) {
+    const HeadState hs{S_in ? S_in + (size_t)bh * D * D : nullptr, z_in + (size_t)bh * D, S_out + (size_t)bh * D * D,
+                       z_out + (size_t)bh * D};
+    auto sum = [&](int u) __attribute__((always_inline)) {
+        if constexpr (P::kSplit) {
+            const int k = (2 * u) / D, v = 2 * u - k * D, kz = 2 * u - D * D;
+            const float *src = u < D * D / 2 ? slots + ((k >> 6) + 2 * (v >> 6)) * P::kSlot + (k & 63) * 64 + (v & 63)
+                                             : slots + (kz >> 6) * P::kSlot + F * F + (kz & 63);
+            return *reinterpret_cast<const f32x2 *>(src);
+        } else {
             f32x2 x[4];
 #pragma unroll
             for (int w = 0; w < 4; ++w) x[w] = *reinterpret_cast<const f32x2 *>(slots + w * P::kSlot + 2 * u);
-            store_coherent(out + 2 * u, (x[0] + x[2]) + (x[1] + x[3]));
+            return (x[0] + x[2]) + (x[1] + x[3]);
         }
+    };
+    if (FINALIZE && C == 1) {
+        state_store_sole<kThreads>(hs, D, tid, sum);
+        return;
     }
+    for (int u = tid; u < elems / 2; u += kThreads) store_coherent(out + 2 * u, sum(u));
     if (FINALIZE) {
         epoch = es.resolve(reinterpret_cast<unsigned long long *>(lds + P::template lds_bytes<ROPE>() - kEpochLdsBytes));
-        const float *Sc = S_in ? S_in + (size_t)bh * D * D : nullptr, *zc = z_in + (size_t)bh * D;
-        const StateSlice sl(c, C, D);
-        f32x2 carry[3];
-        state_slice_carry<kThreads>(sl, Sc, zc, tid, carry);
-        if (!state_publish_and_wait(ws, BH, elems, bh, c, C, 0, epoch, spin_limit, lane))
-            return;                                 // timed out: this wave leaves its part of S, z as it was
-        state_finalize_slice<kThreads, false>(partials, sl, C, Sc, zc, S_out + (size_t)bh * D * D, z_out + (size_t)bh * D,
-                                              tid, carry);
+        state_agree<kThreads>(ws, BH, elems, bh, c, C, D, epoch, spin_limit, lane, partials, hs);
     }
 }
 

@@ -8,6 +8,7 @@
 
 #include "common.hpp"
 #include "rope.hpp"
+#include "wide_state.hpp"
 
 namespace sv {
 
@@ -102,8 +103,8 @@ __global__ __launch_bounds__(kThreads) void state_partial_generic(
 // S_in may be null or equal to S_out (in place).
 // The fixed order makes the result bit-reproducible (no float atomics).
 // grid = (ceil((D*D+D)/256), B*H).  C == 0 zero-fills or leaves the state as is.
-// Partial c of head bh starts at ws + (bh*chunk_stride + c) * (D*D+D).
-template <int D>
+// Partial c of head bh starts at ws + (bh*chunk_stride + c) * (D*D+D); WIDE: laid out by wide_word.
+template <int D, bool WIDE = false>
 __global__ __launch_bounds__(kThreads) void state_reduce(
     const float *__restrict__ ws, int C, int chunk_stride, const float *S_in, const float *z_in, float *S_out,
     float *z_out)
@@ -115,7 +116,12 @@ __global__ __launch_bounds__(kThreads) void state_reduce(
     const int64_t off = e < D * D ? (int64_t)bh * D * D + e : (int64_t)bh * D + (e - D * D);
     float *dst = (e < D * D ? S_out : z_out) + off;
     float x = S_in ? (e < D * D ? S_in : z_in)[off] : 0.f;
-    const float *p = ws + (int64_t)bh * chunk_stride * E + e;
+    int at = e;
+    if (WIDE && e < D * D) {
+        const int row = e / D, col = e - row * D;
+        at = 4 * wide_word(D, row >> 3, (row >> 2) & 1, col) + (row & 3);
+    }
+    const float *p = ws + (int64_t)bh * chunk_stride * E + at;
     for (int c = 0; c < C; ++c) x += p[(int64_t)c * E];
     *dst = x;
 }

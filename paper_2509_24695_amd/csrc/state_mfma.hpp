@@ -342,15 +342,58 @@ __device__ __forceinline__ void state_acc_to_slot(StateAcc &acc, float *dst, int
     }
 }
 
+// One head's carried state (null: none) and new state, in 8-byte units: d*d/2 of S, then d/2 of z.
+struct HeadState {
+    const float *S_in, *z_in;
+    float *S_out, *z_out;
+    // the carried values of units v0 + tid + u * THREADS, u < UNITS; past the end: any valid unit, the value is not used
+    template <int THREADS, int UNITS> __device__ __forceinline__ void carried(int d, int v0, int tid, f32x2 (&x)[UNITS]) const
+    {
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) x[u] = f32x2{0.f, 0.f};
+        if (!S_in) return;
+        const int s_units = d * d / 2, units = s_units + d / 2;
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+            int v = v0 + tid + u * THREADS;
+            v = v < units ? v : units - 1;
+            x[u] = *reinterpret_cast<const f32x2 *>(v < s_units ? S_in + 2 * v : z_in + 2 * (v - s_units));
+        }
+    }
+    __device__ __forceinline__ f32x2 *unit(int d, int v) const
+    {
+        const int s_units = d * d / 2;
+        return reinterpret_cast<f32x2 *>(v < s_units ? S_out + 2 * v : z_out + 2 * (v - s_units));
+    }
+};
+
+// Sums of a workgroup that has the head to itself: unit v of the new state = carried + sum(v), for all units.
+template <int THREADS, class SumFn>
+__device__ __forceinline__ void state_store_sole(const HeadState &hs, int d, int tid, SumFn sum)
+{
+    constexpr int kBatch = 8;
+    const int units = d * d / 2 + d / 2;
+    for (int v0 = 0; v0 < units; v0 += THREADS * kBatch) {
+        f32x2 carry[kBatch];
+        hs.carried<THREADS>(d, v0, tid, carry);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int v = v0 + tid + u * THREADS;
+            if (v < units) *hs.unit(d, v) = carry[u] + sum(v);
+        }
+    }
+}
+
 // d = 64: adds the WAVES waves' accumulators in a fixed tree order and stores the
 // workgroup's partial state, S in [k][v] order followed by z, to `out`
 // (kStateElems floats) with coherent stores spread over all threads: after one
 // barrier each thread adds the waves' slots for its share of the elements,
 // wave w absorbing wave w + h for h = WAVES/2, ..., 1.  Must be called by all
 // threads; the staging tiles are dead afterwards.  LDS: WAVES * kStateElems floats.
+// `sole`: the workgroup has the head to itself, its sums go straight into the new state.
 template <int WAVES, bool ZVALU, bool LOCAL = false>
 __device__ __forceinline__ void state_wg_reduce_store(StateAcc &acc, float *slots, int wave, int lane,
-                                                      float *__restrict__ out)
+                                                      float *__restrict__ out, bool sole, const HeadState &hs)
 {
     constexpr int THREADS = 64 * WAVES;
     wg_barrier();                                   // all waves are done with their staging tiles
@@ -374,7 +417,16 @@ __device__ __forceinline__ void state_wg_reduce_store(StateAcc &acc, float *slot
 #pragma unroll
             for (int w = 0; w < h; ++w) x[r][w] += x[r][w + h];
         const int v = (int)threadIdx.x + r * THREADS;
-        if (v < kUnits) store_coherent<LOCAL>(out + 2 * v, x[r][0]);
+        if (!sole && v < kUnits) store_coherent<LOCAL>(out + 2 * v, x[r][0]);
+    }
+    if (sole) {
+        f32x2 carry[kRounds];
+        hs.carried<THREADS>(64, 0, (int)threadIdx.x, carry);
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int v = (int)threadIdx.x + r * THREADS;
+            if (v < kUnits) *hs.unit(64, v) = carry[r] + x[r][0];
+        }
     }
 }
 
@@ -383,13 +435,13 @@ __device__ __forceinline__ void state_wg_reduce_store(StateAcc &acc, float *slot
 // (row length d) followed by the d key sums (taken from the waves of value
 // block 0) and stored to `out` (d*d + d floats) with coherent stores.
 __device__ __forceinline__ void state_wg_quadrant_store(StateAcc &acc, float *slots, int wave, int lane, int d,
-                                                        float *__restrict__ out)
+                                                        float *__restrict__ out, bool sole, const HeadState &hs)
 {
     wg_barrier();                                   // all waves are done with their staging tiles
     state_acc_to_slot<false>(acc, slots + wave * kStateElems, lane);
     wg_barrier();
     const int s_units = d * d / 2, units = s_units + d / 2;
-    for (int u = threadIdx.x; u < units; u += 4 * kWave) {
+    auto sum = [&](int u) __attribute__((always_inline)) {
         const float *src;
         if (u < s_units) {
             const int k = (2 * u) / d, v = 2 * u - k * d;
@@ -398,70 +450,50 @@ __device__ __forceinline__ void state_wg_quadrant_store(StateAcc &acc, float *sl
             const int k = 2 * (u - s_units);
             src = slots + (k >> 6) * kStateElems + 64 * 64 + (k & 63);
         }
-        store_coherent(out + 2 * u, *reinterpret_cast<const f32x2 *>(src));
+        return *reinterpret_cast<const f32x2 *>(src);
+    };
+    if (sole) {
+        state_store_sole<4 * kWave>(hs, d, (int)threadIdx.x, sum);
+        return;
     }
-}
-
-// The carried values (S_in, z_in; zeros if S_in is null) of the units a thread folds first.  They do
-// not depend on the other workgroups, so they are fetched before the wait for the partials, off
-// the chain of round trips that follows it.
-template <int THREADS, int UNITS>
-__device__ __forceinline__ void state_slice_carry(const StateSlice &sl, const float *S_in, const float *z_in, int tid,
-                                                  f32x2 (&x)[UNITS])
-{
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) x[u] = f32x2{0.f, 0.f};
-    if (S_in) {
-#pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-            int v = sl.lo + tid + u * THREADS;               // beyond the slice: any valid unit, the value is not used
-            v = v < sl.units ? v : sl.units - 1;
-            x[u] = *reinterpret_cast<const f32x2 *>(v < sl.s_units ? S_in + 2 * v : z_in + 2 * (v - sl.s_units));
-        }
-    }
+    for (int u = threadIdx.x; u < units; u += 4 * kWave) store_coherent(out + 2 * u, sum(u));
 }
 
 //   S_out, z_out = (S_in, z_in or 0) + partial[0] + partial[1] + ... + partial[C-1], in that order,
 // for the slice.  S_in may be null (no carried state) or equal to S_out (update in place); `carry`
-// holds what state_slice_carry fetched.  Partials come in through coherent loads, GROUP chunks in
+// holds the carried values of the first round, which do not depend on the other workgroups: they are fetched before
+// the wait for the partials, off the chain of round trips that follows it.  Partials come in through coherent loads, GROUP chunks in
 // flight per unit: the loads of a round trip of ~1 us are all issued before any is used.
 // COHERENT_OUT: also store the result coherently (other workgroups of this kernel are going to
 // read it).  Called by THREADS threads numbered tid = 0 .. THREADS - 1 (a workgroup, or one wave).
-template <int THREADS, bool COHERENT_OUT, int UNITS = 3, int GROUP = 16, bool LOCAL = false>
-__device__ __forceinline__ void state_finalize_slice(const float *__restrict__ partials, const StateSlice &sl, int C,
-                                                     const float *S_in, const float *z_in, float *S_out,
-                                                     float *z_out, int tid, const f32x2 (&carry)[UNITS])
+template <int THREADS, bool COHERENT_OUT, int UNITS, int GROUP, bool MASKED, bool LOCAL = false>
+__device__ __forceinline__ void state_finalize_slice(const float *__restrict__ partials, const StateSlice &sl, int C, int d,
+                                                     const HeadState &hs, int tid, const f32x2 (&carry)[UNITS])
 {
-    const int s_units = sl.s_units, elems = 2 * sl.units, hi = sl.hi;
+    const int elems = 2 * sl.units, hi = sl.hi;
+    const rsrc_t rP = make_rsrc(partials, (uint32_t)(C * elems) * 4u);
     for (int v0 = sl.lo + tid; v0 < hi; v0 += THREADS * UNITS) {
         f32x2 x[UNITS];
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) x[u] = carry[u];
-        if (v0 != sl.lo + tid) {                                 // slices longer than one round: fetched here
-#pragma unroll
-            for (int u = 0; u < UNITS; ++u) {
-                const int v = v0 + u * THREADS;
-                x[u] = f32x2{0.f, 0.f};
-                if (S_in && v < hi) x[u] = *reinterpret_cast<const f32x2 *>(v < s_units ? S_in + 2 * v : z_in + 2 * (v - s_units));
-            }
-        }
-        // Straight-line loads: a wave-uniform base per partial plus one 32-bit offset per unit, no branch (a group
-        // that reaches past C re-reads the last partial and leaves it out of the sum).  This runs on the chain of
-        // round trips by which a head agrees on its state, where every instruction counts.
-        uint32_t off[UNITS];
-#pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-            int v = v0 + u * THREADS;                            // beyond the slice: any valid unit, the sum is not stored
-            v = v < sl.units ? v : sl.units - 1;
-            off[u] = 2u * (uint32_t)v;
-        }
+        if (v0 != sl.lo + tid) hs.carried<THREADS>(d, v0 - tid, tid, x);   // slices longer than one round: fetched here
+        // Straight-line loads without a branch: this runs on the chain of round trips by which a head agrees on its
+        // state, where every instruction counts.  MASKED: units past the slice and partials past C are addressed out of range
+        // and read nothing (two instructions per load; a group or a round that fits badly would read several times what
+        // it needs: 128 heads of 64, 1 560 tokens 35.9 -> 33.1 us); otherwise the last partial and unit are read again.
         for (int c0 = 0; c0 < C; c0 += GROUP) {
             f32x2 p[UNITS][GROUP];
 #pragma unroll
             for (int cc = 0; cc < GROUP; ++cc) {
-                const float *part = partials + (size_t)(c0 + cc < C ? c0 + cc : C - 1) * elems;
+                const int at = c0 + cc < C ? c0 + cc : C - 1;
 #pragma unroll
-                for (int u = 0; u < UNITS; ++u) p[u][cc] = load_coherent(part + off[u]);
+                for (int u = 0; u < UNITS; ++u) {
+                    const int v = v0 + u * THREADS;
+                    if (MASKED)
+                        p[u][cc] = load_coherent8(rP, v < hi && c0 + cc < C ? 8u * (uint32_t)v + (uint32_t)(at * elems) * 4u : kOutOfRange);
+                    else
+                        p[u][cc] = load_coherent(partials + (size_t)at * elems + 2u * (uint32_t)(v < sl.units ? v : sl.units - 1));
+                }
             }
 #pragma unroll
             for (int u = 0; u < UNITS; ++u)
@@ -473,9 +505,9 @@ __device__ __forceinline__ void state_finalize_slice(const float *__restrict__ p
         for (int u = 0; u < UNITS; ++u) {
             const int v = v0 + u * THREADS;
             if (v < hi) {
-                float *dst = v < s_units ? S_out + 2 * v : z_out + 2 * (v - s_units);
-                if (COHERENT_OUT) store_coherent<LOCAL>(dst, x[u]);
-                else *reinterpret_cast<f32x2 *>(dst) = x[u];
+                f32x2 *dst = hs.unit(d, v);
+                if (COHERENT_OUT) store_coherent<LOCAL>(reinterpret_cast<float *>(dst), x[u]);
+                else *dst = x[u];
             }
         }
     }
@@ -510,6 +542,31 @@ __device__ __forceinline__ bool state_publish_and_wait(void *ws, int BH, int ele
 {
     state_publish(ws, BH, elems, bh, c, phase, epoch);
     return state_wait(ws, BH, elems, bh, C, phase, epoch, spin_limit, lane);
+}
+
+// Publishes the workgroup's partial and, once all C partials of the head are there, folds its slice of them.  All threads of
+// the workgroup call.  Few contributors make long slices: more units per thread and fewer partials in flight for each,
+// so that a slice stays one or two round trips (a group of 16 for C = 1 re-read one partial 16 times over eight rounds:
+// 10 us of a 24 us kernel at d = 128).
+template <int THREADS, int UNITS, int GROUP, class WaitFn>
+__device__ __forceinline__ void state_fold(const float *partials, const StateSlice &sl, int C, int d, const HeadState &hs,
+                                           WaitFn wait)
+{
+    f32x2 carry[UNITS];
+    hs.carried<THREADS>(d, sl.lo, (int)threadIdx.x, carry);
+    if (!wait()) return;                                // timed out: this wave leaves its part of S, z as it was
+    state_finalize_slice<THREADS, false, UNITS, GROUP, true>(partials, sl, C, d, hs, (int)threadIdx.x, carry);
+}
+template <int THREADS>
+__device__ __forceinline__ void state_agree(void *ws, int BH, int elems, int bh, int c, int C, int d, unsigned long long epoch,
+                                            uint32_t spin_limit, int lane, const float *partials, const HeadState &hs)
+{
+    const StateSlice sl(c, C, d);
+    auto wait = [&]() __attribute__((always_inline)) {
+        return state_publish_and_wait(ws, BH, elems, bh, c, C, 0, epoch, spin_limit, lane);
+    };
+    if (C <= 4) state_fold<THREADS, 8, 4>(partials, sl, C, d, hs, wait);
+    else state_fold<THREADS, 3, 16>(partials, sl, C, d, hs, wait);
 }
 
 // Dynamic LDS of state_mfma: staging tiles or reduction slots.
@@ -565,18 +622,13 @@ __global__ __launch_bounds__(64 * WAVES, 1) void state_mfma_d64(
     state_accumulate(stream, tileK, tileK + kTileBytes, lane, acc);
 
     float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * kStateElems;
+    const HeadState hs{S_in ? S_in + (size_t)bh * 64 * 64 : nullptr, z_in + (size_t)bh * 64, S_out + (size_t)bh * 64 * 64,
+                       z_out + (size_t)bh * 64};
     state_wg_reduce_store<WAVES, ROPE != kRopeNone>(acc, reinterpret_cast<float *>(lds), wave, lane,
-                                                    partials + (size_t)c * kStateElems);
-    if (FINALIZE) {
+                                                    partials + (size_t)c * kStateElems, FINALIZE && C == 1, hs);
+    if (FINALIZE && C > 1) {
         epoch = es.resolve(reinterpret_cast<unsigned long long *>(lds + state_lds_bytes<TILE, WAVES>() - kEpochLdsBytes));
-        const float *Sc = S_in ? S_in + (size_t)bh * 64 * 64 : nullptr, *zc = z_in + (size_t)bh * 64;
-        const StateSlice sl(c, C, 64);
-        f32x2 carry[3];
-        state_slice_carry<THREADS>(sl, Sc, zc, tid, carry);
-        if (!state_publish_and_wait(ws, BH, kStateElems, bh, c, C, 0, epoch, spin_limit, lane))
-            return;                                     // timed out: this wave leaves its part of S, z as it was
-        state_finalize_slice<THREADS, false>(partials, sl, C, Sc, zc, S_out + (size_t)bh * 64 * 64,
-                                             z_out + (size_t)bh * 64, tid, carry);
+        state_agree<THREADS>(ws, BH, kStateElems, bh, c, C, 64, epoch, spin_limit, lane, partials, hs);
     }
 }
 

@@ -4,6 +4,7 @@
 #include "../../include/sv_measure.h"
 
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <math.h>
 
 #include <atomic>
@@ -78,13 +79,18 @@ template <int DP, int ROPE, bool SHARED = false> struct Kernels;
 template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
     static constexpr int W = 0;
+    static constexpr bool kWideState = false;
     static constexpr auto state = state_mfma_d64<kStateTile, kStateWaves, kStateDepth, true, ROPE>;
     static constexpr auto state_partial = state_mfma_d64<kStateTile, kStateWaves, kStateDepth, false, ROPE>;
     static constexpr auto apply = apply_mfma_d64<kApplyHiLo, kApplyWaves, kApplyDepth, ROPE, false, kDenValu>;
-    static constexpr auto fused = block_step_mfma<kStateTile, kStateWaves, kFusedStateDepth[ROPE], kApplyHiLo,
-                                                  kFusedApplyDepth[ROPE], ROPE, false, kDenValu>;
-    static constexpr auto fused_local = block_step_mfma<kStateTile, kStateWaves, kFusedStateDepth[ROPE], kApplyHiLo,
-                                                        kFusedApplyDepth[ROPE], ROPE, true, kDenValu>;
+    template <bool FEW, bool LOCAL>
+    static constexpr auto fused_form = block_step_mfma<kStateTile, kStateWaves, kFusedStateDepth[ROPE], kApplyHiLo,
+                                                       kFusedApplyDepth[ROPE], ROPE, FEW, LOCAL, kDenValu>;
+    // the one-launch block step for C workgroups per head; the full-table form has no die-local variant
+    static auto fused(int C, bool local) {
+        if (ROPE != kRopeTable && local) return C <= 4 ? fused_form<true, ROPE != kRopeTable> : fused_form<false, ROPE != kRopeTable>;
+        return C <= 4 ? fused_form<true, false> : fused_form<false, false>;
+    }
     static constexpr int state_lds = state_lds_bytes<kStateTile, kStateWaves>() + kTab;
     static constexpr int apply_lds = apply_lds_bytes<kApplyWaves, ROPE>() + kTab;
     static constexpr int fused_lds = block_step_lds_bytes<kStateTile, kStateWaves, ROPE>() + kTab;
@@ -157,12 +163,16 @@ template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::apply), attr, KN::apply_lds);
     int per_cu = 0;
     if constexpr (DP == 64) {                      // the one-launch block step exists for d = 64 only
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::fused), attr, KN::fused_lds);
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::fused_local), attr, KN::fused_lds);
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(KN::fused),
-                                                         64 * kStateWaves, KN::fused_lds) != hipSuccess)
-            per_cu = 0;
-        d.fused_resident_wgs[ROPE] = per_cu * d.num_cu;
+        int least = INT_MAX;
+        for (int C : {1, 8})
+            for (bool local : {false, true}) {
+                const auto kernel = reinterpret_cast<const void *>(KN::fused(C, local));
+                (void)hipFuncSetAttribute(kernel, attr, KN::fused_lds);
+                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * kStateWaves, KN::fused_lds) != hipSuccess)
+                    per_cu = 0;
+                least = per_cu < least ? per_cu : least;
+            }
+        d.fused_resident_wgs[ROPE] = least * d.num_cu;
         per_cu = 0;
     }
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(KN::state),
@@ -423,8 +433,8 @@ void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, c
             KN::state_partial<<<dim3(C, s.BH), 64 * kStateWaves, KN::state_lds, stream>>>(
                 k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, 0ull, 0u, workgroup_order(s));
             with_head_dim(s.d, [&](auto D) {
-                state_reduce<D()><<<rgrid, kThreads, 0, stream>>>(static_cast<float *>(ws), C, kMaxChunks, S_in, z_in,
-                                                                 S_out, z_out);
+                state_reduce<D(), KN::kWideState><<<rgrid, kThreads, 0, stream>>>(static_cast<float *>(ws), C, kMaxChunks,
+                                                                                 S_in, z_in, S_out, z_out);
             });
         }
     });
@@ -644,6 +654,9 @@ sv_status do_block_step(const void *Qb, const void *Kb, const void *Vb, const sv
             // One launch when the whole grid can be resident at once (needed by the in-kernel waits).
             const int C = plan_chunks(s.BH, s.N, KN::fused_wg_tokens, dev.num_cu);
             if ((int64_t)C * s.BH > dev.fused_resident_wgs[rope.mode]) return;
+            // A head per workgroup and a long block: two launches, whose apply fills the device whatever the number of
+            // heads (4 680 tokens, 160 heads: 75.3 against 79.6 us; 1 560 tokens: 38.5 against 33.8).
+            if (C == 1 && s.N > 3072) return;
             // Die-local form: consecutive workgroup ids go round the device's dies, so with B*H a multiple of the
             // die count every head can have all its workgroups on one die and agree on its state through that
             // die's L2 (23.2 against 24.4 us per 4 680-token block, 38.8 against 40.1 us per 10 800-token block).
@@ -652,16 +665,11 @@ sv_status do_block_step(const void *Qb, const void *Kb, const void *Vb, const sv
             // A full rotation table stays with the general form: there die c reads chunk c of every head, so each
             // table row reaches one L2 only; with whole heads on a die all eight would fetch every row.
             const int dies = g_assumed_dies.load(std::memory_order_relaxed);
-            if (dev.num_cu == kDies * kCusPerDie && s.BH % dies == 0 && rope.mode != kRopeTable)
-                KN::fused_local<<<dim3(C * s.BH), 64 * kStateWaves, KN::fused_lds, hs>>>(
-                    static_cast<const uint16_t *>(Qb), static_cast<const uint16_t *>(Kb),
-                    static_cast<const uint16_t *>(Vb), static_cast<uint16_t *>(Ob), rope.arg, s.st, s.H, s.N, C, S_in,
-                    z_in, S_out, z_out, eps, workspace, next_epoch(s.host_epochs_only), spin_limit(), s.BH, dies);
-            else
-                KN::fused<<<dim3(C, s.BH), 64 * kStateWaves, KN::fused_lds, hs>>>(
-                    static_cast<const uint16_t *>(Qb), static_cast<const uint16_t *>(Kb),
-                    static_cast<const uint16_t *>(Vb), static_cast<uint16_t *>(Ob), rope.arg, s.st, s.H, s.N, C, S_in,
-                    z_in, S_out, z_out, eps, workspace, next_epoch(s.host_epochs_only), spin_limit(), s.BH, 0);
+            const bool local = dev.num_cu == kDies * kCusPerDie && s.BH % dies == 0 && rope.mode != kRopeTable;
+            KN::fused(C, local)<<<local ? dim3(C * s.BH) : dim3(C, s.BH), 64 * kStateWaves, KN::fused_lds, hs>>>(
+                static_cast<const uint16_t *>(Qb), static_cast<const uint16_t *>(Kb), static_cast<const uint16_t *>(Vb),
+                static_cast<uint16_t *>(Ob), rope.arg, s.st, s.H, s.N, C, S_in, z_in, S_out, z_out, eps, workspace,
+                next_epoch(s.host_epochs_only), spin_limit(), s.BH, local ? dies : 0);
             launched = true;
         };
         if (rope.mode == kRope3D) launch(Kernels<64, kRope3D>{});

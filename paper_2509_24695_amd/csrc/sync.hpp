@@ -37,6 +37,10 @@ __device__ __forceinline__ f32x2 load_coherent(const float *p) {
     return __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p),
                                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
+// ... through a buffer resource: byte offsets at or past the resource's size read zeros.
+__device__ __forceinline__ f32x2 load_coherent8(rsrc_t r, uint32_t off) {
+    return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 16 /* sc1 */));
+}
 __device__ __forceinline__ float load_coherent1(const float *p) {
     return __builtin_bit_cast(float, __hip_atomic_load(reinterpret_cast<const unsigned int *>(p), __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_AGENT));

@@ -222,24 +222,60 @@ __device__ __forceinline__ void wide_recv_add(const unsigned char *region, int l
         __builtin_amdgcn_sched_barrier(0);
     }
 }
-// Adds the four waves' states in the fixed order (w0 + w2) + (w1 + w3) and stores the workgroup's
-// partial (d x d, row length d, then the d key sums) to `out` with coherent stores.  Must be called
-// by all threads; the tiles and tables in LDS are dead afterwards.
+// Layout of a partial state in the workspace: 16-byte words in the order in which the accumulators hold them, so that
+// storing one takes 16 instructions per lane instead of 64 and folding it needs a third of the loads that 8-byte units
+// of rows took.  A word is four consecutive rows of one column of S; R = row / 8, g = row / 4 % 2:
+//   word(row, col) = R * 2 d + 64 (col / 32) + 32 g + col % 32     (the last, half-wide column block of d = 112: 16 g)
+// which fills d*d/4 words without gaps; the d/4 words of the key sums follow.
+__host__ __device__ __forceinline__ int wide_word(int d, int R, int g, int col)
+{
+    return R * 2 * d + (col & ~31) * 2 + (d < 128 && col >= 96 ? 16 : 32) * g + (col & 31);
+}
+// First row (of four) and column of word v of the S part.
+__device__ __forceinline__ void wide_word_at(int d, int v, int &row, int &col)
+{
+    const int R = v / (2 * d), x = v - R * 2 * d, cb = x >> 6, y = x & 63;
+    const bool narrow = d < 128 && cb == 3;
+    row = 8 * R + 4 * (narrow ? y >> 4 : y >> 5);
+    col = 32 * cb + (narrow ? y & 15 : y & 31);
+}
+struct WideSlice {                   // words [lo, hi) of the s_words + d/4: what contributor c of C folds
+    int s_words, words, lo, hi;
+    __device__ __forceinline__ WideSlice(int c, int C, int d) : s_words(d * d / 4), words(d * d / 4 + d / 4)
+    {
+        const int per = (words + C - 1) / C;
+        lo = c * per < words ? c * per : words;
+        hi = lo + per < words ? lo + per : words;
+    }
+};
+
+// What a workgroup knows about its part of one head: it is contributor c of the C whose partials make the head's state.
+struct WideTarget {
+    const float *S_in, *z_in;        // carried state of the head, or null
+    float *S_out, *z_out;
+    float *partials;                 // the head's partials
+    int d, c, C;
+};
+
+// Adds the four waves' states in the fixed order (w0 + w2) + (w1 + w3) and stores the sum: as the workgroup's
+// partial, with coherent stores, or, if the workgroup is the head's only contributor and FINALIZE, added to the
+// carried state as the new state.  Must be called by all threads; the tiles and tables in LDS are dead afterwards.
 //
 // Two exchanges in the registers' own layout, each halving what a wave still owns: waves w and w ^ 2
 // swap the halves of S the other one keeps (32 KB each way) and add, then w and w ^ 1 swap one band
 // of 32 key features (16 KB).  Wave w ends with band w of the sum and stores it straight from its
-// accumulators, 32 consecutive floats of two rows per instruction.  Because block r of wave w holds
-// key block r ^ w (see WideAcc), the blocks that go out are blocks 2, 3 and then block 1 in every
-// wave, and a parcel's block meets the same key features at the receiver: one code path, whose only
-// dependence on the wave is in addresses.  192 KB go through LDS in 16-byte words; laying all four
-// states out row-major and re-reading them (256 KB of 4-byte writes, which move 64 bytes a clock, and
-// as much again in reads) took 4.8 us of a 22 us kernel.
+// accumulators.  Because block r of wave w holds key block r ^ w (see WideAcc), the blocks that go out are
+// blocks 2, 3 and then block 1 in every wave, and a parcel's block meets the same key features at the
+// receiver: one code path, whose only dependence on the wave is in addresses.  192 KB go through LDS in
+// 16-byte words; laying all four states out row-major and re-reading them (256 KB of 4-byte writes, which
+// move 64 bytes a clock, and as much again in reads) took 4.8 us of a 22 us kernel.
 // A wave's second parcel goes where it read its first (nobody else touches that region any more),
 // so the exchanges need one barrier each.
-__device__ __forceinline__ void wide_state_wg_reduce_store(WideAcc &acc, unsigned char *lds, int wave, int lane, int d,
-                                                           float *__restrict__ out)
+template <bool FINALIZE>
+__device__ __forceinline__ void wide_state_wg_reduce_store(WideAcc &acc, unsigned char *lds, int wave, int lane,
+                                                           const WideTarget &t)
 {
+    const int d = t.d;
     float *zs = reinterpret_cast<float *>(lds + kWideZOffset);  // [wave][128]
     // key sums: lanes with equal lane % 16 hold the same eight features
 #pragma unroll
@@ -273,17 +309,40 @@ __device__ __forceinline__ void wide_state_wg_reduce_store(WideAcc &acc, unsigne
                      [&](int b) -> f32x16 & { return fin[b]; });
     // element i of block cb: row 32 wave + 8 (i / 4) + 4 (lane / 32) + i % 4, column 32 cb + lane % 32.
     // Rows past d lie past the resource's end, columns past d are sent there: both are dropped.
-    const int n = lane & 31, g = lane >> 5;
-    const rsrc_t rS = make_rsrc(out, (uint32_t)d * (uint32_t)d * 4u);
-    const uint32_t base = ((uint32_t)(32 * wave + 4 * g) * (uint32_t)d + (uint32_t)n) * 4u;
+    const int n = lane & 31, g = lane >> 5, half = d / 2;
+    const uint32_t s_bytes = (uint32_t)d * (uint32_t)d * 4u;
+    if (FINALIZE && t.C == 1) {
+        const rsrc_t rS = make_rsrc(t.S_out, s_bytes), rI = make_rsrc(t.S_in ? t.S_in : t.S_out, t.S_in ? s_bytes : 0u);
+        const uint32_t base = ((uint32_t)(32 * wave + 4 * g) * (uint32_t)d + (uint32_t)n) * 4u;
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            const uint32_t col = 32 * cb + n < d ? base + 128u * cb : kOutOfRange;
+            float x[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                           rI, col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0));
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x[i] + fin[cb][i]), rS,
+                                                      col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0);
+        }
+        for (int u = threadIdx.x; u < d; u += 4 * kWave)
+            t.z_out[u] = (t.S_in ? t.z_in[u] : 0.f) + ((zs[u] + zs[256 + u]) + (zs[128 + u] + zs[384 + u]));
+        return;
+    }
+    float *out = t.partials + (size_t)t.c * (d * d + d);
+    const rsrc_t rP = make_rsrc(out, s_bytes);
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) {
-        const uint32_t col = 32 * cb + n < d ? base + 128u * cb : kOutOfRange;
+        const uint32_t base = 32 * cb + n < d ? 16u * (uint32_t)wide_word(d, 4 * wave, g, 32 * cb + n) : kOutOfRange;
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            store_coherent4(rS, col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, fin[cb][i]);
+        for (int q = 0; q < 4; ++q) {
+            f32x4 x;
+            x.x = fin[cb][4 * q];  x.y = fin[cb][4 * q + 1];  x.z = fin[cb][4 * q + 2];  x.w = fin[cb][4 * q + 3];
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rP, base + (uint32_t)(q * 32 * d), 0, 16 /* sc1 */);
+        }
     }
-    const int half = d / 2;
     for (int u = threadIdx.x; u < half; u += 4 * kWave) {
         const int k = 2 * u;
         f32x2 x;
@@ -293,9 +352,77 @@ __device__ __forceinline__ void wide_state_wg_reduce_store(WideAcc &acc, unsigne
     }
 }
 
+// Contributor t.c's slice of the head: publishes its partial, waits for the others (`wait`) and stores
+//   S_out, z_out = (S_in, z_in or 0) + partial[0] + partial[1] + ... + partial[C-1], in that order.
+// UNITS words per thread and round, GROUP partials in flight per word; the carried values of the first round, which do
+// not depend on the other workgroups, are fetched before the wait.  Called by all threads.
+template <int UNITS, int GROUP, class WaitFn>
+__device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
+{
+    const WideSlice sl(t.c, t.C, t.d);
+    const int d = t.d, tid = (int)threadIdx.x;
+    const rsrc_t rP = make_rsrc(t.partials, (uint32_t)t.C * (uint32_t)(d * d + d) * 4u);
+    auto carried = [&](int v0, f32x4 (&x)[UNITS]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (!t.S_in) return;
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+            int v = v0 + u * kThreads;                           // beyond the slice: any valid word, the value is not used
+            v = v < sl.words ? v : sl.words - 1;
+            if (v < sl.s_words) {
+                int row, col;
+                wide_word_at(d, v, row, col);
+                const float *p = t.S_in + row * d + col;
+                x[u] = f32x4{p[0], p[d], p[2 * d], p[3 * d]};
+            } else {
+                x[u] = *reinterpret_cast<const f32x4 *>(t.z_in + 4 * (v - sl.s_words));
+            }
+        }
+    };
+    f32x4 x[UNITS];
+    carried(sl.lo + tid, x);
+    if (!wait()) return;                                         // timed out: this wave leaves its part of S, z as it was
+    for (int v0 = sl.lo + tid; v0 < sl.hi; v0 += kThreads * UNITS) {
+        if (v0 != sl.lo + tid) carried(v0, x);
+        for (int c0 = 0; c0 < t.C; c0 += GROUP) {
+            f32x4 p[UNITS][GROUP];
+#pragma unroll
+            for (int cc = 0; cc < GROUP; ++cc) {
+                // past the last partial and past the slice: out of range, nothing is read
+                const uint32_t part = (uint32_t)(c0 + cc) * (uint32_t)(d * d + d) * 4u;
+#pragma unroll
+                for (int u = 0; u < UNITS; ++u) {
+                    const int v = v0 + u * kThreads;
+                    p[u][cc] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                   rP, v < sl.hi && c0 + cc < t.C ? 16u * (uint32_t)v + part : kOutOfRange, 0, 16 /* sc1 */));
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < UNITS; ++u)
+#pragma unroll
+                for (int cc = 0; cc < GROUP; ++cc)
+                    if (c0 + cc < t.C) x[u] += p[u][cc];
+        }
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+            const int v = v0 + u * kThreads;
+            if (v >= sl.hi) continue;
+            if (v < sl.s_words) {
+                int row, col;
+                wide_word_at(d, v, row, col);
+                float *p = t.S_out + row * d + col;
+                p[0] = x[u].x;  p[d] = x[u].y;  p[2 * d] = x[u].z;  p[3 * d] = x[u].w;
+            } else {
+                *reinterpret_cast<f32x4 *>(t.z_out + 4 * (v - sl.s_words)) = x[u];
+            }
+        }
+    }
+}
+
 // grid = (C, B*H), block = 256.  Wave w of workgroup c owns tiles 4c + w + 4C i of the
 // T = ceil((t1 - t0) / 16) tiles.  FINALIZE as in state_mfma_d64.  ROPE: kRopeNone or kRope3D (the
-// table rows of kRopeTable do not fit in the registers left beside the state).
+// table rows of kRopeTable do not fit in the registers left beside the state).  Partials are laid out by wide_word.
 template <int DEPTH, bool FINALIZE, int ROPE, bool NT>
 __global__ __launch_bounds__(256, 1) void state_mfma_wide(
     const uint16_t *__restrict__ K, const uint16_t *__restrict__ V, RopeArg rope, TokStrides st,
@@ -330,18 +457,18 @@ __global__ __launch_bounds__(256, 1) void state_mfma_wide(
     unsigned char *tileK = lds + wave * 2 * kWideTileBytes, *tileV = tileK + kWideTileBytes;
     wide_state_accumulate(stream, tileK, tileV, wave, lane, acc);
 
-    float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems;
-    wide_state_wg_reduce_store(acc, lds, wave, lane, d, partials + (size_t)c * elems);
-    if (FINALIZE) {
+    WideTarget target{S_in ? S_in + (size_t)bh * d * d : nullptr, z_in + (size_t)bh * d, S_out + (size_t)bh * d * d,
+                      z_out + (size_t)bh * d, static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems, d, c, C};
+    wide_state_wg_reduce_store<FINALIZE>(acc, lds, wave, lane, target);
+    if (FINALIZE && C > 1) {
         epoch = es.resolve(reinterpret_cast<unsigned long long *>(lds + kWideEpochOffset));
-        const float *Sc = S_in ? S_in + (size_t)bh * d * d : nullptr, *zc = z_in + (size_t)bh * d;
-        const StateSlice sl(c, C, d);
-        f32x2 carry[3];
-        state_slice_carry<256>(sl, Sc, zc, (int)threadIdx.x, carry);
-        if (!state_publish_and_wait(ws, BH, elems, bh, c, C, 0, epoch, spin_limit, lane))
-            return;                                     // timed out: this wave leaves its part of S, z as it was
-        state_finalize_slice<256, false>(partials, sl, C, Sc, zc, S_out + (size_t)bh * d * d, z_out + (size_t)bh * d,
-                                         (int)threadIdx.x, carry);
+        auto wait = [&]() __attribute__((always_inline)) {
+            return state_publish_and_wait(ws, BH, elems, bh, c, C, 0, epoch, spin_limit, lane);
+        };
+        if (C <= 2) wide_fold<8, 2>(target, wait);
+        else if (C <= 4) wide_fold<4, 4>(target, wait);
+        else if (C <= 8) wide_fold<3, 8>(target, wait);
+        else wide_fold<2, 12>(target, wait);
     }
 }
 
