@@ -439,7 +439,7 @@ def bench_tconv(w, iters, sv, torch):
         names = ["library kernel", "without the loads into LDS", "without the operand reads from LDS", "without both"]
         loop_variants = {names[v]: variant_us(v) for v in range(4)}
         loop_variants["library kernel, timed again"] = variant_us(0)
-    wg_flops = k_steps * 4 * 32 * 2 * 32 * 32 * 16
+    wg_flops = k_steps * 4 * 64 * 2 * 16 * 16 * 32
     return {"workload": f"{w.name}: B={w.B} T={w.T} HW={w.HW} D={w.D}, {w.n_blocks} block(s)", "us_per_block": us,
             "tokens_per_s": w.tokens / (us * 1e-6), "dtype": "bf16",
             "roofline": {"bound": "mfma", "kernel": "tconv_mfma", "achieved": tflops, "peak": MFMA_BF16_PEAK_TFLOPS,

@@ -35,7 +35,7 @@ sv_status sv_stream_read(const void *src, size_t bytes, void *sink, int32_t wgs,
 sv_status sv_stream_copy(const void *src, void *dst, size_t bytes, int32_t wgs, void *stream);
 
 /* The matrix-core instruction stream of the temporal convolution (sv_tconv.h) with everything else taken
- * away: `wgs` workgroups of four waves, each wave issuing 32 * steps v_mfma_f32_32x32x16_bf16 on a 4 x 4 grid
+ * away: `wgs` workgroups of four waves, each wave issuing 64 * steps v_mfma_f32_16x16x32_bf16 on an 8 x 8 grid
  * of accumulators from operands that stay in registers (one 256 x 256 output tile of the convolution is
  * steps = 3 * D / 32; a workgroup does steps * 4 194 304 flop).  What this device gives that stream at a given
  * number of busy compute units is the ceiling of any kernel built on it.  `sink` is 4 bytes of device memory,

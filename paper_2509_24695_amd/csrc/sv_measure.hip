@@ -45,10 +45,10 @@ __global__ __launch_bounds__(kThreads) void stream_copy(const u32x4 *__restrict_
 }
 
 // What one workgroup of the temporal convolution issues per K-step of 32, and nothing else: four waves, each
-// 2 x 16 MFMAs (32x32x16 bf16) on a 4 x 4 grid of accumulators, operands held in registers (two sets taken in
-// turn, as the convolution alternates its two operand buffers).  No LDS, no memory traffic, no barrier.
+// 64 MFMAs (16x16x32 bf16) on an 8 x 8 grid of accumulators, operands held in registers.  No LDS, no memory traffic,
+// no barrier.
 typedef __attribute__((ext_vector_type(8))) __bf16 ys_bf16x8;
-typedef __attribute__((ext_vector_type(16))) float ys_f32x16;
+typedef __attribute__((ext_vector_type(4))) float ys_f32x4;
 
 __global__ __launch_bounds__(kThreads) void mfma_stream(int steps, float *sink)
 {
@@ -64,28 +64,23 @@ __global__ __launch_bounds__(kThreads) void mfma_stream(int steps, float *sink)
                 x = x * 1664525u + 1013904223u;
                 op[kk][m].h[e] = (uint16_t)(0x3F80u | ((x >> 16) & 0x807Fu));
             }
-    ys_f32x16 acc[4][4];
+    ys_f32x4 acc[8][8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        for (int j = 0; j < 8; ++j) acc[i][j] = ys_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     for (int s = 0; s < steps; ++s) {
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int m = 0; m < 16; ++m)
-                acc[m >> 2][m & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[kk][m >> 2].v, op[kk][4 + (m & 3)].v,
-                                                                              acc[m >> 2][m & 3], 0, 0, 0);
+        for (int m = 0; m < 64; ++m)
+            acc[m >> 3][m & 7] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(op[0][m >> 3].v, op[1][m & 7].v, acc[m >> 3][m & 7], 0, 0, 0);
     }
     float t = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < 8; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) t += acc[i][j][r];
+            for (int r = 0; r < 4; ++r) t += acc[i][j][r];
     if (t == 12345.678f) *sink = t;      // keeps the products alive; practically never true
 }
 

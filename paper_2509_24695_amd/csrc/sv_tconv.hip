@@ -3,6 +3,7 @@
 #include "../../include/sv_measure.h"
 
 #include <mutex>
+#include <type_traits>
 
 #include "tconv_mfma.hpp"
 
@@ -18,8 +19,34 @@ bool overlaps(const void *a, size_t na, const void *b, size_t nb)
     return pa < pb + nb && pb < pa + na;
 }
 
-// The tile kernel needs its 128 KB of dynamic LDS allowed once per device.
-bool tconv_kernel_ready()
+using TconvKernel = void (*)(TconvArgs);
+
+// The tile kernels, and the measurement variants of the 256 x 256 one (0 = the library's own).
+struct TconvForm {
+    int bm, bn, lds;
+    TconvKernel kernel;
+};
+template <int BM, int BN> TconvForm form()
+{
+    using P = TcTile<BM, BN>;
+    return TconvForm{BM, BN, P::kLdsBytes, tconv_mfma<P>};
+}
+enum { kForm256, kForm256x128, kForm128, kForm64, kForm256Long, kForm256LongTail };   // Long: the 32 x 32 x 16 kernel
+const TconvForm kForms[] = {form<256, 256>(), form<256, 128>(), form<128, 128>(), form<64, 64>(),
+                            {kTcBM, kTcBN, kTcLdsBytes, tconv_mfma32<false>}, {kTcBM, kTcBN, kTcLdsBytes, tconv_mfma32<true>}};
+TconvKernel variant_kernel(int variant)
+{
+    using P = TcTile<256, 256>;
+    switch (variant) {
+    case 1: return tconv_mfma<P, 1>;
+    case 2: return tconv_mfma<P, 2>;
+    case 3: return tconv_mfma<P, 3>;
+    default: return tconv_mfma<P>;
+    }
+}
+
+// The kernels need their dynamic LDS allowed once per device.
+bool tconv_kernels_ready()
 {
     static bool ready[64] = {};
     static std::mutex mu;
@@ -27,41 +54,41 @@ bool tconv_kernel_ready()
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
     std::lock_guard<std::mutex> lock(mu);
     if (!ready[dev]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(tconv_mfma<false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kTcLdsBytes) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(tconv_mfma<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kTcLdsBytes) != hipSuccess)
-            return false;
+        auto allow = [](TconvKernel k, int lds) {
+            return hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
+        };
+        for (const TconvForm &f : kForms)
+            if (!allow(f.kernel, f.lds)) return false;
+        for (int v = 1; v < 4; ++v)
+            if (!allow(variant_kernel(v), kForms[0].lds)) return false;
         ready[dev] = true;
     }
     return true;
 }
 
-// The tile kernel for a measurement variant (0 = the library's own), readied once per device.
-using TconvKernel = void (*)(TconvArgs);
-TconvKernel variant_kernel(int variant)
+// Which tile.  A large one reads less per product, but has to fill 256 compute units: what is compared is the time in us per K-step,
+// over the rounds that the tiles take (two of 128 x 128 or five of 64 x 64 share a compute unit), as measured.  256 x 128 pays
+// where rows do not start on 64-byte boundaries, which costs loads more than products.  Measured per call, 256 / 256 long / 256 x 128 /
+// 128 / 64 wide: one frame of 1 560 tokens, 2 240 channels 74 / 120 / - / 42 / 60 us; 4 680 tokens, 2 240 channels 137 / 142 / 250 /
+// 194 / 319; 7 800 tokens, 1 024 channels 68 / 63 / 64 / 64 / 97; 4 200 tokens, 1 800 channels 134 / 133 / 111 / 137; 9 360 tokens, 640
+// channels 47 / 44 / 44 / 36 / 46; 530 tokens, 328 channels 36 / 31 / - / 19 / 12.
+int tconv_form(int64_t M, int D)
 {
-    switch (variant) {
-    case 1: return tconv_mfma<false, 1>;
-    case 2: return tconv_mfma<false, 2>;
-    case 3: return tconv_mfma<false, 3>;
-    default: return tconv_mfma<false, 0>;
-    }
-}
-bool variant_kernel_ready(int variant)
-{
-    static bool ready[64][4] = {};
-    static std::mutex mu;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!ready[dev][variant]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(variant_kernel(variant)),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kTcLdsBytes) != hipSuccess)
-            return false;
-        ready[dev][variant] = true;
-    }
-    return true;
+    constexpr int64_t kCus = 256;
+    auto tiles = [&](int f) { return ((M + kForms[f].bm - 1) / kForms[f].bm) * ((D + kForms[f].bn - 1) / kForms[f].bn); };
+    auto rounds = [&](int64_t n, int64_t at_once) { return (double)((n + at_once - 1) / at_once); };
+    const int64_t t256 = tiles(kForm256), t256x128 = tiles(kForm256x128), t128 = tiles(kForm128), t64 = tiles(kForm64);
+    int best = kForm256;
+    double least = 0.62 * rounds(t256, kCus);
+    auto offer = [&](int f, double us) {
+        if (us < least) { least = us; best = f; }
+    };
+    if (t256 <= 160 || D < 16 * kTcBK) offer(D % kTcBK == 0 ? kForm256Long : kForm256LongTail, 0.56 * rounds(t256, kCus));
+    if (D % kTcBK != 0) offer(kForm256x128, 0.42 * rounds(t256x128, kCus));
+    offer(kForm128, t128 <= 2 * kCus ? 0.30 * (t128 > 290 ? (double)t128 / kCus : 1.13) : 0.60 * rounds(t128, 2 * kCus));
+    const int64_t k64 = (t64 + kCus - 1) / kCus;
+    offer(kForm64, 0.05 * (double)((k64 + 4) / 5) + 0.145 * (double)k64);
+    return best;
 }
 
 sv_status tconv_enqueue(int variant, const void *x, const void *W, const void *cache_in, void *y, void *cache_out,
@@ -84,7 +111,7 @@ sv_status tconv_enqueue(int variant, const void *x, const void *W, const void *c
                       overlaps(cache_out, cache_bytes, W, w_bytes)))
         return SV_ERR_SHAPE;
     if (variant != 0 && D % kTcBK != 0) return SV_ERR_UNSUPPORTED;
-    if (!(variant == 0 ? tconv_kernel_ready() : variant_kernel_ready(variant))) return SV_ERR_LAUNCH;
+    if (!tconv_kernels_ready()) return SV_ERR_LAUNCH;
 
     TconvArgs a;
     a.x = static_cast<const uint16_t *>(x);
@@ -92,14 +119,14 @@ sv_status tconv_enqueue(int variant, const void *x, const void *W, const void *c
     a.cache = static_cast<const uint16_t *>(cache_in);
     a.y = static_cast<uint16_t *>(y);
     a.B = B; a.T = T; a.HW = HW; a.D = D;
-    a.tiles_m = (int)((M + kTcBM - 1) / kTcBM);
-    a.tiles_n = (D + kTcBN - 1) / kTcBN;
+    const TconvForm &f = kForms[variant != 0 ? 0 : tconv_form(M, D)];
+    a.tiles_m = (int)((M + f.bm - 1) / f.bm);
+    a.tiles_n = (D + f.bn - 1) / f.bn;
     const int64_t wgs = tc_grid_size((int64_t)a.tiles_m * a.tiles_n);
     if (wgs >= (int64_t)1 << 31) return SV_ERR_SHAPE;
     auto hs = static_cast<hipStream_t>(stream);
-    if (variant != 0) variant_kernel(variant)<<<dim3((unsigned)wgs), kThreads, kTcLdsBytes, hs>>>(a);
-    else if (D % kTcBK == 0) tconv_mfma<false><<<dim3((unsigned)wgs), kThreads, kTcLdsBytes, hs>>>(a);
-    else tconv_mfma<true><<<dim3((unsigned)wgs), kThreads, kTcLdsBytes, hs>>>(a);
+    const TconvKernel kernel = variant != 0 ? variant_kernel(variant) : f.kernel;
+    kernel<<<dim3((unsigned)wgs), kThreads, f.lds, hs>>>(a);
     if (hipGetLastError() != hipSuccess) return SV_ERR_LAUNCH;
     if (cache_out) {
         const int64_t vecs = (int64_t)B * HW * D / 8;

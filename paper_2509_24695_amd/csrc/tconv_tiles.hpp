@@ -39,4 +39,14 @@ SV_HOST_DEVICE inline bool tc_tile_of(int tiles_m, int tiles_n, int wg, int &tm,
     return true;
 }
 
+// Taps [lo, hi) of the three that some token row of [g0, g1] needs (rows are numbered (batch, frame, position)): a tile whose
+// rows all lie in the last frame has no use for the frame behind it, which is zero, one in the first frame without a
+// cache none for the frame in front.
+SV_HOST_DEVICE inline void tc_taps(int g0, int g1, int HW, int T, bool cache, int &lo, int &hi)
+{
+    const int f0 = g0 / HW, f1 = g1 / HW;                      // frames counted over batches
+    lo = !cache && (T == 1 || (f0 == f1 && f0 % T == 0)) ? 1 : 0;
+    hi = T == 1 || (f0 == f1 && f0 % T == T - 1) ? 2 : 3;
+}
+
 }  // namespace sv
