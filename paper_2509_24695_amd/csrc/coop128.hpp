@@ -1,5 +1,5 @@
-// Token streaming for d = 112 and 128 (DP = 128): the waves of a workgroup work on the same tile
-// together.
+// Apply for d = 112 and 128 (DP = 128): the waves of a workgroup work on the same tile
+// together (the state kernel is in wide_state.hpp).
 //
 // With 64 features a wave can keep a whole 64 x 64 state (or a 64-column panel of it) to itself
 // and never talks to its neighbours.  With 128 the state is four such quadrants and the apply
@@ -9,10 +9,6 @@
 // 5.4).  Here each wave loads whole rows that nobody else loads, the tile is assembled in
 // workgroup-shared LDS, and barriers hand it to the waves that compute:
 //
-//   state (the full-table RoPE form; the other forms use the wave-private kernel of
-//          wide_state.hpp): wave w loads rows 8w .. 8w+8 of K and V of a 32-token tile, then
-//          folds key block w%2 against value block w/2 (a 64 x 64 quadrant) from LDS; one barrier
-//          per tile;
 //   apply: wave w loads rows 8w .. 8w+8 of a 32-token Q tile, computes 32 of the 128 output
 //          features of the whole tile (its 128 x 32 panel of S stays in registers) into a shared
 //          output tile, then stores whole rows 8w .. 8w+8 of O; two barriers per tile, two
@@ -31,132 +27,6 @@ namespace sv {
 
 constexpr int kCoopRow = 128 * 2 + 16;           // LDS row: 128 bf16 features + padding
 constexpr int kCoopTile = 32 * kCoopRow;         // one 32-token tile in LDS
-
-// ---- state ---------------------------------------------------------------------------------------
-
-// One wave's share of the workgroup's K/V stream: rows 8*wave .. +8 of every tile
-// (16 lanes of 16 bytes per row, 4 rows per load instruction), DEPTH tiles in flight.
-template <int DEPTH, int ROPE, bool NT>
-struct CoopStateStream {
-    static constexpr int NLD = 2;
-    rsrc_t rK, rV;
-    uint32_t row_bytes, lane_off;
-    bool valid;
-    TileWalk walk;                       // the workgroup's tiles: identical in all four waves
-    u32x4 k[DEPTH][NLD], v[DEPTH][NLD];
-    Rotator<ROPE, NLD, DEPTH> rot;
-
-    __device__ __forceinline__ CoopStateStream(const uint16_t *Kh, const uint16_t *Vh, const RopeArg &rope,
-                                               const unsigned char *lds_tab, int64_t stride_n, int t1, int d, int wave,
-                                               int lane, const TileWalk &w)
-        : rK(make_rsrc(Kh, (uint32_t)t1 * (uint32_t)stride_n * 2u)),
-          rV(make_rsrc(Vh, (uint32_t)t1 * (uint32_t)stride_n * 2u)), row_bytes((uint32_t)stride_n * 2u),
-          lane_off((uint32_t)(8 * wave + (lane >> 4)) * (uint32_t)stride_n * 2u + (uint32_t)(lane & 15) * 16u),
-          valid((lane & 15) * 8 < d), walk(w),
-          rot(rope, t1, d, 8 * wave + (lane >> 4), 4, 4 * (lane & 15), 1, lds_tab) {}
-
-    __device__ __forceinline__ void request(int s, int i)
-    {
-        const uint32_t base = valid ? walk.offset<32>(i, row_bytes) : kOutOfRange;
-#pragma unroll
-        for (int j = 0; j < NLD; ++j) {
-            k[s][j] = load_stream16<NT>(rK, base + lane_off + (uint32_t)j * 4u * row_bytes);
-            v[s][j] = load_stream16<NT>(rV, base + lane_off + (uint32_t)j * 4u * row_bytes);
-        }
-        rot.request(s, i < walk.count, walk.token<32>(i));
-    }
-};
-
-template <int DEPTH, int ROPE, bool NT>
-__device__ __forceinline__ void coop_state_prefetch(CoopStateStream<DEPTH, ROPE, NT> &st)
-{
-#pragma unroll
-    for (int s = 0; s < DEPTH; ++s) {
-        st.request(s, s);
-        __builtin_amdgcn_sched_barrier(0);   // requests go out in stage order, as they do in the loop
-    }
-}
-
-// LDS of the state phase: K and V tiles, double-buffered; with ROPE also the
-// un-rotated phi(K) (the key sum is never rotated).
-template <int ROPE> __host__ __device__ constexpr int coop_state_lds_bytes() { return (ROPE ? 6 : 4) * kCoopTile; }
-
-// Accumulates quadrant (kb, vb) of the workgroup's partial state over the
-// workgroup's tiles.  Must be called by all four waves (it contains barriers; the
-// tile count is the same in all of them).  Key sums are kept by the waves with vb == 0.
-//
-// Software pipeline, one barrier per tile: while the matrix cores work on tile i
-// (operands from LDS buffer i%2), the wave's vector ALU puts its rows of tile
-// i+1 (ReLU, rotation) into the other buffer; the barrier at the end of the step
-// says both that tile i+1 is complete and that everybody is done reading tile i,
-// whose buffer the next step overwrites.
-template <int DEPTH, int ROPE, bool NT>
-__device__ __forceinline__ void state_accumulate_coop(CoopStateStream<DEPTH, ROPE, NT> &st, unsigned char *lds, int wave,
-                                                      int lane, int kb, int vb, StateAcc &acc)
-{
-    static_assert(DEPTH % 2 == 0, "stage parity selects the LDS buffer");
-    const int wr_off = (8 * wave + (lane >> 4)) * kCoopRow + (lane & 15) * 16;
-    const uint32_t one2 = 0x3f803f80u;   // bf16 (1.0, 1.0)
-    const u32x4 ones4 = {one2, one2, one2, one2};
-    const bf16x8 ones = __builtin_bit_cast(bf16x8, ones4);
-    const int count = st.walk.count;
-    if (count == 0) return;
-
-    // This wave's rows of the workgroup's i-th tile go from stage s into LDS buffer s%2; the stage
-    // is refilled DEPTH tiles ahead whether or not tile i exists (out of range nothing is read).
-    auto prepare = [&](int s, int i) __attribute__((always_inline)) {
-        unsigned char *bufK = lds + (s & 1) * kCoopTile, *bufV = lds + (2 + (s & 1)) * kCoopTile;
-        unsigned char *bufP = lds + (4 + (s & 1)) * kCoopTile;   // un-rotated phi(K), ROPE only
-        if (i < count) {
-            st.rot.template begin_tile<32>(st.walk, i);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const u32x4 kk = relu_bf16x8(st.k[s][j]);
-                if (ROPE) {
-                    *reinterpret_cast<u32x4 *>(bufP + wr_off + 4 * j * kCoopRow) = kk;
-                    *reinterpret_cast<u32x4 *>(bufK + wr_off + 4 * j * kCoopRow) = st.rot.rotate(s, j, kk);
-                } else {
-                    *reinterpret_cast<u32x4 *>(bufK + wr_off + 4 * j * kCoopRow) = kk;
-                }
-                *reinterpret_cast<u32x4 *>(bufV + wr_off + 4 * j * kCoopRow) = st.v[s][j];
-            }
-        }
-        st.request(s, i + DEPTH);
-    };
-
-    prepare(0, 0);
-    lds_barrier();
-    for (int i0 = 0; i0 < count; i0 += DEPTH) {
-#pragma unroll
-        for (int s = 0; s < DEPTH; ++s) {
-            __builtin_amdgcn_sched_barrier(0);   // stages stay in program order
-            if (i0 + s < count) {
-                const unsigned char *bufK = lds + (s & 1) * kCoopTile, *bufV = lds + (2 + (s & 1)) * kCoopTile;
-                const unsigned char *bufP = ROPE ? lds + (4 + (s & 1)) * kCoopTile : bufK;
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const bf16x8 a0 = lds_tr_operand<kCoopRow>(bufK, 16 * ks, 64 * kb, lane);
-                    const bf16x8 a1 = lds_tr_operand<kCoopRow>(bufK, 16 * ks, 64 * kb + 32, lane);
-                    const bf16x8 b0 = lds_tr_operand<kCoopRow>(bufV, 16 * ks, 64 * vb, lane);
-                    const bf16x8 b1 = lds_tr_operand<kCoopRow>(bufV, 16 * ks, 64 * vb + 32, lane);
-                    acc.s[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc.s[0][0], 0, 0, 0);
-                    acc.s[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b1, acc.s[0][1], 0, 0, 0);
-                    acc.s[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc.s[1][0], 0, 0, 0);
-                    acc.s[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc.s[1][1], 0, 0, 0);
-                    if (vb == 0) {
-                        const bf16x8 p0 = ROPE ? lds_tr_operand<kCoopRow>(bufP, 16 * ks, 64 * kb, lane) : a0;
-                        const bf16x8 p1 = ROPE ? lds_tr_operand<kCoopRow>(bufP, 16 * ks, 64 * kb + 32, lane) : a1;
-                        acc.zm[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p0, ones, acc.zm[0], 0, 0, 0);
-                        acc.zm[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p1, ones, acc.zm[1], 0, 0, 0);
-                    }
-                }
-            }
-            prepare((s + 1) % DEPTH, i0 + s + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            if (i0 + s < count) lds_barrier();
-        }
-    }
-}
 
 // ---- apply ---------------------------------------------------------------------------------------
 
@@ -321,58 +191,6 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
 }
 
 // ---- kernels ---------------------------------------------------------------------------------------
-
-// Dynamic LDS: the larger of the streaming buffers and the four reduction slots.
-template <int ROPE>
-__host__ __device__ constexpr int state_d128_lds_bytes() {
-    return (coop_state_lds_bytes<ROPE>() > 4 * kStateElems * 4 ? coop_state_lds_bytes<ROPE>() : 4 * kStateElems * 4) +
-           kEpochLdsBytes;
-}
-
-// State reduction for d = 112 or 128.  grid = (C, B*H), block = 256; workgroup c
-// owns tiles c + C*i of the T = ceil((t1-t0)/32) tiles.  FINALIZE and ROPE as in
-// state_mfma_d64; partial states and S are d x d with row length d.
-template <int DEPTH, bool FINALIZE, int ROPE, bool NT>
-__global__ __launch_bounds__(256, 1) void state_mfma_d128(
-    const uint16_t *__restrict__ K, const uint16_t *__restrict__ V, RopeArg rope, TokStrides st,
-    int H, int d, int t0, int t1, int C, const float *S_in, const float *z_in, float *S_out, float *z_out,
-    void *__restrict__ ws, unsigned long long epoch, uint32_t spin_limit, int order)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const WgRole role(C, order);
-    const int c = role.c, bh = role.bh, BH = gridDim.y;
-    const int b = bh / H, h = bh % H;
-    const int elems = d * d + d;
-    const uint16_t *Kh = K + b * st.b + h * st.h;
-    const uint16_t *Vh = V + b * st.b + h * st.h;
-    const int n_tiles = (t1 - t0 + 31) / 32;
-    EpochSource es;
-    if (FINALIZE) es.begin(ws, BH, elems, epoch, bh, c, C);
-
-    StateAcc acc;
-    acc.clear();
-    CoopStateStream<DEPTH, ROPE, NT> stream(Kh, Vh, rope, lds + state_d128_lds_bytes<ROPE>(), st.n, t1, d, wave, lane,
-                                        TileWalk(t0, c, C, n_tiles, role.phase(b, order)));
-    Rope3dFill tabs;
-    if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
-    coop_state_prefetch(stream);
-    if (ROPE == kRope3D) {
-        rope3d_lds_fill_end(lds + state_d128_lds_bytes<ROPE>(), rope.r3, tabs);
-        wg_barrier();
-    }
-    state_accumulate_coop(stream, lds, wave, lane, wave & 1, wave >> 1, acc);
-
-    float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems;
-    const HeadState hs{S_in ? S_in + (size_t)bh * d * d : nullptr, z_in + (size_t)bh * d, S_out + (size_t)bh * d * d,
-                       z_out + (size_t)bh * d};
-    state_wg_quadrant_store(acc, reinterpret_cast<float *>(lds), wave, lane, d, partials + (size_t)c * elems, FINALIZE && C == 1, hs);
-    if (FINALIZE && C > 1) {
-        epoch = es.resolve(reinterpret_cast<unsigned long long *>(lds + state_d128_lds_bytes<ROPE>() - kEpochLdsBytes));
-        state_agree<256>(ws, BH, elems, bh, c, C, d, epoch, spin_limit, lane, partials, hs);
-    }
-}
 
 // Apply for d = 112 or 128.  grid = (C, B*H), block = 64 * WAVES; workgroup c owns the steps
 // c + C*i of the ceil((t1-t0)/STEP) steps of STEP = 8*WAVES*NB tokens (see CoopApplyStream).

@@ -23,9 +23,7 @@
 // are published, each of its workgroups adds up one slice of them in chunk
 // order (bit-reproducible, no float atomics).
 //
-// d = 112 and 128 are served by the workgroup-cooperative kernels of coop128.hpp,
-// which reuse the pieces below (tile walk, transposing reads, accumulators,
-// partial-state reduction).
+// d = 112 and 128 are served by wide_state.hpp and coop128.hpp, which reuse pieces of this file.
 #pragma once
 
 #include "common.hpp"
@@ -35,7 +33,7 @@
 namespace sv {
 
 constexpr int kRowBytes = 144;   // 128-byte token row + 16 bytes of padding (bank spread, keeps 16-byte alignment)
-constexpr int kStateElems = 64 * 64 + 64;            // S then z of one head, d = 64; also one 64 x 64 quadrant + its z
+constexpr int kStateElems = 64 * 64 + 64;            // S then z of one head, d = 64
 
 // Workspace layout (B*H = BH heads, `elems` = d*d + d):
 //   float  partial[BH][kMaxChunks][elems]
@@ -428,35 +426,6 @@ __device__ __forceinline__ void state_wg_reduce_store(StateAcc &acc, float *slot
             if (v < kUnits) *hs.unit(64, v) = carry[r] + x[r][0];
         }
     }
-}
-
-// d = 112, 128: wave w holds quadrant (key block w%2, value block w/2) of the
-// workgroup's partial state; the four slots are stitched into the d x d matrix
-// (row length d) followed by the d key sums (taken from the waves of value
-// block 0) and stored to `out` (d*d + d floats) with coherent stores.
-__device__ __forceinline__ void state_wg_quadrant_store(StateAcc &acc, float *slots, int wave, int lane, int d,
-                                                        float *__restrict__ out, bool sole, const HeadState &hs)
-{
-    wg_barrier();                                   // all waves are done with their staging tiles
-    state_acc_to_slot<false>(acc, slots + wave * kStateElems, lane);
-    wg_barrier();
-    const int s_units = d * d / 2, units = s_units + d / 2;
-    auto sum = [&](int u) __attribute__((always_inline)) {
-        const float *src;
-        if (u < s_units) {
-            const int k = (2 * u) / d, v = 2 * u - k * d;
-            src = slots + ((k >> 6) + 2 * (v >> 6)) * kStateElems + (k & 63) * 64 + (v & 63);
-        } else {
-            const int k = 2 * (u - s_units);
-            src = slots + (k >> 6) * kStateElems + 64 * 64 + (k & 63);
-        }
-        return *reinterpret_cast<const f32x2 *>(src);
-    };
-    if (sole) {
-        state_store_sole<4 * kWave>(hs, d, (int)threadIdx.x, sum);
-        return;
-    }
-    for (int u = threadIdx.x; u < units; u += 4 * kWave) store_coherent(out + 2 * u, sum(u));
 }
 
 //   S_out, z_out = (S_in, z_in or 0) + partial[0] + partial[1] + ... + partial[C-1], in that order,

@@ -33,10 +33,9 @@ constexpr int kVersion = 500;   // 0.5.0
 constexpr int kStateTile = 32, kStateWaves = 4, kApplyWaves = 4;
 constexpr int kCoopApplyWaves = 4, kCoopApplyNB = 1;   // d = 112/128 apply: one 128 x 32 panel of S per wave, two workgroups per compute unit
 constexpr int kStateDepth = 2, kApplyDepth = 2;
-// 16-token tiles in flight per wave of the wave-private d = 112/128 state kernel: three, or two with the
-// factored rotation tables (that form is bound by its arithmetic and needs the registers)
-constexpr int kWideStateDepth = 3, kWideStateDepth3D = 2;
-constexpr int kCoopStateDepth = 4;            // 32-token tiles of the shared-tile d = 112/128 state kernel (full-table RoPE)
+// 16-token tiles in flight per wave of the wave-private d = 112/128 state kernel: three, or two with a rotation (its table
+// rows or its arithmetic need the registers)
+constexpr int kWideStateDepth = 3, kWideStateDepthRope = 2;
 constexpr int kFusedStateDepth[3] = {2, 2, 2};   // one-launch block step (d = 64), by RoPE mode
 constexpr int kFusedApplyDepth[3] = {6, 2, 6};   // Q tiles held in registers across the in-kernel waits
 constexpr bool kApplyHiLo = true;
@@ -107,19 +106,16 @@ template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
 template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     static constexpr int W = 1;
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
-    // State: wave-private tiles, except with a full rotation table, whose rows need the registers
-    // the wave-private kernel spends on the whole 128 x 128 state (then: one tile shared by the four waves).
-    static constexpr bool kWideState = ROPE != kRopeTable;
+    static constexpr bool kWideState = true;
     template <bool FINALIZE> static constexpr auto pick_state() {
-        if constexpr (kWideState) return &state_mfma_wide<(ROPE == kRope3D ? kWideStateDepth3D : kWideStateDepth), FINALIZE, ROPE, !SHARED>;
-        else return &state_mfma_d128<kCoopStateDepth, FINALIZE, ROPE, !SHARED>;
+        return &state_mfma_wide<(ROPE != kRopeNone ? kWideStateDepthRope : kWideStateDepth), FINALIZE, ROPE, !SHARED>;
     }
     static constexpr auto state = pick_state<true>();
     static constexpr auto state_partial = pick_state<false>();
     static constexpr auto apply = apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB, !SHARED>;
-    static constexpr int state_lds = kWideState ? kWideLdsBytes : state_d128_lds_bytes<ROPE>() + kTab;
+    static constexpr int state_lds = kWideLdsBytes;
     static constexpr int apply_lds = coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
-    static constexpr int state_wg_tokens = kWideState ? 4 * kWideTile : 32;   // four private tiles, or one shared
+    static constexpr int state_wg_tokens = 4 * kWideTile;
     static constexpr int apply_wg_tokens = 8 * kCoopApplyWaves * kCoopApplyNB;   // the waves of a workgroup share its tiles
     static constexpr int apply_threads = 64 * kCoopApplyWaves;
     // workgroups per compute unit: with one 128 x 32 panel per wave (136-164 registers, 17-50 KB of LDS) three are
@@ -424,14 +420,17 @@ void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, c
     with_mfma_kernels(s.d, rope.mode, shares_lines(s), [&](auto kn) {
         using KN = decltype(kn);
         const int C = plan_chunks(s.BH, t1 - t0, KN::state_wg_tokens, dev.num_cu);
+        // d = 112, 128 with a full table: the heads of a chunk on one die, whose L2 then serves them the chunk's table rows (20 heads
+        // of 112, 32 760 tokens, layer: 142.9 against 145.5 us; d = 64, with half the table per token, 500 against 482).
+        const int order = workgroup_order(s) | (s.d > 64 && rope.mode == kRopeTable ? kOrderChunkMajor : 0);
         if ((int64_t)C * s.BH <= dev.state_resident_wgs[KN::W][rope.mode]) {
             // the head's workgroups wait for each other inside the kernel: all must be resident
             KN::state<<<dim3(C, s.BH), 64 * kStateWaves, KN::state_lds, stream>>>(
                 k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, next_epoch(s.host_epochs_only),
-                spin_limit(), workgroup_order(s));
+                spin_limit(), order);
         } else {
             KN::state_partial<<<dim3(C, s.BH), 64 * kStateWaves, KN::state_lds, stream>>>(
-                k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, 0ull, 0u, workgroup_order(s));
+                k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, 0ull, 0u, order);
             with_head_dim(s.d, [&](auto D) {
                 state_reduce<D(), KN::kWideState><<<rgrid, kThreads, 0, stream>>>(static_cast<float *>(ws), C, kMaxChunks,
                                                                                  S_in, z_in, S_out, z_out);

@@ -14,7 +14,8 @@
 // Compared with the workgroup-cooperative kernel (one 32-token tile shared by the four waves
 // behind a barrier) the per-tile costs that do not shrink with the tile - position arithmetic of
 // the rotation, waits, the barrier itself - are paid per 64 tokens of a compute unit's work
-// instead of per 32 and never hold up the other waves.
+// instead of per 32 and never hold up the other waves.  With a full rotation table the rows of two tiles in flight just fit
+// beside the state (20 heads of 112, 32 760 tokens, layer: 154 -> 143 us; three blocks of 4 680 tokens 133 -> 124).
 //
 // At the end the four waves' states are added in a fixed order, exchanged through LDS in the
 // accumulators' own layout, and stored as the workgroup's partial.
@@ -421,15 +422,13 @@ __device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
 }
 
 // grid = (C, B*H), block = 256.  Wave w of workgroup c owns tiles 4c + w + 4C i of the
-// T = ceil((t1 - t0) / 16) tiles.  FINALIZE as in state_mfma_d64.  ROPE: kRopeNone or kRope3D (the
-// table rows of kRopeTable do not fit in the registers left beside the state).  Partials are laid out by wide_word.
+// T = ceil((t1 - t0) / 16) tiles.  FINALIZE as in state_mfma_d64.  Partials are laid out by wide_word.
 template <int DEPTH, bool FINALIZE, int ROPE, bool NT>
 __global__ __launch_bounds__(256, 1) void state_mfma_wide(
     const uint16_t *__restrict__ K, const uint16_t *__restrict__ V, RopeArg rope, TokStrides st,
     int H, int d, int t0, int t1, int C, const float *S_in, const float *z_in, float *S_out, float *z_out,
     void *__restrict__ ws, unsigned long long epoch, uint32_t spin_limit, int order)
 {
-    static_assert(ROPE == kRopeNone || ROPE == kRope3D, "no full-table form of this kernel");
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
