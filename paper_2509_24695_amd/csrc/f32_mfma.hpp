@@ -125,16 +125,17 @@ template <typename T, int D> struct StateF32 {
     static constexpr int kWgTokens = kSplit ? TILE : 4 * TILE;
     template <int ROPE> static constexpr int lds_bytes() {
         constexpr int slots = 4 * kSlot * 4, tab = ROPE == kRope3D ? kRope3dLdsBytes : 0;   // tables, then slots
-        return (slots > tab ? slots : tab) + kEpochLdsBytes;
+        return slots > tab ? slots : tab;
     }
 };
 
-// grid = (C, B*H), block = 256; arguments, FINALIZE and the workspace as in state_mfma_d64.
-template <typename T, int D, bool FINALIZE, int ROPE>
+// grid = (C, B*H), block = 256; arguments and the partials in the workspace as in state_mfma_d64.  No workgroup waits for another:
+// SOLE (C = 1) stores the new state, otherwise state_reduce adds the partials up.  These calls stay free of waits because they
+// always were: they may run beside anything on other streams, and be replayed without preparation.
+template <typename T, int D, bool SOLE, int ROPE>
 __global__ __launch_bounds__(kThreads, 1) void state_f32(
     const T *__restrict__ K, const T *__restrict__ V, RopeArg rope, TokStrides st, int H, int t0, int t1, int C,
-    const float *S_in, const float *z_in, float *S_out, float *z_out, void *__restrict__ ws, unsigned long long epoch,
-    uint32_t spin_limit, int order)
+    const float *S_in, const float *z_in, float *S_out, float *z_out, void *__restrict__ ws, int order)
 {
     using P = StateF32<T, D>;
     constexpr int VEC = P::VEC, W = P::W, U = P::U, TILE = P::TILE, DEPTH = P::DEPTH, F = P::F, E = (int)sizeof(T);
@@ -144,10 +145,8 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
     const WgRole role(C, order);
-    const int c = role.c, bh = role.bh, BH = gridDim.y;
+    const int c = role.c, bh = role.bh;
     const int b = bh / H, h = bh % H;
-    EpochSource es;
-    if (FINALIZE) es.begin(ws, BH, elems, epoch, bh, c, C);
 
     const int kb = P::kSplit ? wave & 1 : 0, vb = P::kSplit ? wave >> 1 : 0;
     const int n_tiles = (t1 - t0 + TILE - 1) / TILE;
@@ -272,15 +271,11 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
             return (x[0] + x[2]) + (x[1] + x[3]);
         }
     };
-    if (FINALIZE && C == 1) {
+    if (SOLE) {
         state_store_sole<kThreads>(hs, D, tid, sum);
         return;
     }
-    for (int u = tid; u < elems / 2; u += kThreads) store_coherent(out + 2 * u, sum(u));
-    if (FINALIZE) {
-        epoch = es.resolve(reinterpret_cast<unsigned long long *>(lds + P::template lds_bytes<ROPE>() - kEpochLdsBytes));
-        state_agree<kThreads>(ws, BH, elems, bh, c, C, D, epoch, spin_limit, lane, partials, hs);
-    }
+    for (int u = tid; u < elems / 2; u += kThreads) *reinterpret_cast<f32x2 *>(out + 2 * u) = sum(u);
 }
 
 // ---- apply ----------------------------------------------------------------------------------------------------

@@ -122,7 +122,15 @@ __global__ __launch_bounds__(kThreads) void state_reduce(
         at = 4 * wide_word(D, row >> 3, (row >> 2) & 1, col) + (row & 3);
     }
     const float *p = ws + (int64_t)bh * chunk_stride * E + at;
-    for (int c = 0; c < C; ++c) x += p[(int64_t)c * E];
+    // sixteen partials in flight; past the last: the last one again, left out of the sum
+    for (int c0 = 0; c0 < C; c0 += 16) {
+        float v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = p[(int64_t)(c0 + j < C ? c0 + j : C - 1) * E];
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+            if (c0 + j < C) x += v[j];
+    }
     *dst = x;
 }
 

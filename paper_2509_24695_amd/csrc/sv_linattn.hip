@@ -67,7 +67,6 @@ struct Device {
     // how many workgroups fit on the device at once, [DP = 128][RoPE mode]
     int state_resident_wgs[2][3] = {{0, 0, 0}, {0, 0, 0}};   // state kernel with in-kernel finalize
     int fused_resident_wgs[3] = {0, 0, 0};                   // one-launch block step (d = 64), by RoPE mode
-    int f32_resident_wgs[5][3] = {};                         // fp32-arithmetic state kernel, [KernelsF32::kIndex][RoPE mode]
     bool ok = false;
 };
 
@@ -129,7 +128,6 @@ template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
 template <typename T_, int D_, int ROPE_> struct KernelsF32 {
     using T = T_;
     static constexpr int D = D_, ROPE = ROPE_;
-    static constexpr int kIndex = sizeof(T) == 2 ? 4 : D == 32 ? 0 : D == 64 ? 1 : D == 112 ? 2 : 3;
     static constexpr auto state = state_f32<T, D, true, ROPE>;
     static constexpr auto state_partial = state_f32<T, D, false, ROPE>;
     static constexpr auto apply = apply_f32<T, D, ROPE>;
@@ -137,17 +135,12 @@ template <typename T_, int D_, int ROPE_> struct KernelsF32 {
     static constexpr int apply_lds = ROPE == kRope3D ? kRope3dLdsBytes : 0;
     static constexpr int state_wg_tokens = StateF32<T, D>::kWgTokens, apply_wg_tokens = ApplyF32<D>::kWgTokens;
 };
-template <typename T, int D, int ROPE> void init_f32_kernels(Device &d)
+template <typename T, int D, int ROPE> void init_f32_kernels()
 {
     using KN = KernelsF32<T, D, ROPE>;
     const auto attr = hipFuncAttributeMaxDynamicSharedMemorySize;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state), attr, KN::state_lds);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state_partial), attr, KN::state_lds);
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(KN::state), kThreads,
-                                                     KN::state_lds) != hipSuccess)
-        per_cu = 0;
-    d.f32_resident_wgs[KN::kIndex][ROPE] = per_cu * d.num_cu;
 }
 
 template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
@@ -257,13 +250,13 @@ const Device &device_info()
         init_kernels<128, kRope3D, true>(d);
         for (int hd : {32, 64, 112, 128})
             with_head_dim(hd, [&](auto D) {
-                init_f32_kernels<float, D(), kRopeNone>(d);
-                init_f32_kernels<float, D(), kRopeTable>(d);
-                init_f32_kernels<float, D(), kRope3D>(d);
+                init_f32_kernels<float, D(), kRopeNone>();
+                init_f32_kernels<float, D(), kRopeTable>();
+                init_f32_kernels<float, D(), kRope3D>();
             });
-        init_f32_kernels<uint16_t, 32, kRopeNone>(d);
-        init_f32_kernels<uint16_t, 32, kRopeTable>(d);
-        init_f32_kernels<uint16_t, 32, kRope3D>(d);
+        init_f32_kernels<uint16_t, 32, kRopeNone>();
+        init_f32_kernels<uint16_t, 32, kRopeTable>();
+        init_f32_kernels<uint16_t, 32, kRope3D>();
         for (int hd : {32, 64, 112, 128})          // the larger generic apply kernels need more than 64 KB of LDS
             with_head_dim(hd, [&](auto D) {
                 const auto attr = hipFuncAttributeMaxDynamicSharedMemorySize;
@@ -466,12 +459,11 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
             using KN = decltype(kn);
             using T = typename KN::T;
             const int C = plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
-            const bool resident = (int64_t)C * s.BH <= dev.f32_resident_wgs[KN::kIndex][rope.mode];
-            const auto kernel = resident ? KN::state : KN::state_partial;
+            const auto kernel = C == 1 ? KN::state : KN::state_partial;
             kernel<<<dim3(C, s.BH), kThreads, KN::state_lds, stream>>>(
                 static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, t0, t1, C, S_in, z_in, S_out,
-                z_out, ws, resident ? next_epoch(s.host_epochs_only) : 0ull, spin_limit(), workgroup_order(s));
-            if (!resident)
+                z_out, ws, workgroup_order(s));
+            if (C > 1)
                 state_reduce<KN::D><<<rgrid, kThreads, 0, stream>>>(wsf, C, kMaxChunks, S_in, z_in, S_out, z_out);
         });
         return launch_status();
