@@ -17,8 +17,8 @@
 //           lane ends up with NB consecutive features of a token and stores them as they are.
 //
 // Measured (both kernels of a layer, before: plain FMAs out of LDS): fp32, 32 heads of 64, 4 680 tokens 120 -> 46.5 us;
-// bf16, 128 heads of 32, 4 096 tokens 130 -> 42 us; fp32, 2 heads of 32, 1 024 tokens unchanged at 18 us.
-// What is left above the streams' time is the start of three kernels.
+// bf16, 128 heads of 32, 4 096 tokens 130 -> 42 us; fp32, 2 heads of 32, 1 024 tokens 17.7 -> 14.9 us.
+// What is left above the streams' time is the start of the kernels.
 //
 // d <= 64: a wave holds the whole state and works alone on its tiles.  d = 112, 128: the waves of a workgroup
 // share the tiles, in the state kernel as 64 x 64 quadrants (each half row is loaded by two waves, the second out
