@@ -121,6 +121,12 @@ template <typename T, int D> struct StateF32 {
     static constexpr int U = 16 / VEC;                     // groups of four tokens per tile: 16 tokens, 32 at d = 32
     static constexpr int TILE = 4 * U;
     static constexpr int DEPTH = 3;                        // tiles in flight per wave
+    // Running sums: a set per stage, and at d = 32 (few registers) one for each parity of the token group.  An fp32 sum's error grows
+    // with the root of its length; one set for the whole share had S up to 1.8 times as far from 64-bit sums as the scalar kernel, whose
+    // chunks are shorter (2 heads of 32, 1 024 tokens: 2.1e-7 against 1.3e-7; 160 heads of 112, 4 680 tokens: 8.7e-7 against
+    // 5.0e-7).  With these it is no further off at any size measured (1.0e-7, 4.9e-7), for less than 0.5 us per launch.  Adding
+    // every tile's products to the share's sum instead was as exact and up to 20 % slower.
+    static constexpr int kChains = VEC == 2 ? 2 : 1;
     static constexpr int kSlot = F * F + F;                // a wave's part in LDS: state, then key sums
     static constexpr int kWgTokens = kSplit ? TILE : 4 * TILE;
     template <int ROPE> static constexpr int lds_bytes() {
@@ -189,14 +195,14 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
     const float inv_rc = ROPE == kRope3D ? 1.0f / (float)(rope.r3.rows * rope.r3.cols) : 0.f;
     const float inv_cols = ROPE == kRope3D ? 1.0f / (float)rope.r3.cols : 0.f;
 
-    f32x4 acc[VEC][VEC] = {};
+    f32x4 acc[DEPTH][P::kChains][VEC][VEC] = {};
     float zs[VEC] = {};
     for (int i0 = 0; i0 < walk.count; i0 += DEPTH) {
 #pragma unroll
         for (int s = 0; s < DEPTH; ++s) {
             if (i0 + s >= walk.count) break;     // short shares: the rest of the round would be code and no work
             __builtin_amdgcn_sched_barrier(0);   // stages stay in program order
-            float kf[U][VEC], vf[U][VEC];
+            float kf[U][VEC], vf[U][VEC], zt[VEC];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 widen<T, VEC>(kw[s][u], kf[u]);
@@ -204,7 +210,7 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
                     kf[u][e] = fmaxf(kf[u][e], 0.f);
-                    zs[e] += kf[u][e];                      // the key sum is never rotated
+                    zt[e] = u == 0 ? kf[u][e] : zt[e] + kf[u][e];          // the key sum is never rotated
                 }
                 if constexpr (ROPE != kRopeNone) {
                     f32x2 cs[VEC / 2];
@@ -223,6 +229,8 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
                     rotate_pairs<VEC>(kf[u], cs);
                 }
             }
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) zs[e] += zt[e];
             request(s, i0 + s + DEPTH);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -230,10 +238,25 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
 #pragma unroll
                 for (int i = 0; i < VEC; ++i)
 #pragma unroll
-                    for (int j = 0; j < VEC; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][i], vf[u][j], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < VEC; ++j) {
+                        f32x4 &a = acc[s][u % P::kChains][i][j];
+                        a = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][i], vf[u][j], a, 0, 0, 0);
+                    }
         }
     }
+    f32x4 sum[VEC][VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) {
+            f32x4 x[DEPTH];
+#pragma unroll
+            for (int s = 0; s < DEPTH; ++s) {
+                x[s] = acc[s][0][i][j];
+                if (P::kChains == 2) x[s] += acc[s][P::kChains - 1][i][j];
+            }
+            sum[i][j] = (x[0] + x[1]) + x[2];
+        }
 
     // The wave's part in [k][v] order in its LDS slot: element r of block (i, j) is key feature VEC (4 g + r) + i, value
     // feature VEC m + j, so a lane's blocks j make VEC consecutive floats.
@@ -245,7 +268,7 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
         for (int r = 0; r < 4; ++r) {
             float *row = mine + (VEC * (4 * g + r) + i) * F + VEC * m;
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) row[j] = acc[i][j][r];
+            for (int j = 0; j < VEC; ++j) row[j] = sum[i][j][r];
         }
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
@@ -258,7 +281,7 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
     float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems, *out = partials + (size_t)c * elems;
     const HeadState hs{S_in ? S_in + (size_t)bh * D * D : nullptr, z_in + (size_t)bh * D, S_out + (size_t)bh * D * D,
                        z_out + (size_t)bh * D};
-    auto sum = [&](int u) __attribute__((always_inline)) {
+    auto unit = [&](int u) __attribute__((always_inline)) {
         if constexpr (P::kSplit) {
             const int k = (2 * u) / D, v = 2 * u - k * D, kz = 2 * u - D * D;
             const float *src = u < D * D / 2 ? slots + ((k >> 6) + 2 * (v >> 6)) * P::kSlot + (k & 63) * 64 + (v & 63)
@@ -272,10 +295,10 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
         }
     };
     if (SOLE) {
-        state_store_sole<kThreads>(hs, D, tid, sum);
+        state_store_sole<kThreads>(hs, D, tid, unit);
         return;
     }
-    for (int u = tid; u < elems / 2; u += kThreads) *reinterpret_cast<f32x2 *>(out + 2 * u) = sum(u);
+    for (int u = tid; u < elems / 2; u += kThreads) *reinterpret_cast<f32x2 *>(out + 2 * u) = unit(u);
 }
 
 // ---- apply ----------------------------------------------------------------------------------------------------

@@ -466,7 +466,7 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
                 static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, t0, t1, C, S_in, z_in, S_out,
                 z_out, ws, workgroup_order(s));
             if (C > 1)
-                state_reduce<KN::D><<<rgrid, kThreads, 0, stream>>>(wsf, C, kMaxChunks, S_in, z_in, S_out, z_out);
+                state_reduce<KN::D, false, true><<<rgrid, kThreads, 0, stream>>>(wsf, C, kMaxChunks, S_in, z_in, S_out, z_out);
         });
         return launch_status();
     }
