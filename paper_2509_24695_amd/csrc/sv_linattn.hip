@@ -43,6 +43,12 @@ constexpr bool kApplyHiLo = true;
 // so few and long ones win (d = 64, 4 680 tokens: 46.5 us for the layer with two, 52.8 with four, 57.8 with eight); at
 // d = 32 the state is small and more waves cover the loads (44.8, 42.1, 41.7 us).
 constexpr int f32_apply_wgs_per_cu(int d) { return d == 32 ? 4 : 2; }
+// d = 32: tokens up to which one workgroup sums a head in one launch, instead of several and a second launch for their sum.  The
+// lines are where the two meet in layers enqueued back to back through the binding, where the second launch costs the host 2.5 us
+// (one / several, fp32: 8 heads, 1 024 tokens 15.9 / 17.4 us, 1 280 17.7 / 17.4; 32 heads, 768 15.8 / 17.7, 1 024 17.4 / 17.3; 64 heads,
+// 512 14.7 / 17.3, 768 17.2 / 17.3, 1 024 19.7 / 17.6; with a rotation some 100 tokens earlier, bf16 some 150 later).  A caller who
+// waits for every layer sees them meet at 512 tokens (fp32) and 1 024 (bf16), 31 against 28 us at 1 024 tokens of fp32.
+int f32_sole_tokens(int BH, int elem_bytes) { return (BH <= 16 ? 1152 : BH <= 32 ? 896 : 768) + (elem_bytes == 2 ? 128 : 0); }
 // d = 64: the denominators phi(Q_i).z ride through the matrix core as two more operand rows (false) or are taken on
 // the vector ALU with a wavefront-level reduction (true).  Measured level (within 1 % either way at 32 760 and
 // 75 600 tokens; the one-launch block step 0.5-1 us per block slower with the vector ALU form), so they stay on
@@ -458,9 +464,8 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
         with_f32_kernels(s, rope.mode, [&](auto kn) {
             using KN = decltype(kn);
             using T = typename KN::T;
-            // d = 32, few tokens: one workgroup per head in one launch, instead of up to eight and a second launch for their sum (layer
-            // of 2 heads, 1 024 tokens: 14.9 against 17.7 us; at d = 64 and 112 the workgroup takes longer than the launch).
-            const int C = KN::D == 32 && n <= 8 * KN::state_wg_tokens ? 1 : plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
+            const bool sole = KN::D == 32 && n <= f32_sole_tokens(s.BH, s.elem_bytes);
+            const int C = sole ? 1 : plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
             const auto kernel = C == 1 ? KN::state : KN::state_partial;
             kernel<<<dim3(C, s.BH), kThreads, KN::state_lds, stream>>>(
                 static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, t0, t1, C, S_in, z_in, S_out,
