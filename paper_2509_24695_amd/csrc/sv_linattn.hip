@@ -18,6 +18,7 @@
 #include "common.hpp"
 #include "f32_mfma.hpp"
 #include "generic_kernels.hpp"
+#include "layout_rules.hpp"
 #include "state_mfma.hpp"
 #include "wide_state.hpp"
 
@@ -337,14 +338,11 @@ sv_status check_desc(const sv_tensor_desc *t, Shape *s)
     return SV_OK;
 }
 
-// The matrix-core kernels address a head's tokens (and the rotation table) with 32-bit byte offsets: what a head spans, and
-// what one tile spans (rows past the end are reached by address before they are dropped), stays below 2 GiB.
+// Do 32-bit offsets reach a head's tokens and the rotation table's rows?
 bool offsets_fit(const Shape &s, const Rope &rope)
 {
-    constexpr int64_t kLimit = int64_t(1) << 31;
-    const int64_t rows = s.N > 64 ? s.N : 64;
-    if (s.st.n >= kLimit / (rows * s.elem_bytes)) return false;
-    return !(rope.mode == kRopeTable && (int64_t)s.N * s.d * 4 >= kLimit);
+    if (!head_offsets_fit(s.N, s.st.n, s.elem_bytes)) return false;
+    return !(rope.mode == kRopeTable && (int64_t)s.N * s.d * 4 >= (int64_t(1) << 31));
 }
 
 // Do the factored tables fit the LDS set aside for them, and the positions the arithmetic?
