@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "layout_rules.hpp"
 #include "tile_walk.hpp"
 
 namespace sv {
@@ -86,8 +87,8 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes) {
 }
 
 // Tokens are read once and outputs written once, so both are marked non-temporal (NT) - except where the cache
-// lines of a row are shared with the neighbouring heads of a [B][N][H][d] tensor (see shares_lines in
-// sv_linattn.hip): there the neighbours' accesses have to meet in the L2.
+// lines of a row are shared with the neighbouring heads of a [B][N][H][d] tensor (see TokenLayout in
+// layout_rules.hpp): there the neighbours' accesses have to meet in the L2.
 template <bool NT = true> __device__ __forceinline__ u32x4 load_stream16(rsrc_t r, uint32_t off) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, NT ? 2 : 0);
 }
@@ -111,9 +112,7 @@ template <> struct Elem<uint16_t> {   // bf16 bit patterns
     static __device__ __forceinline__ void store(uint16_t *p, float x) { *p = f32_to_bf16_bits(x); }
 };
 
-// How a grid's workgroups are dealt to (chunk, head) and the heads' walks staggered (kernel argument `order`):
-constexpr int kOrderChunkMajor = 1;   // chunk_major_role instead of (blockIdx.x, blockIdx.y)
-constexpr int kOrderLockstep = 2;     // all heads of a batch walk in phase: they read pieces of the same cache lines
+// How a grid's workgroups are dealt to (chunk, head) and the heads' walks staggered (kernel argument `order`, see layout_rules.hpp):
 constexpr int kDies = 8;              // MI355X: accelerator dies (XCDs), one L2 each; workgroup ids go round them
 struct WgRole {
     int c, bh;

@@ -78,7 +78,7 @@ struct Device {
 };
 
 // The kernels in use, by padded head dimension and RoPE mode.  LDS sizes include the room for the
-// factored tables where the mode needs it.  SHARED: heads share cache lines (shares_lines); at d = 64 a head's row
+// factored tables where the mode needs it.  SHARED: heads share cache lines (TokenLayout); at d = 64 a head's row
 // is a whole line, one form serves all.
 template <int DP, int ROPE, bool SHARED = false> struct Kernels;
 template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
@@ -389,24 +389,7 @@ sv_status launch_status() { return hipGetLastError() == hipSuccess ? SV_OK : SV_
 
 bool eps_ok(float eps) { return isfinite(eps) && eps >= 0.f; }
 
-// Token rows of all heads side by side: [B][N][H][d], what a projection leaves behind.
-bool token_major(const Shape &s) { return s.H > 1 && s.st.h < s.st.n; }
-
-// ... and neighbouring heads have pieces of the same 128-byte cache lines (d = 112: 224-byte pieces)?  Then the
-// kernels go without the non-temporal hint, which makes a head's pieces of a line leave the L2 before the neighbour's
-// accesses: the apply kernel alone 64 against 104 us (32 760 tokens, 20 heads), both kernels 158 against 174.
-bool shares_lines(const Shape &s) { return token_major(s) && (s.st.h * s.elem_bytes) % 128 != 0; }
-
-// How the workgroups of the layer kernels are dealt to heads and chunks.  Token-major tensors: all heads of a batch
-// walk in phase, so that together they read whole runs of consecutive rows, and where a 256-byte granule of memory
-// holds pieces of several heads (d = 64, 112) the heads of a chunk share a die as well.  Layers of 32 heads of 64,
-// 151 200 tokens: 493 us with both, 523 in phase only, 535 with neither; 40 heads of 112, 32 760 tokens, rotated: 290,
-// 319, 349; 40 heads of 128: 265, 262, 273.
-int workgroup_order(const Shape &s)
-{
-    if (!token_major(s)) return 0;
-    return (s.st.h * s.elem_bytes) % 256 != 0 ? kOrderLockstep | kOrderChunkMajor : kOrderLockstep;
-}
+TokenLayout layout_of(const Shape &s) { return TokenLayout{s.BH, s.H, s.d, s.elem_bytes, s.st.h, s.st.n}; }
 
 // S_out, z_out = (S_in, z_in, or 0 when S_in is null) + state of tokens [t0,t1).  S_in may equal S_out.
 // rope: rotation table or null.  All arguments are already validated.
@@ -414,12 +397,10 @@ void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, c
                        const float *S_in, const float *z_in, float *S_out, float *z_out, void *ws, const Device &dev,
                        dim3 rgrid, hipStream_t stream)
 {
-    with_mfma_kernels(s.d, rope.mode, shares_lines(s), [&](auto kn) {
+    with_mfma_kernels(s.d, rope.mode, layout_of(s).shares_lines(), [&](auto kn) {
         using KN = decltype(kn);
         const int C = plan_chunks(s.BH, t1 - t0, KN::state_wg_tokens, dev.num_cu);
-        // d = 112, 128 with a full table: the heads of a chunk on one die, whose L2 then serves them the chunk's table rows (20 heads
-        // of 112, 32 760 tokens, layer: 142.9 against 145.5 us; d = 64, with half the table per token, 500 against 482).
-        const int order = workgroup_order(s) | (s.d > 64 && rope.mode == kRopeTable ? kOrderChunkMajor : 0);
+        const int order = state_order(layout_of(s), rope.mode == kRopeTable);
         if ((int64_t)C * s.BH <= dev.state_resident_wgs[KN::W][rope.mode]) {
             // the head's workgroups wait for each other inside the kernel: all must be resident
             KN::state<<<dim3(C, s.BH), 64 * kStateWaves, KN::state_lds, stream>>>(
@@ -467,7 +448,7 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
             const auto kernel = C == 1 ? KN::state : KN::state_partial;
             kernel<<<dim3(C, s.BH), kThreads, KN::state_lds, stream>>>(
                 static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, t0, t1, C, S_in, z_in, S_out,
-                z_out, ws, workgroup_order(s));
+                z_out, ws, state_order(layout_of(s), rope.mode == kRopeTable));
             if (C > 1)
                 state_reduce<KN::D, false, true><<<rgrid, kThreads, 0, stream>>>(wsf, C, kMaxChunks, S_in, z_in, S_out, z_out);
         });
@@ -498,7 +479,7 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
     const Device &dev = device_info();
     if (!dev.ok) return SV_ERR_LAUNCH;
     if (mfma_path(s, rope)) {
-        with_mfma_kernels(s.d, rope.mode, shares_lines(s), [&](auto kn) {
+        with_mfma_kernels(s.d, rope.mode, layout_of(s).shares_lines(), [&](auto kn) {
             using KN = decltype(kn);
             int C = KN::apply_wgs_per_cu * dev.num_cu / s.BH;
             const int steps = (n + KN::apply_wg_tokens - 1) / KN::apply_wg_tokens;
@@ -516,7 +497,7 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
             if (C < 1) C = 1;
             KN::apply<<<dim3(C, s.BH), KN::apply_threads, KN::apply_lds, stream>>>(
                 static_cast<const uint16_t *>(Q), static_cast<uint16_t *>(O), rope.arg, s.st, s.H, s.d, t0, t1, C, S,
-                z, eps, workgroup_order(s));
+                z, eps, apply_order(layout_of(s), rope.mode == kRopeTable, rope.mode == kRope3D, n));
         });
         return launch_status();
     }
@@ -530,7 +511,7 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
             if (C < 1) C = 1;
             KN::apply<<<dim3(C, s.BH), kThreads, KN::apply_lds, stream>>>(
                 static_cast<const T *>(Q), static_cast<T *>(O), rope.arg, s.st, s.H, t0, t1, C, S, z, eps,
-                workgroup_order(s));
+                apply_order(layout_of(s), rope.mode == kRopeTable, rope.mode == kRope3D, n));
         });
         return launch_status();
     }
@@ -898,7 +879,8 @@ sv_status sv_measure_apply_variant(int32_t variant, const void *Q, const sv_tens
     auto launch = [&](auto kernel, int lds) {
         static_cast<void>(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         kernel<<<dim3(C, s.BH), KN::apply_threads, lds, static_cast<hipStream_t>(stream)>>>(
-            static_cast<const uint16_t *>(Q), static_cast<uint16_t *>(O), none.arg, s.st, s.H, s.d, tok_begin, tok_end, C, S, z, eps, workgroup_order(s));
+            static_cast<const uint16_t *>(Q), static_cast<uint16_t *>(O), none.arg, s.st, s.H, s.d, tok_begin, tok_end, C, S, z, eps,
+            apply_order(layout_of(s), false, false, n));
     };
     constexpr int lds0 = KN::apply_lds, lds1 = KN::apply_lds + kApplyStateLdsBytes;
     switch (variant) {

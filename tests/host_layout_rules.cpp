@@ -21,6 +21,28 @@ int main()
                         ++cases;
                     }
                 }
+    // the order rules at their lines
+    using sv::TokenLayout;
+    const int both = sv::kOrderChunkMajor | sv::kOrderLockstep, ls = sv::kOrderLockstep, cm = sv::kOrderChunkMajor;
+    auto tm = [](int B, int H, int d, int e) { return TokenLayout{B * H, H, d, e, d, (int64_t)H * d}; };       // [B][N][H][d]
+    auto hm = [](int B, int H, int d, int e) { return TokenLayout{B * H, H, d, e, 1000 * d, d}; };              // [B][H][N][d]
+    struct Want { TokenLayout t; bool table, factored; int n, state, apply; } want[] = {
+        {hm(2, 32, 64, 2), false, false, 20000, 0, 0}, {hm(2, 32, 64, 2), true, false, 20000, 0, 0},
+        {hm(2, 20, 112, 2), true, false, 20000, cm, 0}, {hm(2, 20, 128, 4), true, false, 20000, 0, 0},
+        {tm(1, 1, 64, 2), false, false, 20000, 0, 0},
+        {tm(4, 3, 64, 2), false, false, 20000, both, ls}, {tm(1, 13, 64, 2), false, false, 20000, ls, ls},
+        {tm(2, 32, 64, 2), false, false, 12287, ls, ls}, {tm(2, 32, 64, 2), false, false, 12288, ls, both},
+        {tm(2, 32, 64, 2), false, true, 20000, ls, ls}, {tm(2, 32, 64, 2), true, false, 5, ls, both},
+        {tm(4, 32, 64, 2), false, false, 20000, ls, ls}, {tm(1, 96, 64, 2), false, false, 20000, ls, both},
+        {tm(1, 20, 112, 2), false, true, 5, both, both}, {tm(1, 20, 128, 2), false, false, 5, ls, ls},
+        {tm(1, 20, 128, 2), true, false, 5, both, ls}, {tm(1, 20, 32, 2), false, false, 5, both, both},
+        {tm(1, 20, 64, 4), true, false, 5, ls, ls}, {tm(1, 20, 32, 4), false, false, 5, both, both},
+    };
+    for (const Want &w : want) {
+        const int s = sv::state_order(w.t, w.table), a = sv::apply_order(w.t, w.table, w.factored, w.n);
+        if (s != w.state || a != w.apply) return printf("FAIL order BH=%d H=%d d=%d e=%d n=%d: %d %d\n", w.t.BH, w.t.H, w.t.d, w.t.elem_bytes, w.n, s, a), 1;
+        ++cases;
+    }
     printf("OK %ld\n", cases);
     return 0;
 }
