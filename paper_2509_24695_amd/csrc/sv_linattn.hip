@@ -44,12 +44,21 @@ constexpr bool kApplyHiLo = true;
 // so few and long ones win (d = 64, 4 680 tokens: 46.5 us for the layer with two, 52.8 with four, 57.8 with eight); at
 // d = 32 the state is small and more waves cover the loads (44.8, 42.1, 41.7 us).
 constexpr int f32_apply_wgs_per_cu(int d) { return d == 32 ? 4 : 2; }
-// d = 32: tokens up to which one workgroup sums a head in one launch, instead of several and a second launch for their sum.  The
-// lines are where the two meet in layers enqueued back to back through the binding, where the second launch costs the host 2.5 us
-// (one / several, fp32: 8 heads, 1 024 tokens 15.9 / 17.4 us, 1 280 17.7 / 17.4; 32 heads, 768 15.8 / 17.7, 1 024 17.4 / 17.3; 64 heads,
-// 512 14.7 / 17.3, 768 17.2 / 17.3, 1 024 19.7 / 17.6; with a rotation some 100 tokens earlier, bf16 some 150 later).  A caller who
-// waits for every layer sees them meet at 512 tokens (fp32) and 1 024 (bf16), 31 against 28 us at 1 024 tokens of fp32.
-int f32_sole_tokens(int BH, int elem_bytes) { return (BH <= 16 ? 1152 : BH <= 32 ? 896 : 768) + (elem_bytes == 2 ? 128 : 0); }
+// fp32-arithmetic state: tokens up to which one workgroup sums a head in one launch, instead of several and a second launch for
+// their sum.  The lines are where the two meet in layers enqueued back to back through the binding, where the second launch costs the
+// host 2.5 us.  One / several, fp32:
+//   d = 32   8 heads, 1 024 tokens 15.9 / 17.4 us, 1 280 17.7 / 17.4; 32 heads, 768 15.8 / 17.7, 1 024 17.4 / 17.3; 64 heads, 512 14.7 / 17.3,
+//            768 17.2 / 17.3, 1 024 19.7 / 17.6; with a rotation some 100 tokens earlier, bf16 some 150 later;
+//   d = 64   8 heads, 256 tokens 15.2 / 17.8, 384 17.5 / 17.7; 64 heads, 192 15.5 / 17.4, 256 16.8 / 17.6, with a table 19.1 / 18.1 (the
+//            scalar kernels took 17.6 there: several workgroups had made the smallest calls slower);
+//   d = 112  from 72 to 128 tokens on several are faster.
+// A caller who waits for every layer sees them meet earlier: d = 32 at 512 tokens (fp32) and 1 024 (bf16), 31 against 28 us at 1 024 of
+// fp32; d = 64 at 256.
+int f32_sole_tokens(int d, int BH, int elem_bytes)
+{
+    if (d == 32) return (BH <= 16 ? 1152 : BH <= 32 ? 896 : 768) + (elem_bytes == 2 ? 128 : 0);
+    return d == 64 ? (BH <= 16 ? 256 : 192) : 0;
+}
 // d = 64: the denominators phi(Q_i).z ride through the matrix core as two more operand rows (false) or are taken on
 // the vector ALU with a wavefront-level reduction (true).  Measured level (within 1 % either way at 32 760 and
 // 75 600 tokens; the one-launch block step 0.5-1 us per block slower with the vector ALU form), so they stay on
@@ -443,7 +452,7 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
         with_f32_kernels(s, rope.mode, [&](auto kn) {
             using KN = decltype(kn);
             using T = typename KN::T;
-            const bool sole = KN::D == 32 && n <= f32_sole_tokens(s.BH, s.elem_bytes);
+            const bool sole = n <= f32_sole_tokens(s.d, s.BH, s.elem_bytes);
             const int C = sole ? 1 : plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
             const auto kernel = C == 1 ? KN::state : KN::state_partial;
             kernel<<<dim3(C, s.BH), kThreads, KN::state_lds, stream>>>(

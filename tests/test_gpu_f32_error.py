@@ -30,7 +30,8 @@ def _rms(a, ref):
     return float(np.sqrt(((a.astype(np.float64) - ref) ** 2).sum() / (ref ** 2).sum()))
 
 
-@pytest.mark.parametrize("d,BH,N", [(32, 2, 1024), (32, 20, 384), (32, 2, 1153), (32, 33, 769), (64, 2, 2000), (64, 160, 384), (112, 8, 384),
+@pytest.mark.parametrize("d,BH,N", [(32, 2, 1024), (32, 20, 384), (32, 2, 1153), (32, 33, 769), (64, 2, 256), (64, 33, 193), (64, 2, 2000),
+                                    (64, 160, 384), (112, 8, 384),
                                     (112, 160, 384), (128, 32, 1024)])
 def test_sums_are_as_exact_as_short_chunks(d, BH, N):
     import torch
