@@ -1,8 +1,10 @@
-// Tile order of the temporal-convolution kernel: which tile a workgroup id works on.
-// Plain C++ (no device code), shared by the kernel, the launcher and a host-side test.
+// Tiles of the temporal-convolution kernels: which size a call takes, which tile a workgroup id works on, which taps a tile
+// needs.  Plain C++ (no device code), shared by the kernels, the launcher and host-side tests.
 #pragma once
 
 #include <stdint.h>
+
+#include <initializer_list>
 
 #ifndef SV_HOST_DEVICE
 #if defined(__HIPCC__)
@@ -47,6 +49,62 @@ SV_HOST_DEVICE inline void tc_taps(int g0, int g1, int HW, int T, bool cache, in
     const int f0 = g0 / HW, f1 = g1 / HW;                      // frames counted over batches
     lo = !cache && (T == 1 || (f0 == f1 && f0 % T == 0)) ? 1 : 0;
     hi = T == 1 || (f0 == f1 && f0 % T == T - 1) ? 2 : 3;
+}
+
+// The kernels a call may take: tconv_mfma on tiles of four sizes, and tconv_mfma32 (256 x 256, 32 x 32 x 16 instructions).
+enum TconvFormId { kForm256, kForm256x128, kForm128, kForm64, kForm256Long, kTconvForms };
+struct TconvTileSize { int bm, bn; };
+constexpr TconvTileSize kTconvTile[kTconvForms] = {{256, 256}, {256, 128}, {128, 128}, {64, 64}, {256, 256}};
+
+// Time of a call in us on the tile kernel `f`, as a fit to what it measures: a start that grows with the tile, and a time per
+// K-step of 32 channels that depends on how many tiles a compute unit gets.  From 1 050 calls (1 to 151 200 tokens, 64 to
+// 2 240 channels, 1 to 21 frames, with and without a cache; five boxes), each on all five kernels: the kernel with the smallest
+// fitted time is on average 0.2 % and at worst 14 % slower than the fastest one, and never more than 3.4 % slower than the single
+// kernel of 256 x 256 that served every call before.  A rule without the starts, and with one time per step for each kernel, took 4.9 % and up
+// to 56 % (short contractions on too large tiles; 3 600 tokens of 1 920 channels 110 us where the long kernel takes 103).
+// Where channels are no multiple of 32 rows start inside 64-byte blocks, which costs loads more than products: TAIL.
+inline double tconv_cost(TconvFormId f, int64_t M, int D, int taps, int num_cu)
+{
+    const int64_t tiles = ((M + kTconvTile[f].bm - 1) / kTconvTile[f].bm) * ((D + kTconvTile[f].bn - 1) / kTconvTile[f].bn);
+    const double per_cu = (double)tiles / num_cu;
+    const double rounds = (double)((tiles + num_cu - 1) / num_cu);
+    const double steps = (double)((D + 31) / 32) * taps;
+    const bool tail = D % 32 != 0;
+    // one tile to a compute unit at a time: per step with up to half of the units busy, with all, and per further round
+    struct Large { double start, half, full, more; };
+    constexpr Large k256[2] = {{12.5, 0.555, 0.63, 0.66}, {12, 0.70, 0.81, 0.82}};
+    constexpr Large k256x128[2] = {{9.5, 0.565, 0.565, 0.62}, {9.5, 0.57, 0.64, 0.64}};
+    constexpr Large kLong[2] = {{10.2, 0.535, 0.62, 0.67}, {10, 0.70, 0.82, 0.83}};
+    // two at a time: per step with one tile each (on few units, on all), just above one, with two; then in proportion
+    struct Middle { double start, few, one, above, two, each; };
+    constexpr Middle k128[2] = {{6, 0.36, 0.36, 0.45, 0.66, 0.345}, {6, 0.335, 0.40, 0.62, 0.70, 0.44}};
+    // five at a time: per step by tiles per unit, rounded up
+    struct Small { double start, base, each; };
+    constexpr Small k64[2] = {{4, 0.06, 0.115}, {3.6, 0.01, 0.17}};
+
+    if (f == kForm64) return k64[tail].start + steps * (k64[tail].base + k64[tail].each * rounds);
+    if (f == kForm128) {
+        const Middle &m = k128[tail];
+        const double over = m.each * per_cu;
+        return m.start + steps * (per_cu <= 1 ? m.few + (m.one - m.few) * per_cu
+                                  : per_cu <= 2 ? m.above + (m.two - m.above) * (per_cu - 1) : over > m.two ? over : m.two);
+    }
+    const Large &l = f == kForm256 ? k256[tail] : f == kForm256x128 ? k256x128[tail] : kLong[tail];
+    const double filled = per_cu <= 0.5 ? 0 : 2 * per_cu - 1;
+    return l.start * (1 + 0.4 * (rounds - 1)) + steps * (rounds <= 1 ? l.half + (l.full - l.half) * filled : rounds * l.more);
+}
+
+// Which kernel serves a call of M tokens and D channels in blocks of T frames on num_cu compute units.
+inline TconvFormId tconv_form(int64_t M, int D, int T, bool cache, int num_cu)
+{
+    const int taps = T > 1 ? 3 : cache ? 2 : 1;       // of a tile that needs most (tc_taps)
+    TconvFormId best = kForm256;
+    double least = tconv_cost(kForm256, M, D, taps, num_cu);
+    for (const TconvFormId f : {kForm256x128, kForm128, kForm64, kForm256Long}) {
+        const double us = tconv_cost(f, M, D, taps, num_cu);
+        if (us < least) { least = us; best = f; }
+    }
+    return best;
 }
 
 }  // namespace sv

@@ -1,0 +1,33 @@
+// Prints, for each "M D T cache num_cu" on the command line, the kernel that tconv_form (csrc/tconv_tiles.hpp) chooses.  With no
+// arguments: over a range of calls the choice is one of the kernels, its cost is the smallest, and costs are finite and positive.
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+
+#include "../paper_2509_24695_amd/csrc/tconv_tiles.hpp"
+
+int main(int argc, char **argv)
+{
+    using namespace sv;
+    const char *names[kTconvForms] = {"256x256", "256x128", "128x128", "64x64", "long"};
+    for (int i = 1; i + 4 < argc; i += 5)
+        printf("%s\n", names[tconv_form(atoll(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3]) != 0, atoi(argv[i + 4]))]);
+    if (argc > 1) return 0;
+    long cases = 0;
+    for (int cus : {1, 64, 256, 304})
+        for (long M : {1L, 63L, 64L, 65L, 1560L, 4680L, 32760L, 151200L, 2147483647L})
+            for (int D = 8; D <= 32768; D = D < 512 ? D + 8 : D * 3 / 2 / 8 * 8)
+                for (int T : {1, 2, 21})
+                    for (int cache = 0; cache < 2; ++cache) {
+                        const TconvFormId f = tconv_form(M, D, T, cache != 0, cus);
+                        if (f < 0 || f >= kTconvForms) return printf("FAIL form M=%ld D=%d\n", M, D), 1;
+                        const int taps = T > 1 ? 3 : 1 + cache;
+                        for (int g = 0; g < kTconvForms; ++g) {
+                            const double us = tconv_cost((TconvFormId)g, M, D, taps, cus);
+                            if (!(us > 0) || !std::isfinite(us) || us < tconv_cost(f, M, D, taps, cus)) return printf("FAIL cost M=%ld D=%d form %d\n", M, D, g), 1;
+                        }
+                        ++cases;
+                    }
+    printf("OK %ld calls\n", cases);
+    return 0;
+}
