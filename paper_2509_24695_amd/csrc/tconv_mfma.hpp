@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kThreads) void tconv_mfma(TconvArgs a)
 
     // the taps that some row of the tile needs (tc_taps): frame -1 without a cache and frame T are zero
     int tap_lo, tap_hi;
-    tc_taps(m0, (m0 + P::BM < M ? m0 + P::BM : M) - 1, a.HW, a.T, a.cache != nullptr, tap_lo, tap_hi);
+    tc_taps(m0, tc_last_row(m0, P::BM, M), a.HW, a.T, a.cache != nullptr, tap_lo, tap_hi);
     const int steps = (tap_hi - tap_lo) * KC;
 
     // ---- loader role: one 16-byte chunk of rows r0 + 64 i of both operand tiles ------------------
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kThreads) void tconv_mfma32(TconvArgs a)
     const int m0 = tm * kTcBM, n0 = tn * kTcBN;
     const int KC = (D + kTcBK - 1) / kTcBK;
     int tap_lo, tap_hi;                // the taps that some row of the tile needs
-    tc_taps(m0, (m0 + kTcBM < M ? m0 + kTcBM : M) - 1, a.HW, a.T, a.cache != nullptr, tap_lo, tap_hi);
+    tc_taps(m0, tc_last_row(m0, kTcBM, M), a.HW, a.T, a.cache != nullptr, tap_lo, tap_hi);
     const int steps = (tap_hi - tap_lo) * KC;
 
     // ---- loader role: one 16-byte chunk of rows r0 + 64 i of both operand tiles ------------------

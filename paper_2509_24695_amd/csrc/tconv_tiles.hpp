@@ -107,4 +107,7 @@ inline TconvFormId tconv_form(int64_t M, int D, int T, bool cache, int num_cu)
     return best;
 }
 
+// Last token row of the tile of `bm` rows from m0 on, M tokens in all (m0 < M; m0 + bm may not fit an int).
+SV_HOST_DEVICE inline int tc_last_row(int m0, int bm, int M) { return M - m0 > bm ? m0 + bm - 1 : M - 1; }
+
 }  // namespace sv

@@ -28,6 +28,12 @@ int main(int argc, char **argv)
                         }
                         ++cases;
                     }
+    // rows of a tile: the last one exists, also where the tile's end does not fit an int
+    const int max = 2147483647;
+    struct { int m0, bm, M, want; } rows[] = {{0, 256, 1, 0}, {0, 64, 64, 63}, {64, 64, 65, 64}, {max - 255, 256, max, max - 1}, {max - 7, 64, max, max - 1},
+                                             {max - 300, 256, max, max - 45}};
+    for (auto &r : rows)
+        if (tc_last_row(r.m0, r.bm, r.M) != r.want) return printf("FAIL last row %d\n", tc_last_row(r.m0, r.bm, r.M)), 1;
     printf("OK %ld calls\n", cases);
     return 0;
 }
