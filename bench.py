@@ -436,9 +436,9 @@ def bench_tconv(w, iters, sv, torch):
 
     loop_variants = None
     if w.D % 32 == 0:
-        names = ["library kernel", "without the loads into LDS", "without the operand reads from LDS", "without both"]
+        names = ["256 x 256 kernel", "without the loads into LDS", "without the operand reads from LDS", "without both"]
         loop_variants = {names[v]: variant_us(v) for v in range(4)}
-        loop_variants["library kernel, timed again"] = variant_us(0)
+        loop_variants["256 x 256 kernel, timed again"] = variant_us(0)
     wg_flops = k_steps * 4 * 64 * 2 * 16 * 16 * 32
     return {"workload": f"{w.name}: B={w.B} T={w.T} HW={w.HW} D={w.D}, {w.n_blocks} block(s)", "us_per_block": us,
             "tokens_per_s": w.tokens / (us * 1e-6), "dtype": "bf16",

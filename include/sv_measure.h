@@ -62,9 +62,10 @@ sv_status sv_measure_apply_variant(int32_t variant, const void *Q, const sv_tens
                                    int32_t tok_begin, int32_t tok_end,
                                    const float *S, const float *z, float eps, void *O, void *stream);
 
-/* The tile kernel of sv_tconv_block_step (sv_tconv.h; same arguments without cache_out and dtype, same checks,
- * same grid, bf16 only) with parts of its loop left out, to time what each part costs (no passage of the paper):
- *   variant 0  the kernel sv_tconv_block_step launches;
+/* The kernel with tiles of 256 x 256, which is what sv_tconv_block_step (sv_tconv.h) takes for the largest calls, with parts of its
+ * loop left out, to time what each part costs (no passage of the paper).  Same arguments without cache_out and dtype, same
+ * checks, bf16 only; all variants run this kernel on the same grid, whatever the call's size:
+ *   variant 0  the kernel as it is (its results are those of sv_tconv_block_step);
  *   variant 1  without the loads from memory into LDS inside the tile loop (the prologue's stay);
  *   variant 2  without the operand reads from LDS inside the tile loop;
  *   variant 3  without both: the matrix-core instructions, the barriers, prologue and epilogue.

@@ -34,11 +34,11 @@ template <int F> TconvForm form()
 const TconvForm kForms[kTconvForms + 1] = {form<kForm256>(), form<kForm256x128>(), form<kForm128>(), form<kForm64>(),
                                            {kTcBM, kTcBN, kTcLdsBytes, tconv_mfma32<false>}, {kTcBM, kTcBN, kTcLdsBytes, tconv_mfma32<true>}};
 
-// The measurement variants of the 256 x 256 kernel (sv_measure_tconv_variant).
+// The measurement variants of the 256 x 256 kernel (sv_measure_tconv_variant; 0: the kernel itself).
 constexpr int kVariants = 4;
 const TconvKernel kVariantKernels[kVariants] = {tconv_mfma<TcTile<256, 256>>, tconv_mfma<TcTile<256, 256>, 1>,
                                                 tconv_mfma<TcTile<256, 256>, 2>, tconv_mfma<TcTile<256, 256>, 3>};
-constexpr int kByRule = 0;         // the library's own calls: the form that tconv_form chooses
+constexpr int kByRule = -1;        // "variant" of the library's own calls: the form that tconv_form chooses
 
 // Compute units of the current device; 0 on failure.  The kernels need their dynamic LDS allowed once per device.
 int tconv_ready()

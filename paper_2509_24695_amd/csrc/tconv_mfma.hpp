@@ -164,8 +164,12 @@ __global__ __launch_bounds__(kThreads) void tconv_mfma(TconvArgs a)
         clip_tail();
     };
     // Requests load m (m < MP: A row pass m, else B row pass m - MP) of the step to request next.
-    auto request_one = [&](int stage, int m) {
+    auto request_one = [&](int stage, int m, bool leave_out = false) __attribute__((always_inline)) {
         const uint16_t *p = (m < MP ? srcA[m < MP ? m : 0] : srcB[m < MP ? 0 : m - MP]) + kc_n * kTcBK;
+        if (leave_out) {               // the address all the same: without it the compiler lays out another loop
+            asm volatile("" ::"v"(p));
+            return;
+        }
         tc_load_to_lds(p, lds + stage * P::kStage + (m < MP ? m * 4096 : P::kTileA + (m - MP) * 4096) + wave * 1024);
     };
 
@@ -217,11 +221,9 @@ __global__ __launch_bounds__(kThreads) void tconv_mfma(TconvArgs a)
                 for (int k = 0; k < READS; ++k)
                     if (m == k * (MFMAS * 3 / 4) / READS) op[cur ^ 1][k] = operand(next, k);
             }
-            if (!(SKIP & 1)) {
 #pragma unroll
-                for (int l = 0; l < LOADS; ++l)
-                    if (m == l * MFMAS / LOADS) request_one(stage, l);
-            }
+            for (int l = 0; l < LOADS; ++l)
+                if (m == l * MFMAS / LOADS) request_one(stage, l, SKIP & 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         advance();
