@@ -80,8 +80,8 @@ struct Shape {
 
 struct Device {
     int num_cu = 0;
-    // how many workgroups fit on the device at once, [DP = 128][RoPE mode]
-    int state_resident_wgs[2][3] = {{0, 0, 0}, {0, 0, 0}};   // state kernel with in-kernel finalize
+    // how many workgroups fit on the device at once
+    int state_resident_wgs[2][3][2] = {};                    // state kernel with in-kernel finalize, [DP = 128][RoPE mode][SHARED]
     int fused_resident_wgs[3] = {0, 0, 0};                   // one-launch block step (d = 64), by RoPE mode
     bool ok = false;
 };
@@ -92,7 +92,7 @@ struct Device {
 template <int DP, int ROPE, bool SHARED = false> struct Kernels;
 template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
-    static constexpr int W = 0;
+    static constexpr int W = 0, kShared = 0;         // SHARED makes no difference
     static constexpr bool kWideState = false;
     static constexpr auto state = state_mfma_d64<kStateTile, kStateWaves, kStateDepth, true, ROPE>;
     static constexpr auto state_partial = state_mfma_d64<kStateTile, kStateWaves, kStateDepth, false, ROPE>;
@@ -119,7 +119,7 @@ template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
     static constexpr int apply_wgs_per_cu_short = apply_wgs_per_cu, apply_short_steps = 0;   // no other form for short ranges
 };
 template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
-    static constexpr int W = 1;
+    static constexpr int W = 1, kShared = SHARED;
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
     static constexpr bool kWideState = true;
     template <bool FINALIZE> static constexpr auto pick_state() {
@@ -183,7 +183,7 @@ template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(KN::state),
                                                      64 * kStateWaves, KN::state_lds) != hipSuccess)
         per_cu = 0;
-    d.state_resident_wgs[KN::W][ROPE] = per_cu * d.num_cu;
+    d.state_resident_wgs[KN::W][ROPE][KN::kShared] = per_cu * d.num_cu;
 }
 
 // Calls f(Kernels<DP, ROPE, SHARED>{}) for the MFMA kernel family that serves head dimension d, RoPE mode and layout.
@@ -410,7 +410,7 @@ void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, c
         using KN = decltype(kn);
         const int C = plan_chunks(s.BH, t1 - t0, KN::state_wg_tokens, dev.num_cu);
         const int order = state_order(layout_of(s), rope.mode == kRopeTable);
-        if ((int64_t)C * s.BH <= dev.state_resident_wgs[KN::W][rope.mode]) {
+        if ((int64_t)C * s.BH <= dev.state_resident_wgs[KN::W][rope.mode][KN::kShared]) {
             // the head's workgroups wait for each other inside the kernel: all must be resident
             KN::state<<<dim3(C, s.BH), 64 * kStateWaves, KN::state_lds, stream>>>(
                 k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, next_epoch(s.host_epochs_only),
