@@ -8,7 +8,8 @@ once.  Inputs are synthetic (i.i.d. Gaussian times 0.5, bf16), generated on the
 device and resident in HBM before the timed region starts; buffer sets rotate
 so that repeats are not served from the 256 MB Infinity Cache.
 
-Prints ONE JSON line.  `value` is tokens/s of the layer (B*N / time per step) on
+Prints ONE JSON line, short enough for a caller that keeps the last few kilobytes of the output: no
+lists over blocks, no explanations, numbers below the top level to five digits; --details FILE writes everything.  `value` is tokens/s of the layer (B*N / time per step) on
 the headline workload: the 720p-like bidirectional layer (B = 2, 64 heads of
 75 600 tokens), the largest configuration of the method that one call covers.
 `roofline` refers to the slower of the two kernels of a step (state or apply),
@@ -16,8 +17,8 @@ timed with HIP events on the launch stream over a second pass of the same steps
 (events between kernels cost a few microseconds, so they stay out of `value`).
 `cpu_baseline` is the float64 oracle timed on the host cores on the same
 workload.  The 480p-like layer is reported under `secondary`, the block-causal
-workloads under `block_stream` (with the latency and the device memory of every
-block), the paper's head geometry under `geometry_h20d112`.
+workloads under `block_stream` (latency and device memory of every
+block: --details), the paper's head geometry under `geometry_h20d112`.
 """
 from __future__ import annotations
 
@@ -90,7 +91,36 @@ def _parse():
     ap.add_argument("--calibration-copy", type=int, default=0,
                     help="also run this many plain device copies of one token tensor (known size: "
                          "the same bytes read and written), for scaling rocprofv3 FETCH_SIZE/WRITE_SIZE")
+    ap.add_argument("--details", metavar="FILE", help="write everything measured to FILE as JSON")
     return ap.parse_args()
+
+
+# What only --details FILE holds: values per block, and what is constant or follows from the rest.
+DETAILS = {"latency_us_per_block", "latency_us_per_block_worst_of_3_passes", "allocated_bytes_after_block",
+           "device_bytes_in_use_after_block", "peak_new_device_bytes_during_stream", "library_bytes", "what", "traffic_source",
+           "tokens_per_block", "avg_launch_ms_between_events", "us_per_tile_on_a_full_device", "us_per_tile_on_an_idle_device",
+           "algorithmic_flops_per_launch", "hbm_GBps", "first", "min", "bytes_each", "dtype", "unit", "peak", "bound",
+           "us_8_workgroups", "workgroups", "bytes", "algorithmic_bytes_per_launch", "k_steps", "TFLOPs"}
+WHOLE = {"config", "roofline", "cpu_baseline"}                   # printed as they are
+STREAM_DETAILS = DETAILS | {"roofline", "stream_ceiling", "tokens_per_s", "max"}
+
+
+def _short(v, leave_out):
+    """v without the keys in leave_out, floats to five digits."""
+    if isinstance(v, dict):
+        return {k: _short(x, leave_out) for k, x in v.items() if k not in leave_out}
+    if isinstance(v, list):
+        return [_short(x, leave_out) for x in v]
+    return float(f"{v:.5g}") if isinstance(v, float) else v
+
+
+def printed_line(out):
+    """The one JSON line: the headline's numbers as they are, the rest shortened."""
+    line = {}
+    for k, v in out.items():
+        nested = isinstance(v, (dict, list)) and k not in WHOLE
+        line[k] = _short(v, STREAM_DETAILS if k == "block_stream" else DETAILS) if nested else v
+    return json.dumps(line)
 
 
 def _randn_bf16(shape, gen):
@@ -673,7 +703,10 @@ def main():
         # the other cached operator of the block-causal model (Sec. 3.3.1): dense, so bound by the matrix cores
         out["tconv"] = [bench_tconv(wl.TCONV_WORKLOADS["tconv_480p"], 10, sv, torch),
                         bench_tconv(wl.TCONV_WORKLOADS["tconv_block_480p"], 10, sv, torch)]
-    print(json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f)
+    print(printed_line(out))
 
 
 if __name__ == "__main__":
