@@ -445,7 +445,20 @@ __device__ __forceinline__ void state_finalize_slice(const float *__restrict__ p
         f32x2 x[UNITS];
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) x[u] = carry[u];
-        if (v0 != sl.lo + tid) hs.carried<THREADS>(d, v0 - tid, tid, x);   // slices longer than one round: fetched here
+        if (v0 != sl.lo + tid) {                                 // slices longer than one round: fetched here
+            if (MASKED) {
+                hs.carried<THREADS>(d, v0 - tid, tid, x);
+            } else {
+                // unit by unit under its condition: this round is rare in the one-launch block step, and fetched all at once it
+                // had the compiler lay the full-table form out with 0.5 us more per block (32 heads, 1 560 tokens: 18.2 -> 18.7)
+#pragma unroll
+                for (int u = 0; u < UNITS; ++u) {
+                    const int v = v0 + u * THREADS;
+                    x[u] = f32x2{0.f, 0.f};
+                    if (hs.S_in && v < hi) x[u] = *reinterpret_cast<const f32x2 *>(v < sl.s_units ? hs.S_in + 2 * v : hs.z_in + 2 * (v - sl.s_units));
+                }
+            }
+        }
         // Straight-line loads without a branch: this runs on the chain of round trips by which a head agrees on its
         // state, where every instruction counts.  MASKED: units past the slice and partials past C are addressed out of range
         // and read nothing (two instructions per load; a group or a round that fits badly would read several times what
