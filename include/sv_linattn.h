@@ -152,7 +152,7 @@ void sv_linattn_set_wait_limit(int64_t polls);
  *     accumulate != 0:  S, z += sums            (carried state updated in place)
  * An empty range zero-fills (accumulate == 0) or leaves S, z unchanged.
  * The token range is split over workgroups; their fp32 partial sums go through
- * `workspace` and are combined in chunk order. */
+ * `workspace` and are combined in a fixed order. */
 sv_status sv_linattn_state(const void *K, const void *V, const sv_tensor_desc *kv,
                            int32_t tok_begin, int32_t tok_end, int accumulate,
                            float *S, float *z,

@@ -49,7 +49,9 @@ extern "C" {
  * B, T, HW >= 1; D >= 8 and a multiple of 8; B*T*HW and 3*D*D below 2^31.  All
  * pointers 16-byte aligned.  y must not overlap x, W or cache_in; cache_out must not
  * overlap x, W or y (SV_ERR_SHAPE).  Inputs must
- * be finite.  Arguments are checked on the host before anything is launched; an
+ * be finite: a tap that meets only zeros (frame -1 without a cache, frame T) may or may not be
+ * multiplied out, so infinite or NaN weights of such a tap show in some rows of the first or last
+ * frame and not in others.  Arguments are checked on the host before anything is launched; an
  * error other than SV_ERR_LAUNCH means nothing was written.  Work is enqueued
  * on `stream` (hipStream_t as void*, NULL = default stream); the library
  * allocates nothing and keeps no pointer.  Results are bit-reproducible (fixed

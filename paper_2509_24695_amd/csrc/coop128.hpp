@@ -11,8 +11,8 @@
 //
 //   apply: wave w loads rows 8w .. 8w+8 of a 32-token Q tile, computes 32 of the 128 output
 //          features of the whole tile (its 128 x 32 panel of S stays in registers) into a shared
-//          output tile, then stores whole rows 8w .. 8w+8 of O; two barriers per tile, two
-//          workgroups per compute unit (the stream and the loop are written for other splits of
+//          output tile, then stores whole rows 8w .. 8w+8 of O; two barriers per tile, two or
+//          three workgroups per compute unit (see sv_linattn.hip; the stream and the loop are written for other splits of
 //          the tile among the waves as well, see CoopApplyStream).
 //
 // Barriers are bare s_barrier instructions behind an LDS-only wait, so the global loads of later

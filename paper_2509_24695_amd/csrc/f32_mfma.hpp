@@ -16,8 +16,8 @@
 //           feature(j, 0) + q .. feature(j, 3) + q; the state is kept in registers in the matching order.  Output block b holds features NB*n + b, so that a
 //           lane ends up with NB consecutive features of a token and stores them as they are.
 //
-// Measured (both kernels of a layer, before: plain FMAs out of LDS): fp32, 32 heads of 64, 4 680 tokens 120 -> 46.5 us;
-// bf16, 128 heads of 32, 4 096 tokens 130 -> 42 us; fp32, 2 heads of 32, 1 024 tokens 17.7 -> 14.9 us.
+// Measured (both kernels of a layer, before: plain FMAs out of LDS): fp32, 32 heads of 64, 4 680 tokens 120 -> 45.6 us;
+// bf16, 128 heads of 32, 4 096 tokens 130 -> 40.5 us; fp32, 2 heads of 32, 1 024 tokens 17.8 -> 14.8 us.
 // What is left above the streams' time is the start of the kernels.
 //
 // d <= 64: a wave holds the whole state and works alone on its tiles.  d = 112, 128: the waves of a workgroup
@@ -308,11 +308,11 @@ template <int D> struct ApplyF32 {
     static constexpr int NB = D == 64 ? 4 : 2;              // blocks of 16 output features per wave
     static constexpr int NJ = D / 16;
     static constexpr int TILE = 16;
-    // tiles in flight per wave; the rotation of wide heads leaves registers for one
     // first of the four features that lane (n, g) holds in chunk j: whole 64-byte runs of a row per load
     template <typename T> static __device__ __forceinline__ int feature(int j, int g) {
         return sizeof(T) == 2 ? 8 * g + 4 * j : 16 * j + 4 * g;
     }
+    // tiles in flight per wave; the rotation of wide heads leaves registers for one
     template <int ROPE> static constexpr int kDepth = ROPE != kRopeNone && D > 64 ? 1 : 2;
     static constexpr int kWgTokens = kSplit ? TILE : 4 * TILE;
 };

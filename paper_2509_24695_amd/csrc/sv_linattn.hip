@@ -32,7 +32,7 @@ constexpr int kVersion = 500;   // 0.5.0
 // DP = 64 serves d = 64; DP = 128 serves d = 112 and 128.  Depths are tiles in
 // flight per wave (by RoPE mode: none, table, 3-D, where they differ).
 constexpr int kStateTile = 32, kStateWaves = 4, kApplyWaves = 4;
-constexpr int kCoopApplyWaves = 4, kCoopApplyNB = 1;   // d = 112/128 apply: one 128 x 32 panel of S per wave, two workgroups per compute unit
+constexpr int kCoopApplyWaves = 4, kCoopApplyNB = 1;   // d = 112/128 apply: one 128 x 32 panel of S per wave, two or three workgroups per compute unit
 constexpr int kStateDepth = 2, kApplyDepth = 2;
 // 16-token tiles in flight per wave of the wave-private d = 112/128 state kernel: three, or two with a rotation (its table
 // rows or its arithmetic need the registers)
