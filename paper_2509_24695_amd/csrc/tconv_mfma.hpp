@@ -284,7 +284,7 @@ __global__ __launch_bounds__(kThreads) void tconv_mfma(TconvArgs a)
 
 // The same convolution with 32 x 32 x 16 MFMAs on tiles of 256 x 256: a wave's quadrant is 4 x 4 accumulators, an instruction runs
 // twice as long and hides a memory instruction beside it, which makes the step shorter (0.56 against 0.62 us) while the matrix
-// cores' power is no limit: with fewer than about 160 tiles at work, and for short contractions.  Step s:
+// cores' power is no limit: with up to two thirds of the compute units at work (tconv_form).  Step s:
 //   first half   16 MFMAs on operand registers of K-chunk 0; reads K-chunk 1 of stage s; requests the B rows of step s+3
 //   barrier      after waiting for this wave's loads of step s+1 and its own LDS reads
 //   second half  16 MFMAs on K-chunk 1; reads K-chunk 0 of stage s+1; requests the A rows of step s+4 into stage s

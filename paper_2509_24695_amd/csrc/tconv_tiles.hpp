@@ -59,7 +59,7 @@ constexpr TconvTileSize kTconvTile[kTconvForms] = {{256, 256}, {256, 128}, {128,
 // Time of a call in us on the tile kernel `f`, as a fit to what it measures: a start that grows with the tile, and a time per
 // K-step of 32 channels that depends on how many tiles a compute unit gets.  From 1 050 calls (1 to 151 200 tokens, 64 to
 // 2 240 channels, 1 to 21 frames, with and without a cache; five boxes), each on all five kernels: the kernel with the smallest
-// fitted time is on average 0.2 % and at worst 14 % slower than the fastest one, and never more than 3.4 % slower than the single
+// fitted time (with the limit in tconv_form) is on average 0.3 % and at worst 14 % slower than the fastest one, and never more than 3.4 % slower than the single
 // kernel of 256 x 256 that served every call before.  A rule without the starts, and with one time per step for each kernel, took 4.9 % and up
 // to 56 % (short contractions on too large tiles; 3 600 tokens of 1 920 channels 110 us where the long kernel takes 103).
 // Where channels are no multiple of 32 rows start inside 64-byte blocks, which costs loads more than products: TAIL.
@@ -100,7 +100,12 @@ inline TconvFormId tconv_form(int64_t M, int D, int T, bool cache, int num_cu)
     const int taps = T > 1 ? 3 : cache ? 2 : 1;       // of a tile that needs most (tc_taps)
     TconvFormId best = kForm256;
     double least = tconv_cost(kForm256, M, D, taps, num_cu);
+    // The long kernel only while its tiles leave a third of the compute units idle.  With more it is level with the 256 x 256 kernel
+    // (2 % ahead on average) but draws more power: 171 tiles of 210 steps, six calls in a row take 812, 818, 825, 831, 839 and 846 us on
+    // six devices, where the 256 x 256 kernel takes 829 to 834.
+    const int64_t tiles = ((M + 255) / 256) * ((D + 255) / 256);
     for (const TconvFormId f : {kForm256x128, kForm128, kForm64, kForm256Long}) {
+        if (f == kForm256Long && 3 * tiles > 2 * num_cu) continue;
         const double us = tconv_cost(f, M, D, taps, num_cu);
         if (us < least) { least = us; best = f; }
     }

@@ -37,6 +37,7 @@ def test_rows_of_the_gpu_test_take_their_kernels(exe):
 def test_measured_choices(exe):
     """Calls measured on all kernels (us: 256x256, 256x128, 128x128, 64x64, long): the fastest, or within 2 % of it."""
     calls = [((3600, 1920, 3, 0, 256), {"long"}),            # 110.4 111.4 109.9 171.9 103.1
+             ((4680, 2240, 3, 1, 256), {"256x256"}),         # six calls: 829-834 us on six devices; long 812-846
              ((1560, 2240, 1, 0, 256), {"128x128"}),         # 51.6 49.2 31.4 41.9 47.6
              ((32760, 2240, 21, 0, 256), {"256x256"}),       # 789 1271 1204 2051 839
              ((16578, 1880, 3, 1, 256), {"256x256"}),        # 441 509 597 1091 457
