@@ -58,7 +58,7 @@ constexpr TconvTileSize kTconvTile[kTconvForms] = {{256, 256}, {256, 128}, {128,
 
 // Time of a call in us on the tile kernel `f`, as a fit to what it measures: a start that grows with the tile, and a time per
 // K-step of 32 channels that depends on how many tiles a compute unit gets.  From 1 050 calls (1 to 151 200 tokens, 64 to
-// 2 240 channels, 1 to 21 frames, with and without a cache; five boxes), each on all five kernels: the kernel with the smallest
+// 2 240 channels, 1 to 21 frames, with and without a cache; five devices), each on all five kernels: the kernel with the smallest
 // fitted time (with the limit in tconv_form) is on average 0.3 % and at worst 14 % slower than the fastest one, and never more than 3.4 % slower than the single
 // kernel of 256 x 256 that served every call before.  A rule without the starts, and with one time per step for each kernel, took 4.9 % and up
 // to 56 % (short contractions on too large tiles; 3 600 tokens of 1 920 channels 110 us where the long kernel takes 103).
