@@ -1,4 +1,5 @@
-"""ctypes binding of libsvlinattn.so: argument marshalling only.
+"""Binding of libsvlinattn.so: argument marshalling only, through ctypes and, for the calls that launch, through
+_sventry.so (csrc/py_entry.cpp), which takes 1.2 us per call for it where ctypes took 3.7 to 4.5.
 
 The functions carry the names and argument order of the C ABI
 (include/sv_linattn.h, include/sv_tconv.h, include/sv_measure.h).  Device buffers are torch tensors (or raw integer
@@ -27,7 +28,9 @@ EXPORTS = (
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libsvlinattn.so")
+_ENTRY_PATH = os.path.join(_PKG, "_sventry.so")
 _lib = None
+_entry = None
 
 
 class SvError(RuntimeError):
@@ -64,7 +67,7 @@ def library_path() -> str:
 
 def load_library():
     """Load libsvlinattn.so; raises if it has not been built (no fallback path)."""
-    global _lib
+    global _lib, _entry
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -132,8 +135,22 @@ def load_library():
     lib.sv_status_string.restype = ctypes.c_char_p
     lib.sv_version.argtypes = []
     lib.sv_version.restype = ctypes.c_int
-    _lib = lib
+    import importlib.util
+    if not os.path.exists(_ENTRY_PATH):
+        raise ImportError(f"{_ENTRY_PATH} is missing: build it with `python -m paper_2509_24695_amd.build`.")
+    spec = importlib.util.spec_from_file_location("_sventry", _ENTRY_PATH)
+    entry = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(entry)
+    entry.attach(lib._handle)
+    _lib, _entry = lib, entry
     return lib
+
+
+def _calls():
+    """The entry points of _sventry.so."""
+    if _entry is None:
+        load_library()
+    return _entry
 
 
 def _ptr(x):
@@ -189,81 +206,60 @@ def _check(status: int, where: str):
         raise SvError(status, where)
 
 
+# Each launching call below hands its arguments to the function of the same name in _sventry.so: buffers as tensors, integer
+# addresses or None; a workspace's size is the tensor's when none is given; streams as objects, integer handles or None.
+
 def sv_linattn_state(K, V, kv: TensorDesc, tok_begin: int, tok_end: int, accumulate: int, S, z,
                      workspace, workspace_bytes: int | None = None, stream=None) -> None:
-    d = kv._c() if kv is not None else None
-    wb = _nbytes(workspace) if workspace_bytes is None else int(workspace_bytes)
-    _check(load_library().sv_linattn_state(_ptr(K), _ptr(V), ctypes.byref(d) if d else None, tok_begin, tok_end,
-                                           int(accumulate), _ptr(S), _ptr(z), _ptr(workspace), wb,
-                                           _stream(stream)), "sv_linattn_state")
+    _check((_entry or _calls()).sv_linattn_state(K, V, kv, tok_begin, tok_end, accumulate, S, z, workspace,
+                                                 workspace_bytes, stream), "sv_linattn_state")
 
 
 def sv_linattn_apply(Q, q: TensorDesc, tok_begin: int, tok_end: int, S, z, eps: float, O, stream=None) -> None:
-    d = q._c() if q is not None else None
-    _check(load_library().sv_linattn_apply(_ptr(Q), ctypes.byref(d) if d else None, tok_begin, tok_end, _ptr(S),
-                                           _ptr(z), float(eps), _ptr(O), _stream(stream)), "sv_linattn_apply")
+    _check((_entry or _calls()).sv_linattn_apply(Q, q, tok_begin, tok_end, S, z, eps, O, stream), "sv_linattn_apply")
 
 
 def sv_block_linattn_step(Qb, Kb, Vb, blk: TensorDesc, S, z, eps: float, Ob, workspace,
                           workspace_bytes: int | None = None, stream=None) -> None:
-    d = blk._c() if blk is not None else None
-    wb = _nbytes(workspace) if workspace_bytes is None else int(workspace_bytes)
-    _check(load_library().sv_block_linattn_step(_ptr(Qb), _ptr(Kb), _ptr(Vb), ctypes.byref(d) if d else None,
-                                                _ptr(S), _ptr(z), float(eps), _ptr(Ob), _ptr(workspace), wb,
-                                                _stream(stream)), "sv_block_linattn_step")
+    _check((_entry or _calls()).sv_block_linattn_step(Qb, Kb, Vb, blk, S, z, eps, Ob, workspace, workspace_bytes, stream),
+           "sv_block_linattn_step")
 
 
 def sv_block_linattn_step_static(Qb, Kb, Vb, blk: TensorDesc, S, z, eps: float, Ob, stream=None) -> None:
     """sv_block_linattn_step on the library's own static workspace (no allocation anywhere)."""
-    d = blk._c() if blk is not None else None
-    _check(load_library().sv_block_linattn_step_static(_ptr(Qb), _ptr(Kb), _ptr(Vb), ctypes.byref(d) if d else None,
-                                                       _ptr(S), _ptr(z), float(eps), _ptr(Ob), _stream(stream)),
+    _check((_entry or _calls()).sv_block_linattn_step_static(Qb, Kb, Vb, blk, S, z, eps, Ob, stream),
            "sv_block_linattn_step_static")
 
 
 def sv_block_linattn_lookahead(Qb, Kb, Vb, blk: TensorDesc, S, z, eps: float, Ob, workspace,
                                workspace_bytes: int | None = None, stream=None) -> None:
-    d = blk._c() if blk is not None else None
-    wb = _nbytes(workspace) if workspace_bytes is None else int(workspace_bytes)
-    _check(load_library().sv_block_linattn_lookahead(_ptr(Qb), _ptr(Kb), _ptr(Vb), ctypes.byref(d) if d else None,
-                                                     _ptr(S), _ptr(z), float(eps), _ptr(Ob), _ptr(workspace), wb,
-                                                     _stream(stream)), "sv_block_linattn_lookahead")
+    _check((_entry or _calls()).sv_block_linattn_lookahead(Qb, Kb, Vb, blk, S, z, eps, Ob, workspace, workspace_bytes,
+                                                           stream), "sv_block_linattn_lookahead")
 
 
 def sv_linattn_state_rope(K, V, kv: TensorDesc, rope, tok_begin: int, tok_end: int, accumulate: int, S, z,
                           workspace, workspace_bytes: int | None = None, stream=None) -> None:
-    d = kv._c() if kv is not None else None
-    wb = _nbytes(workspace) if workspace_bytes is None else int(workspace_bytes)
-    _check(load_library().sv_linattn_state_rope(_ptr(K), _ptr(V), ctypes.byref(d) if d else None, _ptr(rope),
-                                                tok_begin, tok_end, int(accumulate), _ptr(S), _ptr(z),
-                                                _ptr(workspace), wb, _stream(stream)), "sv_linattn_state_rope")
+    _check((_entry or _calls()).sv_linattn_state_rope(K, V, kv, rope, tok_begin, tok_end, accumulate, S, z, workspace,
+                                                      workspace_bytes, stream), "sv_linattn_state_rope")
 
 
 def sv_linattn_apply_rope(Q, q: TensorDesc, rope, tok_begin: int, tok_end: int, S, z, eps: float, O,
                           stream=None) -> None:
-    d = q._c() if q is not None else None
-    _check(load_library().sv_linattn_apply_rope(_ptr(Q), ctypes.byref(d) if d else None, _ptr(rope), tok_begin,
-                                                tok_end, _ptr(S), _ptr(z), float(eps), _ptr(O), _stream(stream)),
+    _check((_entry or _calls()).sv_linattn_apply_rope(Q, q, rope, tok_begin, tok_end, S, z, eps, O, stream),
            "sv_linattn_apply_rope")
-
-
-def _block_rope(fn_name, Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace, workspace_bytes, stream):
-    d = blk._c() if blk is not None else None
-    wb = _nbytes(workspace) if workspace_bytes is None else int(workspace_bytes)
-    fn = getattr(load_library(), fn_name)
-    _check(fn(_ptr(Qb), _ptr(Kb), _ptr(Vb), ctypes.byref(d) if d else None, _ptr(rope), _ptr(S), _ptr(z), float(eps),
-              _ptr(Ob), _ptr(workspace), wb, _stream(stream)), fn_name)
 
 
 def sv_block_linattn_step_rope(Qb, Kb, Vb, blk: TensorDesc, rope, S, z, eps: float, Ob, workspace,
                                workspace_bytes: int | None = None, stream=None) -> None:
-    _block_rope("sv_block_linattn_step_rope", Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace, workspace_bytes, stream)
+    _check((_entry or _calls()).sv_block_linattn_step_rope(Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace,
+                                                           workspace_bytes, stream), "sv_block_linattn_step_rope")
 
 
 def sv_block_linattn_lookahead_rope(Qb, Kb, Vb, blk: TensorDesc, rope, S, z, eps: float, Ob, workspace,
                                     workspace_bytes: int | None = None, stream=None) -> None:
-    _block_rope("sv_block_linattn_lookahead_rope", Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace, workspace_bytes,
-                stream)
+    _check((_entry or _calls()).sv_block_linattn_lookahead_rope(Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace,
+                                                                workspace_bytes, stream),
+           "sv_block_linattn_lookahead_rope")
 
 
 def sv_linattn_workspace_init(workspace, B: int, H: int, d: int, workspace_bytes: int | None = None,
@@ -320,55 +316,37 @@ class Rope3D:
                         p(self.cs_w))
 
 
-def _r3(rope):
-    return ctypes.byref(rope._c()) if rope is not None else None
-
-
 def sv_linattn_state_rope3d(K, V, kv: TensorDesc, rope: Rope3D, tok_begin: int, tok_end: int, accumulate: int, S, z,
                             workspace, workspace_bytes: int | None = None, stream=None) -> None:
-    d = kv._c() if kv is not None else None
-    wb = _nbytes(workspace) if workspace_bytes is None else int(workspace_bytes)
-    _check(load_library().sv_linattn_state_rope3d(_ptr(K), _ptr(V), ctypes.byref(d) if d else None, _r3(rope),
-                                                  tok_begin, tok_end, int(accumulate), _ptr(S), _ptr(z),
-                                                  _ptr(workspace), wb, _stream(stream)), "sv_linattn_state_rope3d")
+    _check((_entry or _calls()).sv_linattn_state_rope3d(K, V, kv, rope, tok_begin, tok_end, accumulate, S, z, workspace,
+                                                        workspace_bytes, stream), "sv_linattn_state_rope3d")
 
 
 def sv_linattn_apply_rope3d(Q, q: TensorDesc, rope: Rope3D, tok_begin: int, tok_end: int, S, z, eps: float, O,
                             stream=None) -> None:
-    d = q._c() if q is not None else None
-    _check(load_library().sv_linattn_apply_rope3d(_ptr(Q), ctypes.byref(d) if d else None, _r3(rope), tok_begin,
-                                                  tok_end, _ptr(S), _ptr(z), float(eps), _ptr(O), _stream(stream)),
+    _check((_entry or _calls()).sv_linattn_apply_rope3d(Q, q, rope, tok_begin, tok_end, S, z, eps, O, stream),
            "sv_linattn_apply_rope3d")
-
-
-def _block_rope3d(fn_name, Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace, workspace_bytes, stream):
-    d = blk._c() if blk is not None else None
-    wb = _nbytes(workspace) if workspace_bytes is None else int(workspace_bytes)
-    fn = getattr(load_library(), fn_name)
-    _check(fn(_ptr(Qb), _ptr(Kb), _ptr(Vb), ctypes.byref(d) if d else None, _r3(rope), _ptr(S), _ptr(z), float(eps),
-              _ptr(Ob), _ptr(workspace), wb, _stream(stream)), fn_name)
 
 
 def sv_block_linattn_step_rope3d(Qb, Kb, Vb, blk: TensorDesc, rope: Rope3D, S, z, eps: float, Ob, workspace,
                                  workspace_bytes: int | None = None, stream=None) -> None:
-    _block_rope3d("sv_block_linattn_step_rope3d", Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace, workspace_bytes,
-                  stream)
+    _check((_entry or _calls()).sv_block_linattn_step_rope3d(Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace,
+                                                             workspace_bytes, stream), "sv_block_linattn_step_rope3d")
 
 
 def sv_block_linattn_lookahead_rope3d(Qb, Kb, Vb, blk: TensorDesc, rope: Rope3D, S, z, eps: float, Ob, workspace,
                                       workspace_bytes: int | None = None, stream=None) -> None:
-    _block_rope3d("sv_block_linattn_lookahead_rope3d", Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace,
-                  workspace_bytes, stream)
+    _check((_entry or _calls()).sv_block_linattn_lookahead_rope3d(Qb, Kb, Vb, blk, rope, S, z, eps, Ob, workspace,
+                                                                  workspace_bytes, stream),
+           "sv_block_linattn_lookahead_rope3d")
 
 
 def sv_tconv_block_step(x, W, cache_in, y, cache_out, B: int, T: int, HW: int, D: int, dtype: int = SV_BF16,
                         stream=None) -> None:
     """One block through the Mix-FFN's temporal convolution with shortcut (include/sv_tconv.h):
     x, y [B][T][HW][D], W [3][D][D], cache_in / cache_out [B][HW][D] or None."""
-    rc = load_library().sv_tconv_block_step(_ptr(x), _ptr(W), _ptr(cache_in), _ptr(y), _ptr(cache_out), B, T, HW, D,
-                                            dtype, _stream(stream))
-    if rc != 0:
-        raise SvError(rc, "sv_tconv_block_step")
+    _check((_entry or _calls()).sv_tconv_block_step(x, W, cache_in, y, cache_out, B, T, HW, D, dtype, stream),
+           "sv_tconv_block_step")
 
 
 def sv_measure_apply_variant(variant: int, Q, q: TensorDesc, tok_begin: int, tok_end: int, S, z, eps: float, O,

@@ -1,4 +1,4 @@
-"""Builds libsvlinattn.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libsvlinattn.so (HIP kernels + C ABI) for gfx950 with hipcc and _sventry.so (its Python calls) with g++, in-tree."""
 from __future__ import annotations
 
 import os
@@ -22,6 +22,8 @@ HIPCC_FLAGS = [
     # per-kernel register, scratch and LDS use as compiler remarks (parsed below)
     "-Rpass-analysis=kernel-resource-usage",
 ]
+ENTRY = os.path.join(PKG, "_sventry.so")               # host code only: the calls of binding.py that launch
+ENTRY_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-missing-field-initializers"]
 RESOURCES = os.path.join(PKG, "kernel_resources.txt")   # written by build(): one line per kernel
 
 
@@ -71,6 +73,22 @@ def check_resources(res: dict) -> None:
         raise RuntimeError("kernels that use scratch memory:\n  " + "\n  ".join(bad))
 
 
+def build_entry(verbose: bool = False) -> str:
+    """Compiles csrc/py_entry.cpp against this interpreter's headers."""
+    import sysconfig
+    cmd = [os.environ.get("CXX", "g++"), *ENTRY_FLAGS, "-I" + sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "py_entry.cpp"), "-o", ENTRY + ".tmp", "-ldl"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("the Python entry module did not build:\n" + res.stdout)
+    if verbose and res.stdout.strip():
+        print(res.stdout)
+    os.replace(ENTRY + ".tmp", ENTRY)
+    return ENTRY
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc, *HIPCC_FLAGS, *extra_flags, *SOURCES, "-o", LIB + ".tmp"]
@@ -103,6 +121,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
             f.write(f"{name} VGPRs={u.get('VGPRs')} AGPRs={u.get('AGPRs')} scratch={u.get('ScratchSize')} "
                     f"lds={u.get('LDS Size')} waves_per_simd={u.get('Occupancy')}\n")
     os.replace(LIB + ".tmp", LIB)
+    build_entry(verbose)
     return LIB
 
 
