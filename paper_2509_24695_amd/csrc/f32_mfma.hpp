@@ -17,7 +17,7 @@
 //           lane ends up with NB consecutive features of a token and stores them as they are.
 //
 // Measured (both kernels of a layer, before: plain FMAs out of LDS): fp32, 32 heads of 64, 4 680 tokens 120 -> 45.6 us;
-// bf16, 128 heads of 32, 4 096 tokens 130 -> 40.5 us; fp32, 2 heads of 32, 1 024 tokens 17.8 -> 14.8 us.
+// bf16, 128 heads of 32, 4 096 tokens 130 -> 40.5 us.
 // What is left above the streams' time is the start of the kernels.
 //
 // d <= 64: a wave holds the whole state and works alone on its tiles.  d = 112, 128: the waves of a workgroup
@@ -114,37 +114,45 @@ template <int N> __device__ __forceinline__ void rotate_pairs(float (&f)[N], con
 
 // ---- state ----------------------------------------------------------------------------------------------------
 
-template <typename T, int D> struct StateF32 {
+// SOLE: a workgroup sums a head alone, so its waves are all that work on it.  At d = 32 it has sixteen of them, in the 128 registers that
+// leaves each, instead of four with three tiles in flight each: 2 heads, 1 024 tokens, fp32 11.6 -> 10.0 us (of which the matrix core
+// of the one compute unit needs 3.5).  With two tiles in flight per wave, or at d = 64 with eight waves, the compiler spills.
+template <typename T, int D, bool SOLE, int ROPE> struct StateF32 {
     static constexpr bool kSplit = D > 64;                 // quadrants instead of whole states
+    static constexpr bool kMany = SOLE && D == 32;
+    static constexpr int kWaves = kMany ? 16 : 4;
     static constexpr int F = kSplit ? 64 : D;              // features of a wave's part, on both axes
     static constexpr int VEC = F / 16, W = kWords<T, VEC>;
-    static constexpr int U = 16 / VEC;                     // groups of four tokens per tile: 16 tokens, 32 at d = 32
+    // (the two forms of the rotation keep the same tiles and give the same bits; with sixteen waves eight groups of a full table spill)
+    static constexpr int U = kMany && ROPE != kRopeNone ? 4 : 16 / VEC;          // groups of four tokens per tile: 16 tokens, 32 at d = 32 in a shared head
     static constexpr int TILE = 4 * U;
-    static constexpr int DEPTH = 3;                        // tiles in flight per wave
+    static constexpr int DEPTH = kMany ? 1 : 3;             // tiles in flight per wave
     // Running sums: a set per stage, and at d = 32 (few registers) one for each parity of the token group.  An fp32 sum's error grows
     // with the root of its length; one set for the whole share had S up to 1.8 times as far from 64-bit sums as the scalar kernel, whose
     // chunks are shorter (2 heads of 32, 1 024 tokens: 2.1e-7 against 1.3e-7; 160 heads of 112, 4 680 tokens: 8.7e-7 against
     // 5.0e-7).  With these it is no further off at any size measured (1.0e-7, 4.9e-7), for less than 0.5 us per launch.  Adding
-    // every tile's products to the share's sum instead was as exact and up to 20 % slower.
+    // every tile's products to the share's sum instead was as exact and up to 20 % slower.  Sixteen waves
+    // make 32 sums, four 24.
     static constexpr int kChains = VEC == 2 ? 2 : 1;
     static constexpr int kSlot = F * F + F;                // a wave's part in LDS: state, then key sums
-    static constexpr int kWgTokens = kSplit ? TILE : 4 * TILE;
-    template <int ROPE> static constexpr int lds_bytes() {
-        constexpr int slots = 4 * kSlot * 4, tab = ROPE == kRope3D ? kRope3dLdsBytes : 0;   // tables, then slots
+    static constexpr int kParts = kSplit ? kWaves / 4 : kWaves;   // waves that hold the same part of the state
+    static constexpr int kWgTokens = kParts * TILE;
+    static constexpr int lds_bytes() {
+        constexpr int slots = kWaves * kSlot * 4, tab = ROPE == kRope3D ? kRope3dLdsBytes : 0;   // tables, then slots
         return slots > tab ? slots : tab;
     }
 };
 
-// grid = (C, B*H), block = 256; arguments and the partials in the workspace as in state_mfma_d64.  No workgroup waits for another:
+// grid = (C, B*H), block = 64 * kWaves; arguments and the partials in the workspace as in state_mfma_d64.  No workgroup waits for another:
 // SOLE (C = 1) stores the new state, otherwise state_reduce adds the partials up.  These calls stay free of waits because they
 // always were: they may run beside anything on other streams, and be replayed without preparation.
 template <typename T, int D, bool SOLE, int ROPE>
-__global__ __launch_bounds__(kThreads, 1) void state_f32(
+__global__ __launch_bounds__((64 * StateF32<T, D, SOLE, ROPE>::kWaves)) void state_f32(
     const T *__restrict__ K, const T *__restrict__ V, RopeArg rope, TokStrides st, int H, int t0, int t1, int C,
     const float *S_in, const float *z_in, float *S_out, float *z_out, void *__restrict__ ws, int order)
 {
-    using P = StateF32<T, D>;
-    constexpr int VEC = P::VEC, W = P::W, U = P::U, TILE = P::TILE, DEPTH = P::DEPTH, F = P::F, E = (int)sizeof(T);
+    using P = StateF32<T, D, SOLE, ROPE>;
+    constexpr int kThreads = 64 * P::kWaves, kParts = P::kParts, VEC = P::VEC, W = P::W, U = P::U, TILE = P::TILE, DEPTH = P::DEPTH, F = P::F, E = (int)sizeof(T);
     constexpr int elems = D * D + D;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
@@ -154,9 +162,9 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
     const int c = role.c, bh = role.bh;
     const int b = bh / H, h = bh % H;
 
-    const int kb = P::kSplit ? wave & 1 : 0, vb = P::kSplit ? wave >> 1 : 0;
+    const int kb = P::kSplit ? wave & 1 : 0, vb = P::kSplit ? (wave >> 1) & 1 : 0;
     const int n_tiles = (t1 - t0 + TILE - 1) / TILE;
-    const TileWalk walk(t0, P::kSplit ? c : 4 * c + wave, P::kSplit ? C : 4 * C, n_tiles, role.phase(b, order));
+    const TileWalk walk(t0, kParts * c + (P::kSplit ? wave >> 2 : wave), kParts * C, n_tiles, role.phase(b, order));
     const uint32_t row_bytes = (uint32_t)st.n * E;
     const rsrc_t rK = make_rsrc(K + b * st.b + h * st.h, (uint32_t)t1 * row_bytes);
     const rsrc_t rV = make_rsrc(V + b * st.b + h * st.h, (uint32_t)t1 * row_bytes);
@@ -255,7 +263,9 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
                 x[s] = acc[s][0][i][j];
                 if (P::kChains == 2) x[s] += acc[s][P::kChains - 1][i][j];
             }
-            sum[i][j] = (x[0] + x[1]) + x[2];
+            sum[i][j] = x[0];
+#pragma unroll
+            for (int s = 1; s < DEPTH; ++s) sum[i][j] += x[s];
         }
 
     // The wave's part in [k][v] order in its LDS slot: element r of block (i, j) is key feature VEC (4 g + r) + i, value
@@ -282,20 +292,23 @@ __global__ __launch_bounds__(kThreads, 1) void state_f32(
     const HeadState hs{S_in ? S_in + (size_t)bh * D * D : nullptr, z_in + (size_t)bh * D, S_out + (size_t)bh * D * D,
                        z_out + (size_t)bh * D};
     auto unit = [&](int u) __attribute__((always_inline)) {
+        const float *src = slots + 2 * u;
         if constexpr (P::kSplit) {
             const int k = (2 * u) / D, v = 2 * u - k * D, kz = 2 * u - D * D;
-            const float *src = u < D * D / 2 ? slots + ((k >> 6) + 2 * (v >> 6)) * P::kSlot + (k & 63) * 64 + (v & 63)
-                                             : slots + (kz >> 6) * P::kSlot + F * F + (kz & 63);
-            return *reinterpret_cast<const f32x2 *>(src);
-        } else {
-            f32x2 x[4];
-#pragma unroll
-            for (int w = 0; w < 4; ++w) x[w] = *reinterpret_cast<const f32x2 *>(slots + w * P::kSlot + 2 * u);
-            return (x[0] + x[2]) + (x[1] + x[3]);
+            src = u < D * D / 2 ? slots + ((k >> 6) + 2 * (v >> 6)) * P::kSlot + (k & 63) * 64 + (v & 63)
+                                : slots + (kz >> 6) * P::kSlot + F * F + (kz & 63);
         }
+        f32x2 x[kParts];
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) x[p] = *reinterpret_cast<const f32x2 *>(src + p * (P::kSplit ? 4 : 1) * P::kSlot);
+#pragma unroll
+        for (int h = kParts / 2; h >= 1; h /= 2)
+#pragma unroll
+            for (int p = 0; p < h; ++p) x[p] += x[p + h];
+        return x[0];
     };
     if (SOLE) {
-        state_store_sole<kThreads>(hs, D, tid, unit);
+        state_store_sole<kThreads, D>(hs, tid, unit);
         return;
     }
     for (int u = tid; u < elems / 2; u += kThreads) *reinterpret_cast<f32x2 *>(out + 2 * u) = unit(u);

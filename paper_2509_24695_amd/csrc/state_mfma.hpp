@@ -366,11 +366,10 @@ struct HeadState {
 };
 
 // Sums of a workgroup that has the head to itself: unit v of the new state = carried + sum(v), for all units.
-template <int THREADS, class SumFn>
-__device__ __forceinline__ void state_store_sole(const HeadState &hs, int d, int tid, SumFn sum)
+template <int THREADS, int d, class SumFn>
+__device__ __forceinline__ void state_store_sole(const HeadState &hs, int tid, SumFn sum)
 {
-    constexpr int kBatch = 8;
-    const int units = d * d / 2 + d / 2;
+    constexpr int units = d * d / 2 + d / 2, kRounds = (units + THREADS - 1) / THREADS, kBatch = kRounds < 8 ? kRounds : 8;
     for (int v0 = 0; v0 < units; v0 += THREADS * kBatch) {
         f32x2 carry[kBatch];
         hs.carried<THREADS>(d, v0, tid, carry);

@@ -45,19 +45,19 @@ constexpr bool kApplyHiLo = true;
 // d = 32 the state is small and more waves cover the loads (44.8, 42.1, 41.7 us).
 constexpr int f32_apply_wgs_per_cu(int d) { return d == 32 ? 4 : 2; }
 // fp32-arithmetic state: tokens up to which one workgroup sums a head in one launch, instead of several and a second launch for
-// their sum.  The lines are where the two meet in layers enqueued back to back through the binding, where the second launch costs the
-// host 2.5 us.  One / several, fp32:
-//   d = 32   8 heads, 1 024 tokens 15.9 / 17.4 us, 1 280 17.7 / 17.4; 32 heads, 768 15.8 / 17.7, 1 024 17.4 / 17.3; 64 heads, 512 14.7 / 17.3,
-//            768 17.2 / 17.3, 1 024 19.7 / 17.6; with a rotation some 100 tokens earlier, bf16 some 150 later;
-//   d = 64   8 heads, 256 tokens 15.2 / 17.8, 384 17.5 / 17.7; 64 heads, 192 15.5 / 17.4, 256 16.8 / 17.6, with a table 19.1 / 18.1 (the
-//            scalar kernels took 17.6 there: several workgroups had made the smallest calls slower);
-//   d = 112  from 72 to 128 tokens on several are faster.
-// A caller who waits for every layer sees them meet earlier: d = 32 at 512 tokens (fp32) and 1 024 (bf16), 31 against 28 us at 1 024 of
-// fp32; d = 64 at 256.
+// their sum.  One / several, layers enqueued back to back by a host that keeps ahead of the device, us:
+//   d = 32 (sixteen waves), fp32    2 heads, 768 tokens 11.9 / 12.8, 1 024 13.2 / 12.9; 16 heads, 512 12.2 / 12.9, 1 024 15.5 / 12.9; 32 heads,
+//            512 12.5 / 13.0, 768 14.8 / 13.1; 64 heads, 768 16.3 / 16.2; 128 heads, 1 024 23.8 / 24.8; bf16 some 300 tokens later;
+//   d = 64   8 heads, 128 tokens 12.1 / 13.1, 256 14.2 / 13.2; 64 heads, 192 15.3 / 16.6, 256 16.7 / 16.7;
+//   d = 112  8 heads, 32 tokens 13.9 / 16.4, 64 16.0 / 16.7, 128 21.2 / 18.0; 32 heads, 64 17.9 / 19.2, 128 23.5 / 21.4; 128 heads, 128 31.1 / 36.1.
+// A host that does anything besides is what these small layers wait for, and a third launch costs it 2.5 us (2 heads of 32, 1 024 tokens
+// in a program that changes its buffers from layer to layer: 13.2 / 15.4), so the lines lie where one workgroup is up to that much
+// slower on the device.
 int f32_sole_tokens(int d, int BH, int elem_bytes)
 {
     if (d == 32) return (BH <= 16 ? 1152 : BH <= 32 ? 896 : 768) + (elem_bytes == 2 ? 128 : 0);
-    return d == 64 ? (BH <= 16 ? 256 : 192) : 0;
+    if (d == 64) return BH <= 16 ? 256 : 192;
+    return BH <= 8 ? 64 : BH <= 32 ? 96 : 128;
 }
 // d = 64: the denominators phi(Q_i).z ride through the matrix core as two more operand rows (false) or are taken on
 // the vector ALU with a wavefront-level reduction (true).  Measured level (within 1 % either way at 32 760 and
@@ -147,16 +147,18 @@ template <typename T_, int D_, int ROPE_> struct KernelsF32 {
     static constexpr auto state = state_f32<T, D, true, ROPE>;
     static constexpr auto state_partial = state_f32<T, D, false, ROPE>;
     static constexpr auto apply = apply_f32<T, D, ROPE>;
-    static constexpr int state_lds = StateF32<T, D>::template lds_bytes<ROPE>();
+    static constexpr int state_lds = StateF32<T, D, true, ROPE>::lds_bytes();
+    static constexpr int state_threads = 64 * StateF32<T, D, true, ROPE>::kWaves;
+    static constexpr int partial_lds = StateF32<T, D, false, ROPE>::lds_bytes();
     static constexpr int apply_lds = ROPE == kRope3D ? kRope3dLdsBytes : 0;
-    static constexpr int state_wg_tokens = StateF32<T, D>::kWgTokens, apply_wg_tokens = ApplyF32<D>::kWgTokens;
+    static constexpr int state_wg_tokens = StateF32<T, D, false, ROPE>::kWgTokens, apply_wg_tokens = ApplyF32<D>::kWgTokens;
 };
 template <typename T, int D, int ROPE> void init_f32_kernels()
 {
     using KN = KernelsF32<T, D, ROPE>;
     const auto attr = hipFuncAttributeMaxDynamicSharedMemorySize;
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state), attr, KN::state_lds);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state_partial), attr, KN::state_lds);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state_partial), attr, KN::partial_lds);
 }
 
 template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
@@ -455,7 +457,7 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
             const bool sole = n <= f32_sole_tokens(s.d, s.BH, s.elem_bytes);
             const int C = sole ? 1 : plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
             const auto kernel = C == 1 ? KN::state : KN::state_partial;
-            kernel<<<dim3(C, s.BH), kThreads, KN::state_lds, stream>>>(
+            kernel<<<dim3(C, s.BH), C == 1 ? KN::state_threads : kThreads, C == 1 ? KN::state_lds : KN::partial_lds, stream>>>(
                 static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, t0, t1, C, S_in, z_in, S_out,
                 z_out, ws, state_order(layout_of(s), rope.mode == kRopeTable));
             if (C > 1)

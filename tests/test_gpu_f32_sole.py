@@ -1,0 +1,18 @@
+"""One workgroup per head in the fp32-arithmetic state kernel: sixteen waves at d = 32 (tiles of 32 tokens, of 16 with a
+rotation, 512 or 256 to a round), four at d >= 64.  The edges of their rounds, and both sides of the lines where several workgroups
+take over, against the oracle."""
+import pytest
+
+from tests.test_gpu_f32_mfma import _layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rope", ["none", "table", "axes"])
+@pytest.mark.parametrize("dtype,d,heads,grid,cut", [
+    ("f32", 32, 3, (1, 1, 31), 0), ("f32", 32, 2, (1, 1, 257), 0), ("f32", 32, 2, (1, 16, 32), 0), ("f32", 32, 2, (1, 19, 27), 0),
+    ("f32", 32, 2, (1, 32, 36), 0), ("f32", 32, 17, (1, 28, 32), 0), ("f32", 32, 2, (1, 31, 33), 1), ("bf16", 32, 2, (1, 30, 42), 3),
+    ("bf16", 32, 33, (1, 28, 32), 0), ("f32", 64, 2, (1, 16, 16), 0), ("f32", 64, 2, (1, 1, 257), 0),
+    ("f32", 112, 2, (1, 8, 8), 0), ("f32", 112, 2, (1, 5, 13), 0), ("f32", 128, 9, (1, 6, 16), 0), ("f32", 112, 33, (1, 8, 16), 1)])
+def test_one_workgroup_per_head(dtype, d, heads, grid, cut, rope):
+    _layer(dtype, d, 1, heads, grid, rope, cut, grid[0] * grid[1] * grid[2] - cut)
