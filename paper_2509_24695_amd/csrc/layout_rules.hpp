@@ -69,4 +69,19 @@ inline int apply_order(const TokenLayout &t, bool full_table, bool factored_tabl
     return !d64 || full_table || runs_of_32 ? kOrderLockstep | kOrderChunkMajor : kOrderLockstep;
 }
 
+// d = 112 and 128, state: the kernel of quadrants (quad_state.hpp) instead of whole rows, for ranges whose exchange among workgroups takes
+// longer than their tokens.  Both read in step with the number of head-tokens, the quadrants slower; the lines are where the two meet
+// (quadrants / rows, us):
+//   d = 112  20 heads plain 1 560 tokens 11.9 / 14.3, 4 680 20.0 / 18.8; factored tables 13.1 / 17.4, 22.7 / 21.7; full table 12.9 / 15.5, 26.9 / 20.5
+//   d = 128  20 heads plain 1 560 tokens 11.8 / 15.6, 4 680 19.1 / 20.1; factored tables 13.1 / 17.7, 20.2 / 22.1; full table 12.9 / 16.5, 24.9 / 21.7
+//            64 heads, 1 540 tokens 17.1 / 20.9, 18.4 / 23.9, 21.9 / 23.4; token-major 20 heads, 4 680 tokens plain 20.4 / 20.0, rotated 21.5 / 22.4
+// Four workgroups per chunk have to fill most of the device (40 heads, 4 680 tokens of 112, 160 workgroups: 36.7 / 23.8).
+inline bool quad_state_pays(int BH, int d, int n_tokens, bool rotated, bool full_table, int num_cu)
+{
+    const int C = num_cu / (4 * BH);
+    if (16 * BH * C < 3 * num_cu) return false;
+    const int64_t line = d == 112 ? (full_table ? 50000 : rotated ? 88000 : 76000) : (full_table ? 66000 : rotated ? 130000 : 100000);
+    return (int64_t)BH * n_tokens <= line;
+}
+
 }  // namespace sv

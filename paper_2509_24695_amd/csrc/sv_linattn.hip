@@ -19,6 +19,7 @@
 #include "f32_mfma.hpp"
 #include "generic_kernels.hpp"
 #include "layout_rules.hpp"
+#include "quad_state.hpp"
 #include "state_mfma.hpp"
 #include "wide_state.hpp"
 
@@ -82,6 +83,7 @@ struct Device {
     int num_cu = 0;
     // how many workgroups fit on the device at once
     int state_resident_wgs[2][3][2] = {};                    // state kernel with in-kernel finalize, [DP = 128][RoPE mode][SHARED]
+    int quad_resident_wgs[3] = {0, 0, 0};                    // quadrant state kernel (d = 112, 128), by RoPE mode
     int fused_resident_wgs[3] = {0, 0, 0};                   // one-launch block step (d = 64), by RoPE mode
     bool ok = false;
 };
@@ -139,6 +141,23 @@ template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     // ranges of fewer than apply_short_steps steps per workgroup: two per compute unit (see enqueue_apply)
     static constexpr int apply_wgs_per_cu_short = apply_wgs_per_cu < 2 ? apply_wgs_per_cu : 2, apply_short_steps = 6;
 };
+
+// The quadrant state kernel of d = 112 and 128: tiles of 32 tokens, of 16 with a rotation (its entries need the registers).
+template <int ROPE_> struct KernelsQuad {
+    static constexpr int ROPE = ROPE_, TILE = ROPE == kRopeNone ? 32 : 16, DEPTH = 2;
+    using P = QuadShape<TILE, ROPE>;
+    static constexpr auto state = state_mfma_quad<TILE, DEPTH, ROPE>;
+    static constexpr int lds = P::kLdsBytes, threads = P::THREADS, wg_tokens = P::WAVES * TILE;
+};
+template <int ROPE> void init_quad_kernels(Device &d)
+{
+    using KN = KernelsQuad<ROPE>;
+    const auto kernel = reinterpret_cast<const void *>(KN::state);
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, KN::lds);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, KN::threads, KN::lds) != hipSuccess) per_cu = 0;
+    d.quad_resident_wgs[ROPE] = per_cu * d.num_cu;
+}
 
 // The kernels with fp32 arithmetic: fp32 tokens at every d, bf16 at d = 32.
 template <typename T_, int D_, int ROPE_> struct KernelsF32 {
@@ -263,6 +282,9 @@ const Device &device_info()
         init_kernels<128, kRopeNone>(d);
         init_kernels<128, kRopeTable>(d);
         init_kernels<128, kRope3D>(d);
+        init_quad_kernels<kRopeNone>(d);
+        init_quad_kernels<kRopeTable>(d);
+        init_quad_kernels<kRope3D>(d);
         init_kernels<128, kRopeNone, true>(d);
         init_kernels<128, kRopeTable, true>(d);
         init_kernels<128, kRope3D, true>(d);
@@ -402,12 +424,38 @@ bool eps_ok(float eps) { return isfinite(eps) && eps >= 0.f; }
 
 TokenLayout layout_of(const Shape &s) { return TokenLayout{s.BH, s.H, s.d, s.elem_bytes, s.st.h, s.st.n}; }
 
+// The quadrant kernel, for the ranges it is faster on; false: not launched.
+bool launch_state_quad(const uint16_t *k, const uint16_t *v, const Rope &rope, const Shape &s, int t0, int t1, const float *S_in,
+                       const float *z_in, float *S_out, float *z_out, void *ws, const Device &dev, hipStream_t stream)
+{
+    if (!quad_state_pays(s.BH, s.d, t1 - t0, rope.mode != kRopeNone, rope.mode == kRopeTable, dev.num_cu)) return false;
+    bool launched = false;
+    auto launch = [&](auto kn) {
+        using KN = decltype(kn);
+        int C = dev.num_cu / (4 * s.BH);
+        const int steps = (t1 - t0 + KN::wg_tokens - 1) / KN::wg_tokens;
+        C = C > kQuadMaxChunks ? kQuadMaxChunks : C;
+        C = C > steps ? steps : C;
+        const int grid = quad_grid(C, s.BH, kDies);
+        if (C > 1 && grid > dev.quad_resident_wgs[rope.mode]) return;     // its workgroups wait for each other
+        KN::state<<<grid, KN::threads, KN::lds, stream>>>(k, v, rope.arg, s.st, s.H, s.BH, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws,
+                                                          next_epoch(s.host_epochs_only), spin_limit(),
+                                                          state_order(layout_of(s), rope.mode == kRopeTable));
+        launched = true;
+    };
+    if (rope.mode == kRope3D) launch(KernelsQuad<kRope3D>{});
+    else if (rope.mode == kRopeTable) launch(KernelsQuad<kRopeTable>{});
+    else launch(KernelsQuad<kRopeNone>{});
+    return launched;
+}
+
 // S_out, z_out = (S_in, z_in, or 0 when S_in is null) + state of tokens [t0,t1).  S_in may equal S_out.
 // rope: rotation table or null.  All arguments are already validated.
 void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, const Shape &s, int t0, int t1,
                        const float *S_in, const float *z_in, float *S_out, float *z_out, void *ws, const Device &dev,
                        dim3 rgrid, hipStream_t stream)
 {
+    if (s.d > 64 && launch_state_quad(k, v, rope, s, t0, t1, S_in, z_in, S_out, z_out, ws, dev, stream)) return;
     with_mfma_kernels(s.d, rope.mode, layout_of(s).shares_lines(), [&](auto kn) {
         using KN = decltype(kn);
         const int C = plan_chunks(s.BH, t1 - t0, KN::state_wg_tokens, dev.num_cu);

@@ -74,6 +74,25 @@ SV_HOST_DEVICE inline void chunk_major_role(int id, int C, int BH, int dies, int
     bh = logical - c * BH;
 }
 
+// Which chunk, head and quadrant of the state workgroup `id` of the quadrant kernel works on: the four quadrants of one (chunk, head), which
+// read the same rows, run on one die.  Die e takes groups e, e + dies, ... of the list (head by head, chunk by chunk) or, in the
+// chunk-major order, the e-th part of the chunk-major list.  False: the id has no work (the grid is rounded up to whole
+// groups on every die).
+SV_HOST_DEVICE inline bool quad_role(int id, int C, int BH, int dies, bool chunk_major, int &c, int &bh, int &q)
+{
+    const int slot = id / dies, group = (slot / 4) * dies + id % dies;
+    q = slot & 3;
+    if (group >= C * BH) return false;
+    if (chunk_major) {
+        chunk_major_role(group, C, BH, dies, c, bh);
+    } else {
+        bh = group / C;
+        c = group - bh * C;
+    }
+    return true;
+}
+SV_HOST_DEVICE inline int quad_grid(int C, int BH, int dies) { return 4 * dies * ((C * BH + dies - 1) / dies); }
+
 // Phase key (the `bh` argument of TileWalk) of head bh in the die-local forms of the kernels, where die x
 // holds heads x, x + n_dies, ...: keyed by the head index itself, heads of one die would share phases (two
 // distinct ones for four heads), so the sixteen phases are dealt die by die, the heads of a die as far apart
