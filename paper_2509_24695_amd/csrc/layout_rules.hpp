@@ -69,6 +69,21 @@ inline int apply_order(const TokenLayout &t, bool full_table, bool factored_tabl
     return !d64 || full_table || runs_of_32 ? kOrderLockstep | kOrderChunkMajor : kOrderLockstep;
 }
 
+// d = 112 and 128, apply without a full table: workgroups per compute unit, three or two (layers, state and apply in turn, three -> two).
+//   shared lines, plain    two: the heads of a chunk, which read and write pieces of the same lines, stay closer together (20 heads of 112, 32 760
+//                          tokens 155 -> 150 us, 40 heads 312 -> 266, 64 heads, 14 040 tokens 228 -> 195; with factored tables 299 -> 286 on
+//                          one device and 286 -> 290 on another, so not there).
+//   d = 128, plain         two (64 heads, 14 040 tokens 190 -> 187 us, token-major 40 heads, 32 760 tokens 258 -> 249, 20 heads 140 -> 137; at
+//                          d = 112 level, with a rotation up to 9 % more).
+//   a poor fit             two, where three would leave a tenth of the places empty, that is some compute units with a third less work to share
+//                          (160 heads of 128, 1 560 tokens 68.0 -> 65.8 us, 4 680 tokens 170.6 -> 160.3; of 112 62.4 -> 58.2, 143.7 -> 139.1).
+inline int wide_apply_wgs_per_cu(const TokenLayout &t, bool rotated, int num_cu)
+{
+    if (!rotated && (t.shares_lines() || t.d == 128)) return 2;
+    const int c3 = 3 * num_cu / t.BH, c2 = 2 * num_cu / t.BH;
+    return 10 * c3 * t.BH < 27 * num_cu && 3 * c2 > 2 * c3 ? 2 : 3;
+}
+
 // d = 112 and 128, state: the kernel of quadrants (quad_state.hpp) instead of whole rows, for ranges whose exchange among workgroups takes
 // longer than their tokens.  Both read in step with the number of head-tokens, the quadrants slower; the lines are where the two meet
 // (quadrants / rows, us):

@@ -541,6 +541,8 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
         with_mfma_kernels(s.d, rope.mode, layout_of(s).shares_lines(), [&](auto kn) {
             using KN = decltype(kn);
             int C = KN::apply_wgs_per_cu * dev.num_cu / s.BH;
+            if (KN::kWideState && KN::apply_wgs_per_cu == 3)
+                C = wide_apply_wgs_per_cu(layout_of(s), rope.mode != kRopeNone, dev.num_cu) * dev.num_cu / s.BH;
             const int steps = (n + KN::apply_wg_tokens - 1) / KN::apply_wg_tokens;
             // Short ranges: every workgroup starts by fetching its panels of S, so with only a few steps each,
             // fewer and longer ones win (d = 112, 20 heads, 4 680 tokens: two per compute unit 15.1 against
