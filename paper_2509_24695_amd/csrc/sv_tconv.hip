@@ -5,6 +5,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "tconv_frames.hpp"
 #include "tconv_mfma.hpp"
 
 namespace {
@@ -34,6 +35,18 @@ template <int F> TconvForm form()
 const TconvForm kForms[kTconvForms + 1] = {form<kForm256>(), form<kForm256x128>(), form<kForm128>(), form<kForm64>(),
                                            {kTcBM, kTcBN, kTcLdsBytes, tconv_mfma32<false>}, {kTcBM, kTcBN, kTcLdsBytes, tconv_mfma32<true>}};
 
+// The kernels on tiles of frames x positions, by FrameFormId and whether the call has a cache.
+template <int F> TconvForm frame_form_of(bool front)
+{
+    constexpr FrameShape f = kFrameShape[F];
+    using C = FrameTile<f.frames, f.blocks, f.channels / 64, true, f.back>;
+    using N = FrameTile<f.frames, f.blocks, f.channels / 64, f.back, f.back>;      // of several groups all but the first have a frame in front
+    return front ? TconvForm{C::P, C::BN, C::kLdsBytes, tconv_frames<C>} : TconvForm{N::P, N::BN, N::kLdsBytes, tconv_frames<N>};
+}
+const TconvForm kFrameForm[kFrameForms][2] = {{frame_form_of<kFrames3>(false), frame_form_of<kFrames3>(true)},
+                                              {frame_form_of<kFrames5>(false), frame_form_of<kFrames5>(true)},
+                                              {frame_form_of<kFrames7>(false), frame_form_of<kFrames7>(true)}};
+
 // The measurement variants of the 256 x 256 kernel (sv_measure_tconv_variant; 0: the kernel itself).
 constexpr int kVariants = 4;
 const TconvKernel kVariantKernels[kVariants] = {tconv_mfma<TcTile<256, 256>>, tconv_mfma<TcTile<256, 256>, 1>,
@@ -54,6 +67,9 @@ int tconv_ready()
         };
         for (const TconvForm &f : kForms)
             if (!allow(f.kernel, f.lds)) return 0;
+        for (const auto &forms : kFrameForm)
+            for (const TconvForm &f : forms)
+                if (!allow(f.kernel, f.lds)) return 0;
         for (const TconvKernel k : kVariantKernels)
             if (!allow(k, kForms[kForm256].lds)) return 0;
         int n = 0;
@@ -97,10 +113,12 @@ sv_status tconv_enqueue(int variant, const void *x, const void *W, const void *c
         id = tconv_form(M, D, T, cache_in != nullptr, num_cu);
         if (id == kForm256Long && D % kTcBK != 0) ++id;
     }
-    const TconvForm &f = kForms[id];
-    a.tiles_m = (int)((M + f.bm - 1) / f.bm);
+    const int frames = variant == kByRule ? frame_form(B, T, HW, D, cache_in != nullptr, num_cu) : kNoFrames;
+    const TconvForm &f = frames != kNoFrames ? kFrameForm[frames][cache_in != nullptr] : kForms[id];
+    const int64_t tiles_m = frames != kNoFrames ? frame_tiles_m(kFrameShape[frames], B, T, HW) : (M + f.bm - 1) / f.bm;
+    a.tiles_m = (int)tiles_m;
     a.tiles_n = (D + f.bn - 1) / f.bn;
-    const int64_t wgs = tc_grid_size((int64_t)a.tiles_m * a.tiles_n);
+    const int64_t wgs = tc_grid_size(tiles_m * a.tiles_n);
     if (wgs >= (int64_t)1 << 31) return SV_ERR_SHAPE;
     auto hs = static_cast<hipStream_t>(stream);
     const TconvKernel kernel = variant == kByRule ? f.kernel : kVariantKernels[variant];

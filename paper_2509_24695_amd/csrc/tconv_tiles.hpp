@@ -112,6 +112,46 @@ inline TconvFormId tconv_form(int64_t M, int D, int T, bool cache, int num_cu)
     return best;
 }
 
+// The kernels on tiles of frames x positions (tconv_frames): `frames` x 16 `blocks` positions x `channels`; back: the frames of a call
+// make several groups, otherwise the call has no more than these.
+enum FrameFormId { kFrames3, kFrames5, kFrames7, kFrameForms, kNoFrames = -1 };
+struct FrameShape { int frames, blocks, channels; bool back; };
+constexpr FrameShape kFrameShape[kFrameForms] = {{3, 5, 192, false}, {5, 3, 192, false}, {7, 2, 192, true}};
+// Token tiles of a call: batches x groups of frames x groups of positions.
+inline int64_t frame_tiles_m(const FrameShape &f, int B, int T, int HW)
+{
+    return (int64_t)B * ((T + f.frames - 1) / f.frames) * ((HW + 16 * f.blocks - 1) / (16 * f.blocks));
+}
+// Time of a call in us on a frame kernel: a start, more of it per further round of tiles, and a time per K-step with up to half of the
+// compute units busy, with all, and per round of several.  Fitted to 1 246 calls (1 to 21 frames, 40 to 3 600 positions, 96 to 2 240
+// channels), 5 to 7 % off.
+inline double frame_cost(FrameFormId id, int B, int T, int HW, int D, int num_cu)
+{
+    struct Fit { double start, half, full, more, again; };
+    constexpr Fit kFit[kFrameForms] = {{11.0, 0.93, 1.24, 1.10, 0.43}, {11.9, 0.98, 1.30, 1.15, 1.48}, {11.8, 1.01, 1.32, 1.21, 1.14}};
+    const Fit &f = kFit[id];
+    const int64_t tiles = frame_tiles_m(kFrameShape[id], B, T, HW) * ((D + kFrameShape[id].channels - 1) / kFrameShape[id].channels);
+    const double per_cu = (double)tiles / num_cu, rounds = (double)((tiles + num_cu - 1) / num_cu);
+    const double filled = per_cu <= 0.5 ? 0 : 2 * per_cu - 1, steps = (double)D / 32;
+    return f.start * (1 + f.again * (rounds - 1)) + steps * (rounds <= 1 ? f.half + (f.full - f.half) * filled : rounds * f.more);
+}
+// The frame kernel that serves a call, or kNoFrames: tconv_form's kernel does.  A third of the calls of 32 channels and more, 100 to
+// 3 600 positions and 2 frames and more are faster on tiles of frames, by 4 to 50 %: a block of 3 x 1 560 x 2 240 with a cache 131 -> 101 us,
+// 2 x 3 x 1 447 x 2 240 264 -> 179, 5 x 752 x 2 240 120 -> 86, a clip of 21 x 1 560 x 2 240 809 -> 758; small calls and few channels are not
+// (3 x 449 x 96 7.1 against 15.3).  kNow: what the kernels of tconv_form take of what tconv_cost says since their accumulators stay in one
+// register file and their operand reads go without bank conflicts.  Over those calls the choice costs 0.7 % on average against the fastest
+// kernel of all, and no call takes more than 3 % longer than on tconv_form's.
+inline FrameFormId frame_form(int B, int T, int HW, int D, bool cache, int num_cu)
+{
+    if (D % 32 != 0) return kNoFrames;
+    constexpr double kNow[kTconvForms] = {0.99, 0.725, 0.826, 0.99, 1.0};
+    const int64_t M = (int64_t)B * T * HW;
+    const TconvFormId rows = tconv_form(M, D, T, cache, num_cu);
+    const FrameFormId id = T <= 3 ? kFrames3 : T <= 5 ? kFrames5 : kFrames7;
+    const double rows_us = kNow[rows] * tconv_cost(rows, M, D, T > 1 ? 3 : cache ? 2 : 1, num_cu);
+    return frame_cost(id, B, T, HW, D, num_cu) < rows_us ? id : kNoFrames;
+}
+
 // Last token row of the tile of `bm` rows from m0 on, M tokens in all (m0 < M; m0 + bm may not fit an int).
 SV_HOST_DEVICE inline int tc_last_row(int m0, int bm, int M) { return M - m0 > bm ? m0 + bm - 1 : M - 1; }
 
