@@ -100,6 +100,20 @@ __device__ __forceinline__ f32x4 load_cached16(rsrc_t r, uint32_t off) {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
 
+// x + the sums of the other lanes of a row of 16: every lane ends with the row's total.  Quad, half-row and row permutations of the vector
+// ALU in place of four trips through the LDS crossbar; the same pairs are added.
+template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
+{
+    return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row16_sum(float x)
+{
+    x = dpp_add<0xb1>(x);      // quad_perm 1,0,3,2
+    x = dpp_add<0x4e>(x);      // quad_perm 2,3,0,1
+    x = dpp_add<0x141>(x);     // row_half_mirror: the other quad of eight lanes
+    return dpp_add<0x140>(x);  // row_mirror: the other eight lanes
+}
+
 // ---- typed scalar access used by the generic (any dtype) kernels --------------------------
 
 template <typename T> struct Elem;
