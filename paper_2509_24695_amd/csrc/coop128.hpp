@@ -88,7 +88,9 @@ template <int WAVES, int NB> __host__ __device__ constexpr int coop_apply_lds_by
 // Denominators phi(Q_i) . z + eps: the wave that loads a row also takes its dot product with z on
 // the vector ALU (a lane holds eight features of the row and the matching eight of z, `zr`; 16
 // lanes share a row and add up by row permutations: as four shuffles through LDS the sums took 3 to 6 % of the kernel, 18.0 -> 17.4 us for
-// 20 heads of 112, 4 680 tokens, 62.7 -> 60.4 at 32 760) and leaves it in LDS beside the tile.  The products are exact in fp32, the
+// 20 heads of 112, 4 680 tokens, 62.7 -> 60.4 at 32 760.  Where heads share cache lines (!NT) the shuffles stay: the waves' slower pace
+// keeps the heads in step, a state and an apply of 40 heads, 32 760 tokens take 271 us with shuffles, 288 to 302 without, factored
+// tables 293 and 306; at 4 680 tokens the permutations would gain 0.4 of 40 us) and leaves it in LDS beside the tile.  The products are exact in fp32, the
 // unrotated phi(Q) is at hand there even with ROPE, and the matrix core is left with the numerator.
 template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB, bool NT>
 __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WAVES, NB, NT> &st, unsigned char *lds,
@@ -129,7 +131,10 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
                     dot = __builtin_fmaf(bf16_hi(pq.z), zr[5], dot);
                     dot = __builtin_fmaf(bf16_lo(pq.w), zr[6], dot);
                     dot = __builtin_fmaf(bf16_hi(pq.w), zr[7], dot);
-                    dot = row16_sum(dot);                                               // the 16 lanes of the row
+                    if (NT) dot = row16_sum(dot);                                       // the 16 lanes of the row
+                    else
+#pragma unroll
+                        for (int m = 1; m < 16; m *= 2) dot += __shfl_xor(dot, m);
                     if ((lane & 15) == 0) den[my_row + 4 * j] = dot;
                     *reinterpret_cast<u32x4 *>(bufQ + wr_off + 4 * j * kCoopRow) = st.rot.rotate_with(pq, cs[j]);
                 }
