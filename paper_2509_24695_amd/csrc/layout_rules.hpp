@@ -84,19 +84,29 @@ inline int wide_apply_wgs_per_cu(const TokenLayout &t, bool rotated, int num_cu)
     return 10 * c3 * t.BH < 27 * num_cu && 3 * c2 > 2 * c3 ? 2 : 3;
 }
 
+// d = 112 and 128 without a full table, state: shared tiles (coop_state.hpp) instead of a state in every wave (wide_state.hpp) up to 2 048
+// tokens per workgroup: there the end, which the sum over the waves makes longer, counts.  State + apply, us, a state per wave / shared tiles:
+//   360 to 1 560 tokens each  20 heads of 112, 4 680: 32.5 / 30.3, factored tables 37.3 / 35.5; 20 heads of 128, 14 040, factored tables 72.4 / 70.1;
+//                             64 heads of 112, 6 240, factored tables 87.2 / 84.2; 256 heads, 1 560: 85.1 / 79.6, factored tables 91.7 / 87.8
+//   5 070 to 6 300            plain 64 heads, 20 280: 245 / 242, 160 heads, 6 240: 174 / 187; factored tables 20 heads, 75 600: 271 / 291,
+//                             40 heads, 32 760: 239 / 260, 160 heads, 6 240: 206 / 225
+// With a full table nothing is gained: 20 heads of 112, 9 360, 14 040 and 20 280 tokens 57.8 / 55.9, 75.1 / 75.3, 99.8 / 101.0; of 128 60.8 / 61.1,
+// 81.7 / 82.7, 110.1 / 108.6.
+inline bool coop_state_pays(int n_tokens, int C) { return n_tokens <= 2048 * C; }
+
 // d = 112 and 128, state: the kernel of quadrants (quad_state.hpp) instead of whole rows, for ranges whose exchange among workgroups takes
 // longer than their tokens.  Both read in step with the number of head-tokens, the quadrants slower; the lines are where the two meet
 // (quadrants / rows, us):
-//   d = 112  20 heads plain 1 560 tokens 11.9 / 14.3, 4 680 20.0 / 18.8; factored tables 13.1 / 17.4, 22.7 / 21.7; full table 12.9 / 15.5, 26.9 / 20.5
-//   d = 128  20 heads plain 1 560 tokens 11.8 / 15.6, 4 680 19.1 / 20.1; factored tables 13.1 / 17.7, 20.2 / 22.1; full table 12.9 / 16.5, 24.9 / 21.7
-//            64 heads, 1 540 tokens 17.1 / 20.9, 18.4 / 23.9, 21.9 / 23.4; token-major 20 heads, 4 680 tokens plain 20.4 / 20.0, rotated 21.5 / 22.4
-// Four workgroups per chunk have to fill most of the device (40 heads, 4 680 tokens of 112, 160 workgroups: 36.7 / 23.8).
-inline bool quad_state_pays(int BH, int d, int n_tokens, bool rotated, bool full_table, int num_cu)
+//   d = 112  20 heads, 1 560, 3 120, 4 680 tokens: plain 11.3 / 12.1, 14.5 / 14.4, 20.1 / 16.8; factored tables 12.7 / 14.3, 15.6 / 16.8, 22.2 / 19.2;
+//            12 heads, 4 680: 15.5 / 16.2, 16.6 / 18.0; full table 20 heads, 1 560: 12.5 / 15.1, 12 heads, 4 680: 19.5 / 17.6
+//   d = 128  20 heads, 3 120 and 4 680 tokens: plain 14.0 / 15.5, 18.6 / 18.1; factored tables 16.0 / 17.3, 21.0 / 20.1; full table 17.7 / 18.8, 24.8 / 21.9;
+//            64 heads, 1 560: 17.5 / 18.3, 18.6 / 20.1, 22.1 / 23.2; 12 heads, 9 360: 21.9 / 21.8, 23.5 / 22.7, 29.2 / 25.1
+// Four workgroups per chunk have to fill most of the device (40 heads of 112, 1 560 tokens, 160 workgroups: 15.5 / 13.5).
+inline bool quad_state_pays(int BH, int d, int n_tokens, bool full_table, int num_cu)
 {
     const int C = num_cu / (4 * BH);
     if (16 * BH * C < 3 * num_cu) return false;
-    const int64_t line = d == 112 ? (full_table ? 50000 : rotated ? 88000 : 76000) : (full_table ? 66000 : rotated ? 130000 : 100000);
-    return (int64_t)BH * n_tokens <= line;
+    return (int64_t)BH * n_tokens <= (d == 112 ? (full_table ? 40000 : 76000) : (full_table ? 66000 : 100000));
 }
 
 }  // namespace sv

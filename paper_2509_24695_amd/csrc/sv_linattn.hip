@@ -15,6 +15,7 @@
 #include "apply_mfma.hpp"
 #include "block_step_fused.hpp"
 #include "coop128.hpp"
+#include "coop_state.hpp"
 #include "common.hpp"
 #include "f32_mfma.hpp"
 #include "generic_kernels.hpp"
@@ -83,6 +84,7 @@ struct Device {
     int num_cu = 0;
     // how many workgroups fit on the device at once
     int state_resident_wgs[2][3][2] = {};                    // state kernel with in-kernel finalize, [DP = 128][RoPE mode][SHARED]
+    int coop_resident_wgs[3][2] = {};                        // state kernel on shared tiles (d = 112, 128), [RoPE mode][SHARED]
     int quad_resident_wgs[3] = {0, 0, 0};                    // quadrant state kernel (d = 112, 128), by RoPE mode
     int fused_resident_wgs[3] = {0, 0, 0};                   // one-launch block step (d = 64), by RoPE mode
     bool ok = false;
@@ -95,7 +97,7 @@ template <int DP, int ROPE, bool SHARED = false> struct Kernels;
 template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
     static constexpr int W = 0, kShared = 0;         // SHARED makes no difference
-    static constexpr bool kWideState = false;
+    static constexpr bool kWideState = false, kHasCoop = false;
     static constexpr auto state = state_mfma_d64<kStateTile, kStateWaves, kStateDepth, true, ROPE>;
     static constexpr auto state_partial = state_mfma_d64<kStateTile, kStateWaves, kStateDepth, false, ROPE>;
     static constexpr auto apply = apply_mfma_d64<kApplyHiLo, kApplyWaves, kApplyDepth, ROPE, false, kDenValu>;
@@ -123,12 +125,14 @@ template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
 template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     static constexpr int W = 1, kShared = SHARED;
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
-    static constexpr bool kWideState = true;
+    static constexpr bool kWideState = true, kHasCoop = ROPE != kRopeTable;
     template <bool FINALIZE> static constexpr auto pick_state() {
         return &state_mfma_wide<(ROPE != kRopeNone ? kWideStateDepthRope : kWideStateDepth), FINALIZE, ROPE, !SHARED>;
     }
     static constexpr auto state = pick_state<true>();
     static constexpr auto state_partial = pick_state<false>();
+    template <bool FINALIZE> static constexpr auto coop_state = state_mfma_coop<2, FINALIZE, ROPE, !SHARED>;   // short shares (coop_state_pays)
+    static constexpr int coop_lds = coop_state_lds<ROPE>();
     static constexpr auto apply = apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB, !SHARED>;
     static constexpr int state_lds = kWideLdsBytes;
     static constexpr int apply_lds = coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
@@ -205,6 +209,14 @@ template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
                                                      64 * kStateWaves, KN::state_lds) != hipSuccess)
         per_cu = 0;
     d.state_resident_wgs[KN::W][ROPE][KN::kShared] = per_cu * d.num_cu;
+    if constexpr (KN::kHasCoop) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::template coop_state<true>), attr, KN::coop_lds);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::template coop_state<false>), attr, KN::coop_lds);
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(KN::template coop_state<true>),
+                                                         kCoopThreads, KN::coop_lds) != hipSuccess)
+            per_cu = 0;
+        d.coop_resident_wgs[ROPE][KN::kShared] = per_cu * d.num_cu;
+    }
 }
 
 // Calls f(Kernels<DP, ROPE, SHARED>{}) for the MFMA kernel family that serves head dimension d, RoPE mode and layout.
@@ -428,7 +440,7 @@ TokenLayout layout_of(const Shape &s) { return TokenLayout{s.BH, s.H, s.d, s.ele
 bool launch_state_quad(const uint16_t *k, const uint16_t *v, const Rope &rope, const Shape &s, int t0, int t1, const float *S_in,
                        const float *z_in, float *S_out, float *z_out, void *ws, const Device &dev, hipStream_t stream)
 {
-    if (!quad_state_pays(s.BH, s.d, t1 - t0, rope.mode != kRopeNone, rope.mode == kRopeTable, dev.num_cu)) return false;
+    if (!quad_state_pays(s.BH, s.d, t1 - t0, rope.mode == kRopeTable, dev.num_cu)) return false;
     bool launched = false;
     auto launch = [&](auto kn) {
         using KN = decltype(kn);
@@ -460,13 +472,24 @@ void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, c
         using KN = decltype(kn);
         const int C = plan_chunks(s.BH, t1 - t0, KN::state_wg_tokens, dev.num_cu);
         const int order = state_order(layout_of(s), rope.mode == kRopeTable);
-        if ((int64_t)C * s.BH <= dev.state_resident_wgs[KN::W][rope.mode][KN::kShared]) {
+        auto finalize = KN::state;
+        auto partial = KN::state_partial;
+        int resident = dev.state_resident_wgs[KN::W][rope.mode][KN::kShared], threads = 64 * kStateWaves, lds = KN::state_lds;
+        if constexpr (KN::kHasCoop)
+            if (coop_state_pays(t1 - t0, C)) {
+                finalize = KN::template coop_state<true>;
+                partial = KN::template coop_state<false>;
+                resident = dev.coop_resident_wgs[rope.mode][KN::kShared];
+                threads = kCoopThreads;
+                lds = KN::coop_lds;
+            }
+        if ((int64_t)C * s.BH <= resident) {
             // the head's workgroups wait for each other inside the kernel: all must be resident
-            KN::state<<<dim3(C, s.BH), 64 * kStateWaves, KN::state_lds, stream>>>(
+            finalize<<<dim3(C, s.BH), threads, lds, stream>>>(
                 k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, next_epoch(s.host_epochs_only),
                 spin_limit(), order);
         } else {
-            KN::state_partial<<<dim3(C, s.BH), 64 * kStateWaves, KN::state_lds, stream>>>(
+            partial<<<dim3(C, s.BH), threads, lds, stream>>>(
                 k, v, rope.arg, s.st, s.H, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws, 0ull, 0u, order);
             with_head_dim(s.d, [&](auto D) {
                 state_reduce<D(), KN::kWideState><<<rgrid, kThreads, 0, stream>>>(static_cast<float *>(ws), C, kMaxChunks,

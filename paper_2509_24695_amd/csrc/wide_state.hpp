@@ -258,6 +258,46 @@ struct WideTarget {
     int d, c, C;
 };
 
+// Stores NCB accumulator blocks of S, key features 32 kb .. +32 by value features 32 cb0 ..: into the workgroup's partial, with coherent
+// stores, or, if it is the head's only contributor (`sole`), added to the carried state as the new state.
+// Element i of block cb: row 32 kb + 8 (i / 4) + 4 (lane / 32) + i % 4, column 32 (cb0 + cb) + lane % 32.
+// Rows past d lie past the resource's end, columns past d are sent there: both are dropped.
+template <int NCB>
+__device__ __forceinline__ void wide_store_block(const f32x16 (&fin)[NCB], int kb, int cb0, bool sole, const WideTarget &t, int lane)
+{
+    const int d = t.d, n = lane & 31, g = lane >> 5;
+    const uint32_t s_bytes = (uint32_t)d * (uint32_t)d * 4u;
+    if (sole) {
+        const rsrc_t rS = make_rsrc(t.S_out, s_bytes), rI = make_rsrc(t.S_in ? t.S_in : t.S_out, t.S_in ? s_bytes : 0u);
+        const uint32_t base = ((uint32_t)(32 * kb + 4 * g) * (uint32_t)d + (uint32_t)(32 * cb0 + n)) * 4u;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) {
+            const uint32_t col = 32 * (cb0 + cb) + n < d ? base + 128u * cb : kOutOfRange;
+            float x[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                           rI, col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0));
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x[i] + fin[cb][i]), rS,
+                                                      col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0);
+        }
+        return;
+    }
+    const rsrc_t rP = make_rsrc(t.partials + (size_t)t.c * (d * d + d), s_bytes);
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+        const uint32_t base = 32 * (cb0 + cb) + n < d ? 16u * (uint32_t)wide_word(d, 4 * kb, g, 32 * (cb0 + cb) + n) : kOutOfRange;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            f32x4 x;
+            x.x = fin[cb][4 * q];  x.y = fin[cb][4 * q + 1];  x.z = fin[cb][4 * q + 2];  x.w = fin[cb][4 * q + 3];
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rP, base + (uint32_t)(q * 32 * d), 0, 16 /* sc1 */);
+        }
+    }
+}
+
 // Adds the four waves' states in the fixed order (w0 + w2) + (w1 + w3) and stores the sum: as the workgroup's
 // partial, with coherent stores, or, if the workgroup is the head's only contributor and FINALIZE, added to the
 // carried state as the new state.  Must be called by all threads; the tiles and tables in LDS are dead afterwards.
@@ -308,42 +348,14 @@ __device__ __forceinline__ void wide_state_wg_reduce_store(WideAcc &acc, unsigne
     lds_barrier();
     wide_recv_add<4>(from, lane, [&](int b) -> const f32x16 & { return h[0][b]; },
                      [&](int b) -> f32x16 & { return fin[b]; });
-    // element i of block cb: row 32 wave + 8 (i / 4) + 4 (lane / 32) + i % 4, column 32 cb + lane % 32.
-    // Rows past d lie past the resource's end, columns past d are sent there: both are dropped.
-    const int n = lane & 31, g = lane >> 5, half = d / 2;
-    const uint32_t s_bytes = (uint32_t)d * (uint32_t)d * 4u;
+    const int half = d / 2;
+    wide_store_block<4>(fin, wave, 0, FINALIZE && t.C == 1, t, lane);
     if (FINALIZE && t.C == 1) {
-        const rsrc_t rS = make_rsrc(t.S_out, s_bytes), rI = make_rsrc(t.S_in ? t.S_in : t.S_out, t.S_in ? s_bytes : 0u);
-        const uint32_t base = ((uint32_t)(32 * wave + 4 * g) * (uint32_t)d + (uint32_t)n) * 4u;
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            const uint32_t col = 32 * cb + n < d ? base + 128u * cb : kOutOfRange;
-            float x[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                           rI, col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0));
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x[i] + fin[cb][i]), rS,
-                                                      col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0);
-        }
         for (int u = threadIdx.x; u < d; u += 4 * kWave)
             t.z_out[u] = (t.S_in ? t.z_in[u] : 0.f) + ((zs[u] + zs[256 + u]) + (zs[128 + u] + zs[384 + u]));
         return;
     }
     float *out = t.partials + (size_t)t.c * (d * d + d);
-    const rsrc_t rP = make_rsrc(out, s_bytes);
-#pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-        const uint32_t base = 32 * cb + n < d ? 16u * (uint32_t)wide_word(d, 4 * wave, g, 32 * cb + n) : kOutOfRange;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            f32x4 x;
-            x.x = fin[cb][4 * q];  x.y = fin[cb][4 * q + 1];  x.z = fin[cb][4 * q + 2];  x.w = fin[cb][4 * q + 3];
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rP, base + (uint32_t)(q * 32 * d), 0, 16 /* sc1 */);
-        }
-    }
     for (int u = threadIdx.x; u < half; u += 4 * kWave) {
         const int k = 2 * u;
         f32x2 x;
@@ -357,7 +369,7 @@ __device__ __forceinline__ void wide_state_wg_reduce_store(WideAcc &acc, unsigne
 //   S_out, z_out = (S_in, z_in or 0) + partial[0] + partial[1] + ... + partial[C-1], in that order.
 // UNITS words per thread and round, GROUP partials in flight per word; the carried values of the first round, which do
 // not depend on the other workgroups, are fetched before the wait.  Called by all threads.
-template <int UNITS, int GROUP, class WaitFn>
+template <int THREADS, int UNITS, int GROUP, class WaitFn>
 __device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
 {
     const WideSlice sl(t.c, t.C, t.d);
@@ -369,7 +381,7 @@ __device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
         if (!t.S_in) return;
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) {
-            int v = v0 + u * kThreads;                           // beyond the slice: any valid word, the value is not used
+            int v = v0 + u * THREADS;                           // beyond the slice: any valid word, the value is not used
             v = v < sl.words ? v : sl.words - 1;
             if (v < sl.s_words) {
                 int row, col;
@@ -384,7 +396,7 @@ __device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
     f32x4 x[UNITS];
     carried(sl.lo + tid, x);
     if (!wait()) return;                                         // timed out: this wave leaves its part of S, z as it was
-    for (int v0 = sl.lo + tid; v0 < sl.hi; v0 += kThreads * UNITS) {
+    for (int v0 = sl.lo + tid; v0 < sl.hi; v0 += THREADS * UNITS) {
         if (v0 != sl.lo + tid) carried(v0, x);
         for (int c0 = 0; c0 < t.C; c0 += GROUP) {
             f32x4 p[UNITS][GROUP];
@@ -394,7 +406,7 @@ __device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
                 const uint32_t part = (uint32_t)(c0 + cc) * (uint32_t)(d * d + d) * 4u;
 #pragma unroll
                 for (int u = 0; u < UNITS; ++u) {
-                    const int v = v0 + u * kThreads;
+                    const int v = v0 + u * THREADS;
                     p[u][cc] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
                                    rP, v < sl.hi && c0 + cc < t.C ? 16u * (uint32_t)v + part : kOutOfRange, 0, 16 /* sc1 */));
                 }
@@ -407,7 +419,7 @@ __device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
         }
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) {
-            const int v = v0 + u * kThreads;
+            const int v = v0 + u * THREADS;
             if (v >= sl.hi) continue;
             if (v < sl.s_words) {
                 int row, col;
@@ -464,10 +476,10 @@ __global__ __launch_bounds__(256, 1) void state_mfma_wide(
         auto wait = [&]() __attribute__((always_inline)) {
             return state_publish_and_wait(ws, BH, elems, bh, c, C, 0, epoch, spin_limit, lane);
         };
-        if (C <= 2) wide_fold<8, 2>(target, wait);
-        else if (C <= 4) wide_fold<4, 4>(target, wait);
-        else if (C <= 8) wide_fold<3, 8>(target, wait);
-        else wide_fold<2, 12>(target, wait);
+        if (C <= 2) wide_fold<kThreads, 8, 2>(target, wait);
+        else if (C <= 4) wide_fold<kThreads, 4, 4>(target, wait);
+        else if (C <= 8) wide_fold<kThreads, 3, 8>(target, wait);
+        else wide_fold<kThreads, 2, 12>(target, wait);
     }
 }
 

@@ -33,7 +33,7 @@ int main()
         for (int mode : {0, 1, 2})
             for (int BH = 1; BH <= 300; ++BH)
                 for (int n : {1, 100, 1000, 5000, 40000, 200000}) {
-                    if (!sv::quad_state_pays(BH, d, n, mode != 0, mode == 1, 256)) continue;
+                    if (!sv::quad_state_pays(BH, d, n, mode == 1, 256)) continue;
                     const int C = 256 / (4 * BH);
                     if (C < 1 || 4 * C * BH > 256 || 4 * C * BH < 192) return printf("FAIL fill BH=%d\n", BH), 1;
                     ++cases;
