@@ -88,11 +88,9 @@ template <int WAVES, int NB> __host__ __device__ constexpr int coop_apply_lds_by
 // Denominators phi(Q_i) . z + eps: the wave that loads a row also takes its dot product with z on
 // the vector ALU (a lane holds eight features of the row and the matching eight of z, `zr`; 16
 // lanes share a row and add up by row permutations: as four shuffles through LDS the sums took 3 to 6 % of the kernel, 18.0 -> 17.4 us for
-// 20 heads of 112, 4 680 tokens, 62.7 -> 60.4 at 32 760.  Where heads share cache lines (!NT) the shuffles stay: the waves' slower pace
-// keeps the heads in step, a state and an apply of 40 heads, 32 760 tokens take 271 us with shuffles, 288 to 302 without, factored
-// tables 293 and 306; at 4 680 tokens the permutations would gain 0.4 of 40 us) and leaves it in LDS beside the tile.  The products are exact in fp32, the
-// unrotated phi(Q) is at hand there even with ROPE, and the matrix core is left with the numerator.
-template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB, bool NT>
+// 20 heads of 112, 4 680 tokens, 62.7 -> 60.4 at 32 760; without DPP_SUM the shuffles, see apply_mfma_d128) and leaves it in LDS beside the tile.
+// The products are exact in fp32, the unrotated phi(Q) is at hand there even with ROPE, and the matrix core is left with the numerator.
+template <bool HILO, bool DPP_SUM, int DEPTH, int ROPE, int WAVES, int NB, bool NT>
 __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WAVES, NB, NT> &st, unsigned char *lds,
                                                  int wave, int lane, const ApplyOperands<128, HILO, NB, false> &A,
                                                  const float (&zr)[8], float eps)
@@ -131,7 +129,7 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
                     dot = __builtin_fmaf(bf16_hi(pq.z), zr[5], dot);
                     dot = __builtin_fmaf(bf16_lo(pq.w), zr[6], dot);
                     dot = __builtin_fmaf(bf16_hi(pq.w), zr[7], dot);
-                    if (NT) dot = row16_sum(dot);                                       // the 16 lanes of the row
+                    if (DPP_SUM) dot = row16_sum(dot);                                  // the 16 lanes of the row
                     else
 #pragma unroll
                         for (int m = 1; m < 16; m *= 2) dot += __shfl_xor(dot, m);
@@ -200,29 +198,37 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
 // With NB = 1 a wave keeps one 128 x 32 panel of S and fits in half a SIMD's registers: two
 // workgroups (eight waves) share a compute unit, and while one wave waits at a barrier or works on
 // the vector ALU (ReLU, rotation, scaling) the other wave of its SIMD feeds the matrix core.
-template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB, bool NT>
-__global__ __launch_bounds__(64 * WAVES, NB == 1 ? 2 : 1) void apply_mfma_d128(
+//
+// HEADS = 2, where neighbouring heads share cache lines (224-byte rows side by side): grid = (C, B*H / 2), block = 128 * WAVES, the first
+// half of the waves on head 2 y, the other on 2 y + 1.  As workgroups of their own the two drift apart within a few tiles; here
+// each tile's barriers hold them together, so that a line is read twice by one compute unit and its two parts are written at nearly the
+// same time.  Apply, 40 heads of 112, 32 760 tokens: 149 -> 119 us (586 MB, 4.9 TB/s), factored tables 176 -> 150, full table 175 -> 168.
+// One head to a workgroup (odd H, see pairs_heads): the slower sums by shuffles, whose pace keeps the heads more in step
+// (state and apply 271 us, with row permutations 288 to 302; factored tables 293 and 306).
+template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB, bool NT, int HEADS>
+__global__ __launch_bounds__(64 * WAVES * HEADS, NB == 1 ? 2 : 1) void apply_mfma_d128(
     const uint16_t *__restrict__ Q, uint16_t *__restrict__ O, RopeArg rope, TokStrides st, int H,
     int d, int t0, int t1, int C, const float *__restrict__ S, const float *__restrict__ z, float eps, int order)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & (kWave - 1), wg_wave = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wg_wave % WAVES, half = wg_wave / WAVES;
     const WgRole role(C, order);
-    const int c = role.c, bh = role.bh;
+    const int c = role.c, bh = HEADS * role.bh + half;
     const int b = bh / H, h = bh % H;
     const uint16_t *Qh = Q + b * st.b + h * st.h;
     uint16_t *Oh = O + b * st.b + h * st.h;
     constexpr int STEP = 8 * WAVES * NB;
+    constexpr int kTiles = coop_apply_lds_bytes<WAVES, NB>(), kTabs = HEADS * kTiles;
     const int n_steps = (t1 - t0 + STEP - 1) / STEP;
 
-    CoopApplyStream<DEPTH, ROPE, WAVES, NB, NT> stream(Qh, Oh, rope, lds + coop_apply_lds_bytes<WAVES, NB>(), st.n, t1,
-                                                   d, wave, lane, TileWalk(t0, c, C, n_steps, role.phase(b, order)));
+    CoopApplyStream<DEPTH, ROPE, WAVES, NB, NT> stream(Qh, Oh, rope, lds + kTabs, st.n, t1, d,
+                                                    wave, lane, TileWalk(t0, c, C, n_steps, role.phase(b, order)));
     Rope3dFill tabs;
     if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
     coop_apply_prefetch<0, DEPTH>(stream);   // in flight while S is fetched
     if (ROPE == kRope3D) {
-        rope3d_lds_fill_end(lds + coop_apply_lds_bytes<WAVES, NB>(), rope.r3, tabs);
+        rope3d_lds_fill_end(lds + kTabs, rope.r3, tabs);
         wg_barrier();
     }
     ApplyOperands<128, HILO, NB, false> A;
@@ -234,7 +240,7 @@ __global__ __launch_bounds__(64 * WAVES, NB == 1 ? 2 : 1) void apply_mfma_d128(
         const float x = z[(size_t)bh * d + (k < d ? k : 0)];   // loaded by every lane: a load under a condition is a branch
         zr[e] = k < d ? x : 0.f;
     }
-    apply_tiles_coop<HILO>(stream, lds, wave, lane, A, zr, eps);
+    apply_tiles_coop<HILO, NT || HEADS == 2>(stream, lds + half * kTiles, wave, lane, A, zr, eps);
 }
 
 }  // namespace sv

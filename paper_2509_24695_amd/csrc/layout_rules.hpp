@@ -84,6 +84,18 @@ inline int wide_apply_wgs_per_cu(const TokenLayout &t, bool rotated, int num_cu)
     return 10 * c3 * t.BH < 27 * num_cu && 3 * c2 > 2 * c3 ? 2 : 3;
 }
 
+// d = 112, shared lines, apply: two neighbouring heads to a workgroup (apply_mfma_d128, HEADS = 2), of which one fits on a compute unit.  State +
+// apply, one / two heads to a workgroup:
+//   plain            20 heads, 4 680 tokens 37.8 / 37.1, 14 040 71.2 / 68.6, 32 760 149 / 140; 40 heads, 9 360 88.6 / 85.6, 32 760 274 / 253;
+//                    160 heads, 6 240 238 / 219
+//   rotated          three workgroups of one head per compute unit hide the lookups better than two heads, until drift costs more.  The apply
+//                    alone: factored tables 20 heads, 14 040 tokens 40.7 / 42, 17 160 47.1 / 48.6, 74 880 210 / 170, 40 heads, 32 760 180 / 156,
+//                    80 heads, 17 160 191 / 160; full table 20 heads, 17 160 52 / 55, 32 760 89.5 / 92, 74 880 202 / 195, 40 heads, 32 760 178 / 169
+inline bool pairs_heads(const TokenLayout &t, bool rotated, int n_tokens)
+{
+    return t.shares_lines() && t.H % 2 == 0 && (!rotated || (int64_t)t.BH * n_tokens >= 1 << 20);
+}
+
 // d = 112 and 128 without a full table, state: shared tiles (coop_state.hpp) instead of a state in every wave (wide_state.hpp) up to 2 048
 // tokens per workgroup: there the end, which the sum over the waves makes longer, counts.  State + apply, us, a state per wave / shared tiles:
 //   360 to 1 560 tokens each  20 heads of 112, 4 680: 32.5 / 30.3, factored tables 37.3 / 35.5; 20 heads of 128, 14 040, factored tables 72.4 / 70.1;
@@ -92,6 +104,8 @@ inline int wide_apply_wgs_per_cu(const TokenLayout &t, bool rotated, int num_cu)
 //                             40 heads, 32 760: 239 / 260, 160 heads, 6 240: 206 / 225
 // With a full table nothing is gained: 20 heads of 112, 9 360, 14 040 and 20 280 tokens 57.8 / 55.9, 75.1 / 75.3, 99.8 / 101.0; of 128 60.8 / 61.1,
 // 81.7 / 82.7, 110.1 / 108.6.
+// Shared lines, where the apply takes heads in pairs: always, the state alone gains little at full length, the two together 2 to 4 %
+// (40 heads, 32 760 tokens 263 -> 253, factored tables 294 -> 283; 160 heads, 6 240 tokens 225 -> 219).
 inline bool coop_state_pays(int n_tokens, int C) { return n_tokens <= 2048 * C; }
 
 // d = 112 and 128, state: the kernel of quadrants (quad_state.hpp) instead of whole rows, for ranges whose exchange among workgroups takes

@@ -133,9 +133,12 @@ template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     static constexpr auto state_partial = pick_state<false>();
     template <bool FINALIZE> static constexpr auto coop_state = state_mfma_coop<2, FINALIZE, ROPE, !SHARED>;   // short shares (coop_state_pays)
     static constexpr int coop_lds = coop_state_lds<ROPE>();
-    static constexpr auto apply = apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB, !SHARED>;
+    template <int HEADS> static constexpr auto apply_heads =
+        apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB, !SHARED, HEADS>;
+    static constexpr auto apply = apply_heads<1>;
     static constexpr int state_lds = kWideLdsBytes;
     static constexpr int apply_lds = coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
+    static constexpr int apply_pair_lds = 2 * coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
     static constexpr int state_wg_tokens = 4 * kWideTile;
     static constexpr int apply_wg_tokens = 8 * kCoopApplyWaves * kCoopApplyNB;   // the waves of a workgroup share its tiles
     static constexpr int apply_threads = 64 * kCoopApplyWaves;
@@ -191,6 +194,7 @@ template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state), attr, KN::state_lds);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state_partial), attr, KN::state_lds);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::apply), attr, KN::apply_lds);
+    if constexpr (KN::kShared) (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::template apply_heads<2>), attr, KN::apply_pair_lds);
     int per_cu = 0;
     if constexpr (DP == 64) {                      // the one-launch block step exists for d = 64 only
         int least = INT_MAX;
@@ -476,7 +480,7 @@ void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, c
         auto partial = KN::state_partial;
         int resident = dev.state_resident_wgs[KN::W][rope.mode][KN::kShared], threads = 64 * kStateWaves, lds = KN::state_lds;
         if constexpr (KN::kHasCoop)
-            if (coop_state_pays(t1 - t0, C)) {
+            if (coop_state_pays(t1 - t0, C) || pairs_heads(layout_of(s), rope.mode != kRopeNone, t1 - t0)) {
                 finalize = KN::template coop_state<true>;
                 partial = KN::template coop_state<false>;
                 resident = dev.coop_resident_wgs[rope.mode][KN::kShared];
@@ -563,9 +567,10 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
     if (mfma_path(s, rope)) {
         with_mfma_kernels(s.d, rope.mode, layout_of(s).shares_lines(), [&](auto kn) {
             using KN = decltype(kn);
+            const bool pair = KN::kShared && pairs_heads(layout_of(s), rope.mode != kRopeNone, n);
             int C = KN::apply_wgs_per_cu * dev.num_cu / s.BH;
             if (KN::kWideState && KN::apply_wgs_per_cu == 3)
-                C = wide_apply_wgs_per_cu(layout_of(s), rope.mode != kRopeNone, dev.num_cu) * dev.num_cu / s.BH;
+                C = (pair ? 2 : wide_apply_wgs_per_cu(layout_of(s), rope.mode != kRopeNone, dev.num_cu)) * dev.num_cu / s.BH;
             const int steps = (n + KN::apply_wg_tokens - 1) / KN::apply_wg_tokens;
             // Short ranges: every workgroup starts by fetching its panels of S, so with only a few steps each,
             // fewer and longer ones win (d = 112, 20 heads, 4 680 tokens: two per compute unit 15.1 against
@@ -579,7 +584,15 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
             // 24 measured 81 against 88 us).  Taken when it costs at most a tenth of the workgroups.
             if (rope.mode == kRopeTable && (C - C % kDies) * 10 >= C * 9) C -= C % kDies;
             if (C < 1) C = 1;
-            KN::apply<<<dim3(C, s.BH), KN::apply_threads, KN::apply_lds, stream>>>(
+            auto kernel = KN::apply;
+            int heads = 1, lds = KN::apply_lds;
+            if constexpr (KN::kShared)
+                if (pair) {
+                    kernel = KN::template apply_heads<2>;
+                    heads = 2;
+                    lds = KN::apply_pair_lds;
+                }
+            kernel<<<dim3(C, s.BH / heads), heads * KN::apply_threads, lds, stream>>>(
                 static_cast<const uint16_t *>(Q), static_cast<uint16_t *>(O), rope.arg, s.st, s.H, s.d, t0, t1, C, S,
                 z, eps, apply_order(layout_of(s), rope.mode == kRopeTable, rope.mode == kRope3D, n));
         });
