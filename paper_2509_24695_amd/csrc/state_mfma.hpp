@@ -23,7 +23,7 @@
 // are published, each of its workgroups adds up one slice of them in chunk
 // order (bit-reproducible, no float atomics).
 //
-// d = 112 and 128 are served by wide_state.hpp and coop128.hpp, which reuse pieces of this file.
+// d = 112 and 128 are served by wide_state.hpp, coop_state.hpp, quad_state.hpp and coop128.hpp, which reuse pieces of this file.
 #pragma once
 
 #include "common.hpp"
