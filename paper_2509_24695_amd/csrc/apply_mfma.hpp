@@ -404,16 +404,16 @@ __global__ __launch_bounds__(64 * WAVES, 1) void apply_mfma_d64(
     ApplyStream<DEPTH, ROPE> stream(Qh, Oh, rope, lds + apply_lds_bytes<WAVES, ROPE>(), st.n, t1, lane,
                                     TileWalk(t0, WAVES * c + wave, WAVES * C, n_tiles, role.phase(b, order)));
     Rope3dFill tabs;
-    if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
+    if (is_rope3d(ROPE)) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
     apply_prefetch<0, DEPTH>(stream);   // in flight while S is fetched
-    if (ROPE == kRope3D) {
+    if (is_rope3d(ROPE)) {
         rope3d_lds_fill_end(lds + apply_lds_bytes<WAVES, ROPE>(), rope.r3, tabs);
         wg_barrier();
     }
     ApplyOperands<64, HILO> A;
     static_assert(apply_lds_bytes<WAVES, ROPE>() >= ApplyOperands<64, HILO>::kSharedBytes && WAVES == 4, "the tiles can stage S for load_shared");
     // through the tiles, not yet in use; S_LDS: into an area of their own behind the tiles (and the tables), to stay
-    unsigned char *stage = S_LDS ? lds + apply_lds_bytes<WAVES, ROPE>() + (ROPE == kRope3D ? kRope3dLdsBytes : 0) : lds;
+    unsigned char *stage = S_LDS ? lds + apply_lds_bytes<WAVES, ROPE>() + (is_rope3d(ROPE) ? kRope3dLdsBytes : 0) : lds;
     A.template load_shared<false>(S + (size_t)bh * 64 * 64, z + (size_t)bh * 64, wave, lane, stage);
     float zf[4][8];
     if (DEN_VALU) load_key_sums<false>(z + (size_t)bh * 64, lane, zf);

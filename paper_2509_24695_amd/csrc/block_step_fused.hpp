@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void block_step_mfma(
     const TileWalk walk(0, WAVES * share + wave, WAVES * C, n_tiles, phase_key);
     ApplyStream<DEPTH_A, ROPE> qstream(Q + head_off, O + head_off, rope, lds_tab, st.n, N, lane, walk);
     Rope3dFill tabs;
-    if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
+    if (is_rope3d(ROPE)) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
     apply_prefetch<0, kEarly>(qstream);
 
     // ---- fold this workgroup's share of K_b, V_b ----------------------------------------------
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void block_step_mfma(
         StateStream<TILE, DEPTH_S, ROPE> kvstream(K + head_off, V + head_off, rope, lds_tab, st.n, N, lane, walk);
         unsigned char *tileK = lds + wave * 2 * kTileBytes;
         state_prefetch(kvstream);
-        if (ROPE == kRope3D) {
+        if (is_rope3d(ROPE)) {
             rope3d_lds_fill_end(lds + block_step_lds_bytes<TILE, WAVES, ROPE>(), rope.r3, tabs);
             wg_barrier();
         }

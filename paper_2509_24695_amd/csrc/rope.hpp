@@ -23,6 +23,12 @@
 namespace sv {
 
 constexpr int kRopeNone = 0, kRopeTable = 1, kRope3D = 2;
+// kRope3D whose axes have a multiple of four pairs each: a lane's four pairs, whose first is a multiple of four, lie in one axis side by side, and
+// a chunk's entries are one address and two 16-byte LDS reads instead of four and four of 8.  For the d = 64 kernels, chosen by the
+// launcher: block steps of 32 heads, 4 680 tokens 27.1 -> 25.4 us, 10 800 tokens 44.2 -> 42.2, layer of 2 x 32 heads, 75 600 tokens 447 -> 444
+// (a run-time choice inside the kernel gains nothing: its branch keeps the reads from being moved ahead).
+constexpr int kRope3DWhole = 3;
+constexpr bool is_rope3d(int mode) { return mode >= kRope3D; }
 
 // Factored 3-D rotary tables (device pointers): [frames][n_t][2], [rows][n_h][2],
 // [cols][n_w][2] fp32 (cos, sin).  Token t sits at frame t / (rows*cols), row
@@ -264,6 +270,28 @@ struct Rotator<kRope3D, STEPS, DEPTH> {
         f32x2 e[4];
         fetch(s, j, e);
         return rotate_with(w, e);
+    }
+};
+
+template <int STEPS, int DEPTH>
+struct Rotator<kRope3DWhole, STEPS, DEPTH> : Rotator<kRope3D, STEPS, DEPTH> {
+    using Base = Rotator<kRope3D, STEPS, DEPTH>;
+    using Base::Base;
+    __device__ __forceinline__ void fetch(int /*s*/, int j, f32x2 (&e)[4]) const
+    {
+        const uint32_t addr = this->base[0] + __umul24((uint32_t)this->f[j], this->mul_f[0]) +
+                              __umul24((uint32_t)this->r[j], this->mul_r[0]) + __umul24((uint32_t)this->c[j], this->mul_c[0]);
+        const f32x4 a = *reinterpret_cast<const f32x4 *>(this->tab + addr), b = *reinterpret_cast<const f32x4 *>(this->tab + addr + 16);
+        e[0] = f32x2{a.x, a.y};
+        e[1] = f32x2{a.z, a.w};
+        e[2] = f32x2{b.x, b.y};
+        e[3] = f32x2{b.z, b.w};
+    }
+    __device__ __forceinline__ u32x4 rotate(int s, int j, u32x4 w) const
+    {
+        f32x2 e[4];
+        fetch(s, j, e);
+        return this->rotate_with(w, e);
     }
 };
 

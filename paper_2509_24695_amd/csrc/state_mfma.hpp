@@ -594,9 +594,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void state_mfma_d64(
                                           TileWalk(t0, WAVES * c + wave, WAVES * C, n_tiles, role.phase(b, order)));
     unsigned char *tileK = lds + wave * 2 * kTileBytes;
     Rope3dFill tabs;
-    if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
+    if (is_rope3d(ROPE)) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
     state_prefetch(stream);
-    if (ROPE == kRope3D) {
+    if (is_rope3d(ROPE)) {
         rope3d_lds_fill_end(lds + state_lds_bytes<TILE, WAVES>(), rope.r3, tabs);
         wg_barrier();
     }

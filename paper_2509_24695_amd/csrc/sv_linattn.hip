@@ -39,8 +39,8 @@ constexpr int kStateDepth = 2, kApplyDepth = 2;
 // 16-token tiles in flight per wave of the wave-private d = 112/128 state kernel: three, or two with a rotation (its table
 // rows or its arithmetic need the registers)
 constexpr int kWideStateDepth = 3, kWideStateDepthRope = 2;
-constexpr int kFusedStateDepth[3] = {2, 2, 2};   // one-launch block step (d = 64), by RoPE mode
-constexpr int kFusedApplyDepth[3] = {6, 2, 6};   // Q tiles held in registers across the in-kernel waits
+constexpr int kFusedStateDepth[4] = {2, 2, 2, 2};   // one-launch block step (d = 64), by RoPE mode
+constexpr int kFusedApplyDepth[4] = {6, 2, 6, 6};   // Q tiles held in registers across the in-kernel waits
 constexpr bool kApplyHiLo = true;
 // Workgroups per compute unit of the fp32-arithmetic apply kernel.  Every wave starts by fetching its part of the state,
 // so few and long ones win (d = 64, 4 680 tokens: 46.5 us for the layer with two, 52.8 with four, 57.8 with eight); at
@@ -83,10 +83,10 @@ struct Shape {
 struct Device {
     int num_cu = 0;
     // how many workgroups fit on the device at once
-    int state_resident_wgs[2][3][2] = {};                    // state kernel with in-kernel finalize, [DP = 128][RoPE mode][SHARED]
+    int state_resident_wgs[2][4][2] = {};                    // state kernel with in-kernel finalize, [DP = 128][kernels' RoPE mode][SHARED]
     int coop_resident_wgs[3][2] = {};                        // state kernel on shared tiles (d = 112, 128), [RoPE mode][SHARED]
     int quad_resident_wgs[3] = {0, 0, 0};                    // quadrant state kernel (d = 112, 128), by RoPE mode
-    int fused_resident_wgs[3] = {0, 0, 0};                   // one-launch block step (d = 64), by RoPE mode
+    int fused_resident_wgs[4] = {0, 0, 0, 0};                   // one-launch block step (d = 64), by the kernels' RoPE mode
     bool ok = false;
 };
 
@@ -95,8 +95,8 @@ struct Device {
 // is a whole line, one form serves all.
 template <int DP, int ROPE, bool SHARED = false> struct Kernels;
 template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
-    static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
-    static constexpr int W = 0, kShared = 0;         // SHARED makes no difference
+    static constexpr int kTab = is_rope3d(ROPE) ? kRope3dLdsBytes : 0;
+    static constexpr int W = 0, kShared = 0, kRope = ROPE;         // SHARED makes no difference
     static constexpr bool kWideState = false, kHasCoop = false;
     static constexpr auto state = state_mfma_d64<kStateTile, kStateWaves, kStateDepth, true, ROPE>;
     static constexpr auto state_partial = state_mfma_d64<kStateTile, kStateWaves, kStateDepth, false, ROPE>;
@@ -123,7 +123,7 @@ template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
     static constexpr int apply_wgs_per_cu_short = apply_wgs_per_cu, apply_short_steps = 0;   // no other form for short ranges
 };
 template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
-    static constexpr int W = 1, kShared = SHARED;
+    static constexpr int W = 1, kShared = SHARED, kRope = ROPE;
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
     static constexpr bool kWideState = true, kHasCoop = ROPE != kRopeTable;
     template <bool FINALIZE> static constexpr auto pick_state() {
@@ -227,7 +227,8 @@ template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
 template <typename F> void with_mfma_kernels(int d, int rope_mode, bool shared, F &&f)
 {
     if (d == 64) {
-        if (rope_mode == kRope3D) f(Kernels<64, kRope3D>{});
+        if (rope_mode == kRope3DWhole) f(Kernels<64, kRope3DWhole>{});
+        else if (rope_mode == kRope3D) f(Kernels<64, kRope3D>{});
         else if (rope_mode == kRopeTable) f(Kernels<64, kRopeTable>{});
         else f(Kernels<64, kRopeNone>{});
     } else {
@@ -246,6 +247,13 @@ struct Rope {
     int mode = kRopeNone;
     RopeArg arg{};
 };
+
+// The mode whose kernels serve a rotation at head dimension d.
+int kernel_mode(const Rope &rope, int d)
+{
+    const Rope3D &R = rope.arg.r3;
+    return rope.mode == kRope3D && d == 64 && ((R.n_t | R.n_h | R.n_w) & 3) == 0 ? kRope3DWhole : rope.mode;
+}
 
 // Switches a workspace to device-side epochs and clears its error word.  The ticket counters restart at
 // zero, so the epochs drawn from them repeat those of an earlier life of the same memory: every flag word
@@ -295,6 +303,7 @@ const Device &device_info()
         init_kernels<64, kRopeNone>(d);
         init_kernels<64, kRopeTable>(d);
         init_kernels<64, kRope3D>(d);
+        init_kernels<64, kRope3DWhole>(d);
         init_kernels<128, kRopeNone>(d);
         init_kernels<128, kRopeTable>(d);
         init_kernels<128, kRope3D>(d);
@@ -472,13 +481,13 @@ void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, c
                        dim3 rgrid, hipStream_t stream)
 {
     if (s.d > 64 && launch_state_quad(k, v, rope, s, t0, t1, S_in, z_in, S_out, z_out, ws, dev, stream)) return;
-    with_mfma_kernels(s.d, rope.mode, layout_of(s).shares_lines(), [&](auto kn) {
+    with_mfma_kernels(s.d, kernel_mode(rope, s.d), layout_of(s).shares_lines(), [&](auto kn) {
         using KN = decltype(kn);
         const int C = plan_chunks(s.BH, t1 - t0, KN::state_wg_tokens, dev.num_cu);
         const int order = state_order(layout_of(s), rope.mode == kRopeTable);
         auto finalize = KN::state;
         auto partial = KN::state_partial;
-        int resident = dev.state_resident_wgs[KN::W][rope.mode][KN::kShared], threads = 64 * kStateWaves, lds = KN::state_lds;
+        int resident = dev.state_resident_wgs[KN::W][KN::kRope][KN::kShared], threads = 64 * kStateWaves, lds = KN::state_lds;
         if constexpr (KN::kHasCoop)
             if (coop_state_pays(t1 - t0, C) || pairs_heads(layout_of(s), rope.mode != kRopeNone, t1 - t0)) {
                 finalize = KN::template coop_state<true>;
@@ -565,7 +574,7 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
     const Device &dev = device_info();
     if (!dev.ok) return SV_ERR_LAUNCH;
     if (mfma_path(s, rope)) {
-        with_mfma_kernels(s.d, rope.mode, layout_of(s).shares_lines(), [&](auto kn) {
+        with_mfma_kernels(s.d, kernel_mode(rope, s.d), layout_of(s).shares_lines(), [&](auto kn) {
             using KN = decltype(kn);
             const bool pair = KN::kShared && pairs_heads(layout_of(s), rope.mode != kRopeNone, n);
             int C = KN::apply_wgs_per_cu * dev.num_cu / s.BH;
@@ -727,7 +736,7 @@ sv_status do_block_step(const void *Qb, const void *Kb, const void *Vb, const sv
             using KN = decltype(kn);
             // One launch when the whole grid can be resident at once (needed by the in-kernel waits).
             const int C = plan_chunks(s.BH, s.N, KN::fused_wg_tokens, dev.num_cu);
-            if ((int64_t)C * s.BH > dev.fused_resident_wgs[rope.mode]) return;
+            if ((int64_t)C * s.BH > dev.fused_resident_wgs[KN::kRope]) return;
             // A head per workgroup and a long block: two launches, whose apply fills the device whatever the number of
             // heads (4 680 tokens, 160 heads: 75.3 against 79.6 us; 1 560 tokens: 38.5 against 33.8).
             if (C == 1 && s.N > 3072) return;
@@ -746,7 +755,9 @@ sv_status do_block_step(const void *Qb, const void *Kb, const void *Vb, const sv
                 next_epoch(s.host_epochs_only), spin_limit(), s.BH, local ? dies : 0);
             launched = true;
         };
-        if (rope.mode == kRope3D) launch(Kernels<64, kRope3D>{});
+        const int mode = kernel_mode(rope, s.d);
+        if (mode == kRope3DWhole) launch(Kernels<64, kRope3DWhole>{});
+        else if (mode == kRope3D) launch(Kernels<64, kRope3D>{});
         else if (rope.mode == kRopeTable) launch(Kernels<64, kRopeTable>{});
         else launch(Kernels<64, kRopeNone>{});
         if (launched) return launch_status();
