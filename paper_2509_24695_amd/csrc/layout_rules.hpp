@@ -70,7 +70,7 @@ inline int apply_order(const TokenLayout &t, bool full_table, bool factored_tabl
 }
 
 // d = 112 and 128, apply without a full table: workgroups per compute unit, three or two (layers, state and apply in turn, three -> two).
-//   shared lines, plain    two: the heads of a chunk, which read and write pieces of the same lines, stay closer together (20 heads of 112, 32 760
+//   shared lines, plain    two, also where they go in pairs (pairs_heads): the heads of a chunk, which read and write pieces of the same lines, stay closer together (20 heads of 112, 32 760
 //                          tokens 155 -> 150 us, 40 heads 312 -> 266, 64 heads, 14 040 tokens 228 -> 195; with factored tables 299 -> 286 on
 //                          one device and 286 -> 290 on another, so not there).
 //   d = 128, plain         two (64 heads, 14 040 tokens 190 -> 187 us, token-major 40 heads, 32 760 tokens 258 -> 249, 20 heads 140 -> 137; at
