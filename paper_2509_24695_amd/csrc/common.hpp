@@ -12,7 +12,6 @@ namespace sv {
 constexpr int kWave = 64;            // CDNA wavefront width
 constexpr int kThreads = 256;        // every kernel here runs 4 waves per workgroup
 constexpr int kWavesPerWg = kThreads / kWave;
-constexpr int kMaxChunks = 32;       // upper bound on token chunks per head (workspace sizing)
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

@@ -137,6 +137,7 @@ template <typename T, int D, bool SOLE, int ROPE> struct StateF32 {
     static constexpr int kSlot = F * F + F;                // a wave's part in LDS: state, then key sums
     static constexpr int kParts = kSplit ? kWaves / 4 : kWaves;   // waves that hold the same part of the state
     static constexpr int kWgTokens = kParts * TILE;
+    static_assert(!kSplit || (TILE == kF32WideTile && DEPTH * kChains == kF32WideSums), "f32_sole_tokens counts on these");
     static constexpr int lds_bytes() {
         constexpr int slots = kWaves * kSlot * 4, tab = ROPE == kRope3D ? kRope3dLdsBytes : 0;   // tables, then slots
         return slots > tab ? slots : tab;

@@ -1,10 +1,26 @@
-// What a token tensor's strides mean for the kernels: whether 32-bit offsets reach its heads, and in which order workgroups
-// are dealt to it.  Plain C++ (no device code), shared by the launcher and a host-side test.
+// What a call's sizes and a token tensor's strides mean for the kernels: whether 32-bit offsets reach its heads, in which order workgroups
+// are dealt to it, how many it gets and which kernel serves it.  Plain C++ (no device code), shared by the launcher and host-side tests.
 #pragma once
 
 #include <stdint.h>
 
 namespace sv {
+
+constexpr int kMaxChunks = 32;       // upper bound on token chunks per head (workspace sizing)
+
+// Token chunks (workgroups) per head: about one workgroup per compute unit over
+// the whole grid, never more than kMaxChunks (which sizes the workspace) or
+// than there are tiles.
+inline int plan_chunks(int BH, int n_tokens, int tokens_per_wg_step, int num_cu)
+{
+    if (n_tokens <= 0) return 0;
+    const int steps = (n_tokens + tokens_per_wg_step - 1) / tokens_per_wg_step;
+    int chunks = num_cu / BH;
+    if (chunks > kMaxChunks) chunks = kMaxChunks;
+    if (chunks > steps) chunks = steps;
+    if (chunks < 1) chunks = 1;
+    return chunks;
+}
 
 // The matrix-core kernels address a head's tokens with 32-bit byte offsets below 2^31: what a head spans, and what one tile of 64 rows
 // spans (rows past the end are reached by address before they are dropped).
@@ -121,6 +137,26 @@ inline bool quad_state_pays(int BH, int d, int n_tokens, bool full_table, int nu
     const int C = num_cu / (4 * BH);
     if (16 * BH * C < 3 * num_cu) return false;
     return (int64_t)BH * n_tokens <= (d == 112 ? (full_table ? 40000 : 76000) : (full_table ? 66000 : 100000));
+}
+
+// fp32-arithmetic state: tokens up to which one workgroup sums a head in one launch, instead of several and a second launch for
+// their sum.  One / several, layers enqueued back to back by a host that keeps ahead of the device, us:
+//   d = 32 (sixteen waves), fp32    2 heads, 768 tokens 11.9 / 12.8, 1 024 13.2 / 12.9; 16 heads, 512 12.2 / 12.9, 1 024 15.5 / 12.9; 32 heads,
+//            512 12.5 / 13.0, 768 14.8 / 13.1; 64 heads, 768 16.3 / 16.2; 128 heads, 1 024 23.8 / 24.8; bf16 some 300 tokens later;
+//   d = 64   8 heads, 128 tokens 12.1 / 13.1, 256 14.2 / 13.2; 64 heads, 192 15.3 / 16.6, 256 16.7 / 16.7;
+//   d = 112  8 heads, 32 tokens 13.9 / 16.4.
+// A host that does anything besides is what these small layers wait for, and a third launch costs it 2.5 us (2 heads of 32, 1 024 tokens
+// in a program that changes its buffers from layer to layer: 13.2 / 15.4), so the lines lie where one workgroup is up to that much
+// slower on the device.
+// d = 112 and 128 end where each of a wave's running sums has had one tile: a longer one is further from the exact sum than those of
+// several workgroups (64 heads of 112, 128 tokens: S by 11 to 26 %), although with 128 heads it would be the faster one up to 128 tokens
+// (31.1 / 36.1 us).
+constexpr int kF32WideTile = 16, kF32WideSums = 3;    // of a wave at d = 112 and 128: tokens per tile, running sums (taken in turn by the tiles)
+inline int f32_sole_tokens(int d, int BH, int elem_bytes)
+{
+    if (d == 32) return (BH <= 16 ? 1152 : BH <= 32 ? 896 : 768) + (elem_bytes == 2 ? 128 : 0);
+    if (d == 64) return BH <= 16 ? 256 : 192;
+    return kF32WideTile * kF32WideSums;
 }
 
 }  // namespace sv

@@ -46,21 +46,6 @@ constexpr bool kApplyHiLo = true;
 // so few and long ones win (d = 64, 4 680 tokens: 46.5 us for the layer with two, 52.8 with four, 57.8 with eight); at
 // d = 32 the state is small and more waves cover the loads (44.8, 42.1, 41.7 us).
 constexpr int f32_apply_wgs_per_cu(int d) { return d == 32 ? 4 : 2; }
-// fp32-arithmetic state: tokens up to which one workgroup sums a head in one launch, instead of several and a second launch for
-// their sum.  One / several, layers enqueued back to back by a host that keeps ahead of the device, us:
-//   d = 32 (sixteen waves), fp32    2 heads, 768 tokens 11.9 / 12.8, 1 024 13.2 / 12.9; 16 heads, 512 12.2 / 12.9, 1 024 15.5 / 12.9; 32 heads,
-//            512 12.5 / 13.0, 768 14.8 / 13.1; 64 heads, 768 16.3 / 16.2; 128 heads, 1 024 23.8 / 24.8; bf16 some 300 tokens later;
-//   d = 64   8 heads, 128 tokens 12.1 / 13.1, 256 14.2 / 13.2; 64 heads, 192 15.3 / 16.6, 256 16.7 / 16.7;
-//   d = 112  8 heads, 32 tokens 13.9 / 16.4, 64 16.0 / 16.7, 128 21.2 / 18.0; 32 heads, 64 17.9 / 19.2, 128 23.5 / 21.4; 128 heads, 128 31.1 / 36.1.
-// A host that does anything besides is what these small layers wait for, and a third launch costs it 2.5 us (2 heads of 32, 1 024 tokens
-// in a program that changes its buffers from layer to layer: 13.2 / 15.4), so the lines lie where one workgroup is up to that much
-// slower on the device.
-int f32_sole_tokens(int d, int BH, int elem_bytes)
-{
-    if (d == 32) return (BH <= 16 ? 1152 : BH <= 32 ? 896 : 768) + (elem_bytes == 2 ? 128 : 0);
-    if (d == 64) return BH <= 16 ? 256 : 192;
-    return BH <= 8 ? 64 : BH <= 32 ? 96 : 128;
-}
 // d = 64: the denominators phi(Q_i).z ride through the matrix core as two more operand rows (false) or are taken on
 // the vector ALU with a wavefront-level reduction (true).  Measured level (within 1 % either way at 32 760 and
 // 75 600 tokens; the one-launch block step 0.5-1 us per block slower with the vector ALU form), so they stay on
@@ -346,20 +331,6 @@ unsigned long long next_epoch(bool host_epochs_only = false)
     // odd, never zero, never repeated (2^62 calls apart); the top bit is the kernels' kHostEpochsOnly
     const unsigned long long e = ((ctr.fetch_add(1, std::memory_order_relaxed) << 1) | 1ull) & ~kHostEpochsOnly;
     return host_epochs_only ? e | kHostEpochsOnly : e;
-}
-
-// Token chunks (workgroups) per head: about one workgroup per compute unit over
-// the whole grid, never more than kMaxChunks (which sizes the workspace) or
-// than there are tiles.
-int plan_chunks(int BH, int n_tokens, int tokens_per_wg_step, int num_cu)
-{
-    if (n_tokens <= 0) return 0;
-    const int steps = (n_tokens + tokens_per_wg_step - 1) / tokens_per_wg_step;
-    int chunks = num_cu / BH;
-    if (chunks > kMaxChunks) chunks = kMaxChunks;
-    if (chunks > steps) chunks = steps;
-    if (chunks < 1) chunks = 1;
-    return chunks;
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }

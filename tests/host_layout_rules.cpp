@@ -43,6 +43,19 @@ int main()
         if (s != w.state || a != w.apply) return printf("FAIL order BH=%d H=%d d=%d e=%d n=%d: %d %d\n", w.t.BH, w.t.H, w.t.d, w.t.elem_bytes, w.n, s, a), 1;
         ++cases;
     }
+    // fp32 states of d = 112 and 128: no running sum of a head's only workgroup is longer than it is where several workgroups share
+    // the head's tiles of 16 tokens (three sums per wave, a quadrant of the state to each of four waves)
+    auto longest = [](int n, int C) {
+        const int tiles = (n + 15) / 16, share = (tiles + C - 1) / C;
+        return 16 * ((share + 2) / 3);
+    };
+    for (int d : {112, 128})
+        for (int BH = 1; BH <= 300; ++BH)
+            for (int n = 1; n <= 400; ++n) {
+                if (n > sv::f32_sole_tokens(d, BH, 4)) continue;
+                if (longest(n, 1) > longest(n, sv::plan_chunks(BH, n, 16, 256))) return printf("FAIL sole d=%d BH=%d n=%d\n", d, BH, n), 1;
+                ++cases;
+            }
     printf("OK %ld\n", cases);
     return 0;
 }
