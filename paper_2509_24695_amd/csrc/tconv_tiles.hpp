@@ -120,7 +120,7 @@ constexpr FrameShape kFrameShape[kFrameForms] = {{3, 5, 192, false}, {5, 3, 192,
 // Token tiles of a call: batches x groups of frames x groups of positions.
 inline int64_t frame_tiles_m(const FrameShape &f, int B, int T, int HW)
 {
-    return (int64_t)B * ((T + f.frames - 1) / f.frames) * ((HW + 16 * f.blocks - 1) / (16 * f.blocks));
+    return (int64_t)B * ((T + f.frames - 1) / f.frames) * (((int64_t)HW + 16 * f.blocks - 1) / (16 * f.blocks));
 }
 // Time of a call in us on a frame kernel: a start, more of it per further round of tiles, and a time per K-step with up to half of the
 // compute units busy, with all, and per round of several.  Fitted to 1 246 calls (1 to 21 frames, 40 to 3 600 positions, 96 to 2 240
@@ -143,7 +143,8 @@ inline double frame_cost(FrameFormId id, int B, int T, int HW, int D, int num_cu
 // kernel of all, and no call takes more than 3 % longer than on tconv_form's.
 inline FrameFormId frame_form(int B, int T, int HW, int D, bool cache, int num_cu)
 {
-    if (D % 32 != 0) return kNoFrames;
+    // One frame would fill a third of a tile (and tconv_frames counts positions in 32 bits: of two frames and more there are less than 2^30).
+    if (D % 32 != 0 || T == 1) return kNoFrames;
     constexpr double kNow[kTconvForms] = {0.99, 0.725, 0.826, 0.99, 1.0};
     const int64_t M = (int64_t)B * T * HW;
     const TconvFormId rows = tconv_form(M, D, T, cache, num_cu);

@@ -19,7 +19,7 @@ int main(int argc, char **argv)
     for (int cus : {1, 64, 256, 304})
         for (int B : {1, 2, 7})
             for (int T : {1, 2, 3, 4, 5, 6, 7, 8, 14, 21, 1000})
-                for (int HW : {1, 79, 80, 81, 1560, 3600, 100000})
+                for (int HW : {1, 79, 80, 81, 1560, 3600, 100000, (1 << 30) - 1, 2147483600, 2147483647})
                     for (int D = 8; D <= 26000; D = D < 256 ? D + 8 : D * 3 / 2 / 8 * 8)
                         for (int cache = 0; cache < 2; ++cache) {
                             if ((int64_t)B * T * HW >= (int64_t)1 << 31) continue;
@@ -28,7 +28,7 @@ int main(int argc, char **argv)
                             if (f == kNoFrames) continue;
                             ++taken;
                             const FrameShape &s = kFrameShape[f];
-                            if (D % 32 || (!s.back && T > s.frames)) return printf("FAIL T=%d D=%d\n", T, D), 1;
+                            if (D % 32 || T == 1 || (!s.back && T > s.frames)) return printf("FAIL T=%d D=%d\n", T, D), 1;
                             const int64_t tiles = frame_tiles_m(s, B, T, HW), rows = (int64_t)s.frames * 16 * s.blocks;
                             if (tiles * rows < (int64_t)B * T * HW || !std::isfinite(frame_cost(f, B, T, HW, D, cus))) return printf("FAIL cover\n"), 1;
                         }
