@@ -17,7 +17,7 @@
 //             LDS into the other register set; the loads of W(s + 6) into the slot of W(s) and a third of x(k + 3) into the slot
 //             of x(k), which every wave has read
 // LDS rows, swizzle and the loads straight into LDS are those of tconv_mfma.  Channels are a multiple of 32.  With an odd number of K-steps
-// the last pass takes one more, whose x rows are zeros.
+// the last pass takes one more, of zeros on both sides.
 #pragma once
 
 #include "tconv_mfma.hpp"
@@ -78,9 +78,10 @@ __global__ __launch_bounds__(kThreads) void tconv_frames(TconvArgs a)
         tc_load_to_lds(k < KC ? srcA[i] + k * kTcBK : zero, lds + slot * S::kA + i * 4096 + wave * 1024);
     };
     auto load_w = [&](int k, int t, int slot, int i) __attribute__((always_inline)) {
-        const int kc = k < KC ? k : KC - 1;
-        const unsigned char *base = reinterpret_cast<const unsigned char *>(a.W + ((int64_t)t * D * D + kc * kTcBK));
-        tc_load_to_lds(reinterpret_cast<const uint16_t *>(base + offW[i]), lds + S::kWOffset + slot * S::kW + i * 4096 + wave * 1024);
+        const uint16_t *base = k < KC ? a.W + ((int64_t)t * D * D + k * kTcBK) : tc_zero_row;
+        const uint32_t off = k < KC ? offW[i] : (uint32_t)c4 * 16u;
+        tc_load_to_lds(reinterpret_cast<const uint16_t *>(reinterpret_cast<const unsigned char *>(base) + off),
+                       lds + S::kWOffset + slot * S::kW + i * 4096 + wave * 1024);
     };
 
     // ---- consumer role: lane l holds chunk l / 16 of row l % 16 of a 16-row block ----------------------
