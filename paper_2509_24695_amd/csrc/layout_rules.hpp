@@ -140,23 +140,26 @@ inline bool quad_state_pays(int BH, int d, int n_tokens, bool full_table, int nu
 }
 
 // fp32-arithmetic state: tokens up to which one workgroup sums a head in one launch, instead of several and a second launch for
-// their sum.  One / several, layers enqueued back to back by a host that keeps ahead of the device, us:
-//   d = 32 (sixteen waves), fp32    2 heads, 768 tokens 11.9 / 12.8, 1 024 13.2 / 12.9; 16 heads, 512 12.2 / 12.9, 1 024 15.5 / 12.9; 32 heads,
-//            512 12.5 / 13.0, 768 14.8 / 13.1; 64 heads, 768 16.3 / 16.2; 128 heads, 1 024 23.8 / 24.8; bf16 some 300 tokens later;
-//   d = 64   8 heads, 128 tokens 12.1 / 13.1, 256 14.2 / 13.2; 64 heads, 192 15.3 / 16.6, 256 16.7 / 16.7;
-//   d = 112  8 heads, 32 tokens 13.9 / 16.4.
-// A host that does anything besides is what these small layers wait for, and a third launch costs it 2.5 us (2 heads of 32, 1 024 tokens
-// in a program that changes its buffers from layer to layer: 13.2 / 15.4), so the lines lie where one workgroup is up to that much
-// slower on the device.
+// their sum.  The lines lie where a host that enqueues layers (state, apply) back to back sees the two meet; one / several, us, two devices:
+//   d = 32 (sixteen waves), fp32, plain   2 heads, 1 024 tokens 1.2 less, 1 152 0.5 less, 1 280 0.1 more; 16 heads, 768 1.1 less, 896 0.7 less, 1 024 0.6
+//            more, 1 152 1.7 more; 6 and 12 heads 832 0.3 more; 32 heads, 640 0.6 less, 768 0.1 more, 896 1.2 more; 64 heads, 640 0.9 less; 128, 768 2.3 less;
+//            rotated   2 heads, 768 0.9 less to 0.2 more; 16, 640 0.6 less to 0.6 more, 1 024 3.4 to 3.8 more; 32, 512 0.2 less to 0.3 more, 896 2.7 more;
+//            bf16, plain   16 heads, 1 152 0.5 more, 1 280 1.2 more; rotated   16, 896 0.2 more to 1.1 less, 1 280 2.3 to 4.0 more; 32, 704 level; 64, 640 level;
+//   d = 64   8 heads, 192 tokens 0.7 less, 256 0.6 more; 12 heads, 256 0.3 less; rotated 16 heads, 192 0.7 more, 256 1.7 more; 64 heads, 192 1.2 less.
+// of 12 to 18 us a layer.  In a captured graph, where a launch costs no host time, they meet earlier: d = 32, fp32 at 512 tokens for up to
+// 32 heads, 1 152 tokens are 3 to 5 us slower there on one workgroup; d = 64 at 160.
+// Both forms of the rotation have the same lines, so that they give the same bits.
 // d = 112 and 128 end where each of a wave's running sums has had one tile: a longer one is further from the exact sum than those of
 // several workgroups (64 heads of 112, 128 tokens: S by 11 to 26 %), although with 128 heads it would be the faster one up to 128 tokens
 // (31.1 / 36.1 us).
 constexpr int kF32WideTile = 16, kF32WideSums = 3;    // of a wave at d = 112 and 128: tokens per tile, running sums (taken in turn by the tiles)
-inline int f32_sole_tokens(int d, int BH, int elem_bytes)
+inline int f32_sole_tokens(int d, int BH, int elem_bytes, bool rotated)
 {
-    if (d == 32) return (BH <= 16 ? 1152 : BH <= 32 ? 896 : 768) + (elem_bytes == 2 ? 128 : 0);
-    if (d == 64) return BH <= 16 ? 256 : 192;
-    return kF32WideTile * kF32WideSums;
+    if (d > 64) return kF32WideTile * kF32WideSums;
+    if (d == 64) return BH <= 16 && !rotated ? 256 : 192;
+    constexpr int kTokens[2][2][5] = {{{1152, 832, 640, 640, 768}, {832, 640, 512, 512, 768}},         // fp32: plain, rotated
+                                      {{1280, 1152, 1024, 896, 896}, {960, 896, 704, 640, 896}}};      // bf16
+    return kTokens[elem_bytes == 2][rotated][BH <= 2 ? 0 : BH <= 16 ? 1 : BH <= 32 ? 2 : BH <= 64 ? 3 : 4];
 }
 
 }  // namespace sv

@@ -509,7 +509,7 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
         with_f32_kernels(s, rope.mode, [&](auto kn) {
             using KN = decltype(kn);
             using T = typename KN::T;
-            const bool sole = n <= f32_sole_tokens(s.d, s.BH, s.elem_bytes);
+            const bool sole = n <= f32_sole_tokens(s.d, s.BH, s.elem_bytes, rope.mode != kRopeNone);
             const int C = sole ? 1 : plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
             const auto kernel = C == 1 ? KN::state : KN::state_partial;
             kernel<<<dim3(C, s.BH), C == 1 ? KN::state_threads : kThreads, C == 1 ? KN::state_lds : KN::partial_lds, stream>>>(
