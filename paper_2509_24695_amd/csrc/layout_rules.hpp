@@ -125,18 +125,28 @@ inline bool pairs_heads(const TokenLayout &t, bool rotated, int n_tokens)
 inline bool coop_state_pays(int n_tokens, int C) { return n_tokens <= 2048 * C; }
 
 // d = 112 and 128, state: the kernel of quadrants (quad_state.hpp) instead of whole rows, for ranges whose exchange among workgroups takes
-// longer than their tokens.  Both read in step with the number of head-tokens, the quadrants slower; the lines are where the two meet
-// (quadrants / rows, us):
-//   d = 112  20 heads, 1 560, 3 120, 4 680 tokens: plain 11.3 / 12.1, 14.5 / 14.4, 20.1 / 16.8; factored tables 12.7 / 14.3, 15.6 / 16.8, 22.2 / 19.2;
-//            12 heads, 4 680: 15.5 / 16.2, 16.6 / 18.0; full table 20 heads, 1 560: 12.5 / 15.1, 12 heads, 4 680: 19.5 / 17.6
-//   d = 128  20 heads, 3 120 and 4 680 tokens: plain 14.0 / 15.5, 18.6 / 18.1; factored tables 16.0 / 17.3, 21.0 / 20.1; full table 17.7 / 18.8, 24.8 / 21.9;
-//            64 heads, 1 560: 17.5 / 18.3, 18.6 / 20.1, 22.1 / 23.2; 12 heads, 9 360: 21.9 / 21.8, 23.5 / 22.7, 29.2 / 25.1
-// Four workgroups per chunk have to fill most of the device (40 heads of 112, 1 560 tokens, 160 workgroups: 15.5 / 13.5).
-inline bool quad_state_pays(int BH, int d, int n_tokens, bool full_table, int num_cu)
+// longer than their tokens.  Both read in step with the number of head-tokens, the quadrants slower, and what the quadrants save depends on how
+// many chunks C a head has: all of the exchange with one, little with two, whose quadrants fetch as many partials as twice as many workgroups
+// of whole rows.  The lines, in thousands of head-tokens, are where layers (state, apply) on one kernel and on the other meet; quadrants over rows:
+//   d = 112, plain      C = 1: 64 heads 0.93 to 61, 0.96 at 76, 48 heads 1.00 at 69; C = 2: 26 to 32 heads 0.98 to 1.02 at 24, 1.05 at 40; C = 3:
+//                       0.96 at 24, 0.98 to 1.02 from 40 to 50, 1.05 at 60; C = 4 to 10: 0.95 to 0.99 at 60, 0.99 to 1.02 at 70; 4 and 5 heads: 1.01
+//                       to 1.08 from 40 on; 2 heads: 0.93 to 0.98
+//   d = 112, factored   C = 1: 0.94 to 1.01 at 70; C = 2: 0.97 to 1.00 at 25, 0.98 to 1.02 at 40, 1.01 to 1.06 from 59 on; C = 3: 0.98 to 0.99 at 50,
+//                       0.98 to 1.03 at 60; from 4 on: 0.96 to 1.00 at 70, 0.94 to 1.01 at 79
+//   d = 112, full table 24 heads 0.99, others 0.86 to 0.96 at 40
+//   d = 128, plain      0.91 to 1.00 at 100
+//   d = 128, factored   C = 1: 0.95 to 1.01 at 99; C = 2: 0.98 to 1.02 at 69, up to 1.07 at 89; C = 3: 0.95 to 1.01 at 79, up to 1.04 at 99; from 4
+//                       on: 0.93 to 0.99 at 99
+//   d = 128, full table 0.84 to 0.97 at 68
+// Four workgroups per chunk have to fill most of the device (40 heads of 112, 1 560 tokens, 160 workgroups: 15.5 / 13.5 us).
+inline bool quad_state_pays(int BH, int d, int n_tokens, bool full_table, bool factored_tables, int num_cu)
 {
     const int C = num_cu / (4 * BH);
     if (16 * BH * C < 3 * num_cu) return false;
-    return (int64_t)BH * n_tokens <= (d == 112 ? (full_table ? 40000 : 76000) : (full_table ? 66000 : 100000));
+    constexpr int kThousands[2][3][4] = {{{76, 26, 52, 70}, {76, 32, 56, 76}, {40, 40, 40, 40}},            // d = 112: plain, factored, full table
+                                         {{100, 100, 100, 100}, {100, 68, 78, 100}, {66, 66, 66, 66}}};     // d = 128
+    if (d == 112 && !full_table && !factored_tables && C > 10 && BH >= 4) return false;
+    return (int64_t)BH * n_tokens <= 1000 * kThousands[d == 128][full_table ? 2 : factored_tables ? 1 : 0][C < 4 ? C - 1 : 3];
 }
 
 // fp32-arithmetic state: tokens up to which one workgroup sums a head in one launch, instead of several and a second launch for

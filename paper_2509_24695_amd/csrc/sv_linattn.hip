@@ -424,7 +424,7 @@ TokenLayout layout_of(const Shape &s) { return TokenLayout{s.BH, s.H, s.d, s.ele
 bool launch_state_quad(const uint16_t *k, const uint16_t *v, const Rope &rope, const Shape &s, int t0, int t1, const float *S_in,
                        const float *z_in, float *S_out, float *z_out, void *ws, const Device &dev, hipStream_t stream)
 {
-    if (!quad_state_pays(s.BH, s.d, t1 - t0, rope.mode == kRopeTable, dev.num_cu)) return false;
+    if (!quad_state_pays(s.BH, s.d, t1 - t0, rope.mode == kRopeTable, rope.mode == kRope3D, dev.num_cu)) return false;
     bool launched = false;
     auto launch = [&](auto kn) {
         using KN = decltype(kn);
