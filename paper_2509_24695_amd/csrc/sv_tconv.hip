@@ -22,30 +22,30 @@ bool overlaps(const void *a, size_t na, const void *b, size_t nb)
 
 using TconvKernel = void (*)(TconvArgs);
 
-// The tile kernels in the order of TconvFormId; the long kernel's second form is for channels that are no multiple of the K-step.
+// The kernels on row tiles in the order of TconvFormId; the long kernel's second form is for channels that are no multiple of the K-step.
 struct TconvForm {
-    int bm, bn, lds;
+    int lds;
     TconvKernel kernel;
 };
 template <int F> TconvForm form()
 {
     using P = TcTile<kTconvTile[F].bm, kTconvTile[F].bn>;
-    return TconvForm{P::BM, P::BN, P::kLdsBytes, tconv_mfma<P>};
+    return TconvForm{P::kLdsBytes, tconv_mfma<P>};
 }
-const TconvForm kForms[kTconvForms + 1] = {form<kForm256>(), form<kForm256x128>(), form<kForm128>(), form<kForm64>(),
-                                           {kTcBM, kTcBN, kTcLdsBytes, tconv_mfma32<false>}, {kTcBM, kTcBN, kTcLdsBytes, tconv_mfma32<true>}};
+const TconvForm kForms[kRowForms + 1] = {form<kForm256>(), form<kForm256x128>(), form<kForm128>(), form<kForm64>(),
+                                         {kTcLdsBytes, tconv_mfma32<false>}, {kTcLdsBytes, tconv_mfma32<true>}};
 
-// The kernels on tiles of frames x positions, by FrameFormId and whether the call has a cache.
+// The kernels on tiles of frames x positions, from kFrames3 on and by whether the call has a cache.
 template <int F> TconvForm frame_form_of(bool front)
 {
-    constexpr FrameShape f = kFrameShape[F];
+    constexpr FrameShape f = kFrameShape[F - kFrames3];
     using C = FrameTile<f.frames, f.blocks, f.channels / 64, true, f.back>;
     using N = FrameTile<f.frames, f.blocks, f.channels / 64, f.back, f.back>;      // of several groups all but the first have a frame in front
-    return front ? TconvForm{C::P, C::BN, C::kLdsBytes, tconv_frames<C>} : TconvForm{N::P, N::BN, N::kLdsBytes, tconv_frames<N>};
+    return front ? TconvForm{C::kLdsBytes, tconv_frames<C>} : TconvForm{N::kLdsBytes, tconv_frames<N>};
 }
-const TconvForm kFrameForm[kFrameForms][2] = {{frame_form_of<kFrames3>(false), frame_form_of<kFrames3>(true)},
-                                              {frame_form_of<kFrames5>(false), frame_form_of<kFrames5>(true)},
-                                              {frame_form_of<kFrames7>(false), frame_form_of<kFrames7>(true)}};
+const TconvForm kFrameForms[kTconvForms - kFrames3][2] = {{frame_form_of<kFrames3>(false), frame_form_of<kFrames3>(true)},
+                                                          {frame_form_of<kFrames5>(false), frame_form_of<kFrames5>(true)},
+                                                          {frame_form_of<kFrames7>(false), frame_form_of<kFrames7>(true)}};
 
 // The measurement variants of the 256 x 256 kernel (sv_measure_tconv_variant; 0: the kernel itself).
 constexpr int kVariants = 4;
@@ -67,7 +67,7 @@ int tconv_ready()
         };
         for (const TconvForm &f : kForms)
             if (!allow(f.kernel, f.lds)) return 0;
-        for (const auto &forms : kFrameForm)
+        for (const auto &forms : kFrameForms)
             for (const TconvForm &f : forms)
                 if (!allow(f.kernel, f.lds)) return 0;
         for (const TconvKernel k : kVariantKernels)
@@ -108,16 +108,11 @@ sv_status tconv_enqueue(int variant, const void *x, const void *W, const void *c
     a.cache = static_cast<const uint16_t *>(cache_in);
     a.y = static_cast<uint16_t *>(y);
     a.B = B; a.T = T; a.HW = HW; a.D = D;
-    int id = kForm256;
-    if (variant == kByRule) {
-        id = tconv_form(M, D, T, cache_in != nullptr, num_cu);
-        if (id == kForm256Long && D % kTcBK != 0) ++id;
-    }
-    const int frames = variant == kByRule ? frame_form(B, T, HW, D, cache_in != nullptr, num_cu) : kNoFrames;
-    const TconvForm &f = frames != kNoFrames ? kFrameForm[frames][cache_in != nullptr] : kForms[id];
-    const int64_t tiles_m = frames != kNoFrames ? frame_tiles_m(kFrameShape[frames], B, T, HW) : (M + f.bm - 1) / f.bm;
+    const TconvFormId id = variant == kByRule ? tconv_form(B, T, HW, D, cache_in != nullptr, num_cu) : kForm256;
+    const TconvForm &f = id >= kFrames3 ? kFrameForms[id - kFrames3][cache_in != nullptr] : kForms[id + (id == kForm256Long && D % kTcBK != 0)];
+    const int64_t tiles_m = tconv_tiles_m(id, B, T, HW);
     a.tiles_m = (int)tiles_m;
-    a.tiles_n = (D + f.bn - 1) / f.bn;
+    a.tiles_n = tconv_tiles_n(id, D);
     const int64_t wgs = tc_grid_size(tiles_m * a.tiles_n);
     if (wgs >= (int64_t)1 << 31) return SV_ERR_SHAPE;
     auto hs = static_cast<hipStream_t>(stream);

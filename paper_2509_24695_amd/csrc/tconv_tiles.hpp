@@ -51,10 +51,34 @@ SV_HOST_DEVICE inline void tc_taps(int g0, int g1, int HW, int T, bool cache, in
     hi = T == 1 || (f0 == f1 && f0 % T == T - 1) ? 2 : 3;
 }
 
-// The kernels a call may take: tconv_mfma on tiles of four sizes, and tconv_mfma32 (256 x 256, 32 x 32 x 16 instructions).
-enum TconvFormId { kForm256, kForm256x128, kForm128, kForm64, kForm256Long, kTconvForms };
+// The kernels a call may take: tconv_mfma on tiles of four sizes and tconv_mfma32 (256 x 256, 32 x 32 x 16 instructions), on tiles of
+// consecutive token rows; tconv_frames on tiles of frames x positions.
+enum TconvFormId { kForm256, kForm256x128, kForm128, kForm64, kForm256Long, kFrames3, kFrames5, kFrames7, kTconvForms, kRowForms = kFrames3 };
 struct TconvTileSize { int bm, bn; };
-constexpr TconvTileSize kTconvTile[kTconvForms] = {{256, 256}, {256, 128}, {128, 128}, {64, 64}, {256, 256}};
+constexpr TconvTileSize kTconvTile[kRowForms] = {{256, 256}, {256, 128}, {128, 128}, {64, 64}, {256, 256}};
+// `frames` x 16 `blocks` positions x `channels`; back: the frames of a call make several groups, otherwise the call has no more than these.
+struct FrameShape { int frames, blocks, channels; bool back; };
+constexpr FrameShape kFrameShape[kTconvForms - kFrames3] = {{3, 5, 192, false}, {5, 3, 192, false}, {7, 2, 192, true}};
+
+// Token tiles of a call on kernel `f`: groups of rows, or batches x groups of frames x groups of positions.
+inline int64_t tconv_tiles_m(TconvFormId f, int B, int T, int HW)
+{
+    if (f < kRowForms) return ((int64_t)B * T * HW + kTconvTile[f].bm - 1) / kTconvTile[f].bm;
+    const FrameShape &s = kFrameShape[f - kFrames3];
+    return (int64_t)B * ((T + s.frames - 1) / s.frames) * (((int64_t)HW + 16 * s.blocks - 1) / (16 * s.blocks));
+}
+inline int tconv_tiles_n(TconvFormId f, int D)
+{
+    const int bn = f < kRowForms ? kTconvTile[f].bn : kFrameShape[f - kFrames3].channels;
+    return (D + bn - 1) / bn;
+}
+// May kernel `f` serve the call at all?  Frame tiles take whole K-steps, and not one frame: it would fill a third of a tile
+// (and tconv_frames counts positions in 32 bits: of two frames and more there are less than 2^30).
+inline bool tconv_fits(TconvFormId f, int T, int D)
+{
+    if (f < kRowForms) return true;
+    return D % 32 == 0 && T > 1 && f == (T <= 3 ? kFrames3 : T <= 5 ? kFrames5 : kFrames7);
+}
 
 // Time of a call in us on the tile kernel `f`, as a fit to what it measures: a start that grows with the tile, and a time per
 // K-step of 32 channels that depends on how many tiles a compute unit gets.  From 1 050 calls (1 to 151 200 tokens, 64 to
@@ -63,9 +87,10 @@ constexpr TconvTileSize kTconvTile[kTconvForms] = {{256, 256}, {256, 128}, {128,
 // kernel of 256 x 256 that served every call before.  A rule without the starts, and with one time per step for each kernel, took 4.9 % and up
 // to 56 % (short contractions on too large tiles; 3 600 tokens of 1 920 channels 110 us where the long kernel takes 103).
 // Where channels are no multiple of 32 rows start inside 64-byte blocks, which costs loads more than products: TAIL.
-inline double tconv_cost(TconvFormId f, int64_t M, int D, int taps, int num_cu)
+inline double row_cost(TconvFormId f, int B, int T, int HW, int D, bool cache, int num_cu)
 {
-    const int64_t tiles = ((M + kTconvTile[f].bm - 1) / kTconvTile[f].bm) * ((D + kTconvTile[f].bn - 1) / kTconvTile[f].bn);
+    const int64_t tiles = tconv_tiles_m(f, B, T, HW) * tconv_tiles_n(f, D);
+    const int taps = T > 1 ? 3 : cache ? 2 : 1;       // of a tile that needs most (tc_taps)
     const double per_cu = (double)tiles / num_cu;
     const double rounds = (double)((tiles + num_cu - 1) / num_cu);
     const double steps = (double)((D + 31) / 32) * taps;
@@ -94,63 +119,43 @@ inline double tconv_cost(TconvFormId f, int64_t M, int D, int taps, int num_cu)
     return l.start * (1 + 0.4 * (rounds - 1)) + steps * (rounds <= 1 ? l.half + (l.full - l.half) * filled : rounds * l.more);
 }
 
-// Which kernel serves a call of M tokens and D channels in blocks of T frames on num_cu compute units.
-inline TconvFormId tconv_form(int64_t M, int D, int T, bool cache, int num_cu)
-{
-    const int taps = T > 1 ? 3 : cache ? 2 : 1;       // of a tile that needs most (tc_taps)
-    TconvFormId best = kForm256;
-    double least = tconv_cost(kForm256, M, D, taps, num_cu);
-    // The long kernel only while its tiles leave a third of the compute units idle.  With more it is level with the 256 x 256 kernel
-    // (2 % ahead on average) but draws more power: 171 tiles of 210 steps, six calls in a row take 812, 818, 825, 831, 839 and 846 us on
-    // six devices, where the 256 x 256 kernel takes 829 to 834.
-    const int64_t tiles = ((M + 255) / 256) * ((D + 255) / 256);
-    for (const TconvFormId f : {kForm256x128, kForm128, kForm64, kForm256Long}) {
-        if (f == kForm256Long && 3 * tiles > 2 * num_cu) continue;
-        const double us = tconv_cost(f, M, D, taps, num_cu);
-        if (us < least) { least = us; best = f; }
-    }
-    return best;
-}
-
-// The kernels on tiles of frames x positions (tconv_frames): `frames` x 16 `blocks` positions x `channels`; back: the frames of a call
-// make several groups, otherwise the call has no more than these.
-enum FrameFormId { kFrames3, kFrames5, kFrames7, kFrameForms, kNoFrames = -1 };
-struct FrameShape { int frames, blocks, channels; bool back; };
-constexpr FrameShape kFrameShape[kFrameForms] = {{3, 5, 192, false}, {5, 3, 192, false}, {7, 2, 192, true}};
-// Token tiles of a call: batches x groups of frames x groups of positions.
-inline int64_t frame_tiles_m(const FrameShape &f, int B, int T, int HW)
-{
-    return (int64_t)B * ((T + f.frames - 1) / f.frames) * (((int64_t)HW + 16 * f.blocks - 1) / (16 * f.blocks));
-}
 // Time of a call in us on a frame kernel: a start, more of it per further round of tiles, and a time per K-step with up to half of the
 // compute units busy, with all, and per round of several.  Fitted to 1 246 calls (1 to 21 frames, 40 to 3 600 positions, 96 to 2 240
 // channels), 5 to 7 % off.
-inline double frame_cost(FrameFormId id, int B, int T, int HW, int D, int num_cu)
+inline double frame_cost(TconvFormId f, int B, int T, int HW, int D, int num_cu)
 {
     struct Fit { double start, half, full, more, again; };
-    constexpr Fit kFit[kFrameForms] = {{11.0, 0.93, 1.24, 1.10, 0.43}, {11.9, 0.98, 1.30, 1.15, 1.48}, {11.8, 1.01, 1.32, 1.21, 1.14}};
-    const Fit &f = kFit[id];
-    const int64_t tiles = frame_tiles_m(kFrameShape[id], B, T, HW) * ((D + kFrameShape[id].channels - 1) / kFrameShape[id].channels);
+    constexpr Fit kFit[kTconvForms - kFrames3] = {{11.0, 0.93, 1.24, 1.10, 0.43}, {11.9, 0.98, 1.30, 1.15, 1.48}, {11.8, 1.01, 1.32, 1.21, 1.14}};
+    const Fit &fit = kFit[f - kFrames3];
+    const int64_t tiles = tconv_tiles_m(f, B, T, HW) * tconv_tiles_n(f, D);
     const double per_cu = (double)tiles / num_cu, rounds = (double)((tiles + num_cu - 1) / num_cu);
     const double filled = per_cu <= 0.5 ? 0 : 2 * per_cu - 1, steps = (double)D / 32;
-    return f.start * (1 + f.again * (rounds - 1)) + steps * (rounds <= 1 ? f.half + (f.full - f.half) * filled : rounds * f.more);
+    return fit.start * (1 + fit.again * (rounds - 1)) + steps * (rounds <= 1 ? fit.half + (fit.full - fit.half) * filled : rounds * fit.more);
 }
-// The frame kernel that serves a call, or kNoFrames: tconv_form's kernel does.  A third of the calls of 32 channels and more, 100 to
+// Which kernel serves a call on num_cu compute units: the cheapest on row tiles, or one on frame tiles where that is cheaper.  A third of the calls of 32 channels and more, 100 to
 // 3 600 positions and 2 frames and more are faster on tiles of frames, by 4 to 50 %: a block of 3 x 1 560 x 2 240 with a cache 131 -> 101 us,
 // 2 x 3 x 1 447 x 2 240 264 -> 179, 5 x 752 x 2 240 120 -> 86, a clip of 21 x 1 560 x 2 240 809 -> 758; small calls and few channels are not
-// (3 x 449 x 96 7.1 against 15.3).  kNow: what the kernels of tconv_form take of what tconv_cost says since their accumulators stay in one
+// (3 x 449 x 96 7.1 against 15.3).  kNow: what the kernels on row tiles take of what row_cost says since their accumulators stay in one
 // register file and their operand reads go without bank conflicts.  Over those calls the choice costs 0.7 % on average against the fastest
-// kernel of all, and no call takes more than 3 % longer than on tconv_form's.
-inline FrameFormId frame_form(int B, int T, int HW, int D, bool cache, int num_cu)
+// kernel of all, and no call takes more than 3 % longer than on row tiles.
+inline TconvFormId tconv_form(int B, int T, int HW, int D, bool cache, int num_cu)
 {
-    // One frame would fill a third of a tile (and tconv_frames counts positions in 32 bits: of two frames and more there are less than 2^30).
-    if (D % 32 != 0 || T == 1) return kNoFrames;
-    constexpr double kNow[kTconvForms] = {0.99, 0.725, 0.826, 0.99, 1.0};
-    const int64_t M = (int64_t)B * T * HW;
-    const TconvFormId rows = tconv_form(M, D, T, cache, num_cu);
-    const FrameFormId id = T <= 3 ? kFrames3 : T <= 5 ? kFrames5 : kFrames7;
-    const double rows_us = kNow[rows] * tconv_cost(rows, M, D, T > 1 ? 3 : cache ? 2 : 1, num_cu);
-    return frame_cost(id, B, T, HW, D, num_cu) < rows_us ? id : kNoFrames;
+    TconvFormId best = kForm256;
+    double least = row_cost(kForm256, B, T, HW, D, cache, num_cu);
+    // The long kernel only while its tiles leave a third of the compute units idle.  With more it is level with the 256 x 256 kernel
+    // (2 % ahead on average) but draws more power: 171 tiles of 210 steps, six calls in a row take 812, 818, 825, 831, 839 and 846 us on
+    // six devices, where the 256 x 256 kernel takes 829 to 834.
+    const int64_t tiles = tconv_tiles_m(kForm256Long, B, T, HW) * tconv_tiles_n(kForm256Long, D);
+    for (const TconvFormId f : {kForm256x128, kForm128, kForm64, kForm256Long}) {
+        if (f == kForm256Long && 3 * tiles > 2 * num_cu) continue;
+        const double us = row_cost(f, B, T, HW, D, cache, num_cu);
+        if (us < least) { least = us; best = f; }
+    }
+    constexpr double kNow[kRowForms] = {0.99, 0.725, 0.826, 0.99, 1.0};
+    least *= kNow[best];
+    for (const TconvFormId f : {kFrames3, kFrames5, kFrames7})
+        if (tconv_fits(f, T, D) && frame_cost(f, B, T, HW, D, num_cu) < least) return f;
+    return best;
 }
 
 // Last token row of the tile of `bm` rows from m0 on, M tokens in all (m0 < M; m0 + bm may not fit an int).

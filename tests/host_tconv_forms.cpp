@@ -1,6 +1,6 @@
-// Prints, for each "M D T cache num_cu" on the command line, the kernel that tconv_form (csrc/tconv_tiles.hpp) chooses.  With no
-// arguments: over a range of calls the choice is one of the kernels, its cost is the smallest of those that may serve the call, and costs are
-// finite and positive.
+// Prints, for each "B T HW D cache num_cu" on the command line, the kernel that a temporal convolution takes (tconv_form,
+// csrc/tconv_tiles.hpp).  With no arguments: over a range of calls the choice may serve the call, its tiles cover every row, frame tiles have room for a
+// call's frames or take them in groups, and costs are finite and positive; of the kernels on row tiles it is the cheapest.
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -10,32 +10,45 @@
 int main(int argc, char **argv)
 {
     using namespace sv;
-    const char *names[kTconvForms] = {"256x256", "256x128", "128x128", "64x64", "long"};
-    for (int i = 1; i + 4 < argc; i += 5)
-        printf("%s\n", names[tconv_form(atoll(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3]) != 0, atoi(argv[i + 4]))]);
+    const char *names[kTconvForms] = {"256x256", "256x128", "128x128", "64x64", "long", "3 frames", "5 frames", "7 frames"};
+    for (int i = 1; i + 5 < argc; i += 6)
+        printf("%s\n", names[tconv_form(atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2]), atoi(argv[i + 3]), atoi(argv[i + 4]) != 0, atoi(argv[i + 5]))]);
     if (argc > 1) return 0;
-    long cases = 0;
+    long cases = 0, on_frames = 0;
     for (int cus : {1, 64, 256, 304})
-        for (long M : {1L, 63L, 64L, 65L, 1560L, 4680L, 32760L, 151200L, 2147483647L})
-            for (int D = 8; D <= 32768; D = D < 512 ? D + 8 : D * 3 / 2 / 8 * 8)
-                for (int T : {1, 2, 21})
-                    for (int cache = 0; cache < 2; ++cache) {
-                        const TconvFormId f = tconv_form(M, D, T, cache != 0, cus);
-                        if (f < 0 || f >= kTconvForms) return printf("FAIL form M=%ld D=%d\n", M, D), 1;
-                        const int taps = T > 1 ? 3 : 1 + cache;
-                        for (int g = 0; g < kTconvForms; ++g) {
-                            const double us = tconv_cost((TconvFormId)g, M, D, taps, cus);
-                            const bool may = g != kForm256Long || 3 * ((M + 255) / 256) * ((D + 255) / 256) <= 2 * cus;
-                            if (!(us > 0) || !std::isfinite(us) || (may && us < tconv_cost(f, M, D, taps, cus)) || (!may && f == g)) return printf("FAIL cost M=%ld D=%d form %d\n", M, D, g), 1;
+        for (int B : {1, 2, 7})
+            for (int T : {1, 2, 3, 4, 5, 6, 7, 8, 14, 21, 1000})
+                for (int HW : {1, 63, 64, 65, 79, 80, 81, 1560, 3600, 100000, (1 << 30) - 1, 2147483600, 2147483647})
+                    for (int D = 8; D <= 26000; D = D < 256 ? D + 8 : D * 3 / 2 / 8 * 8)
+                        for (int cache = 0; cache < 2; ++cache) {
+                            if ((int64_t)B * T * HW >= (int64_t)1 << 31) continue;
+                            ++cases;
+                            const TconvFormId f = tconv_form(B, T, HW, D, cache != 0, cus);
+                            if (f < 0 || f >= kTconvForms || !tconv_fits(f, T, D)) return printf("FAIL form T=%d D=%d\n", T, D), 1;
+                            int64_t rows = tconv_tiles_m(f, B, T, HW);
+                            if (f >= kFrames3) {
+                                const FrameShape &s = kFrameShape[f - kFrames3];
+                                ++on_frames;
+                                if (D % 32 || T == 1 || (!s.back && T > s.frames)) return printf("FAIL T=%d D=%d\n", T, D), 1;
+                                rows *= (int64_t)s.frames * 16 * s.blocks;
+                                if (!(frame_cost(f, B, T, HW, D, cus) > 0) || !std::isfinite(frame_cost(f, B, T, HW, D, cus))) return printf("FAIL cost\n"), 1;
+                            } else {
+                                rows *= kTconvTile[f].bm;
+                            }
+                            if (rows < (int64_t)B * T * HW) return printf("FAIL cover B=%d T=%d HW=%d\n", B, T, HW), 1;
+                            for (int g = 0; g < kRowForms; ++g) {
+                                const double us = row_cost((TconvFormId)g, B, T, HW, D, cache != 0, cus);
+                                const bool may = g != kForm256Long || 3 * tconv_tiles_m(kForm256Long, B, T, HW) * tconv_tiles_n(kForm256Long, D) <= 2 * cus;
+                                if (!(us > 0) || !std::isfinite(us) || (!may && f == g) || (may && f < kRowForms && us < row_cost(f, B, T, HW, D, cache != 0, cus)))
+                                    return printf("FAIL cost HW=%d D=%d form %d\n", HW, D, g), 1;
+                            }
                         }
-                        ++cases;
-                    }
     // rows of a tile: the last one exists, also where the tile's end does not fit an int
     const int max = 2147483647;
     struct { int m0, bm, M, want; } rows[] = {{0, 256, 1, 0}, {0, 64, 64, 63}, {64, 64, 65, 64}, {max - 255, 256, max, max - 1}, {max - 7, 64, max, max - 1},
                                              {max - 300, 256, max, max - 45}};
     for (auto &r : rows)
         if (tc_last_row(r.m0, r.bm, r.M) != r.want) return printf("FAIL last row %d\n", tc_last_row(r.m0, r.bm, r.M)), 1;
-    printf("OK %ld calls\n", cases);
-    return 0;
+    printf("OK %ld calls, %ld on frames\n", cases, on_frames);
+    return on_frames > 0 ? 0 : 1;
 }
