@@ -80,81 +80,63 @@ inline bool tconv_fits(TconvFormId f, int T, int D)
     return D % 32 == 0 && T > 1 && f == (T <= 3 ? kFrames3 : T <= 5 ? kFrames5 : kFrames7);
 }
 
-// Time of a call in us on the tile kernel `f`, as a fit to what it measures: a start that grows with the tile, and a time per
-// K-step of 32 channels that depends on how many tiles a compute unit gets.  From 1 050 calls (1 to 151 200 tokens, 64 to
-// 2 240 channels, 1 to 21 frames, with and without a cache; five devices), each on all five kernels: the kernel with the smallest
-// fitted time (with the limit in tconv_form) is on average 0.3 % and at worst 14 % slower than the fastest one, and never more than 3.4 % slower than the single
-// kernel of 256 x 256 that served every call before.  A rule without the starts, and with one time per step for each kernel, took 4.9 % and up
-// to 56 % (short contractions on too large tiles; 3 600 tokens of 1 920 channels 110 us where the long kernel takes 103).
+// Time of a call in us on kernel `f`: a start, more of it per further round of tiles, and a time per K-step of 32 channels (and tap) that
+// depends on how many tiles a compute unit gets.  Fitted to 2 878 calls (1 to 8 batches, 1 to 40 frames, 16 to 7 200 positions, 8 to 3 200 channels, with and
+// without a cache; eight devices), each on all kernels that may serve it, so that the kernel of the smallest cost is the fastest one: the choice is on
+// average 0.2 % slower than the fastest kernel, over 6 % slower for 18 of the calls and 15 % at worst (399 calls of a ninth device that the fit had not seen: 0.1 %, 5 % at worst).  For a kernel
+// within 15 % of the fastest the cost itself is 5 to 11 % off.  Fitted before the kernels had their accumulators in one register file and their
+// operand reads free of bank conflicts, it chose 0.7 % and up to 42 % slower ones: 2 x 2 286 x 2 016 (4 batches, no cache) 430 us on frame tiles,
+// 332 on 256 x 256, 2 x 1 190 rows of 1 728 channels with a cache 63 on 128 x 128, 50 on 256 x 128.
 // Where channels are no multiple of 32 rows start inside 64-byte blocks, which costs loads more than products: TAIL.
-inline double row_cost(TconvFormId f, int B, int T, int HW, int D, bool cache, int num_cu)
+inline double tconv_cost(TconvFormId f, int B, int T, int HW, int D, bool cache, int num_cu)
 {
     const int64_t tiles = tconv_tiles_m(f, B, T, HW) * tconv_tiles_n(f, D);
-    const int taps = T > 1 ? 3 : cache ? 2 : 1;       // of a tile that needs most (tc_taps)
-    const double per_cu = (double)tiles / num_cu;
-    const double rounds = (double)((tiles + num_cu - 1) / num_cu);
+    const double per_cu = (double)tiles / num_cu, rounds = (double)((tiles + num_cu - 1) / num_cu);
+    const int taps = f >= kFrames3 ? 1 : T > 1 ? 3 : cache ? 2 : 1;      // of a row tile that needs most (tc_taps); a frame tile takes all in a K-step
     const double steps = (double)((D + 31) / 32) * taps;
     const bool tail = D % 32 != 0;
     // one tile to a compute unit at a time: per step with up to half of the units busy, with all, and per further round
-    struct Large { double start, half, full, more; };
-    constexpr Large k256[2] = {{12.5, 0.555, 0.63, 0.66}, {12, 0.70, 0.81, 0.82}};
-    constexpr Large k256x128[2] = {{9.5, 0.565, 0.565, 0.62}, {9.5, 0.57, 0.64, 0.64}};
-    constexpr Large kLong[2] = {{10.2, 0.535, 0.62, 0.67}, {10, 0.70, 0.82, 0.83}};
+    struct Large { double start, half, full, more, again; };
+    constexpr Large k256[2] = {{15.3, 0.535, 0.678, 0.652, 0.899}, {12.6, 0.706, 0.849, 0.677, 1.479}};
+    constexpr Large k256x128[2] = {{9.71, 0.371, 0.481, 0.486, 0.587}, {8.60, 0.557, 0.604, 0.602, 0.629}};
+    constexpr Large kLong[2] = {{14.8, 0.506, 0.543, 0.692, 0.934}, {10.7, 0.709, 0.693, 0.845, 0.730}};
+    constexpr Large kFrames[kTconvForms - kFrames3] = {{13.3, 0.915, 1.159, 0.962, 2.213}, {14.2, 0.965, 1.206, 1.133, 1.268}, {14.0, 0.975, 1.274, 1.268, 0.947}};
     // two at a time: per step with one tile each (on few units, on all), just above one, with two; then in proportion
     struct Middle { double start, few, one, above, two, each; };
-    constexpr Middle k128[2] = {{6, 0.36, 0.36, 0.45, 0.66, 0.345}, {6, 0.335, 0.40, 0.62, 0.70, 0.44}};
-    // five at a time: per step by tiles per unit, rounded up
+    constexpr Middle k128[2] = {{5.66, 0.211, 0.303, 0.442, 0.631, 0.339}, {4.97, 0.272, 0.401, 0.693, 0.749, 0.445}};
+    // five at a time: per step by tiles per unit, half of it rounded up
     struct Small { double start, base, each; };
-    constexpr Small k64[2] = {{4, 0.06, 0.115}, {3.6, 0.01, 0.17}};
+    constexpr Small k64[2] = {{3.96, -0.011, 0.141}, {3.97, -0.056, 0.185}};
 
-    if (f == kForm64) return k64[tail].start + steps * (k64[tail].base + k64[tail].each * rounds);
+    if (f == kForm64) {
+        const double each = 0.5 * (rounds + per_cu);
+        return k64[tail].start + steps * (k64[tail].base + k64[tail].each * (each > 1 ? each : 1));
+    }
     if (f == kForm128) {
         const Middle &m = k128[tail];
         const double over = m.each * per_cu;
         return m.start + steps * (per_cu <= 1 ? m.few + (m.one - m.few) * per_cu
                                   : per_cu <= 2 ? m.above + (m.two - m.above) * (per_cu - 1) : over > m.two ? over : m.two);
     }
-    const Large &l = f == kForm256 ? k256[tail] : f == kForm256x128 ? k256x128[tail] : kLong[tail];
+    const Large &l = f >= kFrames3 ? kFrames[f - kFrames3] : f == kForm256 ? k256[tail] : f == kForm256x128 ? k256x128[tail] : kLong[tail];
     const double filled = per_cu <= 0.5 ? 0 : 2 * per_cu - 1;
-    return l.start * (1 + 0.4 * (rounds - 1)) + steps * (rounds <= 1 ? l.half + (l.full - l.half) * filled : rounds * l.more);
+    return l.start * (1 + l.again * (rounds - 1)) + steps * (rounds <= 1 ? l.half + (l.full - l.half) * filled : rounds * l.more);
 }
 
-// Time of a call in us on a frame kernel: a start, more of it per further round of tiles, and a time per K-step with up to half of the
-// compute units busy, with all, and per round of several.  Fitted to 1 246 calls (1 to 21 frames, 40 to 3 600 positions, 96 to 2 240
-// channels), 5 to 7 % off.
-inline double frame_cost(TconvFormId f, int B, int T, int HW, int D, int num_cu)
-{
-    struct Fit { double start, half, full, more, again; };
-    constexpr Fit kFit[kTconvForms - kFrames3] = {{11.0, 0.93, 1.24, 1.10, 0.43}, {11.9, 0.98, 1.30, 1.15, 1.48}, {11.8, 1.01, 1.32, 1.21, 1.14}};
-    const Fit &fit = kFit[f - kFrames3];
-    const int64_t tiles = tconv_tiles_m(f, B, T, HW) * tconv_tiles_n(f, D);
-    const double per_cu = (double)tiles / num_cu, rounds = (double)((tiles + num_cu - 1) / num_cu);
-    const double filled = per_cu <= 0.5 ? 0 : 2 * per_cu - 1, steps = (double)D / 32;
-    return fit.start * (1 + fit.again * (rounds - 1)) + steps * (rounds <= 1 ? fit.half + (fit.full - fit.half) * filled : rounds * fit.more);
-}
-// Which kernel serves a call on num_cu compute units: the cheapest on row tiles, or one on frame tiles where that is cheaper.  A third of the calls of 32 channels and more, 100 to
-// 3 600 positions and 2 frames and more are faster on tiles of frames, by 4 to 50 %: a block of 3 x 1 560 x 2 240 with a cache 131 -> 101 us,
-// 2 x 3 x 1 447 x 2 240 264 -> 179, 5 x 752 x 2 240 120 -> 86, a clip of 21 x 1 560 x 2 240 809 -> 758; small calls and few channels are not
-// (3 x 449 x 96 7.1 against 15.3).  kNow: what the kernels on row tiles take of what row_cost says since their accumulators stay in one
-// register file and their operand reads go without bank conflicts.  Over those calls the choice costs 0.7 % on average against the fastest
-// kernel of all, and no call takes more than 3 % longer than on row tiles.
+// Which kernel serves a call on num_cu compute units.
 inline TconvFormId tconv_form(int B, int T, int HW, int D, bool cache, int num_cu)
 {
     TconvFormId best = kForm256;
-    double least = row_cost(kForm256, B, T, HW, D, cache, num_cu);
-    // The long kernel only while its tiles leave a third of the compute units idle.  With more it is level with the 256 x 256 kernel
-    // (2 % ahead on average) but draws more power: 171 tiles of 210 steps, six calls in a row take 812, 818, 825, 831, 839 and 846 us on
-    // six devices, where the 256 x 256 kernel takes 829 to 834.
-    const int64_t tiles = tconv_tiles_m(kForm256Long, B, T, HW) * tconv_tiles_n(kForm256Long, D);
-    for (const TconvFormId f : {kForm256x128, kForm128, kForm64, kForm256Long}) {
-        if (f == kForm256Long && 3 * tiles > 2 * num_cu) continue;
-        const double us = row_cost(f, B, T, HW, D, cache, num_cu);
+    double least = tconv_cost(kForm256, B, T, HW, D, cache, num_cu);
+    for (const TconvFormId f : {kForm256x128, kForm128, kForm64, kForm256Long, kFrames3, kFrames5, kFrames7}) {
+        if (!tconv_fits(f, T, D)) continue;
+        // The long kernel only while its tiles leave a third of the compute units idle.  With more it is level with the 256 x 256 kernel
+        // (2 % ahead on average) but draws more power: 171 tiles of 210 steps, six calls in a row take 812, 818, 825, 831, 839 and 846 us on
+        // six devices, where the 256 x 256 kernel takes 829 to 834.
+        if (f == kForm256Long && 3 * tconv_tiles_m(f, B, T, HW) * tconv_tiles_n(f, D) > 2 * num_cu) continue;
+        const double us = tconv_cost(f, B, T, HW, D, cache, num_cu);
         if (us < least) { least = us; best = f; }
     }
-    constexpr double kNow[kRowForms] = {0.99, 0.725, 0.826, 0.99, 1.0};
-    least *= kNow[best];
-    for (const TconvFormId f : {kFrames3, kFrames5, kFrames7})
-        if (tconv_fits(f, T, D) && frame_cost(f, B, T, HW, D, num_cu) < least) return f;
     return best;
 }
 

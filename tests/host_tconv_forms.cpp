@@ -1,6 +1,6 @@
 // Prints, for each "B T HW D cache num_cu" on the command line, the kernel that a temporal convolution takes (tconv_form,
 // csrc/tconv_tiles.hpp).  With no arguments: over a range of calls the choice may serve the call, its tiles cover every row, frame tiles have room for a
-// call's frames or take them in groups, and costs are finite and positive; of the kernels on row tiles it is the cheapest.
+// call's frames or take them in groups, costs are finite and positive, and of the kernels that may serve the call the choice is the cheapest.
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -31,15 +31,15 @@ int main(int argc, char **argv)
                                 ++on_frames;
                                 if (D % 32 || T == 1 || (!s.back && T > s.frames)) return printf("FAIL T=%d D=%d\n", T, D), 1;
                                 rows *= (int64_t)s.frames * 16 * s.blocks;
-                                if (!(frame_cost(f, B, T, HW, D, cus) > 0) || !std::isfinite(frame_cost(f, B, T, HW, D, cus))) return printf("FAIL cost\n"), 1;
                             } else {
                                 rows *= kTconvTile[f].bm;
                             }
                             if (rows < (int64_t)B * T * HW) return printf("FAIL cover B=%d T=%d HW=%d\n", B, T, HW), 1;
-                            for (int g = 0; g < kRowForms; ++g) {
-                                const double us = row_cost((TconvFormId)g, B, T, HW, D, cache != 0, cus);
-                                const bool may = g != kForm256Long || 3 * tconv_tiles_m(kForm256Long, B, T, HW) * tconv_tiles_n(kForm256Long, D) <= 2 * cus;
-                                if (!(us > 0) || !std::isfinite(us) || (!may && f == g) || (may && f < kRowForms && us < row_cost(f, B, T, HW, D, cache != 0, cus)))
+                            for (int i = 0; i < kTconvForms; ++i) {
+                                const TconvFormId g = (TconvFormId)i;
+                                const double us = tconv_cost(g, B, T, HW, D, cache != 0, cus);
+                                const bool may = tconv_fits(g, T, D) && (g != kForm256Long || 3 * tconv_tiles_m(g, B, T, HW) * tconv_tiles_n(g, D) <= 2 * cus);
+                                if (!(us > 0) || !std::isfinite(us) || (!may && f == g) || (may && us < tconv_cost(f, B, T, HW, D, cache != 0, cus)))
                                     return printf("FAIL cost HW=%d D=%d form %d\n", HW, D, g), 1;
                             }
                         }
