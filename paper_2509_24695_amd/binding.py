@@ -1,5 +1,6 @@
 """Binding of libsvlinattn.so: argument marshalling only, through ctypes and, for the calls that launch, through
-_sventry.so (csrc/py_entry.cpp), which takes 1.2 us per call for it where ctypes took 3.7 to 4.5.
+the module _sventry (csrc/py_entry.cpp), which takes 1.2 us per call for it where ctypes takes 3.7 to 4.5.  The module is built
+for one interpreter; another one that imports the package makes these calls through ctypes as well.
 
 The functions carry the names and argument order of the C ABI
 (include/sv_linattn.h, include/sv_tconv.h, include/sv_measure.h).  Device buffers are torch tensors (or raw integer
@@ -9,6 +10,8 @@ shared library is missing, loading raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from dataclasses import dataclass
 
@@ -28,7 +31,7 @@ EXPORTS = (
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libsvlinattn.so")
-_ENTRY_PATH = os.path.join(_PKG, "_sventry.so")
+_ENTRY_PATH = os.path.join(_PKG, "_sventry" + importlib.machinery.EXTENSION_SUFFIXES[0])
 _lib = None
 _entry = None
 
@@ -135,19 +138,55 @@ def load_library():
     lib.sv_status_string.restype = ctypes.c_char_p
     lib.sv_version.argtypes = []
     lib.sv_version.restype = ctypes.c_int
-    import importlib.util
+    _entry = _load_entry(lib)
+    _lib = lib
+    return lib
+
+
+def _load_entry(lib):
+    """What makes the launching calls: the module that was built for this interpreter, or, where there is none, ctypes."""
     if not os.path.exists(_ENTRY_PATH):
-        raise ImportError(f"{_ENTRY_PATH} is missing: build it with `python -m paper_2509_24695_amd.build`.")
+        return _CtypesCalls(lib)
     spec = importlib.util.spec_from_file_location("_sventry", _ENTRY_PATH)
     entry = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(entry)
     entry.attach(lib._handle)
-    _lib, _entry = lib, entry
-    return lib
+    return entry
+
+
+class _CtypesCalls:
+    """The launching calls with the arguments that _sventry takes, converted by what the C function declares."""
+
+    def __init__(self, lib):
+        self._functions = lib
+
+    def __getattr__(self, name):
+        fn = getattr(self._functions, name)
+        types, last = fn.argtypes, len(fn.argtypes) - 1
+        flag = 6 - (types[3] is ctypes.c_int32) if name.startswith("sv_linattn_state") else -1      # `accumulate`
+
+        def convert(args, i):
+            x, t = args[i], types[i]
+            if t is ctypes.c_void_p:
+                return _stream(x) if i == last else _ptr(x)
+            if t is ctypes.c_size_t:
+                return _nbytes(args[i - 1]) if x is None else int(x)
+            if t is ctypes.c_float:
+                return float(x)
+            if t is ctypes.c_int32:
+                return int(x) if i == flag else x
+            return ctypes.byref(x._c()) if x is not None else None       # a descriptor or the per-axis tables
+
+        def call(*args):
+            if len(args) != len(types):
+                raise TypeError(f"{name}: takes {len(types)} arguments")
+            return fn(*[convert(args, i) for i in range(len(args))])
+        setattr(self, name, call)
+        return call
 
 
 def _calls():
-    """The entry points of _sventry.so."""
+    """The launching calls (module or ctypes)."""
     if _entry is None:
         load_library()
     return _entry
@@ -206,7 +245,7 @@ def _check(status: int, where: str):
         raise SvError(status, where)
 
 
-# Each launching call below hands its arguments to the function of the same name in _sventry.so: buffers as tensors, integer
+# Each launching call below hands its arguments to the function of the same name in _sventry: buffers as tensors, integer
 # addresses or None; a workspace's size is the tensor's when none is given; streams as objects, integer handles or None.
 
 def sv_linattn_state(K, V, kv: TensorDesc, tok_begin: int, tok_end: int, accumulate: int, S, z,

@@ -1,9 +1,13 @@
-"""Builds libsvlinattn.so (HIP kernels + C ABI) for gfx950 with hipcc and _sventry.so (its Python calls) with g++, in-tree."""
+"""Builds libsvlinattn.so (HIP kernels + C ABI) for gfx950 with hipcc and the module of its Python calls with g++, in-tree."""
 from __future__ import annotations
 
+import glob
+import importlib.machinery
 import os
+import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
@@ -22,7 +26,8 @@ HIPCC_FLAGS = [
     # per-kernel register, scratch and LDS use as compiler remarks (parsed below)
     "-Rpass-analysis=kernel-resource-usage",
 ]
-ENTRY = os.path.join(PKG, "_sventry.so")               # host code only: the calls of binding.py that launch
+# host code only: the calls of binding.py that launch, for the interpreter that builds (its ABI is in the name)
+ENTRY = os.path.join(PKG, "_sventry" + importlib.machinery.EXTENSION_SUFFIXES[0])
 ENTRY_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-missing-field-initializers"]
 RESOURCES = os.path.join(PKG, "kernel_resources.txt")   # written by build(): one line per kernel
 
@@ -73,11 +78,18 @@ def check_resources(res: dict) -> None:
         raise RuntimeError("kernels that use scratch memory:\n  " + "\n  ".join(bad))
 
 
-def build_entry(verbose: bool = False) -> str:
-    """Compiles csrc/py_entry.cpp against this interpreter's headers."""
-    import sysconfig
-    cmd = [os.environ.get("CXX", "g++"), *ENTRY_FLAGS, "-I" + sysconfig.get_paths()["include"],
-           os.path.join(CSRC, "py_entry.cpp"), "-o", ENTRY + ".tmp", "-ldl"]
+def build_entry(verbose: bool = False) -> str | None:
+    """Compiles csrc/py_entry.cpp against this interpreter's headers.  Without a C++ compiler or without the headers there is no
+    module (None), and binding.py makes the same calls through ctypes.  Modules of earlier builds go either way: they are of
+    other sources."""
+    for old in glob.glob(os.path.join(os.path.dirname(ENTRY), "_sventry*.so")):
+        os.remove(old)
+    include = sysconfig.get_paths()["include"]
+    cxx = shutil.which(os.environ.get("CXX", "g++"))
+    if cxx is None or not os.path.exists(os.path.join(include, "Python.h")):
+        print(f"no {'Python.h in ' + include if cxx else 'C++ compiler'}: the Python calls will go through ctypes", flush=True)
+        return None
+    cmd = [cxx, *ENTRY_FLAGS, "-I" + include, os.path.join(CSRC, "py_entry.cpp"), "-o", ENTRY + ".tmp", "-ldl"]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
