@@ -149,6 +149,23 @@ inline bool quad_state_pays(int BH, int d, int n_tokens, bool full_table, bool f
     return (int64_t)BH * n_tokens <= 1000 * kThousands[d == 128][full_table ? 2 : factored_tables ? 1 : 0][C < 4 ? C - 1 : 3];
 }
 
+// Chunks per head of a call on the kernel of quadrants, 0: whole rows serve it.
+constexpr int kQuadMaxChunks = 16;                            // flags: [quadrant][chunk] in the head's 2 x kMaxChunks words
+constexpr int quad_wg_tokens(bool rotated) { return 8 * (rotated ? 16 : 32); }   // a round of a workgroup's waves
+inline int quad_state_chunks(int BH, int d, int n_tokens, bool full_table, bool factored_tables, int num_cu)
+{
+    if (!quad_state_pays(BH, d, n_tokens, full_table, factored_tables, num_cu)) return 0;
+    const int round = quad_wg_tokens(full_table || factored_tables), steps = (n_tokens + round - 1) / round, C = num_cu / (4 * BH);
+    const int most = steps < kQuadMaxChunks ? steps : kQuadMaxChunks;
+    return C < most ? C : most;
+}
+// Whole rows, C chunks per head: shared tiles instead of a state in every wave?
+inline bool coop_state_serves(const TokenLayout &t, int n_tokens, int C, bool full_table, bool factored_tables)
+{
+    return !full_table && (coop_state_pays(n_tokens, C) || pairs_heads(t, factored_tables, n_tokens));
+}
+constexpr int kWideWgTokens = 64;                             // of whole rows: tokens of a workgroup's step
+
 // fp32-arithmetic state: tokens up to which one workgroup sums a head in one launch, instead of several and a second launch for
 // their sum.  The lines lie where a host that enqueues layers (state, apply) back to back sees the two meet; one / several, us, two devices:
 //   d = 32 (sixteen waves), fp32, plain   2 heads, 1 024 tokens 1.2 less, 1 152 0.5 less, 1 280 0.1 more; 16 heads, 768 1.1 less, 896 0.7 less, 1 024 0.6

@@ -20,7 +20,6 @@ constexpr int kQuadWaves = 8;                        // per workgroup, two to a 
 constexpr int kQuadWords = 64 * 64 / 4;              // 16-byte words of a quadrant: four rows of one column
 constexpr int kQuadZWords = 64 / 4;                  // ... and of its key sums
 constexpr int kQuadElems = 4 * (kQuadWords + kQuadZWords);   // floats of a partial in the workspace
-constexpr int kQuadMaxChunks = 16;                   // flags: [quadrant][chunk] in the head's 2 x kMaxChunks words
 static_assert(4 * kQuadMaxChunks <= 2 * kMaxChunks, "a flag per quadrant and chunk");
 static_assert(4 * kQuadMaxChunks * kQuadElems <= kMaxChunks * (112 * 112 + 112), "the partials fit where whole states do");
 

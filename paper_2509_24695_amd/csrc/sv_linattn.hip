@@ -110,7 +110,7 @@ template <int ROPE, bool SHARED> struct Kernels<64, ROPE, SHARED> {
 template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     static constexpr int W = 1, kShared = SHARED, kRope = ROPE;
     static constexpr int kTab = ROPE == kRope3D ? kRope3dLdsBytes : 0;
-    static constexpr bool kWideState = true, kHasCoop = ROPE != kRopeTable;
+    static constexpr bool kWideState = true, kHasCoop = ROPE != kRopeTable;      // as coop_state_serves has it
     template <bool FINALIZE> static constexpr auto pick_state() {
         return &state_mfma_wide<(ROPE != kRopeNone ? kWideStateDepthRope : kWideStateDepth), FINALIZE, ROPE, !SHARED>;
     }
@@ -124,7 +124,8 @@ template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     static constexpr int state_lds = kWideLdsBytes;
     static constexpr int apply_lds = coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
     static constexpr int apply_pair_lds = 2 * coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
-    static constexpr int state_wg_tokens = 4 * kWideTile;
+    static constexpr int state_wg_tokens = kWideWgTokens;
+    static_assert(state_wg_tokens == 4 * kWideTile, "four waves, a tile each");
     static constexpr int apply_wg_tokens = 8 * kCoopApplyWaves * kCoopApplyNB;   // the waves of a workgroup share its tiles
     static constexpr int apply_threads = 64 * kCoopApplyWaves;
     // workgroups per compute unit: with one 128 x 32 panel per wave (136-164 registers, 17-50 KB of LDS) three are
@@ -424,14 +425,12 @@ TokenLayout layout_of(const Shape &s) { return TokenLayout{s.BH, s.H, s.d, s.ele
 bool launch_state_quad(const uint16_t *k, const uint16_t *v, const Rope &rope, const Shape &s, int t0, int t1, const float *S_in,
                        const float *z_in, float *S_out, float *z_out, void *ws, const Device &dev, hipStream_t stream)
 {
-    if (!quad_state_pays(s.BH, s.d, t1 - t0, rope.mode == kRopeTable, rope.mode == kRope3D, dev.num_cu)) return false;
+    const int C = quad_state_chunks(s.BH, s.d, t1 - t0, rope.mode == kRopeTable, rope.mode == kRope3D, dev.num_cu);
+    if (C == 0) return false;
     bool launched = false;
     auto launch = [&](auto kn) {
         using KN = decltype(kn);
-        int C = dev.num_cu / (4 * s.BH);
-        const int steps = (t1 - t0 + KN::wg_tokens - 1) / KN::wg_tokens;
-        C = C > kQuadMaxChunks ? kQuadMaxChunks : C;
-        C = C > steps ? steps : C;
+        static_assert(KN::wg_tokens == quad_wg_tokens(KN::ROPE != kRopeNone), "quad_state_chunks counts on it");
         const int grid = quad_grid(C, s.BH, kDies);
         if (C > 1 && grid > dev.quad_resident_wgs[rope.mode]) return;     // its workgroups wait for each other
         KN::state<<<grid, KN::threads, KN::lds, stream>>>(k, v, rope.arg, s.st, s.H, s.BH, s.d, t0, t1, C, S_in, z_in, S_out, z_out, ws,
@@ -460,7 +459,7 @@ void launch_state_mfma(const uint16_t *k, const uint16_t *v, const Rope &rope, c
         auto partial = KN::state_partial;
         int resident = dev.state_resident_wgs[KN::W][KN::kRope][KN::kShared], threads = 64 * kStateWaves, lds = KN::state_lds;
         if constexpr (KN::kHasCoop)
-            if (coop_state_pays(t1 - t0, C) || pairs_heads(layout_of(s), rope.mode != kRopeNone, t1 - t0)) {
+            if (coop_state_serves(layout_of(s), t1 - t0, C, rope.mode == kRopeTable, rope.mode == kRope3D)) {
                 finalize = KN::template coop_state<true>;
                 partial = KN::template coop_state<false>;
                 resident = dev.coop_resident_wgs[rope.mode][KN::kShared];

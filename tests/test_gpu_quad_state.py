@@ -1,6 +1,7 @@
 """GPU parity of the quadrant state kernel (bf16, d = 112 and 128, short ranges): one chunk to sixteen per head, the edges of its
 tiles (16 and 32 tokens, 128 and 256 per round of a workgroup), token sub-ranges, both layouts, an update in place; the next
-sizes on the kernel of whole rows; and a wait that runs out leaves S and z alone."""
+sizes on the kernels of whole rows; and a wait that runs out leaves S and z alone.  test_host_state_kernels.py asserts that each
+row takes the kernels it names."""
 import numpy as np
 import pytest
 
@@ -10,22 +11,25 @@ from oracle import linattn_oracle as orc
 from sv_workloads import metrics
 from tests.gpu_util import new_state, new_workspace, say, to_dev, to_host
 
-pytestmark = pytest.mark.gpu
+ROPES = ("none", "table", "axes")
+QUAD = ("quad",) * 3
+ROWS = [                                   # d, B, H, grid, tokens cut off at both ends, layout; the kernels without rotation, with a table, with axes
+    (112, 1, 2, (1, 1, 1), 0, "bhnd", QUAD), (128, 1, 1, (1, 3, 5), 0, "bhnd", QUAD), (112, 1, 3, (1, 16, 16), 0, "bhnd", QUAD),
+    (112, 2, 1, (1, 1, 257), 0, "bhnd", QUAD), (128, 1, 2, (3, 41, 37), 7, "bhnd", QUAD), (112, 1, 2, (3, 41, 37), 3, "bhnd", QUAD),
+    (112, 1, 5, (2, 25, 31), 1, "bnhd", ("coop", "quad", "quad")), (112, 1, 8, (2, 25, 31), 1, "bnhd", QUAD), (112, 2, 8, (1, 30, 33), 0, "bnhd", QUAD),
+    (128, 2, 10, (1, 29, 31), 0, "bnhd", QUAD), (112, 1, 32, (1, 25, 31), 2, "bhnd", QUAD), (128, 2, 32, (1, 17, 31), 0, "bhnd", QUAD),
+    (112, 2, 32, (1, 9, 31), 0, "bnhd", QUAD), (112, 1, 40, (1, 9, 31), 0, "bhnd", ("coop", "rows", "coop")),
+    (128, 1, 65, (1, 9, 31), 0, "bhnd", ("coop", "rows", "coop"))]
 
 
-@pytest.mark.parametrize("rope", ["none", "table", "axes"])
-@pytest.mark.parametrize("d,B,H,grid,cut,layout", [
-    (112, 1, 2, (1, 1, 1), 0, "bhnd"), (128, 1, 1, (1, 3, 5), 0, "bhnd"), (112, 1, 3, (1, 16, 16), 0, "bhnd"), (112, 2, 1, (1, 1, 257), 0, "bhnd"),
-    (128, 1, 2, (3, 41, 37), 7, "bhnd"), (112, 1, 5, (2, 25, 31), 1, "bnhd"), (112, 2, 8, (1, 30, 33), 0, "bnhd"), (128, 2, 10, (1, 29, 31), 0, "bnhd"),
-    (112, 1, 32, (1, 25, 31), 2, "bhnd"), (128, 2, 32, (1, 17, 31), 0, "bhnd"), (112, 2, 32, (1, 9, 31), 0, "bnhd"),
-    (112, 1, 40, (1, 9, 31), 0, "bhnd"), (128, 1, 65, (1, 9, 31), 0, "bhnd")])
-def test_quadrants(d, B, H, grid, cut, layout, rope):
+def check_state(name, d, B, H, grid, cut, layout, rope, seeds):
+    """State of tokens [cut, N - cut) in place of, and added to, a carried one, against the oracle."""
     import torch
     N = grid[0] * grid[1] * grid[2]
     t0, t1 = cut, N - cut
-    say(f"quad_state d={d} B={B} H={H} grid={grid} [{t0},{t1}) {layout} {rope}")
-    _, K, V = wl.draw_tensors(9600 + N + d, (B, H, N, d), 0.5, "bf16")
-    rng = np.random.Generator(np.random.PCG64(78))
+    say(f"{name} d={d} B={B} H={H} grid={grid} [{t0},{t1}) {layout} {rope}")
+    _, K, V = wl.draw_tensors(seeds[0] + N + d, (B, H, N, d), 0.5, "bf16")
+    rng = np.random.Generator(np.random.PCG64(seeds[1]))
     S0 = rng.standard_normal((B, H, d, d), dtype=np.float32)
     z0 = np.abs(rng.standard_normal((B, H, d), dtype=np.float32))
     cs = wl.rope_tables_3d_factored(*grid, d)
@@ -51,11 +55,10 @@ def test_quadrants(d, B, H, grid, cut, layout, rope):
     assert metrics.rel_l2(to_host(S), S_ref) <= tol and metrics.rel_l2(to_host(z), z_ref) <= 1e-5
 
 
-def test_wait_that_runs_out_stores_nothing():
+def check_wait_that_runs_out(name, d, B, H, N, seed):
     import torch
-    B, H, N, d = 1, 20, 900, 112
-    say("quad_state wait limit 0")
-    _, K, V = wl.draw_tensors(9700, (B, H, N, d), 0.5, "bf16")
+    say(f"{name} wait limit 0")
+    _, K, V = wl.draw_tensors(seed, (B, H, N, d), 0.5, "bf16")
     Kd, Vd = to_dev(K), to_dev(V)
     S, z = new_state(B, H, d)
     S.fill_(3.0)
@@ -69,3 +72,18 @@ def test_wait_that_runs_out_stores_nothing():
         sv.sv_linattn_set_wait_limit(-1)
     assert sv.sv_linattn_workspace_status(ws, B, H, d) == 1
     assert bool((S == 3.0).all()) and bool((z == 4.0).all())
+
+
+WAIT = (112, 1, 20, 900)                   # d, B, H, tokens: quad
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rope", ROPES)
+@pytest.mark.parametrize("d,B,H,grid,cut,layout,kernels", ROWS)
+def test_quadrants(d, B, H, grid, cut, layout, kernels, rope):
+    check_state("quad_state", d, B, H, grid, cut, layout, rope, (9600, 78))
+
+
+@pytest.mark.gpu
+def test_wait_that_runs_out_stores_nothing():
+    check_wait_that_runs_out("quad_state", *WAIT, 9700)
