@@ -60,15 +60,6 @@ __device__ __forceinline__ uint32_t rope_rotate_pair(uint32_t w, float c, float 
     const float a = bf16_lo(w), b = bf16_hi(w);
     return pack_bf16x2(a * c - b * s, a * s + b * c);
 }
-// Four pairs (16 bytes of a token row) with their four (cos, sin) entries.
-__device__ __forceinline__ u32x4 rope_rotate_bf16x8(u32x4 w, f32x4 cs01, f32x4 cs23) {
-    u32x4 r;
-    r.x = rope_rotate_pair(w.x, cs01.x, cs01.y);
-    r.y = rope_rotate_pair(w.y, cs01.z, cs01.w);
-    r.z = rope_rotate_pair(w.z, cs23.x, cs23.y);
-    r.w = rope_rotate_pair(w.w, cs23.z, cs23.w);
-    return r;
-}
 // ---- range-checked streaming access ------------------------------------------------------------
 //
 // Token tiles are addressed through buffer resources: the hardware compares each

@@ -112,7 +112,6 @@ struct Rotator<kRopeNone, STEPS, DEPTH> {
     __device__ __forceinline__ Rotator(const RopeArg &, int, int, int, int, int, int, const unsigned char *) {}
     __device__ __forceinline__ void request(int, bool, int) {}
     template <int TILE> __device__ __forceinline__ void begin_tile(const TileWalk &, int) {}
-    __device__ __forceinline__ u32x4 rotate(int, int, u32x4 w) const { return w; }
     __device__ __forceinline__ void fetch(int, int, f32x2 (&)[4]) const {}
     __device__ __forceinline__ u32x4 rotate_with(u32x4 w, const f32x2 (&)[4]) const { return w; }
 };
@@ -143,10 +142,6 @@ struct Rotator<kRopeTable, STEPS, DEPTH> {
         }
     }
     template <int TILE> __device__ __forceinline__ void begin_tile(const TileWalk &, int) {}
-    __device__ __forceinline__ u32x4 rotate(int s, int j, u32x4 w) const
-    {
-        return rope_rotate_bf16x8(w, cs[s][j][0], cs[s][j][1]);
-    }
     __device__ __forceinline__ void fetch(int s, int j, f32x2 (&e)[4]) const
     {
         e[0] = f32x2{cs[s][j][0].x, cs[s][j][0].y};
@@ -265,12 +260,6 @@ struct Rotator<kRope3D, STEPS, DEPTH> {
         return u32x4{rope_rotate_pair(w.x, e[0].x, e[0].y), rope_rotate_pair(w.y, e[1].x, e[1].y),
                      rope_rotate_pair(w.z, e[2].x, e[2].y), rope_rotate_pair(w.w, e[3].x, e[3].y)};
     }
-    __device__ __forceinline__ u32x4 rotate(int s, int j, u32x4 w) const
-    {
-        f32x2 e[4];
-        fetch(s, j, e);
-        return rotate_with(w, e);
-    }
 };
 
 template <int STEPS, int DEPTH>
@@ -286,12 +275,6 @@ struct Rotator<kRope3DWhole, STEPS, DEPTH> : Rotator<kRope3D, STEPS, DEPTH> {
         e[1] = f32x2{a.z, a.w};
         e[2] = f32x2{b.x, b.y};
         e[3] = f32x2{b.z, b.w};
-    }
-    __device__ __forceinline__ u32x4 rotate(int s, int j, u32x4 w) const
-    {
-        f32x2 e[4];
-        fetch(s, j, e);
-        return this->rotate_with(w, e);
     }
 };
 
