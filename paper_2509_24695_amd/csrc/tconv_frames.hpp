@@ -163,6 +163,7 @@ __global__ __launch_bounds__(kThreads) void tconv_frames(TconvArgs a)
         substep(k, std::integral_constant<int, 3>{});
         substep(k, std::integral_constant<int, 4>{});
         substep(k, std::integral_constant<int, 5>{});
+        tc_mfma_settle();
     }
 
     tc_mfma_done(acc);

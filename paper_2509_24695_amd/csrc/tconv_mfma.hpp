@@ -93,11 +93,15 @@ __device__ __forceinline__ void tc_load_to_lds(const uint16_t *src, unsigned cha
 // register file to the compiler, which then moved accumulators to the other file and back in every pass of the loop (256 x 128:
 // 192 moves for 64 MFMAs; tconv_frames: 150 for 240).  What the compiler does not see to in return: operands come from LDS
 // reads only (their waits it does insert), an accumulator is used again no sooner than four MFMAs later, and
-// tc_mfma_done() stands before the first other use.
+// tc_mfma_done() stands before the first other use.  What register allocation adds at a loop's end, copies of accumulators, comes before
+// tc_mfma_done(): a loop whose last instructions are products ends with tc_mfma_settle().  test_host_mfma_hazards.py reads the generated code for
+// all of this.
 __device__ __forceinline__ void tc_mfma(f32x4 &acc, bf16x8 a, bf16x8 b)
 {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
+// Eight wait states, what a 16 x 16 x 32 product needs before anything but a product of the same accumulator reads what it wrote.
+__device__ __forceinline__ void tc_mfma_settle() { asm volatile("s_nop 7" ::: "memory"); }
 template <int M, int N> __device__ __forceinline__ void tc_mfma_done(f32x4 (&acc)[M][N])
 {
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
