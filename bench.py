@@ -452,8 +452,9 @@ def bench_tconv(w, iters, sv, torch):
 
     full_us, few_us = stream_us(tiles), stream_us(8)
 
-    # The tile kernel with parts of its loop left out (sv_measure_tconv_variant), on the stream's first block:
-    # what the loads into LDS and the operand reads from LDS cost on top of the matrix-core instructions.
+    # The 256 x 256 kernel on row tiles with parts of its loop left out (sv_measure_tconv_variant), on the stream's first block:
+    # what the loads into LDS and the operand reads from LDS cost on top of the matrix-core instructions.  The calls timed
+    # above run on tiles of frames x positions; this is the kernel of large calls whose channels do not allow them.
     def variant_us(variant):
         for _ in range(2):
             sv.sv_measure_tconv_variant(variant, xs[0], W, None, ys[0], w.B, w.T, w.HW, w.D, stream=stream)
@@ -472,7 +473,7 @@ def bench_tconv(w, iters, sv, torch):
     wg_flops = k_steps * 4 * 64 * 2 * 16 * 16 * 32
     return {"workload": f"{w.name}: B={w.B} T={w.T} HW={w.HW} D={w.D}, {w.n_blocks} block(s)", "us_per_block": us,
             "tokens_per_s": w.tokens / (us * 1e-6), "dtype": "bf16",
-            "roofline": {"bound": "mfma", "kernel": "tconv_mfma", "achieved": tflops, "peak": MFMA_BF16_PEAK_TFLOPS,
+            "roofline": {"bound": "mfma", "kernel": "tconv_frames" if w.D % 32 == 0 and w.T > 1 else "tconv_mfma", "achieved": tflops, "peak": MFMA_BF16_PEAK_TFLOPS,
                          "unit": "TFLOP/s", "frac": tflops / MFMA_BF16_PEAK_TFLOPS,
                          "algorithmic_flops_per_launch": w.algorithmic_flops},
             "mfma_stream": {"what": "the tile loop's MFMAs alone, operands in registers, no LDS or memory traffic "

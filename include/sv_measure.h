@@ -62,8 +62,8 @@ sv_status sv_measure_apply_variant(int32_t variant, const void *Q, const sv_tens
                                    int32_t tok_begin, int32_t tok_end,
                                    const float *S, const float *z, float eps, void *O, void *stream);
 
-/* The kernel with tiles of 256 x 256, which is what sv_tconv_block_step (sv_tconv.h) takes for the largest calls, with parts of its
- * loop left out, to time what each part costs (no passage of the paper).  Same arguments without cache_out and dtype, same
+/* The kernel with tiles of 256 token rows x 256 channels, which is what sv_tconv_block_step (sv_tconv.h) takes for large calls that tiles of frames x
+ * positions do not serve better, with parts of its loop left out, to time what each part costs (no passage of the paper).  Same arguments without cache_out and dtype, same
  * checks, bf16 only; all variants run this kernel on the same grid, whatever the call's size:
  *   variant 0  the kernel as it is (its results are those of sv_tconv_block_step);
  *   variant 1  without the loads from memory into LDS inside the tile loop (the prologue's stay);
