@@ -32,7 +32,7 @@ def _rms(a, ref):
 
 @pytest.mark.parametrize("d,BH,N", [(32, 2, 1024), (32, 20, 384), (32, 2, 1153), (32, 33, 769), (64, 2, 256), (64, 33, 193), (64, 2, 2000),
                                     (64, 160, 384), (112, 8, 384),
-                                    (112, 160, 384), (128, 32, 1024)])
+                                    (112, 160, 384), (128, 32, 1024), (112, 64, 128), (128, 128, 128)])
 def test_sums_are_as_exact_as_short_chunks(d, BH, N):
     import torch
     say(f"f32_error d={d} BH={BH} N={N}")
