@@ -128,23 +128,24 @@ inline bool coop_state_pays(int n_tokens, int C) { return n_tokens <= 2048 * C; 
 // longer than their tokens.  Both read in step with the number of head-tokens, the quadrants slower, and what the quadrants save depends on how
 // many chunks C a head has: all of the exchange with one, little with two, whose quadrants fetch as many partials as twice as many workgroups
 // of whole rows.  The lines, in thousands of head-tokens, are where layers (state, apply) on one kernel and on the other meet; quadrants over rows:
-//   d = 112, plain      C = 1: 64 heads 0.93 to 61, 0.96 at 76, 48 heads 1.00 at 69; C = 2: 26 to 32 heads 0.98 to 1.02 at 24, 1.05 at 40; C = 3:
-//                       0.96 at 24, 0.98 to 1.02 from 40 to 50, 1.05 at 60; C = 4 to 10: 0.95 to 0.99 at 60, 0.99 to 1.02 at 70; 4 and 5 heads: 1.01
-//                       to 1.08 from 40 on; 2 heads: 0.93 to 0.98
-//   d = 112, factored   C = 1: 0.94 to 1.01 at 70; C = 2: 0.97 to 1.00 at 25, 0.98 to 1.02 at 40, 1.01 to 1.06 from 59 on; C = 3: 0.98 to 0.99 at 50,
-//                       0.98 to 1.03 at 60; from 4 on: 0.96 to 1.00 at 70, 0.94 to 1.01 at 79
+//   d = 112, plain      C = 1: 64 heads 0.93 to 61, 0.96 at 76, 48 heads 1.00 at 69; C = 2: 1.00 at 20, 1.02 at 30, 1.05 at 40; C = 3: 0.97 at 20, 0.99
+//                       at 30, 1.00 to 1.01 from 40 to 60, 1.03 at 70; C = 4 to 10: 0.95 to 0.99 at 60, 0.99 to 1.02 at 70; 4 and 5 heads: 1.01 to 1.08
+//                       from 40 on; 2 heads: 0.93 to 0.98
+//   d = 112, factored   C = 1: 0.94 to 1.01 at 70; C = 2: 0.98 at 20, 0.99 at 30, 1.00 at 40, 1.03 at 60; C = 3: 0.98 at 50, 1.00 at 60 and 70, 1.02 at 80;
+//                       from 4 on: 0.96 to 1.00 at 70, 0.94 to 1.01 at 79
 //   d = 112, full table 24 heads 0.99, others 0.86 to 0.96 at 40
 //   d = 128, plain      0.91 to 1.00 at 100
-//   d = 128, factored   C = 1: 0.95 to 1.01 at 99; C = 2: 0.98 to 1.02 at 69, up to 1.07 at 89; C = 3: 0.95 to 1.01 at 79, up to 1.04 at 99; from 4
-//                       on: 0.93 to 0.99 at 99
+//   d = 128, factored   C = 1: 0.95 to 1.01 at 99; C = 2: 0.99 at 70, 1.00 at 80, 1.01 at 90 (24 heads 1.03); C = 3: 0.99 at 80 to 100; from 4 on: 0.93 to
+//                       0.99 at 99
 //   d = 128, full table 0.84 to 0.97 at 68
+// (C = 2 and 3: averages over 17 to 32 heads and both layouts, four devices, single calls up to 4 % to either side.)
 // Four workgroups per chunk have to fill most of the device (40 heads of 112, 1 560 tokens, 160 workgroups: 15.5 / 13.5 us).
 inline bool quad_state_pays(int BH, int d, int n_tokens, bool full_table, bool factored_tables, int num_cu)
 {
     const int C = num_cu / (4 * BH);
     if (16 * BH * C < 3 * num_cu) return false;
-    constexpr int kThousands[2][3][4] = {{{76, 26, 52, 70}, {76, 32, 56, 76}, {40, 40, 40, 40}},            // d = 112: plain, factored, full table
-                                         {{100, 100, 100, 100}, {100, 68, 78, 100}, {66, 66, 66, 66}}};     // d = 128
+    constexpr int kThousands[2][3][4] = {{{76, 22, 60, 70}, {76, 38, 70, 76}, {40, 40, 40, 40}},            // d = 112: plain, factored, full table
+                                         {{100, 100, 100, 100}, {100, 80, 100, 100}, {66, 66, 66, 66}}};    // d = 128
     if (d == 112 && !full_table && !factored_tables && C > 10 && BH >= 4) return false;
     return (int64_t)BH * n_tokens <= 1000 * kThousands[d == 128][full_table ? 2 : factored_tables ? 1 : 0][C < 4 ? C - 1 : 3];
 }

@@ -44,7 +44,7 @@ int main()
         {112, 0, 18, 3360, 105}, {112, 0, 12, 4680, 95}, {112, 0, 8, 6840, 97}, {112, 0, 5, 12840, 104}, {112, 0, 4, 9960, 108}, {112, 0, 2, 32040, 94},
         {112, 2, 64, 960, 94}, {112, 2, 24, 2520, 104}, {112, 2, 32, 2640, 105}, {112, 2, 26, 2640, 105}, {112, 2, 20, 2040, 97}, {112, 2, 16, 2520, 95},
         {112, 2, 8, 8760, 97}, {112, 1, 20, 1560, 94}, {112, 1, 24, 2640, 105}, {112, 1, 64, 600, 87}, {128, 0, 24, 2880, 95}, {128, 0, 20, 4560, 96},
-        {128, 0, 64, 1440, 91}, {128, 2, 24, 3720, 107}, {128, 2, 18, 5520, 104}, {128, 2, 16, 4320, 96}, {128, 2, 64, 1440, 95}, {128, 1, 20, 3240, 94}};
+        {128, 0, 64, 1440, 91}, {128, 2, 24, 3720, 107}, {128, 2, 21, 3840, 95}, {112, 0, 30, 1320, 105}, {112, 0, 19, 1200, 95}, {112, 2, 28, 840, 98}, {112, 2, 19, 2160, 97}, {128, 2, 16, 4320, 96}, {128, 2, 64, 1440, 95}, {128, 1, 20, 3240, 94}};
     for (const Layer &l : layers) {
         if (sv::quad_state_pays(l.BH, l.d, l.n, l.mode == 1, l.mode == 2, 256) != (l.percent < 100)) return printf("FAIL line d=%d mode=%d BH=%d n=%d\n", l.d, l.mode, l.BH, l.n), 1;
         ++cases;

@@ -17,7 +17,7 @@ ROWS = [                                   # d, B, H, grid, tokens cut off at bo
     (112, 1, 2, (1, 1, 1), 0, "bhnd", QUAD), (128, 1, 1, (1, 3, 5), 0, "bhnd", QUAD), (112, 1, 3, (1, 16, 16), 0, "bhnd", QUAD),
     (112, 2, 1, (1, 1, 257), 0, "bhnd", QUAD), (128, 1, 2, (3, 41, 37), 7, "bhnd", QUAD), (112, 1, 2, (3, 41, 37), 3, "bhnd", QUAD),
     (112, 1, 5, (2, 25, 31), 1, "bnhd", ("coop", "quad", "quad")), (112, 1, 8, (2, 25, 31), 1, "bnhd", QUAD), (112, 2, 8, (1, 30, 33), 0, "bnhd", QUAD),
-    (128, 2, 10, (1, 29, 31), 0, "bnhd", QUAD), (112, 1, 32, (1, 25, 31), 2, "bhnd", QUAD), (128, 2, 32, (1, 17, 31), 0, "bhnd", QUAD),
+    (128, 2, 10, (1, 29, 31), 0, "bnhd", QUAD), (112, 1, 32, (1, 25, 31), 2, "bhnd", ("coop", "quad", "quad")), (112, 1, 32, (1, 20, 31), 2, "bhnd", QUAD), (128, 2, 32, (1, 17, 31), 0, "bhnd", QUAD),
     (112, 2, 32, (1, 9, 31), 0, "bnhd", QUAD), (112, 1, 40, (1, 9, 31), 0, "bhnd", ("coop", "rows", "coop")),
     (128, 1, 65, (1, 9, 31), 0, "bhnd", ("coop", "rows", "coop"))]
 
