@@ -178,8 +178,9 @@ constexpr int kWideWgTokens = 64;                             // of whole rows: 
 // 32 heads, 1 152 tokens are 3 to 5 us slower there on one workgroup; d = 64 at 160.
 // Both forms of the rotation have the same lines, so that they give the same bits.
 // d = 112 and 128 end where each of a wave's running sums has had one tile: a longer one is further from the exact sum than those of
-// several workgroups (64 heads of 112, 128 tokens: S by 11 to 26 %), although with 128 heads it would be the faster one up to 128 tokens
-// (31.1 / 36.1 us).
+// several workgroups (64 heads of 112, 128 tokens: S 9.4e-8 against 7.3e-8), although with many heads it would be the faster one up to 128 tokens
+// (8 heads, 64 tokens 16.0 / 16.7 us, 128 heads, 64 tokens 24 / 32, 128 tokens 31 / 36).  Adding the sums to a total after every round of tiles
+// would keep them short, but neither in registers nor in LDS does the compiler get by without spilling.
 constexpr int kF32WideTile = 16, kF32WideSums = 3;    // of a wave at d = 112 and 128: tokens per tile, running sums (taken in turn by the tiles)
 inline int f32_sole_tokens(int d, int BH, int elem_bytes, bool rotated)
 {
