@@ -104,6 +104,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void block_step_mfma(
         StateStream<TILE, DEPTH_S, ROPE> kvstream(K + head_off, V + head_off, rope, lds_tab, st.n, N, lane, walk);
         unsigned char *tileK = lds + wave * 2 * kTileBytes;
         state_prefetch(kvstream);
+        kvstream.rot.template begin_tile<TILE>(walk, 0);
         if (is_rope3d(ROPE)) {
             rope3d_lds_fill_end(lds + block_step_lds_bytes<TILE, WAVES, ROPE>(), rope.r3, tabs);
             wg_barrier();

@@ -205,8 +205,9 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
 // same time.  Apply, 40 heads of 112, 32 760 tokens: 149 -> 119 us (586 MB, 4.9 TB/s), factored tables 176 -> 150, full table 175 -> 168.
 // One head to a workgroup (odd H, see pairs_heads): the slower sums by shuffles, whose pace keeps the heads more in step
 // (state and apply 271 us, with row permutations 288 to 302; factored tables 293 and 306).
+// Three workgroups to a compute unit leave a wave 168 registers; with factored tables the compiler takes 177 if it may.
 template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB, bool NT, int HEADS>
-__global__ __launch_bounds__(64 * WAVES * HEADS, NB == 1 ? 2 : 1) void apply_mfma_d128(
+__global__ __launch_bounds__(64 * WAVES * HEADS, NB != 1 ? 1 : ROPE == kRope3D && HEADS == 1 ? 3 : 2) void apply_mfma_d128(
     const uint16_t *__restrict__ Q, uint16_t *__restrict__ O, RopeArg rope, TokStrides st, int H,
     int d, int t0, int t1, int C, const float *__restrict__ S, const float *__restrict__ z, float eps, int order)
 {

@@ -156,47 +156,29 @@ struct Rotator<kRopeTable, STEPS, DEPTH> {
     }
 };
 
-template <int STEPS, int DEPTH>
-struct Rotator<kRope3D, STEPS, DEPTH> {
-    const unsigned char *tab;          // the three tables in LDS
-    uint32_t base[4], mul_f[4], mul_r[4], mul_c[4];   // entry address of pair q = base + f*mul_f + r*mul_r + c*mul_c
-    int rows, cols, rc, frames_m1, row0, rows_per_step;
+// Where a lane's STEPS rows of the tile in work are on the three axes.  BYTES: positions are byte offsets into the axes' tables, one position
+// n pairs * 8 bytes from the next (8 where the axis has no pairs: its offsets are not used); otherwise frame, row and column themselves.
+template <int STEPS, bool BYTES>
+struct Rope3dPositions {
+    int rows, cols, rc, row0, rows_per_step;
+    int bytes_t, bytes_h, bytes_w;     // wave-uniform: bytes from one position to the next
+    int last_t, end_h, end_w;          // the last frame; past the last row, column
     float inv_rows, inv_cols;
-    int sf, sr, sc;                    // wave-uniform: one stride of the walk as (frames, rows, columns)
-    int f[STEPS], r[STEPS], c[STEPS];  // position of the lane's rows of the tile in work
+    int st, sh, sw;                    // wave-uniform: one stride of the walk as (frames, rows, columns)
+    int t[STEPS], h[STEPS], w[STEPS];
 
-    __device__ __forceinline__ Rotator(const RopeArg &a, int /*t1*/, int d, int row0_, int rows_per_step_, int pair0,
-                                       int /*lane_valid*/, const unsigned char *lds_tab)
-        : tab(lds_tab), rows(a.r3.rows), cols(a.r3.cols), rc(a.r3.rows * a.r3.cols), frames_m1(a.r3.frames - 1),
-          row0(row0_), rows_per_step(rows_per_step_), inv_rows(1.0f / (float)a.r3.rows),
-          inv_cols(1.0f / (float)a.r3.cols), sf(0), sr(0), sc(0)
-    {
-        const Rope3D &R = a.r3;
-        const uint32_t off_h = (uint32_t)(R.frames * R.n_t) * 8u, off_w = off_h + (uint32_t)(R.rows * R.n_h) * 8u;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int p = pair0 + q;
-            p = p < d / 2 ? p : d / 2 - 1;        // lanes past d (their features are zero) look at a valid entry
-            mul_f[q] = mul_r[q] = mul_c[q] = 0u;
-            if (p < R.n_t) {
-                base[q] = (uint32_t)p * 8u;
-                mul_f[q] = (uint32_t)R.n_t * 8u;
-            } else if (p < R.n_t + R.n_h) {
-                base[q] = off_h + (uint32_t)(p - R.n_t) * 8u;
-                mul_r[q] = (uint32_t)R.n_h * 8u;
-            } else {
-                base[q] = off_w + (uint32_t)(p - R.n_t - R.n_h) * 8u;
-                mul_c[q] = (uint32_t)R.n_w * 8u;
-            }
-        }
-    }
-
-    __device__ __forceinline__ void request(int, bool, int) {}
+    __device__ __forceinline__ Rope3dPositions(const Rope3D &R, int row0_, int rows_per_step_)
+        : rows(R.rows), cols(R.cols), rc(R.rows * R.cols), row0(row0_), rows_per_step(rows_per_step_), bytes_t(8 * (R.n_t ? R.n_t : 1)),
+          bytes_h(8 * (R.n_h ? R.n_h : 1)), bytes_w(8 * (R.n_w ? R.n_w : 1)), last_t((R.frames - 1) * step_t()), end_h(R.rows * step_h()),
+          end_w(R.cols * step_w()), inv_rows(1.0f / (float)R.rows), inv_cols(1.0f / (float)R.cols), st(0), sh(0), sw(0) {}
+    __device__ __forceinline__ int step_t() const { return BYTES ? bytes_t : 1; }
+    __device__ __forceinline__ int step_h() const { return BYTES ? bytes_h : 1; }
+    __device__ __forceinline__ int step_w() const { return BYTES ? bytes_w : 1; }
 
     // Positions of the lane's rows of the i-th tile of the walk; call for i = 0, 1, 2, ... in turn.
     // A walk visits tiles a constant stride apart except where its cyclic order wraps around, so
     // normally every row is the same row of the previous tile plus the stride's (frames, rows,
-    // columns), with two carries: ten integer instructions per row and one scalar comparison.
+    // columns), with two carries: a dozen integer instructions per row and one scalar comparison.
     // Integer divisions (long instruction sequences on this hardware) are left to the first tile
     // and the wrap; there the rows inside the tile are reached from the tile's own position
     // with small carries done in floating point: (x + 0.5) / n is at least 0.5 / n away from
@@ -204,17 +186,16 @@ struct Rotator<kRope3D, STEPS, DEPTH> {
     // reciprocal is the exact quotient.  A frame index is capped at the last frame: that
     // happens to rows past the last token only (they hold zeros, any entry will do), and a
     // row past the end stays past the end until the walk wraps.
-    template <int TILE> __device__ __forceinline__ void begin_tile(const TileWalk &w, int i)
+    template <int TILE> __device__ __forceinline__ void begin_tile(const TileWalk &walk, int i)
     {
-        if (i == 0 || i + w.rot == w.count) {
+        if (i == 0 || i + walk.rot == walk.count) {
             if (i == 0) {                                  // one stride as (frames, rows, columns)
-                const int stride = w.step * TILE;
-                sf = stride / rc;
-                const int srem = stride - sf * rc;
-                sr = srem / cols;
-                sc = srem - sr * cols;
+                const int stride = walk.step * TILE, f = stride / rc, srem = stride - f * rc, r = srem / cols;
+                st = f * step_t();
+                sh = r * step_h();
+                sw = (srem - r * cols) * step_w();
             }
-            const int tok0 = w.template token<TILE>(i);
+            const int tok0 = walk.template token<TILE>(i);
             const int f0 = tok0 / rc, rem = tok0 - f0 * rc, r0 = rem / cols, c0 = rem - r0 * cols;
 #pragma unroll
             for (int j = 0; j < STEPS; ++j) {
@@ -222,25 +203,56 @@ struct Rotator<kRope3D, STEPS, DEPTH> {
                 const int dr = (int)(((float)c1 + 0.5f) * inv_cols);
                 const int r1 = r0 + dr;
                 const int df = (int)(((float)r1 + 0.5f) * inv_rows);
-                c[j] = c1 - __mul24(dr, cols);
-                r[j] = r1 - __mul24(df, rows);
-                const int ff = f0 + df;
-                f[j] = ff < frames_m1 ? ff : frames_m1;
+                w[j] = __mul24(c1 - __mul24(dr, cols), step_w());
+                h[j] = __mul24(r1 - __mul24(df, rows), step_h());
+                const int tt = __mul24(f0 + df, step_t());
+                t[j] = tt < last_t ? tt : last_t;
             }
         } else {
 #pragma unroll
             for (int j = 0; j < STEPS; ++j) {
-                const int cc = c[j] + sc;
-                const bool cr = cc >= cols;
-                c[j] = cr ? cc - cols : cc;
-                const int rr = r[j] + sr + (cr ? 1 : 0);
-                const bool cf = rr >= rows;
-                r[j] = cf ? rr - rows : rr;
-                const int ff = f[j] + sf + (cf ? 1 : 0);
-                f[j] = ff < frames_m1 ? ff : frames_m1;
+                const int cc = w[j] + sw;
+                const bool cr = cc >= end_w;
+                w[j] = cr ? cc - end_w : cc;
+                const int rr = h[j] + sh + (cr ? step_h() : 0);
+                const bool cf = rr >= end_h;
+                h[j] = cf ? rr - end_h : rr;
+                const int tt = t[j] + st + (cf ? step_t() : 0);
+                t[j] = tt < last_t ? tt : last_t;
             }
         }
     }
+
+};
+
+template <int STEPS, int DEPTH>
+struct Rotator<kRope3D, STEPS, DEPTH> {
+    const unsigned char *tab;          // the three tables in LDS
+    // Entry of pair q: base + the position on its axis, in bytes.  Which axis a pair follows are two lane masks in scalar registers: two selections and an
+    // addition per pair, where position times a stride that is zero on the other axes took four instructions and twelve vector
+    // registers (d = 112 layers 1 to 2 % less; what it frees lets the one-launch block step of d = 112 fit).
+    uint32_t base[4];
+    bool on_t[4], on_h[4];
+    Rope3dPositions<STEPS, true> pos;
+
+    __device__ __forceinline__ Rotator(const RopeArg &a, int /*t1*/, int d, int row0, int rows_per_step, int pair0, int /*lane_valid*/,
+                                       const unsigned char *lds_tab)
+        : tab(lds_tab), pos(a.r3, row0, rows_per_step)
+    {
+        const Rope3D &R = a.r3;
+        const uint32_t off_h = (uint32_t)(R.frames * R.n_t) * 8u, off_w = off_h + (uint32_t)(R.rows * R.n_h) * 8u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            int p = pair0 + q;
+            p = p < d / 2 ? p : d / 2 - 1;        // lanes past d (their features are zero) look at a valid entry
+            on_t[q] = p < R.n_t;
+            on_h[q] = p < R.n_t + R.n_h;          // looked at where on_t is false
+            base[q] = on_t[q] ? (uint32_t)p * 8u : on_h[q] ? off_h + (uint32_t)(p - R.n_t) * 8u : off_w + (uint32_t)(p - R.n_t - R.n_h) * 8u;
+        }
+    }
+
+    __device__ __forceinline__ void request(int, bool, int) {}
+    template <int TILE> __device__ __forceinline__ void begin_tile(const TileWalk &walk, int i) { pos.template begin_tile<TILE>(walk, i); }
 
     // The (cos, sin) entries of the lane's four pairs of chunk j: four LDS reads.  Split from the
     // arithmetic so that a caller can issue the reads of a whole tile first and do other work
@@ -249,10 +261,8 @@ struct Rotator<kRope3D, STEPS, DEPTH> {
     {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            // 24-bit multiplies run at full rate (32-bit ones at a quarter); positions and strides are far below 2^24
-            const uint32_t addr = base[q] + __umul24((uint32_t)f[j], mul_f[q]) + __umul24((uint32_t)r[j], mul_r[q]) +
-                                  __umul24((uint32_t)c[j], mul_c[q]);
-            e[q] = *reinterpret_cast<const f32x2 *>(tab + addr);
+            const int t = pos.t[j], h = pos.h[j], w = pos.w[j];   // values: a choice between the array elements would put them into memory
+            e[q] = *reinterpret_cast<const f32x2 *>(tab + base[q] + (uint32_t)(on_t[q] ? t : on_h[q] ? h : w));
         }
     }
     __device__ __forceinline__ u32x4 rotate_with(u32x4 w, const f32x2 (&e)[4]) const
@@ -263,18 +273,48 @@ struct Rotator<kRope3D, STEPS, DEPTH> {
 };
 
 template <int STEPS, int DEPTH>
-struct Rotator<kRope3DWhole, STEPS, DEPTH> : Rotator<kRope3D, STEPS, DEPTH> {
-    using Base = Rotator<kRope3D, STEPS, DEPTH>;
-    using Base::Base;
+struct Rotator<kRope3DWhole, STEPS, DEPTH> {
+    const unsigned char *tab;          // the three tables in LDS
+    // Address of the lane's four entries = base + f * mul_f + r * mul_r + c * mul_c, one of the three not zero.  (With the offsets and lane masks of
+    // kRope3D, which this form's single address gains nothing from, block steps of 64 heads and more took 1 % longer.)
+    uint32_t base, mul_f, mul_r, mul_c;
+    Rope3dPositions<STEPS, false> pos;
+
+    __device__ __forceinline__ Rotator(const RopeArg &a, int /*t1*/, int d, int row0, int rows_per_step, int pair0, int /*lane_valid*/,
+                                       const unsigned char *lds_tab)
+        : tab(lds_tab), base(0), mul_f(0), mul_r(0), mul_c(0), pos(a.r3, row0, rows_per_step)
+    {
+        const Rope3D &R = a.r3;
+        const uint32_t off_h = (uint32_t)(R.frames * R.n_t) * 8u, off_w = off_h + (uint32_t)(R.rows * R.n_h) * 8u;
+        const int p = pair0 < d / 2 ? pair0 : d / 2 - 1;
+        if (p < R.n_t) {
+            base = (uint32_t)p * 8u;
+            mul_f = (uint32_t)R.n_t * 8u;
+        } else if (p < R.n_t + R.n_h) {
+            base = off_h + (uint32_t)(p - R.n_t) * 8u;
+            mul_r = (uint32_t)R.n_h * 8u;
+        } else {
+            base = off_w + (uint32_t)(p - R.n_t - R.n_h) * 8u;
+            mul_c = (uint32_t)R.n_w * 8u;
+        }
+    }
+
+    __device__ __forceinline__ void request(int, bool, int) {}
+    template <int TILE> __device__ __forceinline__ void begin_tile(const TileWalk &walk, int i) { pos.template begin_tile<TILE>(walk, i); }
     __device__ __forceinline__ void fetch(int /*s*/, int j, f32x2 (&e)[4]) const
     {
-        const uint32_t addr = this->base[0] + __umul24((uint32_t)this->f[j], this->mul_f[0]) +
-                              __umul24((uint32_t)this->r[j], this->mul_r[0]) + __umul24((uint32_t)this->c[j], this->mul_c[0]);
-        const f32x4 a = *reinterpret_cast<const f32x4 *>(this->tab + addr), b = *reinterpret_cast<const f32x4 *>(this->tab + addr + 16);
+        // 24-bit multiplies run at full rate (32-bit ones at a quarter); positions and strides are far below 2^24
+        const uint32_t addr = base + __umul24((uint32_t)pos.t[j], mul_f) + __umul24((uint32_t)pos.h[j], mul_r) + __umul24((uint32_t)pos.w[j], mul_c);
+        const f32x4 a = *reinterpret_cast<const f32x4 *>(tab + addr), b = *reinterpret_cast<const f32x4 *>(tab + addr + 16);
         e[0] = f32x2{a.x, a.y};
         e[1] = f32x2{a.z, a.w};
         e[2] = f32x2{b.x, b.y};
         e[3] = f32x2{b.z, b.w};
+    }
+    __device__ __forceinline__ u32x4 rotate_with(u32x4 w, const f32x2 (&e)[4]) const
+    {
+        return u32x4{rope_rotate_pair(w.x, e[0].x, e[0].y), rope_rotate_pair(w.y, e[1].x, e[1].y),
+                     rope_rotate_pair(w.z, e[2].x, e[2].y), rope_rotate_pair(w.w, e[3].x, e[3].y)};
     }
 };
 
