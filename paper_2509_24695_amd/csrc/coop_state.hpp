@@ -59,6 +59,80 @@ struct CoopStateStream {
     }
 };
 
+// Sums the workgroup's share, whose first DEPTH tiles are requested and whose rotation is at the first one (begin_tile): wave w ends with S of key features 32 (w / 2) .. +32 by value features
+// 64 (w % 2) .. +64 in `fin`, and with its rows' key sums in zw[w][128] (LDS).  The tiles pass through `lds`.  Called by all waves; a
+// barrier has to follow before the key sums are read or the tiles' memory is used again.
+template <int DEPTH, int ROPE, bool NT>
+__device__ __forceinline__ void coop_state_sum(CoopStateStream<DEPTH, ROPE, NT> &stream, unsigned char *lds, float *zw, int wave, int lane,
+                                               f32x16 (&fin)[2])
+{
+    const int kb = wave >> 1, vb = wave & 1;
+    f32x16 acc[kCoopSets][2] = {};
+    float zs[8] = {};
+    const int wr_off = (8 * wave + (lane >> 4)) * kWideRow + (lane & 15) * 16;
+    // tile i0 + s, staged in registers s, through buffer (i0 + s) % 2
+    auto tile = [&](int i, int s) __attribute__((always_inline)) {
+        constexpr int NLD = CoopStateStream<DEPTH, ROPE, NT>::NLD;
+        __builtin_amdgcn_sched_barrier(0);       // stages stay in program order
+        unsigned char *bufK = lds + (i & 1) * 2 * kCoopTileBytes, *bufV = bufK + kCoopTileBytes;
+        f32x2 cs[NLD][4];
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) stream.rot.fetch(s, j, cs[j]);
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) {
+            const u32x4 kk = relu_bf16x8(stream.k[s][j]);
+            zs[0] += bf16_lo(kk.x);  zs[1] += bf16_hi(kk.x);
+            zs[2] += bf16_lo(kk.y);  zs[3] += bf16_hi(kk.y);
+            zs[4] += bf16_lo(kk.z);  zs[5] += bf16_hi(kk.z);
+            zs[6] += bf16_lo(kk.w);  zs[7] += bf16_hi(kk.w);
+            *reinterpret_cast<u32x4 *>(bufK + wr_off + 4 * j * kWideRow) = stream.rot.rotate_with(kk, cs[j]);
+            *reinterpret_cast<u32x4 *>(bufV + wr_off + 4 * j * kWideRow) = stream.v[s][j];
+        }
+        stream.request(s, i + DEPTH);            // refill this stage
+        // The tile is complete.  It is overwritten two tiles on, by waves that have passed the next tile's barrier, which every wave
+        // reaches after its reads of this one.
+        lds_barrier();
+        stream.rot.template begin_tile<kCoopTokens>(stream.walk, i + 1);
+#pragma unroll
+        for (int ks = 0; ks < kCoopTokens / 16; ++ks) {
+            const bf16x8 a = lds_tr_operand<kWideRow>(bufK, 16 * ks, 32 * kb, lane);
+            const bf16x8 b0 = lds_tr_operand<kWideRow>(bufV, 16 * ks, 64 * vb, lane), b1 = lds_tr_operand<kWideRow>(bufV, 16 * ks, 64 * vb + 32, lane);
+            f32x16(&x)[2] = acc[ks % kCoopSets];
+            x[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b0, x[0], 0, 0, 0);
+            x[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b1, x[1], 0, 0, 0);
+        }
+    };
+    // Tiles past the share hold zeros and add nothing; all waves take the same number.
+    for (int i0 = 0; i0 < stream.walk.count; i0 += DEPTH) {
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s)
+            if (i0 + s < stream.walk.count) tile(i0 + s, s);
+    }
+
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) fin[cb] = (acc[0][cb] + acc[1][cb]) + (acc[2][cb] + acc[3][cb]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {                               // lanes with equal lane % 16 hold the same eight features
+        float x = zs[e];
+        x += __shfl_xor(x, 16);
+        x += __shfl_xor(x, 32);
+        if (lane < 16) zw[wave * 128 + lane * 8 + e] = x;
+    }
+}
+
+// The workgroup's sum of key k, from the waves' rows in zw.
+__device__ __forceinline__ float coop_key_sum(const float *zw, int k)
+{
+    float x[kCoopWaves];
+#pragma unroll
+    for (int w = 0; w < kCoopWaves; ++w) x[w] = zw[w * 128 + k];
+#pragma unroll
+    for (int s = kCoopWaves / 2; s >= 1; s /= 2)
+#pragma unroll
+        for (int w = 0; w < s; ++w) x[w] += x[w + s];
+    return x[0];
+}
+
 // grid = (C, B*H), block = kCoopThreads; chunk c owns tiles c + C i of the ceil((t1 - t0) / 64) tiles.  FINALIZE as in state_mfma_d64.
 // Partials are laid out by wide_word.
 template <int DEPTH, bool FINALIZE, int ROPE, bool NT>
@@ -87,83 +161,23 @@ __global__ __launch_bounds__(kCoopThreads, 2) void state_mfma_coop(
         stream.request(s, s);
         __builtin_amdgcn_sched_barrier(0);
     }
+    stream.rot.template begin_tile<kCoopTokens>(stream.walk, 0);   // while the tables and the first tiles are on their way
     if (ROPE == kRope3D) {
         rope3d_lds_fill_end(lds + kCoopTabOffset, rope.r3, tabs);
         wg_barrier();
     }
-    const int kb = wave >> 1, vb = wave & 1;
-    f32x16 acc[kCoopSets][2] = {};
-    float zs[8] = {};
-    const int wr_off = (8 * wave + (lane >> 4)) * kWideRow + (lane & 15) * 16;
-    // tile i0 + s, staged in registers s, through buffer (i0 + s) % 2
-    auto tile = [&](int i, int s) __attribute__((always_inline)) {
-        constexpr int NLD = CoopStateStream<DEPTH, ROPE, NT>::NLD;
-        __builtin_amdgcn_sched_barrier(0);       // stages stay in program order
-        unsigned char *bufK = lds + (i & 1) * 2 * kCoopTileBytes, *bufV = bufK + kCoopTileBytes;
-        stream.rot.template begin_tile<kCoopTokens>(stream.walk, i);
-        f32x2 cs[NLD][4];
-#pragma unroll
-        for (int j = 0; j < NLD; ++j) stream.rot.fetch(s, j, cs[j]);
-#pragma unroll
-        for (int j = 0; j < NLD; ++j) {
-            const u32x4 kk = relu_bf16x8(stream.k[s][j]);
-            zs[0] += bf16_lo(kk.x);  zs[1] += bf16_hi(kk.x);
-            zs[2] += bf16_lo(kk.y);  zs[3] += bf16_hi(kk.y);
-            zs[4] += bf16_lo(kk.z);  zs[5] += bf16_hi(kk.z);
-            zs[6] += bf16_lo(kk.w);  zs[7] += bf16_hi(kk.w);
-            *reinterpret_cast<u32x4 *>(bufK + wr_off + 4 * j * kWideRow) = stream.rot.rotate_with(kk, cs[j]);
-            *reinterpret_cast<u32x4 *>(bufV + wr_off + 4 * j * kWideRow) = stream.v[s][j];
-        }
-        stream.request(s, i + DEPTH);            // refill this stage
-        // The tile is complete.  It is overwritten two tiles on, by waves that have passed the next tile's barrier, which every wave
-        // reaches after its reads of this one.
-        lds_barrier();
-#pragma unroll
-        for (int ks = 0; ks < kCoopTokens / 16; ++ks) {
-            const bf16x8 a = lds_tr_operand<kWideRow>(bufK, 16 * ks, 32 * kb, lane);
-            const bf16x8 b0 = lds_tr_operand<kWideRow>(bufV, 16 * ks, 64 * vb, lane), b1 = lds_tr_operand<kWideRow>(bufV, 16 * ks, 64 * vb + 32, lane);
-            f32x16(&x)[2] = acc[ks % kCoopSets];
-            x[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b0, x[0], 0, 0, 0);
-            x[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b1, x[1], 0, 0, 0);
-        }
-    };
-    // Tiles past the share hold zeros and add nothing; all waves take the same number.
-    for (int i0 = 0; i0 < stream.walk.count; i0 += DEPTH) {
-#pragma unroll
-        for (int s = 0; s < DEPTH; ++s)
-            if (i0 + s < stream.walk.count) tile(i0 + s, s);
-    }
-
     f32x16 fin[2];
-#pragma unroll
-    for (int cb = 0; cb < 2; ++cb) fin[cb] = (acc[0][cb] + acc[1][cb]) + (acc[2][cb] + acc[3][cb]);
     float *zw = reinterpret_cast<float *>(lds + kCoopZOffset);  // [wave][128]
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {                               // lanes with equal lane % 16 hold the same eight features
-        float x = zs[e];
-        x += __shfl_xor(x, 16);
-        x += __shfl_xor(x, 32);
-        if (lane < 16) zw[wave * 128 + lane * 8 + e] = x;
-    }
+    coop_state_sum(stream, lds, zw, wave, lane, fin);
     lds_barrier();
-    auto key_sum = [&](int k) __attribute__((always_inline)) {
-        float x[kCoopWaves];
-#pragma unroll
-        for (int w = 0; w < kCoopWaves; ++w) x[w] = zw[w * 128 + k];
-#pragma unroll
-        for (int s = kCoopWaves / 2; s >= 1; s /= 2)
-#pragma unroll
-            for (int w = 0; w < s; ++w) x[w] += x[w + s];
-        return x[0];
-    };
     const WideTarget target{S_in ? S_in + (size_t)bh * d * d : nullptr, z_in + (size_t)bh * d, S_out + (size_t)bh * d * d,
                             z_out + (size_t)bh * d, static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems, d, c, C};
-    wide_store_block<2>(fin, kb, 2 * vb, FINALIZE && C == 1, target, lane);
+    wide_store_block<2>(fin, wave >> 1, 2 * (wave & 1), FINALIZE && C == 1, target, lane);
     if (FINALIZE && C == 1) {
-        if (tid < d) target.z_out[tid] = (target.S_in ? target.z_in[tid] : 0.f) + key_sum(tid);
+        if (tid < d) target.z_out[tid] = (target.S_in ? target.z_in[tid] : 0.f) + coop_key_sum(zw, tid);
         return;
     }
-    if (tid < d / 2) store_coherent(target.partials + (size_t)c * elems + (size_t)d * d + 2 * tid, f32x2{key_sum(2 * tid), key_sum(2 * tid + 1)});
+    if (tid < d / 2) store_coherent(target.partials + (size_t)c * elems + (size_t)d * d + 2 * tid, f32x2{coop_key_sum(zw, 2 * tid), coop_key_sum(zw, 2 * tid + 1)});
     if (FINALIZE) {
         epoch = es.resolve(reinterpret_cast<unsigned long long *>(lds + kCoopEpochOffset));
         auto wait = [&]() __attribute__((always_inline)) {

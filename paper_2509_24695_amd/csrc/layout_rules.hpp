@@ -4,6 +4,8 @@
 
 #include <stdint.h>
 
+#include "tile_walk.hpp"
+
 namespace sv {
 
 constexpr int kMaxChunks = 32;       // upper bound on token chunks per head (workspace sizing)
@@ -189,6 +191,66 @@ inline int f32_sole_tokens(int d, int BH, int elem_bytes, bool rotated)
     constexpr int kTokens[2][2][5] = {{{1152, 832, 640, 640, 768}, {832, 640, 512, 512, 768}},         // fp32: plain, rotated
                                       {{1280, 1152, 1024, 896, 896}, {960, 896, 704, 640, 896}}};      // bf16
     return kTokens[elem_bytes == 2][rotated][BH <= 2 ? 0 : BH <= 16 ? 1 : BH <= 32 ? 2 : BH <= 64 ? 3 : 4];
+}
+
+// d = 112 and 128, block step: one launch (block_step_wide.hpp) or two (a state kernel, the apply kernel).  Streams of two to four blocks, two
+// launches / one, us per stream:
+//   plain           20 heads of 112, 4 680 tokens 133 / 120, 32 760 238 / 221, 75 600 503 / 475; 64 heads, 4 680 131 / 120; 8 heads, 1 560 77 / 64; of
+//                   128: 32 heads, 9 360 145 / 137; two workgroups per head: 128 heads, 1 560 207 / 179, 4 680 230 / 258 (of 128 286 / 279), 100 heads, 4 680
+//                   194 / 196
+//   factored        20 heads, 4 680 154 / 137, 32 760 262 / 257, 75 600 555 / 560; 40 heads, 32 760 488 / 492; 128 heads, 1 560 240 / 208, 4 680 250 / 272
+//   full table      20 heads, 4 680 120 / 112, 9 360 115 / 111, 18 000 256 / 258, 32 760 292 / 302; 40 heads, 4 680 170 / 162, 9 360 184 / 189; 80 heads,
+//                   1 560 146 / 124, 4 680 272 / 272
+//   shared lines    plain 20 heads, 4 680 78 / 73, 40 heads 219 / 216 to 221, 20 heads, 14 040 136 / 148; factored tables 20 heads, 4 680 85 / 78,
+//                   32 760 318 / 318
+//   few heads       a head on all dies: 2 heads, 600 tokens 64 / 56, 4 680 40.1 / 41.7, 5 heads, 4 680 47.1 / 48.1
+// A workgroup per head, by how much of the device the heads fill (130, 160, 192 to 256, more than 256 heads):
+//   plain           130 of 112: 624 98 / 85, 2 000 138 / 132, 3 120 265 / 269; 160: 3 120 297 / 280, 4 680 402 / 403; 200 and 256: 9 360 655 / 599 and 775 / 743;
+//                   400: 240 319 / 107, 9 360 1 383 / 1 251; 130 of 128: 4 680 415 / 404, 9 360 516 / 538; 160: 9 360 586 / 601
+//   factored        130: 624 118 / 100, 2 000 157 / 166; 160: 3 120 354 / 345, 4 680 488 / 502; 192: 4 680 365 / 375; 200: 4 680 582 / 560, 9 360 737 / 743; 256: 9 360
+//                   843 / 857; 400: 9 360 1 586 / 1 477
+//   full table      160: 600 87 / 83, 1 560 223 / 237; 256: 240 70 / 54, 1 560 190 / 184; 400: 1 560 452 / 325
+//   shared lines    160 heads, 600 76 / 69, 4 680 334 / 398 (factored 376 / 411)
+inline bool wide_step_serves(const TokenLayout &t, int n_tokens, int C, bool full_table, bool factored_tables, int num_cu)
+{
+    const int64_t head_tokens = (int64_t)t.BH * n_tokens;
+    if (C > 1) {
+        if (t.BH < 8) return n_tokens <= 2048;
+        if (full_table) return head_tokens <= 200000;
+        if (t.shares_lines() && !factored_tables) return head_tokens <= 200000;
+        if (C == 2 && (t.d == 112 || factored_tables)) return n_tokens <= 3072;
+        return !factored_tables || n_tokens <= 4096 * C;
+    }
+    if (t.shares_lines()) return n_tokens <= 1024;
+    if (t.BH > num_cu) return !full_table || n_tokens <= 2048;
+    if (full_table) return n_tokens <= 768;
+    const int fill = 100 * t.BH / num_cu;
+    if (fill < 57) return n_tokens <= (factored_tables ? 1280 : t.d == 112 ? 2560 : 4680);
+    if (fill < 75) return n_tokens <= (factored_tables ? 3120 : 4680);
+    return !factored_tables || n_tokens <= 4096;
+}
+
+// ... its workgroups: as many heads as fill the dies evenly live on one die each, where its workgroups exchange their sums through that die's L2, the
+// others are spread over all dies; of the splits of a die's compute units between the two, the one whose worst-off head has the most
+// workgroups, a spread head counted for eight tenths: its exchange takes 2 to 3 us longer.  (20 heads, 4 680 tokens, plain and factored tables, all spread: 32.0
+// and 38.0 us a block; 16 local heads of 13 workgroups and 4 spread of 12: 28.8 and 34.3, of 12 and 16: 27.8 and 33.0.)  Not where heads share cache lines,
+// which then lie on different dies; with a full table, whose rows every die fetches then, up to 2 048 tokens (20 heads, 1 560 tokens 74.8 -> 69.5
+// us per stream, 4 680 level, 18 000 258 -> 291).
+inline WideRoles wide_roles(const TokenLayout &t, int n_tokens, int n_steps, bool full_table, int num_cu, int dies)
+{
+    WideRoles best{0, 0, 0, 0, t.BH};
+    if (dies <= 0 || t.BH < dies || t.BH * 2 > num_cu || t.shares_lines() || (full_table && n_tokens > 2048)) return best;
+    const int cus = num_cu / dies, per_die = t.BH / dies, spread = t.BH % dies, most = n_steps < kMaxChunks ? n_steps : kMaxChunks;
+    int worst = 0;
+    for (int C = cus / per_die < most ? cus / per_die : most; C >= 1; --C) {
+        int Cs = spread ? dies * (cus - per_die * C) / spread : C;
+        Cs = Cs < most ? Cs : most;
+        const int score = 10 * C < 8 * Cs || !spread ? 10 * C : 8 * Cs;
+        if (score <= worst) continue;
+        worst = score;
+        best = WideRoles{dies, per_die, C, Cs, t.BH};
+    }
+    return best;
 }
 
 }  // namespace sv

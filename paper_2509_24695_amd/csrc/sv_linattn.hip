@@ -14,6 +14,7 @@
 
 #include "apply_mfma.hpp"
 #include "block_step_fused.hpp"
+#include "block_step_wide.hpp"
 #include "coop128.hpp"
 #include "coop_state.hpp"
 #include "common.hpp"
@@ -70,6 +71,7 @@ struct Device {
     // how many workgroups fit on the device at once
     int state_resident_wgs[2][4][2] = {};                    // state kernel with in-kernel finalize, [DP = 128][kernels' RoPE mode][SHARED]
     int coop_resident_wgs[3][2] = {};                        // state kernel on shared tiles (d = 112, 128), [RoPE mode][SHARED]
+    int wide_fused_resident_wgs[3][2] = {};                  // one-launch block step (d = 112, 128), [RoPE mode][SHARED]
     int quad_resident_wgs[3] = {0, 0, 0};                    // quadrant state kernel (d = 112, 128), by RoPE mode
     int fused_resident_wgs[4] = {0, 0, 0, 0};                   // one-launch block step (d = 64), by the kernels' RoPE mode
     bool ok = false;
@@ -118,6 +120,8 @@ template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     static constexpr auto state_partial = pick_state<false>();
     template <bool FINALIZE> static constexpr auto coop_state = state_mfma_coop<2, FINALIZE, ROPE, !SHARED>;   // short shares (coop_state_pays)
     static constexpr int coop_lds = coop_state_lds<ROPE>();
+    template <bool SOLE> static constexpr auto fused_form = block_step_mfma_wide<ROPE, !SHARED, SOLE>;   // block step in one launch
+    static constexpr int fused_lds = block_step_wide_lds<ROPE>();
     template <int HEADS> static constexpr auto apply_heads =
         apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB, !SHARED, HEADS>;
     static constexpr auto apply = apply_heads<1>;
@@ -199,6 +203,14 @@ template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
                                                      64 * kStateWaves, KN::state_lds) != hipSuccess)
         per_cu = 0;
     d.state_resident_wgs[KN::W][ROPE][KN::kShared] = per_cu * d.num_cu;
+    if constexpr (KN::kWideState) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::template fused_form<true>), attr, KN::fused_lds);
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::template fused_form<false>), attr, KN::fused_lds);
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(KN::template fused_form<false>),
+                                                         kCoopThreads, KN::fused_lds) != hipSuccess)
+            per_cu = 0;
+        d.wide_fused_resident_wgs[ROPE][KN::kShared] = per_cu * d.num_cu;
+    }
     if constexpr (KN::kHasCoop) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::template coop_state<true>), attr, KN::coop_lds);
         (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::template coop_state<false>), attr, KN::coop_lds);
@@ -698,7 +710,7 @@ sv_status do_block_step(const void *Qb, const void *Kb, const void *Vb, const sv
         z_out = S_out + (size_t)s.BH * s.d * s.d;
     }
     auto hs = static_cast<hipStream_t>(stream);
-    if (mfma_path(s, rope) && s.d == 64) {             // one launch; d = 112, 128 are faster as two (measured)
+    if (mfma_path(s, rope) && s.d == 64) {
         const Device &dev = device_info();
         if (!dev.ok) return SV_ERR_LAUNCH;
         bool launched = false;
@@ -730,6 +742,31 @@ sv_status do_block_step(const void *Qb, const void *Kb, const void *Vb, const sv
         else if (mode == kRope3D) launch(Kernels<64, kRope3D>{});
         else if (rope.mode == kRopeTable) launch(Kernels<64, kRopeTable>{});
         else launch(Kernels<64, kRopeNone>{});
+        if (launched) return launch_status();
+    }
+    if (mfma_path(s, rope) && s.d > 64) {
+        const Device &dev = device_info();
+        if (!dev.ok) return SV_ERR_LAUNCH;
+        const TokenLayout layout = layout_of(s);
+        const int C = plan_chunks(s.BH, s.N, kCoopTokens, dev.num_cu);
+        bool launched = false;
+        with_mfma_kernels(s.d, rope.mode, layout.shares_lines(), [&](auto kn) {
+            using KN = decltype(kn);
+            if constexpr (KN::kWideState) {
+                if (!wide_step_serves(layout, s.N, C, rope.mode == kRopeTable, rope.mode == kRope3D, dev.num_cu)) return;
+                // The heads' places on the dies are those of the 8 x 32 compute-unit part; the kernel checks them itself (see block_step_mfma).
+                const int dies = C > 1 && dev.num_cu == kDies * kCusPerDie ? g_assumed_dies.load(std::memory_order_relaxed) : 0;
+                const WideRoles roles = wide_roles(layout, s.N, (s.N + kCoopTokens - 1) / kCoopTokens, rope.mode == kRopeTable, dev.num_cu, dies);
+                const dim3 grid = roles.dies ? dim3(roles.grid()) : dim3(C, s.BH);
+                if (C > 1 && (int64_t)grid.x * grid.y > dev.wide_fused_resident_wgs[rope.mode][KN::kShared]) return;   // its workgroups wait for each other
+                const auto kernel = C == 1 ? KN::template fused_form<true> : KN::template fused_form<false>;
+                kernel<<<grid, kCoopThreads, KN::fused_lds, hs>>>(
+                    static_cast<const uint16_t *>(Qb), static_cast<const uint16_t *>(Kb), static_cast<const uint16_t *>(Vb),
+                    static_cast<uint16_t *>(Ob), rope.arg, s.st, s.H, s.d, s.N, C, S_in, z_in, S_out, z_out, eps, workspace,
+                    next_epoch(s.host_epochs_only), spin_limit(), state_order(layout, rope.mode == kRopeTable), roles);
+                launched = true;
+            }
+        });
         if (launched) return launch_status();
     }
     rc = enqueue_state(Kb, Vb, rope, s, 0, s.N, S_in, z_in, S_out, z_out, workspace, hs);

@@ -93,6 +93,32 @@ SV_HOST_DEVICE inline bool quad_role(int id, int C, int BH, int dies, bool chunk
 }
 SV_HOST_DEVICE inline int quad_grid(int C, int BH, int dies) { return 4 * dies * ((C * BH + dies - 1) / dies); }
 
+// How the one-launch block step of d = 112 and 128 is dealt to the dies: heads 0 .. dies * per_die - 1 live on one die each, C_local workgroups,
+// the others are spread over all of them, C_spread workgroups.  dies = 0: every head is spread, by a grid of (C, BH).
+struct WideRoles {
+    int dies, per_die, C_local, C_spread, BH;
+    SV_HOST_DEVICE inline int grid() const {
+        return dies * (per_die * C_local + ((BH - dies * per_die) * C_spread + dies - 1) / dies);
+    }
+};
+// What workgroup `id` of such a grid works on; false: nothing.
+SV_HOST_DEVICE inline bool wide_role(int id, const WideRoles &r, int &c, int &C, int &bh, bool &local)
+{
+    const int die = id % r.dies, slot = id / r.dies, of_heads = r.per_die * r.C_local;
+    local = slot < of_heads;
+    if (local) {
+        C = r.C_local;
+        bh = die + r.dies * (slot / C);
+        c = slot % C;
+        return true;
+    }
+    C = r.C_spread;
+    const int k = (slot - of_heads) * r.dies + die;
+    bh = r.dies * r.per_die + k / C;
+    c = k % C;
+    return bh < r.BH;
+}
+
 // Phase key (the `bh` argument of TileWalk) of head bh in the die-local forms of the kernels, where die x
 // holds heads x, x + n_dies, ...: keyed by the head index itself, heads of one die would share phases (two
 // distinct ones for four heads), so the sixteen phases are dealt die by die, the heads of a die as far apart

@@ -258,33 +258,45 @@ struct WideTarget {
     int d, c, C;
 };
 
-// Stores NCB accumulator blocks of S, key features 32 kb .. +32 by value features 32 cb0 ..: into the workgroup's partial, with coherent
-// stores, or, if it is the head's only contributor (`sole`), added to the carried state as the new state.
+// NCB accumulator blocks of S, key features 32 kb .. +32 by value features 32 cb0 ..:
 // Element i of block cb: row 32 kb + 8 (i / 4) + 4 (lane / 32) + i % 4, column 32 (cb0 + cb) + lane % 32.
 // Rows past d lie past the resource's end, columns past d are sent there: both are dropped.
+//
+// The head's only contributor: adds the carried state to the blocks and stores them as the new state.
 template <int NCB>
-__device__ __forceinline__ void wide_store_block(const f32x16 (&fin)[NCB], int kb, int cb0, bool sole, const WideTarget &t, int lane)
+__device__ __forceinline__ void wide_store_sole(f32x16 (&fin)[NCB], int kb, int cb0, const WideTarget &t, int lane)
 {
     const int d = t.d, n = lane & 31, g = lane >> 5;
     const uint32_t s_bytes = (uint32_t)d * (uint32_t)d * 4u;
-    if (sole) {
-        const rsrc_t rS = make_rsrc(t.S_out, s_bytes), rI = make_rsrc(t.S_in ? t.S_in : t.S_out, t.S_in ? s_bytes : 0u);
-        const uint32_t base = ((uint32_t)(32 * kb + 4 * g) * (uint32_t)d + (uint32_t)(32 * cb0 + n)) * 4u;
+    const rsrc_t rS = make_rsrc(t.S_out, s_bytes), rI = make_rsrc(t.S_in ? t.S_in : t.S_out, t.S_in ? s_bytes : 0u);
+    const uint32_t base = ((uint32_t)(32 * kb + 4 * g) * (uint32_t)d + (uint32_t)(32 * cb0 + n)) * 4u;
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-            const uint32_t col = 32 * (cb0 + cb) + n < d ? base + 128u * cb : kOutOfRange;
-            float x[16];
+    for (int cb = 0; cb < NCB; ++cb) {
+        const uint32_t col = 32 * (cb0 + cb) + n < d ? base + 128u * cb : kOutOfRange;
+        float x[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
-                x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                           rI, col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0));
+        for (int i = 0; i < 16; ++i)
+            x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                       rI, col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0));
 #pragma unroll
-            for (int i = 0; i < 16; ++i)
-                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x[i] + fin[cb][i]), rS,
-                                                      col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0);
+        for (int i = 0; i < 16; ++i) {
+            const float y = x[i] + fin[cb][i];
+            fin[cb][i] = y;
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, y), rS,
+                                                  col + (uint32_t)(8 * (i >> 2) + (i & 3)) * (uint32_t)d * 4u, 0, 0);
         }
+    }
+}
+// One of several: stores them into the workgroup's partial, with coherent stores (LOCAL: see store_coherent).  `sole`: wide_store_sole.
+template <int NCB, bool LOCAL = false>
+__device__ __forceinline__ void wide_store_block(f32x16 (&fin)[NCB], int kb, int cb0, bool sole, const WideTarget &t, int lane)
+{
+    if (sole) {
+        wide_store_sole<NCB>(fin, kb, cb0, t, lane);
         return;
     }
+    const int d = t.d, n = lane & 31, g = lane >> 5;
+    const uint32_t s_bytes = (uint32_t)d * (uint32_t)d * 4u;
     const rsrc_t rP = make_rsrc(t.partials + (size_t)t.c * (d * d + d), s_bytes);
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
@@ -293,7 +305,7 @@ __device__ __forceinline__ void wide_store_block(const f32x16 (&fin)[NCB], int k
         for (int q = 0; q < 4; ++q) {
             f32x4 x;
             x.x = fin[cb][4 * q];  x.y = fin[cb][4 * q + 1];  x.z = fin[cb][4 * q + 2];  x.w = fin[cb][4 * q + 3];
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rP, base + (uint32_t)(q * 32 * d), 0, 16 /* sc1 */);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rP, base + (uint32_t)(q * 32 * d), 0, LOCAL ? 0 : 16 /* sc1 */);
         }
     }
 }
@@ -365,39 +377,49 @@ __device__ __forceinline__ void wide_state_wg_reduce_store(WideAcc &acc, unsigne
     }
 }
 
-// Contributor t.c's slice of the head: publishes its partial, waits for the others (`wait`) and stores
-//   S_out, z_out = (S_in, z_in or 0) + partial[0] + partial[1] + ... + partial[C-1], in that order.
-// UNITS words per thread and round, GROUP partials in flight per word; the carried values of the first round, which do
-// not depend on the other workgroups, are fetched before the wait.  Called by all threads.
-template <int THREADS, int UNITS, int GROUP, class WaitFn>
-__device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
+// The carried values of words v0 + u * THREADS, u < UNITS, of the head's state (zeros without one).
+template <int THREADS, int UNITS> __device__ __forceinline__ void wide_carried(const WideTarget &t, const WideSlice &sl, int v0, f32x4 (&x)[UNITS])
 {
-    const WideSlice sl(t.c, t.C, t.d);
+    const int d = t.d;
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (!t.S_in) return;
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+        int v = v0 + u * THREADS;                           // beyond the slice: any valid word, the value is not used
+        v = v < sl.words ? v : sl.words - 1;
+        if (v < sl.s_words) {
+            int row, col;
+            wide_word_at(d, v, row, col);
+            const float *p = t.S_in + row * d + col;
+            x[u] = f32x4{p[0], p[d], p[2 * d], p[3 * d]};
+        } else {
+            x[u] = *reinterpret_cast<const f32x4 *>(t.z_in + 4 * (v - sl.s_words));
+        }
+    }
+}
+// Word v of the new state to its place in S_out, z_out.
+__device__ __forceinline__ void wide_store_word(const WideTarget &t, const WideSlice &sl, int v, f32x4 x)
+{
+    if (v < sl.s_words) {
+        int row, col;
+        wide_word_at(t.d, v, row, col);
+        float *p = t.S_out + row * t.d + col;
+        p[0] = x.x;  p[t.d] = x.y;  p[2 * t.d] = x.z;  p[3 * t.d] = x.w;
+    } else {
+        *reinterpret_cast<f32x4 *>(t.z_out + 4 * (v - sl.s_words)) = x;
+    }
+}
+// Contributor t.c's slice of the head, once all partials are there: store(word, value) of every word of
+//   (S_in, z_in or 0) + partial[0] + partial[1] + ... + partial[C-1], in that order.
+// UNITS words per thread and round, GROUP partials in flight per word; `x` holds the carried values of the first round.
+template <int THREADS, int UNITS, int GROUP, class StoreFn>
+__device__ __forceinline__ void wide_fold_slice(const WideTarget &t, const WideSlice &sl, f32x4 (&x)[UNITS], StoreFn store)
+{
     const int d = t.d, tid = (int)threadIdx.x;
     const rsrc_t rP = make_rsrc(t.partials, (uint32_t)t.C * (uint32_t)(d * d + d) * 4u);
-    auto carried = [&](int v0, f32x4 (&x)[UNITS]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < UNITS; ++u) x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (!t.S_in) return;
-#pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-            int v = v0 + u * THREADS;                           // beyond the slice: any valid word, the value is not used
-            v = v < sl.words ? v : sl.words - 1;
-            if (v < sl.s_words) {
-                int row, col;
-                wide_word_at(d, v, row, col);
-                const float *p = t.S_in + row * d + col;
-                x[u] = f32x4{p[0], p[d], p[2 * d], p[3 * d]};
-            } else {
-                x[u] = *reinterpret_cast<const f32x4 *>(t.z_in + 4 * (v - sl.s_words));
-            }
-        }
-    };
-    f32x4 x[UNITS];
-    carried(sl.lo + tid, x);
-    if (!wait()) return;                                         // timed out: this wave leaves its part of S, z as it was
     for (int v0 = sl.lo + tid; v0 < sl.hi; v0 += THREADS * UNITS) {
-        if (v0 != sl.lo + tid) carried(v0, x);
+        if (v0 != sl.lo + tid) wide_carried<THREADS>(t, sl, v0, x);
         for (int c0 = 0; c0 < t.C; c0 += GROUP) {
             f32x4 p[UNITS][GROUP];
 #pragma unroll
@@ -420,17 +442,20 @@ __device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
 #pragma unroll
         for (int u = 0; u < UNITS; ++u) {
             const int v = v0 + u * THREADS;
-            if (v >= sl.hi) continue;
-            if (v < sl.s_words) {
-                int row, col;
-                wide_word_at(d, v, row, col);
-                float *p = t.S_out + row * d + col;
-                p[0] = x[u].x;  p[d] = x[u].y;  p[2 * d] = x[u].z;  p[3 * d] = x[u].w;
-            } else {
-                *reinterpret_cast<f32x4 *>(t.z_out + 4 * (v - sl.s_words)) = x[u];
-            }
+            if (v < sl.hi) store(v, x[u]);
         }
     }
+}
+// Publishes the workgroup's partial, waits for the others (`wait`) and stores its slice of the new state; the carried values of the first
+// round, which do not depend on the other workgroups, are fetched before the wait.  Called by all threads.
+template <int THREADS, int UNITS, int GROUP, class WaitFn>
+__device__ __forceinline__ void wide_fold(const WideTarget &t, WaitFn wait)
+{
+    const WideSlice sl(t.c, t.C, t.d);
+    f32x4 x[UNITS];
+    wide_carried<THREADS>(t, sl, sl.lo + (int)threadIdx.x, x);
+    if (!wait()) return;                                         // timed out: this wave leaves its part of S, z as it was
+    wide_fold_slice<THREADS, UNITS, GROUP>(t, sl, x, [&](int v, f32x4 y) __attribute__((always_inline)) { wide_store_word(t, sl, v, y); });
 }
 
 // grid = (C, B*H), block = 256.  Wave w of workgroup c owns tiles 4c + w + 4C i of the

@@ -1,0 +1,54 @@
+"""How the one-launch block step of d = 112 and 128 is dealt and when it is used, compiled with g++ and run here; the rows of its GPU test take the
+forms they name."""
+import os
+import subprocess
+
+import pytest
+
+from tests import test_gpu_block_step_wide as wide
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    out = tmp_path_factory.mktemp("wide") / "host_wide_step"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Wextra", "-fsanitize=undefined", "-fno-sanitize-recover",
+                    os.path.join(ROOT, "tests", "host_wide_step.cpp"), "-o", str(out)], check=True)
+    return str(out)
+
+
+def _served(exe, calls):
+    """(form, workgroups of a spread head, of a local head) of calls (d, B, H, tokens, rope, layout)."""
+    args = [str(v) for call in calls for v in call]
+    lines = subprocess.run([exe, *args], stdout=subprocess.PIPE, text=True, check=True).stdout.splitlines()
+    return [(f, int(s), int(c)) for f, s, c in (line.split() for line in lines)]
+
+
+def test_heads_are_dealt_once(exe):
+    res = subprocess.run([exe], stdout=subprocess.PIPE, text=True)
+    assert res.returncode == 0 and res.stdout.startswith("OK"), res.stdout
+
+
+def test_rows_of_the_gpu_test_take_their_forms(exe):
+    rows = [((d, B, H, g[0] * g[1] * g[2], rope, layout), form)
+            for d, B, H, g, layout, forms in wide.ROWS for rope, form in zip(wide.ROPES, forms)]
+    got = _served(exe, [c for c, _ in rows])
+    assert [f for f, _, _ in got] == [f for _, f in rows]
+    # every form of the fold, for heads on one die and for spread ones, in every rotation
+    for kind in (1, 2):
+        seen = {(c[4], next(f for f in (2, 4, 8, 32) if g[kind] <= f)) for (c, _), g in zip(rows, got) if g[kind] > 1}
+        assert seen >= {(r, f) for r in wide.ROPES for f in (2, 4, 8, 32)}, (kind, seen)
+
+
+def test_lines(exe):
+    """Calls on both sides of the lines between one launch and two."""
+    calls = {(112, 1, 20, 75600, "none", "bhnd"): 1, (112, 1, 20, 75600, "axes", "bhnd"): 0, (112, 1, 20, 32760, "axes", "bhnd"): 1,
+             (112, 8, 16, 1560, "none", "bhnd"): 1, (112, 4, 32, 4680, "none", "bhnd"): 0, (128, 4, 32, 4680, "none", "bhnd"): 1,
+             (112, 1, 20, 9360, "table", "bhnd"): 1, (112, 1, 20, 32760, "table", "bhnd"): 0, (112, 1, 20, 4680, "none", "bnhd"): 1,
+             (112, 1, 20, 14040, "none", "bnhd"): 0, (112, 1, 20, 14040, "axes", "bnhd"): 1, (112, 1, 2, 600, "none", "bhnd"): 1,
+             (112, 1, 2, 4680, "none", "bhnd"): 0, (112, 5, 26, 2000, "none", "bhnd"): 1, (112, 5, 26, 3120, "none", "bhnd"): 0,
+             (112, 5, 26, 2000, "axes", "bhnd"): 0, (112, 10, 40, 9360, "axes", "bhnd"): 1, (112, 8, 20, 4680, "none", "bnhd"): 0,
+             (112, 8, 20, 1560, "table", "bhnd"): 0, (112, 8, 32, 9360, "none", "bhnd"): 1, (112, 8, 32, 9360, "axes", "bhnd"): 0}
+    got = _served(exe, list(calls))
+    assert {c: int(g[0] != "two") for c, g in zip(calls, got)} == calls
