@@ -114,30 +114,42 @@ template <int N> __device__ __forceinline__ void rotate_pairs(float (&f)[N], con
 
 // ---- state ----------------------------------------------------------------------------------------------------
 
-// SOLE: a workgroup sums a head alone, so its waves are all that work on it.  At d = 32 it has sixteen of them, in the 128 registers that
-// leaves each, instead of four with three tiles in flight each: 2 heads, 1 024 tokens, fp32 11.6 -> 10.0 us (of which the matrix core
-// of the one compute unit needs 3.5).  With two tiles in flight per wave, or at d = 64 with eight waves, the compiler spills.
-template <typename T, int D, bool SOLE, int ROPE> struct StateF32 {
+// How a head's tokens and its state are shared out (HOW):
+//   kF32Shared    C workgroups, a share of the tokens each; state_reduce adds their partial states up.
+//   kF32Sole      one workgroup, which stores the new state.
+//   kF32Quarters  four workgroups, all tokens and a quarter of the state each (d = 32 and 64): half of the 16 x 16 blocks in either direction.  They load
+//                 what one would, the second to fourth time out of their die's L2, but the matrix products, of which one compute unit needs
+//                 3.5 us for 1 024 tokens of 32 features or 256 of 64, are shared out and nothing has to be added up: the same bits.
+// Eight waves, two to a SIMD, so that one multiplies while the other converts and requests (four waves with three tiles in flight each,
+// before: 32 heads of 64, 4 680 tokens, layer 45.6 -> 43.5 us; 20 heads of 112 88.6 -> 83.1; 128 heads of 32, bf16, 4 096 tokens, rotated 48.5 -> 45.0).  At d = 32
+// a head that is not shared by its tokens gets sixteen waves in the 128 registers that leaves each (2 heads, 1 024 tokens, one workgroup: 11.6 -> 10.0 us).
+constexpr int kF32Shared = 0, kF32Sole = 1, kF32Quarters = 2;
+template <typename T, int D, int HOW, int ROPE> struct StateF32 {
     static constexpr bool kSplit = D > 64;                 // quadrants instead of whole states
-    static constexpr bool kMany = SOLE && D == 32;
-    static constexpr int kWaves = kMany ? 16 : 4;
+    static constexpr bool kAlone = HOW != kF32Shared, kQuarter = HOW == kF32Quarters;
+    static_assert(!kQuarter || !kSplit, "wide heads are dealt to the waves as quadrants already");
+    static constexpr bool kMany = kAlone && D == 32;
+    static constexpr int kWaves = kMany ? 16 : 8;
     static constexpr int F = kSplit ? 64 : D;              // features of a wave's part, on both axes
     static constexpr int VEC = F / 16, W = kWords<T, VEC>;
-    // (the two forms of the rotation keep the same tiles and give the same bits; with sixteen waves eight groups of a full table spill)
-    static constexpr int U = kMany && ROPE != kRopeNone ? 4 : 16 / VEC;          // groups of four tokens per tile: 16 tokens, 32 at d = 32 in a shared head
+    static constexpr int NB = kQuarter ? VEC / 2 : VEC;    // blocks of 16 features that a wave multiplies, on both axes
+    // Groups of four tokens per tile: what the registers hold (three or four at d = 64 and more: level to 5 % slower, and rotated they spill).
+    // The two forms of the rotation keep the same tiles and give the same bits.
+    static constexpr int U = D > 32 ? 2 : kMany && ROPE == kRopeNone ? 8 : 4;
     static constexpr int TILE = 4 * U;
-    static constexpr int DEPTH = kMany ? 1 : 3;             // tiles in flight per wave
+    static constexpr int DEPTH = kMany ? 1 : D == 32 ? 3 : 2;    // tiles in flight per wave
     // Running sums: a set per stage, and at d = 32 (few registers) one for each parity of the token group.  An fp32 sum's error grows
     // with the root of its length; one set for the whole share had S up to 1.8 times as far from 64-bit sums as the scalar kernel, whose
     // chunks are shorter (2 heads of 32, 1 024 tokens: 2.1e-7 against 1.3e-7; 160 heads of 112, 4 680 tokens: 8.7e-7 against
     // 5.0e-7).  With these it is no further off at any size measured (1.0e-7, 4.9e-7), for less than 0.5 us per launch.  Adding
-    // every tile's products to the share's sum instead was as exact and up to 20 % slower.  Sixteen waves
-    // make 32 sums, four 24.
+    // every tile's products to the share's sum instead was as exact and up to 20 % slower.
     static constexpr int kChains = VEC == 2 ? 2 : 1;
-    static constexpr int kSlot = F * F + F;                // a wave's part in LDS: state, then key sums
+    static constexpr int FQ = kQuarter ? F / 2 : F;        // features of the part that is summed, on both axes
+    static constexpr int kSlot = FQ * FQ + F;              // a wave's part in LDS: state, then key sums
     static constexpr int kParts = kSplit ? kWaves / 4 : kWaves;   // waves that hold the same part of the state
     static constexpr int kWgTokens = kParts * TILE;
-    static_assert(!kSplit || (TILE == kF32WideTile && DEPTH * kChains == kF32WideSums), "f32_sole_tokens counts on these");
+    // of a head that one workgroup sums, each running sum takes at most the tokens that f32_sole_tokens counts on
+    static_assert(!kSplit || kF32WideTile * kF32WideSums <= kWgTokens * DEPTH * kChains * 2, "see f32_sole_tokens");
     static constexpr int lds_bytes() {
         constexpr int slots = kWaves * kSlot * 4, tab = ROPE == kRope3D ? kRope3dLdsBytes : 0;   // tables, then slots
         return slots > tab ? slots : tab;
@@ -145,23 +157,25 @@ template <typename T, int D, bool SOLE, int ROPE> struct StateF32 {
 };
 
 // grid = (C, B*H), block = 64 * kWaves; arguments and the partials in the workspace as in state_mfma_d64.  No workgroup waits for another:
-// SOLE (C = 1) stores the new state, otherwise state_reduce adds the partials up.  These calls stay free of waits because they
-// always were: they may run beside anything on other streams, and be replayed without preparation.
-template <typename T, int D, bool SOLE, int ROPE>
-__global__ __launch_bounds__((64 * StateF32<T, D, SOLE, ROPE>::kWaves)) void state_f32(
-    const T *__restrict__ K, const T *__restrict__ V, RopeArg rope, TokStrides st, int H, int t0, int t1, int C,
+// with kF32Sole (C = 1) and kF32Quarters (grid = quad_grid(1, B*H, kDies), C = 1) the new state is stored, otherwise state_reduce adds the partials up.  These calls stay
+// free of waits because they always were: they may run beside anything on other streams, and be replayed without preparation.
+template <typename T, int D, int HOW, int ROPE>
+__global__ __launch_bounds__((64 * StateF32<T, D, HOW, ROPE>::kWaves), (StateF32<T, D, HOW, ROPE>::kWaves / 4)) void state_f32(
+    const T *__restrict__ K, const T *__restrict__ V, RopeArg rope, TokStrides st, int H, int BH, int t0, int t1, int C,
     const float *S_in, const float *z_in, float *S_out, float *z_out, void *__restrict__ ws, int order)
 {
-    using P = StateF32<T, D, SOLE, ROPE>;
-    constexpr int kThreads = 64 * P::kWaves, kParts = P::kParts, VEC = P::VEC, W = P::W, U = P::U, TILE = P::TILE, DEPTH = P::DEPTH, F = P::F, E = (int)sizeof(T);
+    using P = StateF32<T, D, HOW, ROPE>;
+    constexpr int kThreads = 64 * P::kWaves, kParts = P::kParts, VEC = P::VEC, NB = P::NB, W = P::W, U = P::U, TILE = P::TILE, DEPTH = P::DEPTH, F = P::F, E = (int)sizeof(T);
     constexpr int elems = D * D + D;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
     const WgRole role(C, order);
-    const int c = role.c, bh = role.bh;
+    int c = role.c, bh = role.bh, quarter = 0;
+    if (P::kQuarter && !quad_role((int)blockIdx.x, 1, BH, kDies, (order & kOrderChunkMajor) != 0, c, bh, quarter)) return;
     const int b = bh / H, h = bh % H;
+    const bool hi_k = quarter & 1, hi_v = quarter & 2;      // the upper half of the blocks
 
     const int kb = P::kSplit ? wave & 1 : 0, vb = P::kSplit ? (wave >> 1) & 1 : 0;
     const int n_tiles = (t1 - t0 + TILE - 1) / TILE;
@@ -204,12 +218,13 @@ __global__ __launch_bounds__((64 * StateF32<T, D, SOLE, ROPE>::kWaves)) void sta
     const float inv_rc = ROPE == kRope3D ? 1.0f / (float)(rope.r3.rows * rope.r3.cols) : 0.f;
     const float inv_cols = ROPE == kRope3D ? 1.0f / (float)rope.r3.cols : 0.f;
 
-    f32x4 acc[DEPTH][P::kChains][VEC][VEC] = {};
+    f32x4 acc[DEPTH][P::kChains][NB][NB] = {};
     float zs[VEC] = {};
     for (int i0 = 0; i0 < walk.count; i0 += DEPTH) {
 #pragma unroll
         for (int s = 0; s < DEPTH; ++s) {
-            if (i0 + s >= walk.count) break;     // short shares: the rest of the round would be code and no work
+            // short shares: the rest of the round would be code and no work (the wide ones skip only the products: leaving the loop costs registers there)
+            if (D == 32 && i0 + s >= walk.count) break;
             __builtin_amdgcn_sched_barrier(0);   // stages stay in program order
             float kf[U][VEC], vf[U][VEC], zt[VEC];
 #pragma unroll
@@ -242,22 +257,24 @@ __global__ __launch_bounds__((64 * StateF32<T, D, SOLE, ROPE>::kWaves)) void sta
             for (int e = 0; e < VEC; ++e) zs[e] += zt[e];
             request(s, i0 + s + DEPTH);
             __builtin_amdgcn_sched_barrier(0);
+            if (D == 32 || i0 + s < walk.count)
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+                for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int i = 0; i < VEC; ++i)
+                    for (int i = 0; i < NB; ++i)
 #pragma unroll
-                    for (int j = 0; j < VEC; ++j) {
-                        f32x4 &a = acc[s][u % P::kChains][i][j];
-                        a = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[u][i], vf[u][j], a, 0, 0, 0);
-                    }
+                        for (int j = 0; j < NB; ++j) {
+                            f32x4 &a = acc[s][u % P::kChains][i][j];
+                            const float k0 = kf[u][i], k1 = kf[u][VEC - NB + i], v0 = vf[u][j], v1 = vf[u][VEC - NB + j];
+                            a = __builtin_amdgcn_mfma_f32_16x16x4f32(hi_k ? k1 : k0, hi_v ? v1 : v0, a, 0, 0, 0);
+                        }
         }
     }
-    f32x4 sum[VEC][VEC];
+    f32x4 sum[NB][NB];
 #pragma unroll
-    for (int i = 0; i < VEC; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) {
+        for (int j = 0; j < NB; ++j) {
             f32x4 x[DEPTH];
 #pragma unroll
             for (int s = 0; s < DEPTH; ++s) {
@@ -270,28 +287,47 @@ __global__ __launch_bounds__((64 * StateF32<T, D, SOLE, ROPE>::kWaves)) void sta
         }
 
     // The wave's part in [k][v] order in its LDS slot: element r of block (i, j) is key feature VEC (4 g + r) + i, value
-    // feature VEC m + j, so a lane's blocks j make VEC consecutive floats.
+    // feature VEC m + j, so a lane's blocks j make VEC consecutive floats.  (A quarter's: NB in the place of VEC.)
     float *slots = reinterpret_cast<float *>(lds), *mine = slots + wave * P::kSlot;
     wg_barrier();                                   // everybody is done with the tables
 #pragma unroll
-    for (int i = 0; i < VEC; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            float *row = mine + (VEC * (4 * g + r) + i) * F + VEC * m;
+            float *row = mine + (NB * (4 * g + r) + i) * P::FQ + NB * m;
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) row[j] = sum[i][j][r];
+            for (int j = 0; j < NB; ++j) row[j] = sum[i][j][r];
         }
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
         float x = zs[e];
         x += __shfl_xor(x, 16);
         x += __shfl_xor(x, 32);
-        if (lane < 16) mine[F * F + VEC * m + e] = x;
+        if (lane < 16) mine[P::FQ * P::FQ + VEC * m + e] = x;
     }
     wg_barrier();
     float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * elems, *out = partials + (size_t)c * elems;
     const HeadState hs{S_in ? S_in + (size_t)bh * D * D : nullptr, z_in + (size_t)bh * D, S_out + (size_t)bh * D * D,
                        z_out + (size_t)bh * D};
+    if constexpr (P::kQuarter) {
+        auto total = [&](const float *src) __attribute__((always_inline)) {
+            float x[kParts];
+#pragma unroll
+            for (int p = 0; p < kParts; ++p) x[p] = src[p * P::kSlot];
+#pragma unroll
+            for (int h = kParts / 2; h >= 1; h /= 2)
+#pragma unroll
+                for (int p = 0; p < h; ++p) x[p] += x[p + h];
+            return x[0];
+        };
+        for (int e = tid; e < P::FQ * P::FQ; e += kThreads) {
+            const int kk = e / P::FQ, vv = e % P::FQ;
+            const int at = (VEC * (kk / NB) + (hi_k ? VEC - NB : 0) + kk % NB) * D + VEC * (vv / NB) + (hi_v ? VEC - NB : 0) + vv % NB;
+            hs.S_out[at] = (hs.S_in ? hs.S_in[at] : 0.f) + total(slots + e);
+        }
+        if (quarter == 0 && tid < D) hs.z_out[tid] = (hs.S_in ? hs.z_in[tid] : 0.f) + total(slots + P::FQ * P::FQ + tid);
+        return;
+    }
     auto unit = [&](int u) __attribute__((always_inline)) {
         const float *src = slots + 2 * u;
         if constexpr (P::kSplit) {
@@ -308,7 +344,7 @@ __global__ __launch_bounds__((64 * StateF32<T, D, SOLE, ROPE>::kWaves)) void sta
             for (int p = 0; p < h; ++p) x[p] += x[p + h];
         return x[0];
     };
-    if (SOLE) {
+    if (P::kAlone) {
         state_store_sole<kThreads, D>(hs, tid, unit);
         return;
     }

@@ -160,21 +160,23 @@ template <int ROPE> void init_quad_kernels(Device &d)
 template <typename T_, int D_, int ROPE_> struct KernelsF32 {
     using T = T_;
     static constexpr int D = D_, ROPE = ROPE_;
-    static constexpr auto state = state_f32<T, D, true, ROPE>;
-    static constexpr auto state_partial = state_f32<T, D, false, ROPE>;
+    template <int HOW> using P = StateF32<T, D, HOW, ROPE>;
+    template <int HOW> static constexpr auto state = state_f32<T, D, HOW, ROPE>;
+    static constexpr bool kHasQuarters = D <= 64;
     static constexpr auto apply = apply_f32<T, D, ROPE>;
-    static constexpr int state_lds = StateF32<T, D, true, ROPE>::lds_bytes();
-    static constexpr int state_threads = 64 * StateF32<T, D, true, ROPE>::kWaves;
-    static constexpr int partial_lds = StateF32<T, D, false, ROPE>::lds_bytes();
     static constexpr int apply_lds = ROPE == kRope3D ? kRope3dLdsBytes : 0;
-    static constexpr int state_wg_tokens = StateF32<T, D, false, ROPE>::kWgTokens, apply_wg_tokens = ApplyF32<D>::kWgTokens;
+    static constexpr int state_wg_tokens = P<kF32Shared>::kWgTokens, apply_wg_tokens = ApplyF32<D>::kWgTokens;
 };
 template <typename T, int D, int ROPE> void init_f32_kernels()
 {
     using KN = KernelsF32<T, D, ROPE>;
     const auto attr = hipFuncAttributeMaxDynamicSharedMemorySize;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state), attr, KN::state_lds);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state_partial), attr, KN::partial_lds);
+    auto init = [&](auto how) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::template state<how()>), attr, KN::template P<how()>::lds_bytes());
+    };
+    init(std::integral_constant<int, kF32Shared>{});
+    init(std::integral_constant<int, kF32Sole>{});
+    if constexpr (KN::kHasQuarters) init(std::integral_constant<int, kF32Quarters>{});
 }
 
 template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
@@ -522,10 +524,22 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
             using T = typename KN::T;
             const bool sole = n <= f32_sole_tokens(s.d, s.BH, s.elem_bytes, rope.mode != kRopeNone);
             const int C = sole ? 1 : plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
-            const auto kernel = C == 1 ? KN::state : KN::state_partial;
-            kernel<<<dim3(C, s.BH), C == 1 ? KN::state_threads : kThreads, C == 1 ? KN::state_lds : KN::partial_lds, stream>>>(
-                static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, t0, t1, C, S_in, z_in, S_out,
-                z_out, ws, state_order(layout_of(s), rope.mode == kRopeTable));
+            auto launch = [&](auto how, dim3 grid) {
+                using P = typename KN::template P<how()>;
+                KN::template state<how()><<<grid, 64 * P::kWaves, P::lds_bytes(), stream>>>(
+                    static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, s.BH, t0, t1, C, S_in, z_in, S_out, z_out, ws,
+                    state_order(layout_of(s), rope.mode == kRopeTable));
+            };
+            if (C > 1) launch(std::integral_constant<int, kF32Shared>{}, dim3(C, s.BH));
+            else {
+                // Quarters of a head while they all fit on the device at once.
+                if constexpr (KN::kHasQuarters)
+                    if (4 * s.BH <= dev.num_cu) {
+                        launch(std::integral_constant<int, kF32Quarters>{}, dim3(quad_grid(1, s.BH, kDies)));
+                        return;
+                    }
+                launch(std::integral_constant<int, kF32Sole>{}, dim3(1, s.BH));
+            }
             if (C > 1)
                 state_reduce<KN::D, false, true><<<rgrid, kThreads, 0, stream>>>(wsf, C, kMaxChunks, S_in, z_in, S_out, z_out);
         });
