@@ -16,9 +16,9 @@
 //           feature(j, 0) + q .. feature(j, 3) + q; the state is kept in registers in the matching order.  Output block b holds features NB*n + b, so that a
 //           lane ends up with NB consecutive features of a token and stores them as they are.
 //
-// Measured (both kernels of a layer, before: plain FMAs out of LDS): fp32, 32 heads of 64, 4 680 tokens 120 -> 45.6 us;
-// bf16, 128 heads of 32, 4 096 tokens 130 -> 40.5 us.
-// What is left above the streams' time is the start of the kernels.
+// Measured (a layer, in turn: plain FMAs out of LDS; this with four waves in the state kernel; with eight, and the state in pieces for bf16): fp32, 32 heads
+// of 64, 4 680 tokens 120 -> 45.6 -> 43.4 us (3.5 TB/s); bf16, 128 heads of 32, 4 096 tokens 130 -> 40.4 -> 34.4 us (3.9 TB/s).
+// What is left above the streams' time is the start of the kernels and the launch that adds the partial states up.
 //
 // d <= 64: a wave holds the whole state and works alone on its tiles.  d = 112, 128: the waves of a workgroup
 // share the tiles, in the state kernel as 64 x 64 quadrants (each half row is loaded by two waves, the second out
@@ -119,7 +119,9 @@ template <int N> __device__ __forceinline__ void rotate_pairs(float (&f)[N], con
 //   kF32Sole      one workgroup, which stores the new state.
 //   kF32Quarters  four workgroups, all tokens and a quarter of the state each (d = 32 and 64): half of the 16 x 16 blocks in either direction.  They load
 //                 what one would, the second to fourth time out of their die's L2, but the matrix products, of which one compute unit needs
-//                 3.5 us for 1 024 tokens of 32 features or 256 of 64, are shared out and nothing has to be added up: the same bits.
+//                 3.5 us for 1 024 tokens of 32 features or 256 of 64, are shared out and nothing has to be added up: the same bits.  (Layers: 2 heads of 32,
+//                 1 024 tokens 13.7 -> 12.4 us, 64 heads of 64, 192 tokens 15.4 -> 12.1; with the quarters on four dies 8 heads, 640
+//                 tokens had taken 13.3 us instead of 11.8, on one 11.0.)
 // Eight waves, two to a SIMD, so that one multiplies while the other converts and requests (four waves with three tiles in flight each,
 // before: 32 heads of 64, 4 680 tokens, layer 45.6 -> 43.5 us; 20 heads of 112 88.6 -> 83.1; 128 heads of 32, bf16, 4 096 tokens, rotated 48.5 -> 45.0).  At d = 32
 // a head that is not shared by its tokens gets sixteen waves in the 128 registers that leaves each (2 heads, 1 024 tokens, one workgroup: 11.6 -> 10.0 us).
@@ -437,6 +439,37 @@ __global__ __launch_bounds__(kThreads, 2) void apply_f32(
             for (int e = 0; e < NB; ++e) sr[j][q][e] = x[e];            // columns that do not exist are never stored
         }
 
+    // bf16 tokens without a rotation (d = 32): the state in three bf16 pieces, which hold all of its 24 bits, so the products stay those of
+    // fp32, at a fifth of the matrix core's time.  Lane (n, g)'s eight features of a token are the operand of one 16 x 16 x 32 product.
+    // (Layer of 128 heads, 4 096 tokens 36.2 -> 34.4 us; rotated features are fp32 values and stay with fp32 products.)
+    constexpr bool kPieces = E == 2 && ROPE == kRopeNone;
+    bf16x8 piece[kPieces ? 3 : 1][NB];
+    if constexpr (kPieces) {
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            uint32_t w[3][4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const int j = p >> 1, q = 2 * (p & 1);
+                uint32_t half[2][3];
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    float x = sr[j][q + a][e];
+#pragma unroll
+                    for (int l = 0; l < 3; ++l) {
+                        half[a][l] = __float_as_uint(x) >> 16;          // the leading eight bits
+                        const float y = __uint_as_float(half[a][l] << 16);
+                        x = x == y ? 0.f : x - y;                       // (an infinity is its first piece)
+                    }
+                }
+#pragma unroll
+                for (int l = 0; l < 3; ++l) w[l][p] = half[0][l] | half[1][l] << 16;
+            }
+#pragma unroll
+            for (int l = 0; l < 3; ++l) piece[l][e] = __builtin_bit_cast(bf16x8, u32x4{w[l][0], w[l][1], w[l][2], w[l][3]});
+        }
+    }
+
     for (int i0 = 0; i0 < walk.count; i0 += DEPTH) {
 #pragma unroll
         for (int s = 0; s < DEPTH; ++s) {
@@ -478,7 +511,18 @@ __global__ __launch_bounds__(kThreads, 2) void apply_f32(
             __builtin_amdgcn_sched_barrier(0);
             den += __shfl_xor(den, 16);
             den += __shfl_xor(den, 32);                                 // that of MFMA row n, in all its lanes
+            // bf16: the row's reciprocal, once per token (a layer of 128 heads of 32, 4 096 tokens 39.4 -> 36.2 us); the product's error is far below
+            // the result's rounding
+            const float scale = E == 2 ? 1.0f / (den + eps) : den + eps;
             f32x4 acc[NB] = {};
+            if constexpr (kPieces) {
+                const u32x4 w = {pack_bf16x2(qf[0][0], qf[0][1]), pack_bf16x2(qf[0][2], qf[0][3]), pack_bf16x2(qf[1][0], qf[1][1]), pack_bf16x2(qf[1][2], qf[1][3])};
+#pragma unroll
+                for (int l = 2; l >= 0; --l)                            // small terms first
+#pragma unroll
+                    for (int e = 0; e < NB; ++e)
+                        acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), piece[l][e], acc[e], 0, 0, 0);
+            } else
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -490,10 +534,10 @@ __global__ __launch_bounds__(kThreads, 2) void apply_f32(
             const uint32_t out = exists ? walk.offset<TILE>(i, row_bytes) + offO : kOutOfRange;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float dd = __shfl(den, 4 * g + r) + eps;
+                const float dd = __shfl(scale, 4 * g + r);
                 float o[NB];
 #pragma unroll
-                for (int e = 0; e < NB; ++e) o[e] = acc[e][r] / dd;
+                for (int e = 0; e < NB; ++e) o[e] = E == 2 ? acc[e][r] * dd : acc[e][r] / dd;
                 store_words(rO, out + (uint32_t)(4 * r) * row_bytes, narrow<T, NB>(o));
             }
         }
