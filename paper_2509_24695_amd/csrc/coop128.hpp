@@ -191,6 +191,96 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
     for (int i0 = DEPTH; i0 < st.walk.count; i0 += DEPTH) round(i0);
 }
 
+// The same for eight waves with NB = 1, two tiles a step, pipelined over two Q and two O tiles of each in LDS, with one barrier per step: between two barriers a
+// wave multiplies step i, prepares step i + 1 (ReLU, denominators, rotation) and stores step i - 1, so that vector and matrix
+// instructions of one wave can overlap, and a step is one meeting of the waves instead of two.  The tiles are 64 tokens of one head (WAVES = 8, the one-launch block
+// step) or 32 tokens each of two heads (WAVES = 4, apply_mfma_d128 with two heads to a workgroup); `wave` counts the workgroup's
+// eight.  The stream's rotation is at the first step (begin_tile).
+constexpr int kStepTileBytes = 2 * kCoopTile;    // a step's 64 rows
+constexpr int step_apply_lds_bytes() { return 4 * kStepTileBytes + 2 * 64 * 4; }
+template <int DEPTH, int ROPE, int WAVES, bool NT>
+__device__ __forceinline__ void apply_tiles_steps(CoopApplyStream<DEPTH, ROPE, WAVES, 1, NT> &st, unsigned char *lds, int wave, int lane,
+                                                  const ApplyOperands<128, true, 1, false> &A, const float (&zr)[8], float eps)
+{
+    static_assert(DEPTH % 2 == 0, "a stage's tile lies in the same buffer every round");
+    constexpr int NLD = 2, STEP = CoopApplyStream<DEPTH, ROPE, WAVES, 1, NT>::STEP;
+    const int t = wave >> 2, vb = wave & 3, n = lane & 31, g = lane >> 5;
+    const int my_row = 8 * wave + (lane >> 4);                                      // + 4 j: the rows this lane loads and stores
+    const int wr_off = my_row * kCoopRow + (lane & 15) * 16;
+    const int b_off = (32 * t + n) * kCoopRow + 16 * g, o_off = (32 * t + n) * kCoopRow + (32 * vb + 16 * g) * 2;
+    auto q_tile = [&](int p) __attribute__((always_inline)) { return lds + p * kStepTileBytes; };
+    auto o_tile = [&](int p) __attribute__((always_inline)) { return lds + (2 + p) * kStepTileBytes; };
+    auto dens = [&](int p) __attribute__((always_inline)) { return reinterpret_cast<float *>(lds + 4 * kStepTileBytes) + p * 64; };
+
+    auto prepare = [&](int i, int s) __attribute__((always_inline)) {
+        f32x2 cs[NLD][4];
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) st.rot.fetch(s, j, cs[j]);
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) {
+            const u32x4 pq = relu_bf16x8(st.q[s][j]);                          // phi(Q)
+            float dot = bf16_lo(pq.x) * zr[0];
+            dot = __builtin_fmaf(bf16_hi(pq.x), zr[1], dot);
+            dot = __builtin_fmaf(bf16_lo(pq.y), zr[2], dot);
+            dot = __builtin_fmaf(bf16_hi(pq.y), zr[3], dot);
+            dot = __builtin_fmaf(bf16_lo(pq.z), zr[4], dot);
+            dot = __builtin_fmaf(bf16_hi(pq.z), zr[5], dot);
+            dot = __builtin_fmaf(bf16_lo(pq.w), zr[6], dot);
+            dot = __builtin_fmaf(bf16_hi(pq.w), zr[7], dot);
+            dot = row16_sum(dot);
+            dens(s & 1)[my_row + 4 * j] = dot;                                 // the same value from the row's sixteen lanes
+            *reinterpret_cast<u32x4 *>(q_tile(s & 1) + wr_off + 4 * j * kCoopRow) = st.rot.rotate_with(pq, cs[j]);
+        }
+    };
+    uint32_t out_prev = kOutOfRange;
+    auto store = [&](int p) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < NLD; ++j)
+            store_stream16<NT>(st.rO, out_prev + st.lane_off + (uint32_t)j * 4u * st.row_bytes,
+                               *reinterpret_cast<const u32x4 *>(o_tile(p) + wr_off + 4 * j * kCoopRow));
+    };
+    if (st.walk.count == 0) return;
+    prepare(0, 0);
+    lds_barrier();
+    for (int i0 = 0; i0 < st.walk.count; i0 += DEPTH) {
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) {
+            if (i0 + s >= st.walk.count) break;
+            __builtin_amdgcn_sched_barrier(0);
+            st.request(s, i0 + s + DEPTH);           // the stage was prepared one step ago
+            st.rot.template begin_tile<STEP>(st.walk, i0 + s + 1);     // past the share: zeros
+            __builtin_amdgcn_sched_barrier(0);
+            const float den = dens(s & 1)[32 * t + n];
+            bf16x8 bq[8];
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) bq[ks] = *reinterpret_cast<const bf16x8 *>(q_tile(s & 1) + b_off + 32 * ks);
+            f32x16 acc = {};
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+                for (int p = 1; p >= 0; --p)         // small (lo) terms first
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A.s[p][0][ks], bq[ks], acc, 0, 0, 0);
+            store((s & 1) ^ 1);
+            prepare(i0 + s + 1, (s + 1) % DEPTH);
+            const float inv = 1.0f / (den + eps);
+            u32x4 lo4, hi4;
+            lo4.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
+            lo4.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
+            lo4.z = pack_bf16x2(acc[4] * inv, acc[5] * inv);
+            lo4.w = pack_bf16x2(acc[6] * inv, acc[7] * inv);
+            hi4.x = pack_bf16x2(acc[8] * inv, acc[9] * inv);
+            hi4.y = pack_bf16x2(acc[10] * inv, acc[11] * inv);
+            hi4.z = pack_bf16x2(acc[12] * inv, acc[13] * inv);
+            hi4.w = pack_bf16x2(acc[14] * inv, acc[15] * inv);
+            *reinterpret_cast<u32x4 *>(o_tile(s & 1) + o_off) = lo4;
+            *reinterpret_cast<u32x4 *>(o_tile(s & 1) + o_off + 16) = hi4;
+            out_prev = st.valid ? st.walk.template offset<STEP>(i0 + s, st.row_bytes) : kOutOfRange;
+            lds_barrier();
+        }
+    }
+    store((st.walk.count - 1) & 1);
+}
+
 // ---- kernels ---------------------------------------------------------------------------------------
 
 // Apply for d = 112 or 128.  grid = (C, B*H), block = 64 * WAVES; workgroup c owns the steps
@@ -206,7 +296,7 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
 // One head to a workgroup (odd H, see pairs_heads): the slower sums by shuffles, whose pace keeps the heads more in step
 // (state and apply 271 us, with row permutations 288 to 302; factored tables 293 and 306).
 // Three workgroups to a compute unit leave a wave 168 registers; with factored tables the compiler takes 177 if it may.
-template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB, bool NT, int HEADS>
+template <bool HILO, int DEPTH, int ROPE, int WAVES, int NB, bool NT, int HEADS, bool STEPS>
 __global__ __launch_bounds__(64 * WAVES * HEADS, NB != 1 ? 1 : ROPE == kRope3D && HEADS == 1 ? 3 : 2) void apply_mfma_d128(
     const uint16_t *__restrict__ Q, uint16_t *__restrict__ O, RopeArg rope, TokStrides st, int H,
     int d, int t0, int t1, int C, const float *__restrict__ S, const float *__restrict__ z, float eps, int order)
@@ -220,7 +310,7 @@ __global__ __launch_bounds__(64 * WAVES * HEADS, NB != 1 ? 1 : ROPE == kRope3D &
     const uint16_t *Qh = Q + b * st.b + h * st.h;
     uint16_t *Oh = O + b * st.b + h * st.h;
     constexpr int STEP = 8 * WAVES * NB;
-    constexpr int kTiles = coop_apply_lds_bytes<WAVES, NB>(), kTabs = HEADS * kTiles;
+    constexpr int kTiles = coop_apply_lds_bytes<WAVES, NB>(), kTabs = STEPS ? step_apply_lds_bytes() : HEADS * kTiles;
     const int n_steps = (t1 - t0 + STEP - 1) / STEP;
 
     CoopApplyStream<DEPTH, ROPE, WAVES, NB, NT> stream(Qh, Oh, rope, lds + kTabs, st.n, t1, d,
@@ -240,6 +330,11 @@ __global__ __launch_bounds__(64 * WAVES * HEADS, NB != 1 ? 1 : ROPE == kRope3D &
         const int k = 8 * (lane & 15) + e;
         const float x = z[(size_t)bh * d + (k < d ? k : 0)];   // loaded by every lane: a load under a condition is a branch
         zr[e] = k < d ? x : 0.f;
+    }
+    if constexpr (STEPS) {
+        stream.rot.template begin_tile<STEP>(stream.walk, 0);
+        apply_tiles_steps(stream, lds, wg_wave, lane, A, zr, eps);
+        return;
     }
     apply_tiles_coop<HILO, NT || HEADS == 2>(stream, lds + half * kTiles, wave, lane, A, zr, eps);
 }

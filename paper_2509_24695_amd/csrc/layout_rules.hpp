@@ -106,13 +106,16 @@ inline int wide_apply_wgs_per_cu(const TokenLayout &t, bool rotated, int num_cu)
 // apply, one / two heads to a workgroup:
 //   plain            20 heads, 4 680 tokens 37.8 / 37.1, 14 040 71.2 / 68.6, 32 760 149 / 140; 40 heads, 9 360 88.6 / 85.6, 32 760 274 / 253;
 //                    160 heads, 6 240 238 / 219
-//   rotated          three workgroups of one head per compute unit hide the lookups better than two heads, until drift costs more.  The apply
-//                    alone: factored tables 20 heads, 14 040 tokens 40.7 / 42, 17 160 47.1 / 48.6, 74 880 210 / 170, 40 heads, 32 760 180 / 156,
-//                    80 heads, 17 160 191 / 160; full table 20 heads, 17 160 52 / 55, 32 760 89.5 / 92, 74 880 202 / 195, 40 heads, 32 760 178 / 169
+//   rotated          with one barrier per step (pipelines_pairs) from 65 536 head-tokens on, below it is level.  Layers: factored tables 20 heads, 4 680 tokens 35.9 / 35.3, 9 360 74.4 / 70.2, 80 heads, 4 680 tokens 99.1 / 93.8, 160 heads, 1 560 75.0 / 71.9; full table 20
+//                    heads, 9 360 63.3 / 62.1, 17 160 100.5 / 95.6, 32 760 173 / 165, 160 heads, 1 560 84.7 / 81.5
 inline bool pairs_heads(const TokenLayout &t, bool rotated, int n_tokens)
 {
-    return t.shares_lines() && t.H % 2 == 0 && (!rotated || (int64_t)t.BH * n_tokens >= 1 << 20);
+    return t.shares_lines() && t.H % 2 == 0 && (!rotated || (int64_t)t.BH * n_tokens >= 1 << 16);
 }
+// ... their steps with one barrier instead of two (apply_tiles_steps): 1 to 6 % less (40 heads, 32 760 tokens, plain 252 / 241 us, factored tables 284 / 269, full
+// table 324 / 307; 16 heads, 75 600, factored 258 / 249), but plain where the token rows are multiples of 1 KB (32 heads: 7 KB), which it costs
+// 2 to 5 %: 64 heads, 32 760 tokens 405 / 427, 14 040 189 / 193, 32 heads, 32 760 214 / 220.
+inline bool pipelines_pairs(const TokenLayout &t, bool rotated) { return rotated || t.stride_n * t.elem_bytes % 1024 != 0; }
 
 // d = 112 and 128 without a full table, state: shared tiles (coop_state.hpp) instead of a state in every wave (wide_state.hpp) up to 2 048
 // tokens per workgroup: there the end, which the sum over the waves makes longer, counts.  State + apply, us, a state per wave / shared tiles:
@@ -216,8 +219,7 @@ inline bool wide_step_serves(const TokenLayout &t, int n_tokens, int C, bool ful
     const int64_t head_tokens = (int64_t)t.BH * n_tokens;
     if (C > 1) {
         if (t.BH < 8) return n_tokens <= 2048;
-        if (full_table) return head_tokens <= 200000;
-        if (t.shares_lines() && !factored_tables) return head_tokens <= 200000;
+        if (full_table || t.shares_lines()) return head_tokens <= 200000;
         if (C == 2 && (t.d == 112 || factored_tables)) return n_tokens <= 3072;
         return !factored_tables || n_tokens <= 4096 * C;
     }

@@ -122,12 +122,14 @@ template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     static constexpr int coop_lds = coop_state_lds<ROPE>();
     template <bool SOLE> static constexpr auto fused_form = block_step_mfma_wide<ROPE, !SHARED, SOLE>;   // block step in one launch
     static constexpr int fused_lds = block_step_wide_lds<ROPE>();
-    template <int HEADS> static constexpr auto apply_heads =
-        apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB, !SHARED, HEADS>;
-    static constexpr auto apply = apply_heads<1>;
+    template <int HEADS, bool STEPS> static constexpr auto apply_heads =
+        apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB, !SHARED, HEADS, STEPS>;
+    static constexpr auto apply = apply_heads<1, false>;
+    // two heads to a workgroup, one barrier per step or (plain only) two
+    static auto apply_pair(bool steps) { return ROPE != kRopeNone || steps ? apply_heads<2, true> : apply_heads<2, ROPE != kRopeNone>; }
     static constexpr int state_lds = kWideLdsBytes;
     static constexpr int apply_lds = coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
-    static constexpr int apply_pair_lds = 2 * coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
+    static constexpr int apply_pair_lds = step_apply_lds_bytes() + kTab;
     static constexpr int state_wg_tokens = kWideWgTokens;
     static_assert(state_wg_tokens == 4 * kWideTile, "four waves, a tile each");
     static constexpr int apply_wg_tokens = 8 * kCoopApplyWaves * kCoopApplyNB;   // the waves of a workgroup share its tiles
@@ -186,7 +188,8 @@ template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state), attr, KN::state_lds);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state_partial), attr, KN::state_lds);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::apply), attr, KN::apply_lds);
-    if constexpr (KN::kShared) (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::template apply_heads<2>), attr, KN::apply_pair_lds);
+    if constexpr (KN::kShared)
+        for (bool steps : {false, true}) (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::apply_pair(steps)), attr, KN::apply_pair_lds);
     int per_cu = 0;
     if constexpr (DP == 64) {                      // the one-launch block step exists for d = 64 only
         int least = INT_MAX;
@@ -593,7 +596,7 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
             int heads = 1, lds = KN::apply_lds;
             if constexpr (KN::kShared)
                 if (pair) {
-                    kernel = KN::template apply_heads<2>;
+                    kernel = KN::apply_pair(pipelines_pairs(layout_of(s), rope.mode != kRopeNone));
                     heads = 2;
                     lds = KN::apply_pair_lds;
                 }

@@ -46,7 +46,7 @@ def test_lines(exe):
     calls = {(112, 1, 20, 75600, "none", "bhnd"): 1, (112, 1, 20, 75600, "axes", "bhnd"): 0, (112, 1, 20, 32760, "axes", "bhnd"): 1,
              (112, 8, 16, 1560, "none", "bhnd"): 1, (112, 4, 32, 4680, "none", "bhnd"): 0, (128, 4, 32, 4680, "none", "bhnd"): 1,
              (112, 1, 20, 9360, "table", "bhnd"): 1, (112, 1, 20, 32760, "table", "bhnd"): 0, (112, 1, 20, 4680, "none", "bnhd"): 1,
-             (112, 1, 20, 14040, "none", "bnhd"): 0, (112, 1, 20, 14040, "axes", "bnhd"): 1, (112, 1, 2, 600, "none", "bhnd"): 1,
+             (112, 1, 20, 14040, "none", "bnhd"): 0, (112, 1, 20, 4680, "axes", "bnhd"): 1, (112, 1, 20, 14040, "axes", "bnhd"): 0, (112, 1, 2, 600, "none", "bhnd"): 1,
              (112, 1, 2, 4680, "none", "bhnd"): 0, (112, 5, 26, 2000, "none", "bhnd"): 1, (112, 5, 26, 3120, "none", "bhnd"): 0,
              (112, 5, 26, 2000, "axes", "bhnd"): 0, (112, 10, 40, 9360, "axes", "bhnd"): 1, (112, 8, 20, 4680, "none", "bnhd"): 0,
              (112, 8, 20, 1560, "table", "bhnd"): 0, (112, 8, 32, 9360, "none", "bhnd"): 1, (112, 8, 32, 9360, "axes", "bhnd"): 0}
