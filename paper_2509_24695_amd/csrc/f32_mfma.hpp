@@ -16,9 +16,9 @@
 //           feature(j, 0) + q .. feature(j, 3) + q; the state is kept in registers in the matching order.  Output block b holds features NB*n + b, so that a
 //           lane ends up with NB consecutive features of a token and stores them as they are.
 //
-// Measured (a layer, in turn: plain FMAs out of LDS; this with four waves in the state kernel; with eight, and the state in pieces for bf16): fp32, 32 heads
-// of 64, 4 680 tokens 120 -> 45.6 -> 43.4 us (3.5 TB/s); bf16, 128 heads of 32, 4 096 tokens 130 -> 40.4 -> 34.4 us (3.9 TB/s).
-// What is left above the streams' time is the start of the kernels and the launch that adds the partial states up.
+// Measured (a layer, in turn: plain FMAs out of LDS; this with four waves in the state kernel; with eight, and the state in pieces and the last workgroup's fold
+// for bf16): fp32, 32 heads of 64, 4 680 tokens 120 -> 45.6 -> 43.4 us (3.5 TB/s); bf16, 128 heads of 32, 4 096 tokens 130 -> 40.4 -> 33.0 us (4.1 TB/s).
+// What is left above the streams' time is the start of the kernels and adding the partial states up.
 //
 // d <= 64: a wave holds the whole state and works alone on its tiles.  d = 112, 128: the waves of a workgroup
 // share the tiles, in the state kernel as 64 x 64 quadrants (each half row is loaded by two waves, the second out
@@ -115,7 +115,7 @@ template <int N> __device__ __forceinline__ void rotate_pairs(float (&f)[N], con
 // ---- state ----------------------------------------------------------------------------------------------------
 
 // How a head's tokens and its state are shared out (HOW):
-//   kF32Shared    C workgroups, a share of the tokens each; state_reduce adds their partial states up.
+//   kF32Shared    C workgroups, a share of the tokens each; the last of them or state_reduce adds their partial states up.
 //   kF32Sole      one workgroup, which stores the new state.
 //   kF32Quarters  four workgroups, all tokens and a quarter of the state each (d = 32 and 64): half of the 16 x 16 blocks in either direction.  They load
 //                 what one would, the second to fourth time out of their die's L2, but the matrix products, of which one compute unit needs
@@ -158,17 +158,100 @@ template <typename T, int D, int HOW, int ROPE> struct StateF32 {
     }
 };
 
+// A head's C workgroups count themselves in a word of the workspace, whose contents are undefined before the call: the one that finds all others
+// counted is the last and adds the partials up.  Nobody waits.  The word holds tag + workgroups that have stored their partial; `tag` is the
+// call's own, its low six bits zero.  Every workgroup sees to the word early on, while its first tiles are on their way: if it holds no count of this call,
+// it is replaced, provided that it is still what was seen (otherwise another workgroup of the call has been there, and nobody else writes it).  The last one
+// leaves zero, so that a replayed launch, whose tag is the same, starts anew.
+struct LastFold {
+    unsigned long long seen = 0;                   // thread 0's only, like all that follows but arrive()'s result
+    __device__ __forceinline__ void look(unsigned long long *word)
+    {
+        if (threadIdx.x == 0) seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ void open(unsigned long long *word, unsigned long long tag)
+    {
+        if (threadIdx.x != 0) return;
+        unsigned long long was = seen;
+        asm volatile("" : "+v"(was));              // looked at here, behind the requests of the first tiles, and not before
+        if ((was & ~63ull) != tag)
+            (void)__hip_atomic_compare_exchange_strong(word, &was, tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // Called by all threads when the workgroup's partial is stored (coherently): is this the head's last workgroup?  `lds_word` may be in use until then.
+    __device__ __forceinline__ bool arrive(unsigned long long *word, int C, int *lds_word) const
+    {
+        coherent_stores_done();
+        wg_barrier();
+        if (threadIdx.x == 0) {
+            const unsigned long long n = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 63ull;
+            *lds_word = (int)n == C - 1;
+            if ((int)n == C - 1) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        wg_barrier();
+        return *lds_word != 0;
+    }
+};
+// What state_reduce does with TREE, in the same order: the carried state, then sixteen partials at a time.
+template <int THREADS, int D> __device__ __forceinline__ void fold_partials(const HeadState &hs, const float *partials, int C, int tid)
+{
+    constexpr int elems = D * D + D, kWords = elems / 4, kS = D * D / 4, UNITS = (kWords + THREADS - 1) / THREADS;
+    const rsrc_t rP = make_rsrc(partials, (uint32_t)C * (uint32_t)(elems * 4));
+    f32x4 x[UNITS];
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+        const int v = tid + u * THREADS;
+        x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (hs.S_in && v < kWords) x[u] = *reinterpret_cast<const f32x4 *>(v < kS ? hs.S_in + 4 * v : hs.z_in + 4 * (v - kS));
+    }
+    for (int c0 = 0; c0 < C; c0 += 16) {
+        f32x4 p[UNITS][8];
+        auto load = [&](int u, int c) __attribute__((always_inline)) {        // past the last partial and past the state: zeros, nothing is read
+            const int v = tid + u * THREADS;
+            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                rP, v < kWords && c < C ? 16u * (uint32_t)v + (uint32_t)c * (uint32_t)(elems * 4) : kOutOfRange, 0, 16 /* sc1 */));
+        };
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) p[u][j] = load(u, c0 + j);
+        if (c0 + 8 < C)
+#pragma unroll
+            for (int u = 0; u < UNITS; ++u) {
+                f32x4 q[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) q[j] = load(u, c0 + 8 + j);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) p[u][j] += q[j];
+            }
+#pragma unroll
+        for (int u = 0; u < UNITS; ++u) {
+#pragma unroll
+            for (int h = 4; h >= 1; h /= 2)
+#pragma unroll
+                for (int j = 0; j < h; ++j) p[u][j] += p[u][j + h];
+            x[u] += p[u][0];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+        const int v = tid + u * THREADS;
+        if (v < kWords) *reinterpret_cast<f32x4 *>(v < kS ? hs.S_out + 4 * v : hs.z_out + 4 * (v - kS)) = x[u];
+    }
+}
+
 // grid = (C, B*H), block = 64 * kWaves; arguments and the partials in the workspace as in state_mfma_d64.  No workgroup waits for another:
-// with kF32Sole (C = 1) and kF32Quarters (grid = quad_grid(1, B*H, kDies), C = 1) the new state is stored, otherwise state_reduce adds the partials up.  These calls stay
+// with kF32Sole (C = 1) and kF32Quarters (grid = quad_grid(1, B*H, kDies), C = 1) the new state is stored; otherwise the head's last workgroup adds the
+// partials up (LastFold; tag != 0, see f32_last_folds) or state_reduce does.  These calls stay
 // free of waits because they always were: they may run beside anything on other streams, and be replayed without preparation.
 template <typename T, int D, int HOW, int ROPE>
 __global__ __launch_bounds__((64 * StateF32<T, D, HOW, ROPE>::kWaves), (StateF32<T, D, HOW, ROPE>::kWaves / 4)) void state_f32(
     const T *__restrict__ K, const T *__restrict__ V, RopeArg rope, TokStrides st, int H, int BH, int t0, int t1, int C,
-    const float *S_in, const float *z_in, float *S_out, float *z_out, void *__restrict__ ws, int order)
+    const float *S_in, const float *z_in, float *S_out, float *z_out, void *__restrict__ ws, unsigned long long tag, int order)
 {
     using P = StateF32<T, D, HOW, ROPE>;
     constexpr int kThreads = 64 * P::kWaves, kParts = P::kParts, VEC = P::VEC, NB = P::NB, W = P::W, U = P::U, TILE = P::TILE, DEPTH = P::DEPTH, F = P::F, E = (int)sizeof(T);
     constexpr int elems = D * D + D;
+    constexpr bool kCanFold = HOW == kF32Shared && D <= 64;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -209,10 +292,13 @@ __global__ __launch_bounds__((64 * StateF32<T, D, HOW, ROPE>::kWaves), (StateF32
         }
     };
 
+    LastFold fold;
+    if (kCanFold && tag) fold.look(ws_flags(ws, BH, elems, bh, 0));
     Rope3dFill tabs;
     if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);
 #pragma unroll
     for (int s = 0; s < DEPTH; ++s) request(s, s);
+    if (kCanFold && tag) fold.open(ws_flags(ws, BH, elems, bh, 0), tag);
     if (ROPE == kRope3D) {
         rope3d_lds_fill_end(lds, rope.r3, tabs);
         wg_barrier();
@@ -350,6 +436,12 @@ __global__ __launch_bounds__((64 * StateF32<T, D, HOW, ROPE>::kWaves), (StateF32
         state_store_sole<kThreads, D>(hs, tid, unit);
         return;
     }
+    if constexpr (kCanFold)
+        if (tag) {
+            for (int u = tid; u < elems / 2; u += kThreads) store_coherent(out + 2 * u, unit(u));
+            if (fold.arrive(ws_flags(ws, BH, elems, bh, 0), C, reinterpret_cast<int *>(lds))) fold_partials<kThreads, D>(hs, partials, C, tid);
+            return;
+        }
     for (int u = tid; u < elems / 2; u += kThreads) *reinterpret_cast<f32x2 *>(out + 2 * u) = unit(u);
 }
 

@@ -196,6 +196,12 @@ inline int f32_sole_tokens(int d, int BH, int elem_bytes, bool rotated)
     return kTokens[elem_bytes == 2][rotated][BH <= 2 ? 0 : BH <= 16 ? 1 : BH <= 32 ? 2 : BH <= 64 ? 3 : 4];
 }
 
+// fp32 arithmetic, state of a head that C workgroups share: the last of them adds the partial states up (LastFold) instead of a second launch.  One
+// compute unit then reads C partials, which costs what the launch did at 130 KB.  Layers, us, second launch / last workgroup: d = 32
+// (4 KB each), bf16 128 heads, 4 096 tokens, C = 2 34.6 / 33.4, 32 heads, C = 8 16.9 / 16.2, 20 heads, 1 560 tokens, C = 12 11.6 / 11.0; fp32 32 heads, 4 680 tokens 26.5 / 25.9;
+// C = 32 15.5 / 15.8; d = 64 (17 KB), 64 heads, 2 000 tokens, C = 4 39.8 / 38.7, 32 heads, 4 680, C = 8 44.3 / 44.3, 16 heads, 1 560, C = 16 20.1 / 21.5.
+inline bool f32_last_folds(int d, int C) { return d == 32 ? C <= 16 : d == 64 && C <= 4; }
+
 // d = 112 and 128, block step: one launch (block_step_wide.hpp) or two (a state kernel, the apply kernel).  Streams of two to four blocks, two
 // launches / one, us per stream:
 //   plain           20 heads of 112, 4 680 tokens 133 / 120, 32 760 238 / 221, 75 600 503 / 475; 64 heads, 4 680 131 / 120; 8 heads, 1 560 77 / 64; of

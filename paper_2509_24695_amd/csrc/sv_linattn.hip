@@ -527,10 +527,12 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
             using T = typename KN::T;
             const bool sole = n <= f32_sole_tokens(s.d, s.BH, s.elem_bytes, rope.mode != kRopeNone);
             const int C = sole ? 1 : plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
+            const bool folds = C > 1 && f32_last_folds(s.d, C);
+            const unsigned long long tag = folds ? next_epoch() << 6 : 0;
             auto launch = [&](auto how, dim3 grid) {
                 using P = typename KN::template P<how()>;
                 KN::template state<how()><<<grid, 64 * P::kWaves, P::lds_bytes(), stream>>>(
-                    static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, s.BH, t0, t1, C, S_in, z_in, S_out, z_out, ws,
+                    static_cast<const T *>(K), static_cast<const T *>(V), rope.arg, s.st, s.H, s.BH, t0, t1, C, S_in, z_in, S_out, z_out, ws, tag,
                     state_order(layout_of(s), rope.mode == kRopeTable));
             };
             if (C > 1) launch(std::integral_constant<int, kF32Shared>{}, dim3(C, s.BH));
@@ -543,7 +545,7 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
                     }
                 launch(std::integral_constant<int, kF32Sole>{}, dim3(1, s.BH));
             }
-            if (C > 1)
+            if (C > 1 && !folds)
                 state_reduce<KN::D, false, true><<<rgrid, kThreads, 0, stream>>>(wsf, C, kMaxChunks, S_in, z_in, S_out, z_out);
         });
         return launch_status();
