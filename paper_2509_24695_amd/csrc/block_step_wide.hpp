@@ -114,12 +114,15 @@ __global__ __launch_bounds__(kCoopThreads, 2) void block_step_mfma_wide(
         rope3d_lds_fill_end(lds + kCoopTabOffset, rope.r3, tabs);
         wg_barrier();
     }
-    // The queries' positions are worked out when the state phase is over: the compiler would keep them in registers all along.
+    // The queries' positions are worked out when the state phase is over: the compiler would keep them in registers all along.  Factored tables
+    // only: with a full table the rotator holds the rows requested with the first tiles of Q.
     auto q_positions = [&]() __attribute__((always_inline)) {
-        int l = lane;
-        asm volatile("" : "+v"(l));
-        qstream.rot = decltype(qstream.rot)(rope, N, d, 8 * wave + (l >> 4), 4, 4 * (l & 15), 1, lds + kCoopTabOffset);
-        qstream.rot.template begin_tile<kCoopTokens>(walk, 0);
+        if constexpr (ROPE == kRope3D) {
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            qstream.rot = decltype(qstream.rot)(rope, N, d, 8 * wave + (l >> 4), 4, 4 * (l & 15), 1, lds + kCoopTabOffset);
+            qstream.rot.template begin_tile<kCoopTokens>(walk, 0);
+        }
     };
     float *zw = reinterpret_cast<float *>(lds + kCoopZOffset);  // [wave][128]
     ApplyOperands<128, true, 1, false> A;

@@ -129,6 +129,8 @@ struct Rotator<kRopeTable, STEPS, DEPTH> {
         : rT(make_rsrc(a.table, (uint32_t)t1 * (uint32_t)d * 4u)), table_row_bytes((uint32_t)d * 4u),
           lane_off((uint32_t)row0 * (uint32_t)d * 4u + (uint32_t)pair0 * 8u),
           step_bytes((uint32_t)rows_per_step * (uint32_t)d * 4u) {}
+    // A new one holds no rows: assigned over another it would take the requested ones with it.
+    Rotator &operator=(const Rotator &) = delete;
 
     // Requests the table rows of the tile that starts at token tok0 into stage s (nothing
     // is read if !valid: out-of-range offsets return zeros).
