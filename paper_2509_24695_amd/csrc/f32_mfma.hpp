@@ -119,7 +119,7 @@ template <int N> __device__ __forceinline__ void rotate_pairs(float (&f)[N], con
 //   kF32Sole      one workgroup, which stores the new state.
 //   kF32Quarters  four workgroups, all tokens and a quarter of the state each (d = 32 and 64): half of the 16 x 16 blocks in either direction.  They load
 //                 what one would, the second to fourth time out of their die's L2, but the matrix products, of which one compute unit needs
-//                 3.5 us for 1 024 tokens of 32 features or 256 of 64, are shared out and nothing has to be added up: the same bits.  (Layers: 2 heads of 32,
+//                 3.5 us for 1 024 tokens of 32 features or 256 of 64, are shared out and nothing has to be added up: the same bits as one workgroup's.  (Layers: 2 heads of 32,
 //                 1 024 tokens 13.7 -> 12.4 us, 64 heads of 64, 192 tokens 15.4 -> 12.1; with the quarters on four dies 8 heads, 640
 //                 tokens had taken 13.3 us instead of 11.8, on one 11.0.)
 // Eight waves, two to a SIMD, so that one multiplies while the other converts and requests (four waves with three tiles in flight each,
@@ -264,7 +264,8 @@ __global__ __launch_bounds__((64 * StateF32<T, D, HOW, ROPE>::kWaves), (StateF32
 
     const int kb = P::kSplit ? wave & 1 : 0, vb = P::kSplit ? (wave >> 1) & 1 : 0;
     const int n_tiles = (t1 - t0 + TILE - 1) / TILE;
-    const TileWalk walk(t0, kParts * c + (P::kSplit ? wave >> 2 : wave), kParts * C, n_tiles, role.phase(b, order));
+    const int phase = order & kOrderLockstep ? 5 * b : bh;       // of the head worked on: a quarter's is not the grid's
+    const TileWalk walk(t0, kParts * c + (P::kSplit ? wave >> 2 : wave), kParts * C, n_tiles, phase);
     const uint32_t row_bytes = (uint32_t)st.n * E;
     const rsrc_t rK = make_rsrc(K + b * st.b + h * st.h, (uint32_t)t1 * row_bytes);
     const rsrc_t rV = make_rsrc(V + b * st.b + h * st.h, (uint32_t)t1 * row_bytes);

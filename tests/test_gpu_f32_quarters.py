@@ -45,6 +45,30 @@ def test_quarters_of_the_state(dtype, d, B, H, grid, layout, rope):
         assert metrics.rel_l2(to_host(S), S_want) <= 1e-5 and metrics.rel_l2(to_host(z), z_want) <= 1e-5     # fp32 sums
 
 
+@pytest.mark.parametrize("layout", ["bhnd", "bnhd"])
+@pytest.mark.parametrize("rope", ["none", "axes"])
+@pytest.mark.parametrize("dtype,d,N", [("f32", 32, (640, 512)), ("bf16", 32, (896, 640)), ("f32", 64, (191, 192))])
+def test_quarters_give_the_bits_of_one_workgroup(dtype, d, N, rope, layout):
+    """64 heads are summed by quarters, 65 and 66 by one workgroup each; waves with several tiles, whose order is the head's (token-major: the batch's)."""
+    import torch
+    n, B, most = N[rope != "none"], *((1, 65) if layout == "bhnd" else (2, 33))
+    say(f"f32_quarters bits {dtype} d={d} {rope} {layout}")
+    _, K, V = wl.draw_tensors(9960 + d, (B, most, n, d), 0.5, dtype)
+    Kd, Vd = to_dev(K), to_dev(V)
+    keep = [torch.from_numpy(np.ascontiguousarray(t)).cuda() for t in wl.rope_tables_3d_factored(1, n // 16, 16, d)] if rope != "none" else []
+    got = []
+    for H in (most, most - 1):
+        k, v = Kd[:, :H].contiguous(), Vd[:, :H].contiguous()
+        if layout == "bnhd":
+            k, v = (x.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3) for x in (k, v))
+        S, z = new_state(B, H, d)
+        call = sv.sv_linattn_state if rope == "none" else sv.sv_linattn_state_rope3d
+        call(k, v, sv.desc_of(k), *([] if rope == "none" else [sv.Rope3D.from_tensors(*keep)]), 0, n, 0, S, z, new_workspace(B, H, n, d))
+        torch.cuda.synchronize()
+        got.append((S[:, :most - 1], z[:, :most - 1]))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
 @pytest.mark.parametrize("N", [1, 15, 16, 17, 67])
 def test_state_in_three_pieces(N):
     """State entries of 24 significant bits over forty orders of magnitude down to 1e-20: every output within its own rounding to bf16 (2^-8 of it, and the
