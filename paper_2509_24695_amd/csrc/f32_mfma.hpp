@@ -535,9 +535,23 @@ __global__ __launch_bounds__(kThreads, 2) void apply_f32(
     // bf16 tokens without a rotation (d = 32): the state in three bf16 pieces, which hold all of its 24 bits, so the products stay those of
     // fp32, at a fifth of the matrix core's time.  Lane (n, g)'s eight features of a token are the operand of one 16 x 16 x 32 product.
     // (Layer of 128 heads, 4 096 tokens 36.2 -> 34.4 us; rotated features are fp32 values and stay with fp32 products.)
+    // An entry below 2^-110 has bits below 2^-133, the last of bf16's denormal numbers (which the products take as they are): a wave that meets one
+    // takes fp32 products.
     constexpr bool kPieces = E == 2 && ROPE == kRopeNone;
     bf16x8 piece[kPieces ? 3 : 1][NB];
+    bool whole = false;                                         // wave-uniform: the pieces hold the state
     if constexpr (kPieces) {
+        uint32_t least = ~0u;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < NB; ++e) {
+                    const uint32_t twice = 2u * __float_as_uint(sr[j][q][e]) - 1u;     // magnitudes in order, zero behind all others
+                    least = twice < least ? twice : least;
+                }
+        whole = __all(least >= 2u * __float_as_uint(0x1p-110f) - 1u);
 #pragma unroll
         for (int e = 0; e < NB; ++e) {
             uint32_t w[3][4];
@@ -563,78 +577,98 @@ __global__ __launch_bounds__(kThreads, 2) void apply_f32(
         }
     }
 
-    for (int i0 = 0; i0 < walk.count; i0 += DEPTH) {
+    // bf16 results take a row's reciprocal, once per token, in place of quotients (a layer of 128 heads of 32, 4 096 tokens 39.4 -> 36.2 us): the
+    // product's error is far below the result's rounding.  Not where it may be infinite: the quotients themselves.  What decides that, and with it
+    // whether the pieces hold, is looked at before the loop: with eps a normal number and no key sum negative every denominator has a reciprocal, and
+    // such a wave's loop is without checks (layer of 128 heads, 4 096 tokens 33.7 us; with checks in every tile 34.6).
+    bool plain = E != 2 || eps >= 0x1p-126f;
+    if constexpr (E == 2) {
 #pragma unroll
-        for (int s = 0; s < DEPTH; ++s) {
-            const int i = i0 + s;
-            if (i >= walk.count) break;
-            __builtin_amdgcn_sched_barrier(0);
-            float qf[NJ][4], den = 0.f;
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                if constexpr (E == 2) {
-                    const Words<2> half = {{qw[s][0].w[2 * j], qw[s][0].w[2 * j + 1]}};
-                    widen<T, 4>(half, qf[j]);
-                } else {
-                    widen<T, 4>(qw[s][j], qf[j]);
-                }
+            for (int q = 0; q < 4; ++q) plain = plain && zr[j][q] >= 0.f;
+        plain = __all(plain) && (whole || !kPieces);
+    }
+    auto tokens = [&](auto checked) __attribute__((always_inline)) {
+        for (int i0 = 0; i0 < walk.count; i0 += DEPTH) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    qf[j][q] = fmaxf(qf[j][q], 0.f);
-                    den = fmaf(qf[j][q], zr[j][q], den);                // the denominator takes the plain features
-                }
-            }
-            if constexpr (ROPE == kRopeTable) {
+            for (int s = 0; s < DEPTH; ++s) {
+                const int i = i0 + s;
+                if (i >= walk.count) break;
+                __builtin_amdgcn_sched_barrier(0);
+                float qf[NJ][4], den = 0.f;
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
-                    const f32x2 cs[2] = {{__uint_as_float(tw[s][j].w[0]), __uint_as_float(tw[s][j].w[1])},
-                                         {__uint_as_float(tw[s][j].w[2]), __uint_as_float(tw[s][j].w[3])}};
-                    rotate_pairs<4>(qf[j], cs);
+                    if constexpr (E == 2) {
+                        const Words<2> half = {{qw[s][0].w[2 * j], qw[s][0].w[2 * j + 1]}};
+                        widen<T, 4>(half, qf[j]);
+                    } else {
+                        widen<T, 4>(qw[s][j], qf[j]);
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        qf[j][q] = fmaxf(qf[j][q], 0.f);
+                        den = fmaf(qf[j][q], zr[j][q], den);                // the denominator takes the plain features
+                    }
                 }
-            } else if constexpr (ROPE == kRope3D) {
-                const GridPos pos(rope.r3, walk.token<TILE>(i) + tok, inv_rc, inv_cols);
+                if constexpr (ROPE == kRopeTable) {
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const f32x2 cs[2] = {rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2),
-                                         rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2 + 1)};
-                    rotate_pairs<4>(qf[j], cs);
+                    for (int j = 0; j < NJ; ++j) {
+                        const f32x2 cs[2] = {{__uint_as_float(tw[s][j].w[0]), __uint_as_float(tw[s][j].w[1])},
+                                             {__uint_as_float(tw[s][j].w[2]), __uint_as_float(tw[s][j].w[3])}};
+                        rotate_pairs<4>(qf[j], cs);
+                    }
+                } else if constexpr (ROPE == kRope3D) {
+                    const GridPos pos(rope.r3, walk.token<TILE>(i) + tok, inv_rc, inv_cols);
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) {
+                        const f32x2 cs[2] = {rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2),
+                                             rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2 + 1)};
+                        rotate_pairs<4>(qf[j], cs);
+                    }
                 }
-            }
-            request(s, i + DEPTH);
-            __builtin_amdgcn_sched_barrier(0);
-            den += __shfl_xor(den, 16);
-            den += __shfl_xor(den, 32);                                 // that of MFMA row n, in all its lanes
-            // bf16: the row's reciprocal, once per token (a layer of 128 heads of 32, 4 096 tokens 39.4 -> 36.2 us); the product's error is far below
-            // the result's rounding
-            const float scale = E == 2 ? 1.0f / (den + eps) : den + eps;
-            f32x4 acc[NB] = {};
-            if constexpr (kPieces) {
-                const u32x4 w = {pack_bf16x2(qf[0][0], qf[0][1]), pack_bf16x2(qf[0][2], qf[0][3]), pack_bf16x2(qf[1][0], qf[1][1]), pack_bf16x2(qf[1][2], qf[1][3])};
+                request(s, i + DEPTH);
+                __builtin_amdgcn_sched_barrier(0);
+                den += __shfl_xor(den, 16);
+                den += __shfl_xor(den, 32);                                 // that of MFMA row n, in all its lanes
+                const float dn = den + eps;
+                const bool reciprocal = E == 2 && (!checked() || __all(fabsf(dn) >= 0x1p-126f));
+                const float scale = reciprocal ? 1.0f / dn : dn;
+                f32x4 acc[NB] = {};
+                if (kPieces && (!checked() || whole)) {
+                    const u32x4 w = {pack_bf16x2(qf[0][0], qf[0][1]), pack_bf16x2(qf[0][2], qf[0][3]), pack_bf16x2(qf[1][0], qf[1][1]), pack_bf16x2(qf[1][2], qf[1][3])};
 #pragma unroll
-                for (int l = 2; l >= 0; --l)                            // small terms first
+                    for (int l = 2; l >= 0; --l)                            // small terms first
 #pragma unroll
-                    for (int e = 0; e < NB; ++e)
-                        acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), piece[l][e], acc[e], 0, 0, 0);
-            } else
+                        for (int e = 0; e < NB; ++e)
+                            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), piece[l][e], acc[e], 0, 0, 0);
+                } else
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
+                for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+                    for (int q = 0; q < 4; ++q)
 #pragma unroll
-                    for (int e = 0; e < NB; ++e)
-                        acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[j][q], sr[j][q][e], acc[e], 0, 0, 0);
-            // element r of block e: MFMA row 4 g + r, token 4 r + g, feature f_out + e
-            const uint32_t out = exists ? walk.offset<TILE>(i, row_bytes) + offO : kOutOfRange;
+                        for (int e = 0; e < NB; ++e)
+                            acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[j][q], sr[j][q][e], acc[e], 0, 0, 0);
+                // element r of block e: MFMA row 4 g + r, token 4 r + g, feature f_out + e
+                const uint32_t out = exists ? walk.offset<TILE>(i, row_bytes) + offO : kOutOfRange;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float dd = __shfl(scale, 4 * g + r);
-                float o[NB];
+                for (int r = 0; r < 4; ++r) {
+                    const float dd = __shfl(scale, 4 * g + r);
+                    float o[NB];
+                    if (reciprocal)
 #pragma unroll
-                for (int e = 0; e < NB; ++e) o[e] = E == 2 ? acc[e][r] * dd : acc[e][r] / dd;
-                store_words(rO, out + (uint32_t)(4 * r) * row_bytes, narrow<T, NB>(o));
+                        for (int e = 0; e < NB; ++e) o[e] = acc[e][r] * dd;
+                    else
+#pragma unroll
+                        for (int e = 0; e < NB; ++e) o[e] = acc[e][r] / dd;
+                    store_words(rO, out + (uint32_t)(4 * r) * row_bytes, narrow<T, NB>(o));
+                }
             }
         }
-    }
+    };
+    if (plain) tokens(std::false_type{});
+    else if constexpr (E == 2) tokens(std::true_type{});
 }
 
 }  // namespace sv

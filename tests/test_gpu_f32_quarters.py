@@ -101,3 +101,41 @@ def test_state_in_three_pieces(N):
             assert np.isposinf(got[:, :, :, 7][positive]).all() and np.isnan(got[:, :, :, 7][~positive]).all()
             ok[:, :, :, 7] = True
         assert ok.all()
+
+
+# sizes (powers of two) of the queries, the state and the key sums; eps = 0
+@pytest.mark.parametrize("rope", ["none", "axes"])
+@pytest.mark.parametrize("q2,s2,z2", [(0, -127, -127), (0, -121, -121), (0, -113, -113), (0, -110, -110), (0, -20, -136), (0, -20, -131), (0, 100, 121), (-130, 0, 0),
+                                      (-130, 0, -6), (-60, -60, -60), (-64, -64, -64), (0, 0, 0)])
+def test_small_states_and_denominators(q2, s2, z2, rope):
+    """bf16, d = 32: the quotients, where a reciprocal of the denominator is infinite or its state's bf16 pieces are below the normal numbers: within
+    the rounding to bf16 and that of sums and products to multiples of 2^-149 (2^-16 of the sum of magnitudes); rotated features: five times that.
+    A column of zeros stays zero."""
+    import torch
+    B, H, N, d = 1, 3, 70, 32
+    say(f"f32 small states {q2} {s2} {z2} {rope}")
+    rng = np.random.Generator(np.random.PCG64(97))
+    Qd = torch.from_numpy(np.ldexp(np.abs(rng.standard_normal((B, H, N, d))) + 0.25, q2).astype(np.float32)).cuda().bfloat16()
+    S0 = np.ldexp(rng.standard_normal((B, H, d, d)), s2).astype(np.float32)
+    S0[..., 5] = 0.0
+    z0 = np.ldexp(np.abs(rng.standard_normal((B, H, d))) + 0.25, z2).astype(np.float32)
+    S, z = new_state(B, H, d)
+    S.copy_(torch.from_numpy(S0))
+    z.copy_(torch.from_numpy(z0))
+    cs = wl.rope_tables_3d_factored(1, 7, 10, d)
+    keep = [torch.from_numpy(np.ascontiguousarray(t)).cuda() for t in cs]
+    O = torch.full_like(Qd, float("nan"))
+    if rope == "none":
+        sv.sv_linattn_apply(Qd, sv.desc_of(Qd), 0, N, S, z, 0.0, O)
+    else:
+        sv.sv_linattn_apply_rope3d(Qd, sv.desc_of(Qd), sv.Rope3D.from_tensors(*keep), 0, N, S, z, 0.0, O)
+    torch.cuda.synchronize()
+    q, got = to_host(Qd).astype(np.float64), to_host(O).astype(np.float64)
+    den = np.matmul(q, z0.astype(np.float64)[..., None])
+    if rope != "none":
+        T = wl.expand_rope_tables(*cs).astype(np.float64)                  # [N][d/2][2]
+        a, b = q[..., 0::2], q[..., 1::2]
+        q = np.stack([a * T[..., 0] - b * T[..., 1], a * T[..., 1] + b * T[..., 0]], -1).reshape(q.shape)
+    want, size = np.matmul(q, S0.astype(np.float64)) / den, np.matmul(np.abs(q), np.abs(S0).astype(np.float64)) / den
+    assert (np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + (1 if rope == "none" else 5) * 2.0 ** -16 * size).all()
+    assert (got[..., 5] == 0).all()
