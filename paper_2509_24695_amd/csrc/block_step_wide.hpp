@@ -84,8 +84,11 @@ __global__ __launch_bounds__(kCoopThreads, 2) void block_step_mfma_wide(
         BH = roles.BH;
         if (!wide_role((int)blockIdx.x, roles, c, C, bh, local)) return;
     }
-    const int phase = roles.dies ? die_local_phase_key(bh, roles.dies, BH) : role.phase(bh / H, order);
     const int b = bh / H, h = bh % H;
+    // The state kernels' phase keys, wherever the head lives.  With keys dealt die by die (die_local_phase_key) the eight neighbouring heads of the dies walked
+    // in phase; where as many head strides come near a power of two (4 680, 9 360, 18 720 tokens) their streams met on the same DRAM
+    // resources (128 heads of 128, 9 360 tokens 261 -> 225 us a block, 80 heads 162 -> 140, 128 heads of 112, 18 720 tokens 426 -> 356; nothing slower).
+    const int phase = order & kOrderLockstep ? 5 * b : bh;
     const int64_t head_off = b * st.b + h * st.h;
     const int elems = d * d + d;
     const int n_tiles = (N + kCoopTokens - 1) / kCoopTokens;

@@ -67,6 +67,29 @@ def test_block_step_wide(d, B, H, grid, layout, forms, rope):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("rope", ["none", "axes"])
+@pytest.mark.parametrize("d,B,H,layout", [(112, 1, 32, "bhnd"), (128, 2, 32, "bhnd"), (128, 4, 32, "bnhd"), (112, 2, 64, "bhnd")])
+def test_walks_are_those_of_the_state_kernel(d, B, H, layout, rope):
+    """Heads on one die, as many workgroups each as the state kernel gives them: the same shares, met in the same order, make the same sums."""
+    import torch
+    grid = (1, 45, 68)
+    N = grid[0] * grid[1] * grid[2]
+    say(f"block_step_wide walks d={d} B={B} H={H} {layout} {rope}")
+    _, (q, k, v), _, _, _, arg, _keep = _case(9170, d, B, H, grid, layout, rope)
+    dsc, sfx, got = sv.desc_of(q), {"none": "", "axes": "_rope3d"}[rope], []
+    for call in ("state", "step"):
+        S, z = new_state(B, H, d)
+        ws = new_workspace(B, H, N, d)
+        if call == "state":
+            getattr(sv, "sv_linattn_state" + sfx)(k, v, dsc, *arg, 0, N, 0, S, z, ws)
+        else:
+            getattr(sv, "sv_block_linattn_step" + sfx)(q, k, v, dsc, *arg, S, z, 1e-6, torch.empty_like(q), ws)
+        torch.cuda.synchronize()
+        got.append((S, z))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("why", ["wait", "dies"])
 @pytest.mark.parametrize("H", [16, 20])
 def test_a_step_that_gives_up_stores_nothing(H, why):
