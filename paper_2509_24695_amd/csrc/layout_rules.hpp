@@ -202,40 +202,57 @@ inline int f32_sole_tokens(int d, int BH, int elem_bytes, bool rotated)
 // C = 32 15.5 / 15.8; d = 64 (17 KB), 64 heads, 2 000 tokens, C = 4 39.8 / 38.7, 32 heads, 4 680, C = 8 44.3 / 44.3, 16 heads, 1 560, C = 16 20.1 / 21.5.
 inline bool f32_last_folds(int d, int C) { return d == 32 ? C <= 16 : d == 64 && C <= 4; }
 
-// d = 112 and 128, block step: one launch (block_step_wide.hpp) or two (a state kernel, the apply kernel).  Streams of two to four blocks, two
-// launches / one, us per stream:
-//   plain           20 heads of 112, 4 680 tokens 133 / 120, 32 760 238 / 221, 75 600 503 / 475; 64 heads, 4 680 131 / 120; 8 heads, 1 560 77 / 64; of
-//                   128: 32 heads, 9 360 145 / 137; two workgroups per head: 128 heads, 1 560 207 / 179, 4 680 230 / 258 (of 128 286 / 279), 100 heads, 4 680
-//                   194 / 196
-//   factored        20 heads, 4 680 154 / 137, 32 760 262 / 257, 75 600 555 / 560; 40 heads, 32 760 488 / 492; 128 heads, 1 560 240 / 208, 4 680 250 / 272
-//   full table      20 heads, 4 680 120 / 112, 9 360 115 / 111, 18 000 256 / 258, 32 760 292 / 302; 40 heads, 4 680 170 / 162, 9 360 184 / 189; 80 heads,
-//                   1 560 146 / 124, 4 680 272 / 272
-//   shared lines    plain 20 heads, 4 680 78 / 73, 40 heads 219 / 216 to 221, 20 heads, 14 040 136 / 148; factored tables 20 heads, 4 680 85 / 78,
-//                   32 760 318 / 318
-//   few heads       a head on all dies: 2 heads, 600 tokens 64 / 56, 4 680 40.1 / 41.7, 5 heads, 4 680 47.1 / 48.1
-// A workgroup per head, by how much of the device the heads fill (130, 160, 192 to 256, more than 256 heads):
-//   plain           130 of 112: 624 98 / 85, 2 000 138 / 132, 3 120 265 / 269; 160: 3 120 297 / 280, 4 680 402 / 403; 200 and 256: 9 360 655 / 599 and 775 / 743;
-//                   400: 240 319 / 107, 9 360 1 383 / 1 251; 130 of 128: 4 680 415 / 404, 9 360 516 / 538; 160: 9 360 586 / 601
-//   factored        130: 624 118 / 100, 2 000 157 / 166; 160: 3 120 354 / 345, 4 680 488 / 502; 192: 4 680 365 / 375; 200: 4 680 582 / 560, 9 360 737 / 743; 256: 9 360
-//                   843 / 857; 400: 9 360 1 586 / 1 477
-//   full table      160: 600 87 / 83, 1 560 223 / 237; 256: 240 70 / 54, 1 560 190 / 184; 400: 1 560 452 / 325
+// d = 112 and 128, block step: one launch (block_step_wide.hpp) or two (a state kernel, the apply kernel).  Streams of three look-ahead passes and a
+// committing one, us per block, two launches / one:
+//   plain           20 heads of 112, 4 680 tokens 32.9 / 29.0, 32 760 114 / 104, 98 280 309 / 294; 64 heads, 32 760 333 / 311; 8 heads, 131 040 178 / 158; of
+//                   128: 20 heads, 9 360 50 / 46, 98 280 354 / 332; 64 heads, 32 760 394 / 395; 9 to 15 heads, whose worst-off have ten workgroups, 1 040 tokens 0.90 to
+//                   0.98 of two launches', 1 560 0.95 to 1.07, 3 120 0.96 to 1.05, 4 680 0.93 to 1.02, 5 460 0.93 to 0.99
+//   factored        20 heads, 4 680 37.7 / 32.1, 49 920 175 / 162, 98 280 341 / 346; 16 heads, 65 520 186 / 181; 68 heads, 10 920 147 / 146, 12 480 160 / 161
+//   two workgroups  of 128, plain: 128 heads, 9 360 243 / 225, 16 380 396 / 370, 100 heads, 9 360 189 / 184, 16 380 306 / 301, 87 heads, 9 360 168 / 167, 12 480 223 / 217,
+//   per head        15 600 266 / 271.  (Of 112 and with factored tables the line could lie further out: 128 heads, 4 680 111 / 98, factored 119 / 112, 7 800
+//                   196 / 175; 87 heads, factored, 7 800 154 / 149, 9 360 163 / 168.)
+//   full table      20 heads, 4 680 38.6 / 35.9, 9 360 53 / 52; 64 heads, 3 000 55 / 53; 100 heads of 128, 2 048 69 / 66; few heads of 128, all spread: 8, 4 680
+//                   26.4 / 30.0, 6 240 28.9 / 32.6, 7 800 33.0 / 32.9, 10, 3 120 24.7 / 27.5, 15, 3 120 27.6 / 29.0, 4 680 39.0 / 35.2
+//   shared lines    plain 20 heads, 4 680 36 / 34, 7 800 45.5 / 45.8, 9 360 52 / 53, 40 heads, 3 120 42 / 41, 4 680 52 / 53, 16 heads, 9 360 44.7 / 44.7; factored tables 40 heads,
+//                   4 680 58 / 56, 20 heads, 9 360 58 / 56
+//   few heads       a head on all dies.  Of 112: 5 heads, 2 028 tokens 19.7 / 18.0, 6, 1 560 18.1 / 17.9, 2 028 18.4 / 18.7, 7, 1 560 18.2 / 19.0, factored tables 20.8 / 21.1, full
+//                   table, 2 028 20.4 / 20.4, shared lines 19.2 / 19.2.  Of 128: 3 heads, 1 560 16.2 / 16.1, 2 028 16.5 / 17.4, 5, 1 040 16.3 / 15.8, 1 560 16.9 / 17.9, factored tables
+//                   20.0 / 20.1, 7, 1 040 19.6 / 19.7, full table 18.9 / 18.9, 5, 2 028 20.9 / 20.6
+// A workgroup per head, by how much of the device the heads fill:
+//   plain           130 of 112: 2 560 75 / 72; 146: 3 900 113 / 107, 4 680 123 / 126; 160: 4 680 129 / 129; 192: 14 040 433 / 427, 18 720 563 / 559, 32 760 994 / 1 026; 200:
+//                   32 760 1 102 / 1 038; of 128, 130: 4 680 137 / 136; 192: 32 760 1 189 / 1 144; 256: 18 720 and 32 760 of 112 754 / 739 and 1 309 / 1 282, of 128 14 040 671 / 629,
+//                   32 760 1 551 / 1 585
+//   factored        130: 1 248 53 / 52, 1 560 61 / 62; 150: 1 560 62 / 62, 2 560 91 / 93; 160: 2 560 94 / 94, 3 120 109 / 112; 180: 3 120 117 / 114; 192: 3 900 155 / 150
+//   full table      130: 780 45 / 44; 160: 600 40 / 36; 185: 780 52 / 45
+//   more heads      than compute units: a second round, nearly empty at first, which the state kernel of two launches has too, its apply not.  257 of 112: 1 560
+//                   148 / 110, 4 680 310 / 288, 7 800 473 / 474, 9 360 551 / 559, 18 720 1 050 / 1 109; 320: 9 360 591 / 569, 18 720 1 107 / 1 128; 350: 14 040 889 / 878, 18 720
+//                   1 155 / 1 151; 400: 18 720 1 278 / 1 192; factored tables 257: 4 680 342 / 338, 5 460 396 / 397, 9 360 624 / 660; 350: 9 360 691 / 688, 10 920 790 / 791; 400:
+//                   9 360 794 / 731; full table 257: 1 560 184 / 146; shared lines 257: 960 129 / 83; of 128 the lines lie further out: 257: 9 360 625 / 623
 //   shared lines    160 heads, 600 76 / 69, 4 680 334 / 398 (factored 376 / 411)
 inline bool wide_step_serves(const TokenLayout &t, int n_tokens, int C, bool full_table, bool factored_tables, int num_cu)
 {
     const int64_t head_tokens = (int64_t)t.BH * n_tokens;
+    const bool plain = !full_table && !factored_tables;
     if (C > 1) {
-        if (t.BH < 8) return n_tokens <= 2048;
-        if (full_table || t.shares_lines()) return head_tokens <= 200000;
+        if (t.BH < 8) {
+            if (t.d == 112) return n_tokens <= 2048 && (full_table || t.shares_lines() || head_tokens <= 10240);
+            return n_tokens <= 2048 && head_tokens <= (plain ? 5200 : factored_tables ? 8192 : 10240);
+        }
+        if (full_table && t.d == 128 && t.BH < 16 && n_tokens > 2048 && n_tokens < 7000) return false;
+        if (full_table || t.shares_lines()) return head_tokens <= (plain ? 150000 : 200000);
+        if (plain && t.d == 128 && t.BH > 8 && t.BH < 16 && n_tokens > 1250 && n_tokens < 5000) return false;
         if (C == 2 && (t.d == 112 || factored_tables)) return n_tokens <= 3072;
-        return !factored_tables || n_tokens <= 4096 * C;
+        if (C == 2 && 4 * C * t.BH < 3 * num_cu) return n_tokens <= 12288;
+        return n_tokens <= (factored_tables ? 4096 : 8192) * C;
     }
     if (t.shares_lines()) return n_tokens <= 1024;
-    if (t.BH > num_cu) return !full_table || n_tokens <= 2048;
-    if (full_table) return n_tokens <= 768;
     const int fill = 100 * t.BH / num_cu;
-    if (fill < 57) return n_tokens <= (factored_tables ? 1280 : t.d == 112 ? 2560 : 4680);
-    if (fill < 75) return n_tokens <= (factored_tables ? 3120 : 4680);
-    return !factored_tables || n_tokens <= 4096;
+    if (t.BH > num_cu) return n_tokens <= (full_table ? 2048 : fill <= 125 ? (factored_tables ? 5120 : 8192) : factored_tables ? 10240 : 18720);
+    if (full_table) return n_tokens <= 768;
+    if (factored_tables) return n_tokens <= (fill < 60 ? 1280 : fill < 70 ? 2560 : fill < 75 ? 3120 : 4096);
+    if (fill < 57 && t.d == 112) return n_tokens <= 2560;
+    if (fill < 75) return n_tokens <= (fill < 60 && t.d == 112 ? 4096 : 4680);
+    return n_tokens <= (fill < 78 ? 18720 : 32760);
 }
 
 // ... its workgroups: as many heads as fill the dies evenly live on one die each, where its workgroups exchange their sums through that die's L2, the

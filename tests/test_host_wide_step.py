@@ -52,3 +52,20 @@ def test_lines(exe):
              (112, 8, 20, 1560, "table", "bhnd"): 0, (112, 8, 32, 9360, "none", "bhnd"): 1, (112, 8, 32, 9360, "axes", "bhnd"): 0}
     got = _served(exe, list(calls))
     assert {c: int(g[0] != "two") for c, g in zip(calls, got)} == calls
+
+
+def test_lines_end_where_two_launches_were_measured_ahead(exe):
+    """Both sides of lines that were once left open or drawn where one launch is the slower one."""
+    calls = {}
+    for d, rope, BH, serves, two in ((112, "none", 260, 7800, 9360), (112, "axes", 260, 4680, 6240), (112, "none", 350, 14040, 32760), (112, "axes", 400, 9360, 14040),
+                                     (128, "none", 300, 7800, 14040), (112, "none", 192, 18720, 32760), (112, "none", 240, 32760, 65520), (112, "none", 146, 3900, 4680),
+                                     (112, "axes", 150, 1248, 2560), (112, "axes", 160, 2560, 3120), (128, "none", 128, 15600, 32760), (128, "none", 87, 9360, 15600),
+                                     (128, "none", 84, 23400, 32760), (112, "none", 20, 75600, 131040), (112, "none", 7, 1040, 1560), (112, "axes", 7, 1040, 2028),
+                                     (112, "table", 7, 2028, 4680), (128, "none", 3, 1560, 2028), (128, "none", 5, 1040, 1560), (128, "axes", 5, 1560, 2028),
+                                     (128, "table", 7, 1040, 1560), (128, "none", 13, 1040, 1560), (128, "none", 10, 6240, 3120), (128, "none", 16, 3120, 500000),
+                                     (128, "table", 8, 1560, 4680), (128, "table", 10, 9360, 3120), (128, "axes", 13, 3120, 200000)):
+        calls[(d, 1, BH, serves, rope, "bhnd")], calls[(d, 1, BH, two, rope, "bhnd")] = 1, 0
+    for H, n, serves in ((20, 4680, 1), (20, 9360, 0), (40, 3120, 1), (40, 4680, 0), (7, 2028, 1)):
+        calls[(112, 1, H, n, "none", "bnhd")] = serves
+    got = _served(exe, list(calls))
+    assert {c: int(g[0] != "two") for c, g in zip(calls, got)} == calls
