@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kCoopThreads, 2) void block_step_mfma_wide(
         const uint32_t my_die = local ? die_id() : 0u;
         // tells the head's other workgroups that this one's stores are done; waits for theirs
         auto publish = [&](int phase) __attribute__((always_inline)) {
-            unsigned long long *flag = ws_flags(ws, BH, elems, bh, phase) + c;
+            unsigned long long *flag = ws_flags(ws, BH, elems, bh, 0) + wide_flag_word(local, phase, c, C, kMaxChunks);
             if (tid != 0) return;
             if (local) flag_publish<true>(flag, flag_with_die(epoch, my_die));
             else flag_publish(flag, epoch);
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kCoopThreads, 2) void block_step_mfma_wide(
         auto wait = [&](int phase) __attribute__((always_inline)) {
             if (!local) return state_wait(ws, BH, elems, bh, C, phase, epoch, spin_limit, lane);
             bool same_die;
-            const bool ok = flags_wait_all_local(ws_flags(ws, BH, elems, bh, phase), C, epoch, spin_limit, lane, my_die, &same_die) && same_die;
+            const bool ok = flags_wait_all_local(ws_flags(ws, BH, elems, bh, 0) + wide_flag_word(local, phase, 0, C, kMaxChunks), C, epoch, spin_limit, lane, my_die, &same_die) && same_die;
             if (!ok && lane == 0) __hip_atomic_store(ws_error(ws, BH, elems), kWsTimeoutMark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return ok;
         };

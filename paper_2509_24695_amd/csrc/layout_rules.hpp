@@ -261,13 +261,16 @@ inline bool wide_step_serves(const TokenLayout &t, int n_tokens, int C, bool ful
 // and 38.0 us a block; 16 local heads of 13 workgroups and 4 spread of 12: 28.8 and 34.3, of 12 and 16: 27.8 and 33.0.)  Not where heads share cache lines,
 // which then lie on different dies; with a full table, whose rows every die fetches then, up to 2 048 tokens (20 heads, 1 560 tokens 74.8 -> 69.5
 // us per stream, 4 680 level, 18 000 258 -> 291).
-inline WideRoles wide_roles(const TokenLayout &t, int n_tokens, int n_steps, bool full_table, int num_cu, int dies)
+// `flags_at`: address of the workspace's flags (see wide_flag_word; 9 heads of 112, the only ones with more than 24 workgroups beside spread heads, lose none
+// to it where the workspace starts a line).
+inline WideRoles wide_roles(const TokenLayout &t, int n_tokens, int n_steps, bool full_table, int num_cu, int dies, uint64_t flags_at = 0)
 {
     WideRoles best{0, 0, 0, 0, t.BH};
     if (dies <= 0 || t.BH < dies || t.BH * 2 > num_cu || t.shares_lines() || (full_table && n_tokens > 2048)) return best;
     const int cus = num_cu / dies, per_die = t.BH / dies, spread = t.BH % dies, most = n_steps < kMaxChunks ? n_steps : kMaxChunks;
+    const int beside = spread ? wide_most_beside_spread((int)(flags_at % 128), kMaxChunks) : kMaxChunks, most_local = most < beside ? most : beside;
     int worst = 0;
-    for (int C = cus / per_die < most ? cus / per_die : most; C >= 1; --C) {
+    for (int C = cus / per_die < most_local ? cus / per_die : most_local; C >= 1; --C) {
         int Cs = spread ? dies * (cus - per_die * C) / spread : C;
         Cs = Cs < most ? Cs : most;
         const int score = 10 * C < 8 * Cs || !spread ? 10 * C : 8 * Cs;

@@ -775,7 +775,8 @@ sv_status do_block_step(const void *Qb, const void *Kb, const void *Vb, const sv
                 if (!wide_step_serves(layout, s.N, C, rope.mode == kRopeTable, rope.mode == kRope3D, dev.num_cu)) return;
                 // The heads' places on the dies are those of the 8 x 32 compute-unit part; the kernel checks them itself (see block_step_mfma).
                 const int dies = C > 1 && dev.num_cu == kDies * kCusPerDie ? g_assumed_dies.load(std::memory_order_relaxed) : 0;
-                const WideRoles roles = wide_roles(layout, s.N, (s.N + kCoopTokens - 1) / kCoopTokens, rope.mode == kRopeTable, dev.num_cu, dies);
+                const WideRoles roles = wide_roles(layout, s.N, (s.N + kCoopTokens - 1) / kCoopTokens, rope.mode == kRopeTable, dev.num_cu, dies,
+                                                   reinterpret_cast<uint64_t>(ws_flag_base(workspace, s.BH, s.d * s.d + s.d)));
                 const dim3 grid = roles.dies ? dim3(roles.grid()) : dim3(C, s.BH);
                 if (C > 1 && (int64_t)grid.x * grid.y > dev.wide_fused_resident_wgs[rope.mode][KN::kShared]) return;   // its workgroups wait for each other
                 const auto kernel = C == 1 ? KN::template fused_form<true> : KN::template fused_form<false>;

@@ -119,6 +119,12 @@ SV_HOST_DEVICE inline bool wide_role(int id, const WideRoles &r, int &c, int &C,
     return bh < r.BH;
 }
 
+// The flag words of such a head, of the 2 * kMaxChunks it has in the workspace: the phases side by side, or packed where the head lives on one die.
+// Its flags are stored into that die's L2; the next head's, where it is spread, are polled across dies, and the two have to stay off one cache line.  Where
+// the flags lie `past_line` bytes past a multiple of 128 (a multiple of 16), a packed head of at most this many workgroups ends a line early enough.
+SV_HOST_DEVICE inline int wide_flag_word(bool local, int phase, int c, int C, int max_chunks) { return phase * (local ? C : max_chunks) + c; }
+SV_HOST_DEVICE inline int wide_most_beside_spread(int past_line, int max_chunks) { return max_chunks - past_line / 16; }
+
 // Phase key (the `bh` argument of TileWalk) of head bh in the die-local forms of the kernels, where die x
 // holds heads x, x + n_dies, ...: keyed by the head index itself, heads of one die would share phases (two
 // distinct ones for four heads), so the sixteen phases are dealt die by die, the heads of a die as far apart

@@ -17,6 +17,7 @@ ROWS = [                                   # d, B, H, grid, layout; the forms wi
     (112, 1, 20, (1, 23, 37), "bhnd", ("mixed",) * 3), (128, 1, 20, (1, 23, 37), "bnhd", ("mixed",) * 3), (112, 1, 3, (2, 17, 31), "bhnd", ("spread",) * 3),
     (112, 1, 20, (1, 23, 37), "bnhd", ("spread",) * 3), (112, 1, 16, (3, 23, 31), "bhnd", ("local", "spread", "local")),
     (112, 2, 16, (1, 23, 31), "bhnd", ("local",) * 3), (112, 3, 20, (1, 15, 29), "bhnd", ("mixed",) * 3), (128, 4, 20, (1, 13, 31), "bhnd", ("local",) * 3), (112, 4, 31, (1, 11, 19), "bhnd", ("mixed",) * 3),
+    (112, 1, 9, (4, 15, 31), "bhnd", ("mixed",) * 3),
     (112, 5, 26, (1, 11, 19), "bhnd", ("sole",) * 3), (128, 8, 20, (1, 11, 13), "bnhd", ("sole",) * 3), (112, 10, 30, (1, 7, 19), "bhnd", ("sole",) * 3)]
 
 

@@ -10,12 +10,16 @@ from tests import test_gpu_block_step_wide as wide
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
+def _compiled(folder, name):
+    out = folder / name
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Wextra", "-fsanitize=undefined", "-fno-sanitize-recover",
+                    os.path.join(ROOT, "tests", name + ".cpp"), "-o", str(out)], check=True)
+    return str(out)
+
+
 @pytest.fixture(scope="module")
 def exe(tmp_path_factory):
-    out = tmp_path_factory.mktemp("wide") / "host_wide_step"
-    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Wextra", "-fsanitize=undefined", "-fno-sanitize-recover",
-                    os.path.join(ROOT, "tests", "host_wide_step.cpp"), "-o", str(out)], check=True)
-    return str(out)
+    return _compiled(tmp_path_factory.mktemp("wide"), "host_wide_step")
 
 
 def _served(exe, calls):
@@ -69,3 +73,8 @@ def test_lines_end_where_two_launches_were_measured_ahead(exe):
         calls[(112, 1, H, n, "none", "bnhd")] = serves
     got = _served(exe, list(calls))
     assert {c: int(g[0] != "two") for c, g in zip(calls, got)} == calls
+
+
+def test_flags_of_the_two_kinds_of_heads_share_no_line(tmp_path):
+    res = subprocess.run([_compiled(tmp_path, "host_wide_flags")], stdout=subprocess.PIPE, text=True)
+    assert res.returncode == 0 and res.stdout.startswith("OK"), res.stdout
