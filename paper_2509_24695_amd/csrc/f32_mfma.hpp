@@ -150,8 +150,9 @@ template <typename T, int D, int HOW, int ROPE> struct StateF32 {
     static constexpr int kSlot = FQ * FQ + F;              // a wave's part in LDS: state, then key sums
     static constexpr int kParts = kSplit ? kWaves / 4 : kWaves;   // waves that hold the same part of the state
     static constexpr int kWgTokens = kParts * TILE;
-    // of a head that one workgroup sums, each running sum takes at most the tokens that f32_sole_tokens counts on
-    static_assert(!kSplit || kF32WideTile * kF32WideSums <= kWgTokens * DEPTH * kChains * 2, "see f32_sole_tokens");
+    // tokens that a running sum takes of the longest head that one workgroup sums at d = 112 and 128 (see f32_sole_tokens)
+    static constexpr int kSoleTiles = (kF32WideSoleTokens + kWgTokens - 1) / kWgTokens;      // of a wave
+    static_assert(!kSplit || (kSoleTiles + DEPTH * kChains - 1) / (DEPTH * kChains) * TILE == kF32WideSumTokens, "f32_sole_tokens counts on it");
     static constexpr int lds_bytes() {
         constexpr int slots = kWaves * kSlot * 4, tab = ROPE == kRope3D ? kRope3dLdsBytes : 0;   // tables, then slots
         return slots > tab ? slots : tab;

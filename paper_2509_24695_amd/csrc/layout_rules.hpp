@@ -182,14 +182,14 @@ constexpr int kWideWgTokens = 64;                             // of whole rows: 
 // of 12 to 18 us a layer.  In a captured graph, where a launch costs no host time, they meet earlier: d = 32, fp32 at 512 tokens for up to
 // 32 heads, 1 152 tokens are 3 to 5 us slower there on one workgroup; d = 64 at 160.
 // Both forms of the rotation have the same lines, so that they give the same bits.
-// d = 112 and 128 end where each of a wave's running sums has had one tile: a longer one is further from the exact sum than those of
+// d = 112 and 128 end at 48 tokens, of which no running sum takes more than 16 (two groups of waves, tiles of 8, two sums each): a longer one is further from the exact sum than those of
 // several workgroups (64 heads of 112, 128 tokens: S 9.4e-8 against 7.3e-8), although with many heads it would be the faster one up to 128 tokens
 // (8 heads, 64 tokens 16.0 / 16.7 us, 128 heads, 64 tokens 24 / 32, 128 tokens 31 / 36).  Adding the sums to a total after every round of tiles
 // would keep them short, but neither in registers nor in LDS does the compiler get by without spilling.
-constexpr int kF32WideTile = 16, kF32WideSums = 3;    // of a wave at d = 112 and 128: tokens per tile, running sums (taken in turn by the tiles)
+constexpr int kF32WideSoleTokens = 48, kF32WideSumTokens = 16;
 inline int f32_sole_tokens(int d, int BH, int elem_bytes, bool rotated)
 {
-    if (d > 64) return kF32WideTile * kF32WideSums;
+    if (d > 64) return kF32WideSoleTokens;
     if (d == 64) return BH <= 16 && !rotated ? 256 : 192;
     constexpr int kTokens[2][2][5] = {{{1152, 832, 640, 640, 768}, {832, 640, 512, 512, 768}},         // fp32: plain, rotated
                                       {{1280, 1152, 1024, 896, 896}, {960, 896, 704, 640, 896}}};      // bf16

@@ -1,6 +1,6 @@
-"""One workgroup per head in the fp32-arithmetic state kernel: sixteen waves at d = 32 (tiles of 32 tokens, of 16 with a
-rotation, 512 or 256 to a round), four at d >= 64.  The edges of their rounds, and both sides of the lines where several workgroups
-take over, against the oracle."""
+"""One workgroup, or four with a quarter of the state each, per head in the fp32-arithmetic state kernel: sixteen waves at d = 32 (tiles of 32 tokens, of 16 with
+a rotation, 512 or 256 to a round), eight at d >= 64 (tiles of 8, 64 to a round; at d = 112 and 128 two groups that share the state, 16 to a round).  The
+edges of their rounds, and both sides of the lines where several workgroups take over, against the oracle."""
 import pytest
 
 from tests.test_gpu_f32_mfma import _layer
