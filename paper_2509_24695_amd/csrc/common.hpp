@@ -10,8 +10,7 @@
 namespace sv {
 
 constexpr int kWave = 64;            // CDNA wavefront width
-constexpr int kThreads = 256;        // every kernel here runs 4 waves per workgroup
-constexpr int kWavesPerWg = kThreads / kWave;
+constexpr int kThreads = 256;        // four waves, the workgroup of the kernels that name no other
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

@@ -82,6 +82,34 @@ template <int WAVES, int NB> __host__ __device__ constexpr int coop_apply_lds_by
     return 2 * (WAVES * NB / 4) * kCoopTile + 8 * WAVES * NB * 4;
 }
 
+// The lane's part of phi(Q_i) . z: eight features of a row and the matching key sums.
+__device__ __forceinline__ float key_sum_products(u32x4 pq, const float (&zr)[8])
+{
+    float dot = bf16_lo(pq.x) * zr[0];
+    dot = __builtin_fmaf(bf16_hi(pq.x), zr[1], dot);
+    dot = __builtin_fmaf(bf16_lo(pq.y), zr[2], dot);
+    dot = __builtin_fmaf(bf16_hi(pq.y), zr[3], dot);
+    dot = __builtin_fmaf(bf16_lo(pq.z), zr[4], dot);
+    dot = __builtin_fmaf(bf16_hi(pq.z), zr[5], dot);
+    dot = __builtin_fmaf(bf16_lo(pq.w), zr[6], dot);
+    return __builtin_fmaf(bf16_hi(pq.w), zr[7], dot);
+}
+// Sixteen numerators of a row, times the row's reciprocal, as bf16 into an O tile.
+__device__ __forceinline__ void store_scaled(unsigned char *row, const f32x16 &a, float inv)
+{
+    u32x4 lo4, hi4;
+    lo4.x = pack_bf16x2(a[0] * inv, a[1] * inv);
+    lo4.y = pack_bf16x2(a[2] * inv, a[3] * inv);
+    lo4.z = pack_bf16x2(a[4] * inv, a[5] * inv);
+    lo4.w = pack_bf16x2(a[6] * inv, a[7] * inv);
+    hi4.x = pack_bf16x2(a[8] * inv, a[9] * inv);
+    hi4.y = pack_bf16x2(a[10] * inv, a[11] * inv);
+    hi4.z = pack_bf16x2(a[12] * inv, a[13] * inv);
+    hi4.w = pack_bf16x2(a[14] * inv, a[15] * inv);
+    *reinterpret_cast<u32x4 *>(row) = lo4;
+    *reinterpret_cast<u32x4 *>(row + 16) = hi4;
+}
+
 // Applies the state panel in `A` (value block wave % (4/NB)) to tile wave / (4/NB) of every step
 // of the workgroup's share.  Must be called by all waves of the workgroup.
 //
@@ -121,14 +149,7 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
 #pragma unroll
                 for (int j = 0; j < NLD; ++j) {
                     const u32x4 pq = relu_bf16x8(st.q[s][j]);                          // phi(Q)
-                    float dot = bf16_lo(pq.x) * zr[0];
-                    dot = __builtin_fmaf(bf16_hi(pq.x), zr[1], dot);
-                    dot = __builtin_fmaf(bf16_lo(pq.y), zr[2], dot);
-                    dot = __builtin_fmaf(bf16_hi(pq.y), zr[3], dot);
-                    dot = __builtin_fmaf(bf16_lo(pq.z), zr[4], dot);
-                    dot = __builtin_fmaf(bf16_hi(pq.z), zr[5], dot);
-                    dot = __builtin_fmaf(bf16_lo(pq.w), zr[6], dot);
-                    dot = __builtin_fmaf(bf16_hi(pq.w), zr[7], dot);
+                    float dot = key_sum_products(pq, zr);
                     if (DPP_SUM) dot = row16_sum(dot);                                  // the 16 lanes of the row
                     else
 #pragma unroll
@@ -161,20 +182,7 @@ __device__ __forceinline__ void apply_tiles_coop(CoopApplyStream<DEPTH, ROPE, WA
                     }
                 }
 #pragma unroll
-                for (int rb = 0; rb < NB; ++rb) {
-                    const f32x16 &a = acc[rb];
-                    u32x4 lo4, hi4;
-                    lo4.x = pack_bf16x2(a[0] * inv, a[1] * inv);
-                    lo4.y = pack_bf16x2(a[2] * inv, a[3] * inv);
-                    lo4.z = pack_bf16x2(a[4] * inv, a[5] * inv);
-                    lo4.w = pack_bf16x2(a[6] * inv, a[7] * inv);
-                    hi4.x = pack_bf16x2(a[8] * inv, a[9] * inv);
-                    hi4.y = pack_bf16x2(a[10] * inv, a[11] * inv);
-                    hi4.z = pack_bf16x2(a[12] * inv, a[13] * inv);
-                    hi4.w = pack_bf16x2(a[14] * inv, a[15] * inv);
-                    *reinterpret_cast<u32x4 *>(orow + 32 * rb) = lo4;
-                    *reinterpret_cast<u32x4 *>(orow + 32 * rb + 16) = hi4;
-                }
+                for (int rb = 0; rb < NB; ++rb) store_scaled(orow + 32 * rb, acc[rb], inv);
                 // O tiles complete after this barrier; they are overwritten after the first
                 // barrier of the next round, which every wave reaches after the reads below.
                 lds_barrier();
@@ -219,14 +227,7 @@ __device__ __forceinline__ void apply_tiles_steps(CoopApplyStream<DEPTH, ROPE, W
 #pragma unroll
         for (int j = 0; j < NLD; ++j) {
             const u32x4 pq = relu_bf16x8(st.q[s][j]);                          // phi(Q)
-            float dot = bf16_lo(pq.x) * zr[0];
-            dot = __builtin_fmaf(bf16_hi(pq.x), zr[1], dot);
-            dot = __builtin_fmaf(bf16_lo(pq.y), zr[2], dot);
-            dot = __builtin_fmaf(bf16_hi(pq.y), zr[3], dot);
-            dot = __builtin_fmaf(bf16_lo(pq.z), zr[4], dot);
-            dot = __builtin_fmaf(bf16_hi(pq.z), zr[5], dot);
-            dot = __builtin_fmaf(bf16_lo(pq.w), zr[6], dot);
-            dot = __builtin_fmaf(bf16_hi(pq.w), zr[7], dot);
+            float dot = key_sum_products(pq, zr);
             dot = row16_sum(dot);
             dens(s & 1)[my_row + 4 * j] = dot;                                 // the same value from the row's sixteen lanes
             *reinterpret_cast<u32x4 *>(q_tile(s & 1) + wr_off + 4 * j * kCoopRow) = st.rot.rotate_with(pq, cs[j]);
@@ -263,17 +264,7 @@ __device__ __forceinline__ void apply_tiles_steps(CoopApplyStream<DEPTH, ROPE, W
             store((s & 1) ^ 1);
             prepare(i0 + s + 1, (s + 1) % DEPTH);
             const float inv = 1.0f / (den + eps);
-            u32x4 lo4, hi4;
-            lo4.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
-            lo4.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
-            lo4.z = pack_bf16x2(acc[4] * inv, acc[5] * inv);
-            lo4.w = pack_bf16x2(acc[6] * inv, acc[7] * inv);
-            hi4.x = pack_bf16x2(acc[8] * inv, acc[9] * inv);
-            hi4.y = pack_bf16x2(acc[10] * inv, acc[11] * inv);
-            hi4.z = pack_bf16x2(acc[12] * inv, acc[13] * inv);
-            hi4.w = pack_bf16x2(acc[14] * inv, acc[15] * inv);
-            *reinterpret_cast<u32x4 *>(o_tile(s & 1) + o_off) = lo4;
-            *reinterpret_cast<u32x4 *>(o_tile(s & 1) + o_off + 16) = hi4;
+            store_scaled(o_tile(s & 1) + o_off, acc, inv);
             out_prev = st.valid ? st.walk.template offset<STEP>(i0 + s, st.row_bytes) : kOutOfRange;
             lds_barrier();
         }

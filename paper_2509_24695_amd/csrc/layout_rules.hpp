@@ -106,16 +106,16 @@ inline int wide_apply_wgs_per_cu(const TokenLayout &t, bool rotated, int num_cu)
 // apply, one / two heads to a workgroup:
 //   plain            20 heads, 4 680 tokens 37.8 / 37.1, 14 040 71.2 / 68.6, 32 760 149 / 140; 40 heads, 9 360 88.6 / 85.6, 32 760 274 / 253;
 //                    160 heads, 6 240 238 / 219
-//   rotated          with one barrier per step (pipelines_pairs) from 65 536 head-tokens on, below it is level.  Layers: factored tables 20 heads, 4 680 tokens 35.9 / 35.3, 9 360 74.4 / 70.2, 80 heads, 4 680 tokens 99.1 / 93.8, 160 heads, 1 560 75.0 / 71.9; full table 20
+//   rotated          with one barrier per step from 65 536 head-tokens on, below it is level.  Layers: factored tables 20 heads, 4 680 tokens 35.9 / 35.3, 9 360 74.4 / 70.2, 80 heads, 4 680 tokens 99.1 / 93.8, 160 heads, 1 560 75.0 / 71.9; full table 20
 //                    heads, 9 360 63.3 / 62.1, 17 160 100.5 / 95.6, 32 760 173 / 165, 160 heads, 1 560 84.7 / 81.5
 inline bool pairs_heads(const TokenLayout &t, bool rotated, int n_tokens)
 {
     return t.shares_lines() && t.H % 2 == 0 && (!rotated || (int64_t)t.BH * n_tokens >= 1 << 16);
 }
-// ... their steps with one barrier instead of two (apply_tiles_steps): 1 to 6 % less (40 heads, 32 760 tokens, plain 252 / 241 us, factored tables 284 / 269, full
-// table 324 / 307; 16 heads, 75 600, factored 258 / 249), but plain where the token rows are multiples of 1 KB (32 heads: 7 KB), which it costs
+// ... their steps with one barrier instead of two (apply_tiles_steps): rotated calls always, 5 to 6 % less (40 heads, 32 760 tokens, factored tables 284 / 269 us, full
+// table 324 / 307; 16 heads, 75 600, factored 258 / 249); plain ones (252 / 241) unless the token rows are multiples of 1 KB (32 heads: 7 KB), where it costs
 // 2 to 5 %: 64 heads, 32 760 tokens 405 / 427, 14 040 189 / 193, 32 heads, 32 760 214 / 220.
-inline bool pipelines_pairs(const TokenLayout &t, bool rotated) { return rotated || t.stride_n * t.elem_bytes % 1024 != 0; }
+inline bool pipelines_plain_pairs(const TokenLayout &t) { return t.stride_n * t.elem_bytes % 1024 != 0; }
 
 // d = 112 and 128 without a full table, state: shared tiles (coop_state.hpp) instead of a state in every wave (wide_state.hpp) up to 2 048
 // tokens per workgroup: there the end, which the sum over the waves makes longer, counts.  State + apply, us, a state per wave / shared tiles:

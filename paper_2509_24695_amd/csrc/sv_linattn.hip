@@ -125,8 +125,12 @@ template <int ROPE, bool SHARED> struct Kernels<128, ROPE, SHARED> {
     template <int HEADS, bool STEPS> static constexpr auto apply_heads =
         apply_mfma_d128<kApplyHiLo, kApplyDepth, ROPE, kCoopApplyWaves, kCoopApplyNB, !SHARED, HEADS, STEPS>;
     static constexpr auto apply = apply_heads<1, false>;
-    // two heads to a workgroup, one barrier per step or (plain only) two
-    static auto apply_pair(bool steps) { return ROPE != kRopeNone || steps ? apply_heads<2, true> : apply_heads<2, ROPE != kRopeNone>; }
+    // two heads to a workgroup, one barrier per step; plain: or two
+    static auto apply_pair(bool pipelines_plain) {
+        if constexpr (ROPE == kRopeNone)
+            if (!pipelines_plain) return apply_heads<2, false>;
+        return apply_heads<2, true>;
+    }
     static constexpr int state_lds = kWideLdsBytes;
     static constexpr int apply_lds = coop_apply_lds_bytes<kCoopApplyWaves, kCoopApplyNB>() + kTab;
     static constexpr int apply_pair_lds = step_apply_lds_bytes() + kTab;
@@ -189,7 +193,8 @@ template <int DP, int ROPE, bool SHARED = false> void init_kernels(Device &d)
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::state_partial), attr, KN::state_lds);
     (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::apply), attr, KN::apply_lds);
     if constexpr (KN::kShared)
-        for (bool steps : {false, true}) (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::apply_pair(steps)), attr, KN::apply_pair_lds);
+        for (bool pipelines_plain : {false, true})
+            (void)hipFuncSetAttribute(reinterpret_cast<const void *>(KN::apply_pair(pipelines_plain)), attr, KN::apply_pair_lds);
     int per_cu = 0;
     if constexpr (DP == 64) {                      // the one-launch block step exists for d = 64 only
         int least = INT_MAX;
@@ -598,7 +603,7 @@ sv_status enqueue_apply(const void *Q, const Rope &rope, const Shape &s, int t0,
             int heads = 1, lds = KN::apply_lds;
             if constexpr (KN::kShared)
                 if (pair) {
-                    kernel = KN::apply_pair(pipelines_pairs(layout_of(s), rope.mode != kRopeNone));
+                    kernel = KN::apply_pair(pipelines_plain_pairs(layout_of(s)));
                     heads = 2;
                     lds = KN::apply_pair_lds;
                 }
