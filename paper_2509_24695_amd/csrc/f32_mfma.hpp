@@ -463,17 +463,17 @@ template <int D> struct ApplyF32 {
     static constexpr int kWgTokens = kSplit ? TILE : 4 * TILE;
 };
 
-// grid = (C, B*H), block = 256; dynamic LDS: kRope3dLdsBytes with kRope3D.
-template <typename T, int D, int ROPE>
-__global__ __launch_bounds__(kThreads, 2) void apply_f32(
-    const T *__restrict__ Q, T *__restrict__ O, RopeArg rope, TokStrides st, int H, int t0, int t1, int C,
+// What apply_f32 does.  bf16 tokens: false where denominators or a state were met that want the loop with checks, CHECKED, which does all of the wave's share again.
+// (Checks in every tile cost the kernel 1 to 3 %, a look at state and key sums before the loop 0.2 to 0.3 us.)
+template <typename T, int D, int ROPE, bool CHECKED>
+__device__ __forceinline__ bool apply_f32_tiles(
+    unsigned char *lds, const T *__restrict__ Q, T *__restrict__ O, const RopeArg &rope, const TokStrides &st, int H, int t0, int t1, int C,
     const float *__restrict__ S, const float *__restrict__ z, float eps, int order)
 {
     using P = ApplyF32<D>;
     constexpr int NB = P::NB, NJ = P::NJ, TILE = P::TILE, DEPTH = P::template kDepth<ROPE>, E = (int)sizeof(T);
     // a lane's features of a token come in NL loads of LC chunks (16 bytes)
     constexpr int LC = E == 2 ? 2 : 1, NL = NJ / LC;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
@@ -507,10 +507,10 @@ __global__ __launch_bounds__(kThreads, 2) void apply_f32(
         }
     };
     Rope3dFill tabs;
-    if (ROPE == kRope3D) rope3d_lds_fill_begin(rope.r3, tabs);
+    if (ROPE == kRope3D && !CHECKED) rope3d_lds_fill_begin(rope.r3, tabs);
 #pragma unroll
     for (int s = 0; s < DEPTH; ++s) request(s, s);
-    if (ROPE == kRope3D) {
+    if (ROPE == kRope3D && !CHECKED) {                                   // they are there the second time
         rope3d_lds_fill_end(lds, rope.r3, tabs);
         wg_barrier();
     }
@@ -579,97 +579,94 @@ __global__ __launch_bounds__(kThreads, 2) void apply_f32(
     }
 
     // bf16 results take a row's reciprocal, once per token, in place of quotients (a layer of 128 heads of 32, 4 096 tokens 39.4 -> 36.2 us): the
-    // product's error is far below the result's rounding.  Not where it may be infinite: the quotients themselves.  What decides that, and with it
-    // whether the pieces hold, is looked at before the loop: with eps a normal number and no key sum negative every denominator has a reciprocal, and
-    // such a wave's loop is without checks (layer of 128 heads, 4 096 tokens 33.7 us; with checks in every tile 34.6).
-    bool plain = E != 2 || eps >= 0x1p-126f;
-    if constexpr (E == 2) {
+    // product's error is far below the result's rounding.  Not where it may be infinite: the quotients themselves.
+    float low = 1.f;                                                    // smallest denominator met
+    for (int i0 = 0; i0 < walk.count; i0 += DEPTH) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
+        for (int s = 0; s < DEPTH; ++s) {
+            const int i = i0 + s;
+            if (i >= walk.count) break;
+            __builtin_amdgcn_sched_barrier(0);
+            float qf[NJ][4], den = 0.f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) plain = plain && zr[j][q] >= 0.f;
-        plain = __all(plain) && (whole || !kPieces);
-    }
-    auto tokens = [&](auto checked) __attribute__((always_inline)) {
-        for (int i0 = 0; i0 < walk.count; i0 += DEPTH) {
-#pragma unroll
-            for (int s = 0; s < DEPTH; ++s) {
-                const int i = i0 + s;
-                if (i >= walk.count) break;
-                __builtin_amdgcn_sched_barrier(0);
-                float qf[NJ][4], den = 0.f;
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    if constexpr (E == 2) {
-                        const Words<2> half = {{qw[s][0].w[2 * j], qw[s][0].w[2 * j + 1]}};
-                        widen<T, 4>(half, qf[j]);
-                    } else {
-                        widen<T, 4>(qw[s][j], qf[j]);
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        qf[j][q] = fmaxf(qf[j][q], 0.f);
-                        den = fmaf(qf[j][q], zr[j][q], den);                // the denominator takes the plain features
-                    }
+            for (int j = 0; j < NJ; ++j) {
+                if constexpr (E == 2) {
+                    const Words<2> half = {{qw[s][0].w[2 * j], qw[s][0].w[2 * j + 1]}};
+                    widen<T, 4>(half, qf[j]);
+                } else {
+                    widen<T, 4>(qw[s][j], qf[j]);
                 }
-                if constexpr (ROPE == kRopeTable) {
 #pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        const f32x2 cs[2] = {{__uint_as_float(tw[s][j].w[0]), __uint_as_float(tw[s][j].w[1])},
-                                             {__uint_as_float(tw[s][j].w[2]), __uint_as_float(tw[s][j].w[3])}};
-                        rotate_pairs<4>(qf[j], cs);
-                    }
-                } else if constexpr (ROPE == kRope3D) {
-                    const GridPos pos(rope.r3, walk.token<TILE>(i) + tok, inv_rc, inv_cols);
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) {
-                        const f32x2 cs[2] = {rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2),
-                                             rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2 + 1)};
-                        rotate_pairs<4>(qf[j], cs);
-                    }
-                }
-                request(s, i + DEPTH);
-                __builtin_amdgcn_sched_barrier(0);
-                den += __shfl_xor(den, 16);
-                den += __shfl_xor(den, 32);                                 // that of MFMA row n, in all its lanes
-                const float dn = den + eps;
-                const bool reciprocal = E == 2 && (!checked() || __all(fabsf(dn) >= 0x1p-126f));
-                const float scale = reciprocal ? 1.0f / dn : dn;
-                f32x4 acc[NB] = {};
-                if (kPieces && (!checked() || whole)) {
-                    const u32x4 w = {pack_bf16x2(qf[0][0], qf[0][1]), pack_bf16x2(qf[0][2], qf[0][3]), pack_bf16x2(qf[1][0], qf[1][1]), pack_bf16x2(qf[1][2], qf[1][3])};
-#pragma unroll
-                    for (int l = 2; l >= 0; --l)                            // small terms first
-#pragma unroll
-                        for (int e = 0; e < NB; ++e)
-                            acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), piece[l][e], acc[e], 0, 0, 0);
-                } else
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int e = 0; e < NB; ++e)
-                            acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[j][q], sr[j][q][e], acc[e], 0, 0, 0);
-                // element r of block e: MFMA row 4 g + r, token 4 r + g, feature f_out + e
-                const uint32_t out = exists ? walk.offset<TILE>(i, row_bytes) + offO : kOutOfRange;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float dd = __shfl(scale, 4 * g + r);
-                    float o[NB];
-                    if (reciprocal)
-#pragma unroll
-                        for (int e = 0; e < NB; ++e) o[e] = acc[e][r] * dd;
-                    else
-#pragma unroll
-                        for (int e = 0; e < NB; ++e) o[e] = acc[e][r] / dd;
-                    store_words(rO, out + (uint32_t)(4 * r) * row_bytes, narrow<T, NB>(o));
+                for (int q = 0; q < 4; ++q) {
+                    qf[j][q] = fmaxf(qf[j][q], 0.f);
+                    den = fmaf(qf[j][q], zr[j][q], den);                // the denominator takes the plain features
                 }
             }
+            if constexpr (ROPE == kRopeTable) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    const f32x2 cs[2] = {{__uint_as_float(tw[s][j].w[0]), __uint_as_float(tw[s][j].w[1])},
+                                         {__uint_as_float(tw[s][j].w[2]), __uint_as_float(tw[s][j].w[3])}};
+                    rotate_pairs<4>(qf[j], cs);
+                }
+            } else if constexpr (ROPE == kRope3D) {
+                const GridPos pos(rope.r3, walk.token<TILE>(i) + tok, inv_rc, inv_cols);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    const f32x2 cs[2] = {rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2),
+                                         rope3d_entry_lds(lds, rope.r3, pos, P::template feature<T>(j, g) / 2 + 1)};
+                    rotate_pairs<4>(qf[j], cs);
+                }
+            }
+            request(s, i + DEPTH);
+            __builtin_amdgcn_sched_barrier(0);
+            den += __shfl_xor(den, 16);
+            den += __shfl_xor(den, 32);                                 // that of MFMA row n, in all its lanes
+            const float dn = den + eps;
+            const bool reciprocal = E == 2 && (!CHECKED || __all(fabsf(dn) >= 0x1p-126f));
+            const float scale = reciprocal ? 1.0f / dn : dn;
+            if (E == 2 && !CHECKED) low = fminf(low, fabsf(dn));
+            f32x4 acc[NB] = {};
+            if (kPieces && (!CHECKED || whole)) {
+                const u32x4 w = {pack_bf16x2(qf[0][0], qf[0][1]), pack_bf16x2(qf[0][2], qf[0][3]), pack_bf16x2(qf[1][0], qf[1][1]), pack_bf16x2(qf[1][2], qf[1][3])};
+#pragma unroll
+                for (int l = 2; l >= 0; --l)                            // small terms first
+#pragma unroll
+                    for (int e = 0; e < NB; ++e)
+                        acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), piece[l][e], acc[e], 0, 0, 0);
+            } else
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int e = 0; e < NB; ++e)
+                        acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(qf[j][q], sr[j][q][e], acc[e], 0, 0, 0);
+            // element r of block e: MFMA row 4 g + r, token 4 r + g, feature f_out + e
+            const uint32_t out = exists ? walk.offset<TILE>(i, row_bytes) + offO : kOutOfRange;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float dd = __shfl(scale, 4 * g + r);
+                float o[NB];
+#pragma unroll
+                for (int e = 0; e < NB; ++e) o[e] = reciprocal ? acc[e][r] * dd : acc[e][r] / dd;
+                store_words(rO, out + (uint32_t)(4 * r) * row_bytes, narrow<T, NB>(o));
+            }
         }
-    };
-    if (plain) tokens(std::false_type{});
-    else if constexpr (E == 2) tokens(std::true_type{});
+    }
+    return E != 2 || CHECKED || (__all(low >= 0x1p-126f) && (whole || !kPieces));
+}
+
+// grid = (C, B*H), block = 256; dynamic LDS: kRope3dLdsBytes with kRope3D.
+template <typename T, int D, int ROPE>
+__global__ __launch_bounds__(kThreads, 2) void apply_f32(
+    const T *__restrict__ Q, T *__restrict__ O, RopeArg rope, TokStrides st, int H, int t0, int t1, int C,
+    const float *__restrict__ S, const float *__restrict__ z, float eps, int order)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const bool done = apply_f32_tiles<T, D, ROPE, false>(lds, Q, O, rope, st, H, t0, t1, C, S, z, eps, order);
+    if constexpr (sizeof(T) == 2)
+        if (__builtin_expect(!done, 0)) apply_f32_tiles<T, D, ROPE, true>(lds, Q, O, rope, st, H, t0, t1, C, S, z, eps, order);
 }
 
 }  // namespace sv
