@@ -43,17 +43,17 @@ int main()
         if (s != w.state || a != w.apply) return printf("FAIL order BH=%d H=%d d=%d e=%d n=%d: %d %d\n", w.t.BH, w.t.H, w.t.d, w.t.elem_bytes, w.n, s, a), 1;
         ++cases;
     }
-    // fp32 states of d = 112 and 128: no running sum of a head's only workgroup is longer than it is where several workgroups share
-    // the head's tiles of 16 tokens (three sums per wave, a quadrant of the state to each of four waves)
-    auto longest = [](int n, int C) {
-        const int tiles = (n + 15) / 16, share = (tiles + C - 1) / C;
-        return 16 * ((share + 2) / 3);
+    // fp32 states of d = 112 and 128: no running sum of a head's only workgroup takes more than 16 tokens (tiles of 8 tokens dealt to two groups of four
+    // waves, a quadrant of the state to each; two sums per wave, taken in turn)
+    auto longest = [](int n) {
+        const int tiles = (n + 7) / 8, share = (tiles + 1) / 2;
+        return 8 * ((share + 1) / 2);
     };
     for (int d : {112, 128})
         for (int BH = 1; BH <= 300; ++BH)
             for (int n = 1; n <= 400; ++n) {
                 if (n > sv::f32_sole_tokens(d, BH, 4, false) && n > sv::f32_sole_tokens(d, BH, 4, true)) continue;
-                if (longest(n, 1) > longest(n, sv::plan_chunks(BH, n, 16, 256))) return printf("FAIL sole d=%d BH=%d n=%d\n", d, BH, n), 1;
+                if (longest(n) > 16) return printf("FAIL sole d=%d BH=%d n=%d\n", d, BH, n), 1;
                 ++cases;
             }
     // d = 32 and 64: layers on one workgroup per head and on several, one's time less the other's (0.1 us, the slower of two devices where both
@@ -67,6 +67,14 @@ int main()
         {64, 8, 4, false, 192, -7}, {64, 2, 4, false, 320, 6}, {64, 16, 4, true, 256, 18}, {64, 64, 4, true, 192, -9}};
     for (const Layer &l : layers) {
         if ((l.n <= sv::f32_sole_tokens(l.d, l.BH, l.bytes, l.rotated)) != (l.tenths < 0)) return printf("FAIL line d=%d BH=%d n=%d\n", l.d, l.BH, l.n), 1;
+        ++cases;
+    }
+    // ... of the heads that several workgroups share, layers with their partial states added up by a launch and by the last workgroup: the rule takes the faster one
+    struct Shared { int d, BH, C; double launch, last; } shared[] = {
+        {32, 128, 2, 33.4, 32.4}, {32, 32, 8, 15.9, 15.4}, {32, 16, 16, 12.4, 12.3}, {32, 2, 32, 10.5, 11.3}, {64, 1, 4, 13.9, 14.7}, {64, 8, 4, 14.2, 14.8}, {64, 32, 4, 16.0, 16.2},
+        {64, 48, 4, 16.6, 16.4}, {64, 64, 4, 38.9, 37.8}, {64, 128, 2, 63.3, 61.1}, {64, 32, 8, 18.0, 19.5}, {112, 64, 4, 0, 1}, {128, 128, 2, 0, 1}};
+    for (const Shared &l : shared) {
+        if (sv::f32_last_folds(l.d, l.C, l.BH) != (l.last < l.launch)) return printf("FAIL fold d=%d BH=%d C=%d\n", l.d, l.BH, l.C), 1;
         ++cases;
     }
     printf("OK %ld\n", cases);
