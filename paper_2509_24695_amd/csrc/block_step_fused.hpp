@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void block_step_mfma(
             rope3d_lds_fill_end(lds + block_step_lds_bytes<TILE, WAVES, ROPE>(), rope.r3, tabs);
             wg_barrier();
         }
-        state_accumulate(kvstream, tileK, tileK + kTileBytes, lane, acc);
+        state_accumulate<true>(kvstream, tileK, tileK + kTileBytes, lane, acc);
         state_wg_reduce_store<WAVES, ROPE != kRopeNone, LOCAL>(acc, reinterpret_cast<float *>(lds), wave, lane,
                                            partials + (size_t)share * elems,    // slot = share: the fold adds the shares in tile order
                                            FEW && C == 1, hs);

@@ -234,10 +234,12 @@ __device__ __forceinline__ void state_prefetch(StateStream<TILE, DEPTH, ROPE> &s
 }
 
 // Accumulates the wave's share, whose first DEPTH tiles state_prefetch has
-// requested and whose rotation is at the first one (begin_tile: while the tables and tiles are on their way).  Tiles are taken DEPTH at a time; in the last round the stages past
+// requested.  AHEAD: the rotation is at the first one (begin_tile: while the tables and tiles are on their way), and each tile's positions are worked out while
+// the one before is multiplied: block steps, stream of four blocks of 10 800 tokens 163.9 -> 163.0 us.  Layers gain nothing, and the smallest lose 0.15 us of
+// 6.4 to the positions past the share.  Tiles are taken DEPTH at a time; in the last round the stages past
 // the share hold zeros, as do tokens past t1, and add nothing to either sum.
 // `tileK`/`tileV` are this wave's private LDS tiles.
-template <int TILE, int DEPTH, int ROPE>
+template <bool AHEAD, int TILE, int DEPTH, int ROPE>
 __device__ __forceinline__ void state_accumulate(StateStream<TILE, DEPTH, ROPE> &st, unsigned char *tileK,
                                                  unsigned char *tileV, int lane, StateAcc &acc)
 {
@@ -251,6 +253,7 @@ __device__ __forceinline__ void state_accumulate(StateStream<TILE, DEPTH, ROPE> 
             // waited for) before this stage has been refilled
             __builtin_amdgcn_sched_barrier(0);
             // phi(K) on the packed pairs
+            if (!AHEAD) st.rot.template begin_tile<TILE>(st.walk, i0 + s);
             // the table lookups of the tile go out first; ReLU and key sums fill their latency
             f32x2 cs[TILE / 8][4];
 #pragma unroll
@@ -276,7 +279,7 @@ __device__ __forceinline__ void state_accumulate(StateStream<TILE, DEPTH, ROPE> 
                 *reinterpret_cast<u32x4 *>(tileV + wr_off + 8 * i * kRowBytes) = st.v[s][i];
             }
             st.request(s, i0 + s + DEPTH);   // refill this stage: DEPTH tiles ahead
-            st.rot.template begin_tile<TILE>(st.walk, i0 + s + 1);
+            if (AHEAD) st.rot.template begin_tile<TILE>(st.walk, i0 + s + 1);
             __builtin_amdgcn_sched_barrier(0);
             wave_lds_fence();
 #pragma unroll
@@ -596,12 +599,11 @@ __global__ __launch_bounds__(64 * WAVES, 1) void state_mfma_d64(
     Rope3dFill tabs;
     if (is_rope3d(ROPE)) rope3d_lds_fill_begin(rope.r3, tabs);   // the first loads of the kernel
     state_prefetch(stream);
-    stream.rot.template begin_tile<TILE>(stream.walk, 0);
     if (is_rope3d(ROPE)) {
         rope3d_lds_fill_end(lds + state_lds_bytes<TILE, WAVES>(), rope.r3, tabs);
         wg_barrier();
     }
-    state_accumulate(stream, tileK, tileK + kTileBytes, lane, acc);
+    state_accumulate<false>(stream, tileK, tileK + kTileBytes, lane, acc);
 
     float *partials = static_cast<float *>(ws) + (size_t)bh * kMaxChunks * kStateElems;
     const HeadState hs{S_in ? S_in + (size_t)bh * 64 * 64 : nullptr, z_in + (size_t)bh * 64, S_out + (size_t)bh * 64 * 64,
