@@ -200,9 +200,11 @@ inline int f32_sole_tokens(int d, int BH, int elem_bytes, bool rotated)
 // compute unit then reads C partials, which costs what the launch did at 130 KB.  Layers, us, second launch / last workgroup: d = 32
 // (4 KB each), bf16 128 heads, 4 096 tokens, C = 2 34.6 / 33.4, 32 heads, C = 8 16.9 / 16.2, 20 heads, 1 560 tokens, C = 12 11.6 / 11.0; fp32 32 heads, 4 680 tokens 26.5 / 25.9;
 // C = 32 15.5 / 15.8; d = 64 (17 KB), 64 heads, 2 000 tokens, C = 4 39.8 / 38.7, 32 heads, 4 680, C = 8 44.3 / 44.3, 16 heads, 1 560, C = 16 20.1 / 21.5.
-// Up to 32 heads of 64 that are shared at all in so few parts have little more than f32_sole_tokens, and the launch is the shorter end: rotated, 1 head, 240 tokens 13.9 / 14.7,
-// 8, 220 14.2 / 14.8, 32, 256 16.0 / 16.2, 48, 200 16.6 / 16.4.  (d = 32, up to 16 heads: in a captured graph 1 to 3 % longer, from a host that enqueues up to 13 % shorter.)
-inline bool f32_last_folds(int d, int C, int BH) { return d == 32 ? C <= 16 : d == 64 && C <= 4 && BH > 32; }
+// Where few heads share little more than f32_sole_tokens the kernels alone are as long either way or the launch a little shorter, but a host that enqueues call by call is what
+// paces such a layer, and a launch costs it more.  d = 64, rotated, from the host / in a captured graph: 1 head, 240 tokens 16.1 / 13.3 with the launch, 14.9 / 14.1 with the last workgroup, 8, 220
+// 16.0 / 13.7 and 15.2 / 14.4, 20, 200 16.3 / 14.7 and 15.6 / 15.3, 32, 256 17.0 / 16.1 and 16.1 / 16.0; plain, 16, 260 16.0 / 13.1 and 15.3 / 13.1.  (From a faster host 1 head 13.9 and 14.7, 48, 200 16.6
+// and 16.4.  d = 32, up to 16 heads: in a graph 1 to 3 % longer, from the host up to 13 % shorter.)
+inline bool f32_last_folds(int d, int C) { return d == 32 ? C <= 16 : d == 64 && C <= 4; }
 
 // d = 112 and 128, block step: one launch (block_step_wide.hpp) or two (a state kernel, the apply kernel).  Streams of three look-ahead passes and a
 // committing one, us per block, two launches / one:

@@ -532,7 +532,7 @@ sv_status enqueue_state(const void *K, const void *V, const Rope &rope, const Sh
             using T = typename KN::T;
             const bool sole = n <= f32_sole_tokens(s.d, s.BH, s.elem_bytes, rope.mode != kRopeNone);
             const int C = sole ? 1 : plan_chunks(s.BH, n, KN::state_wg_tokens, dev.num_cu);
-            const bool folds = C > 1 && f32_last_folds(s.d, C, s.BH);
+            const bool folds = C > 1 && f32_last_folds(s.d, C);
             const unsigned long long tag = folds ? next_epoch() << 6 : 0;
             auto launch = [&](auto how, dim3 grid) {
                 using P = typename KN::template P<how()>;
