@@ -162,7 +162,9 @@ sv_status sv_linattn_state(const void *K, const void *V, const sv_tensor_desc *k
  *     O[b][h][i][:] = phi(Q[b][h][i][:]) S[b][h] / (phi(Q[b][h][i][:]) . z[b][h] + eps)
  * for i in [tok_begin, tok_end); other rows of O are not written.  O has the
  * descriptor's shape, strides and dtype.  A row whose phi(Q) is all zero gives
- * exactly 0 (0 / eps), never NaN, for eps > 0. */
+ * exactly 0 (0 / eps), never NaN, for eps > 0.  SV_BF16 with d >= 64 multiplies by
+ * the fp32 reciprocal of the denominator, here and in the block steps: with eps = 0
+ * and a denominator below 2^-126 a row may be infinite or NaN. */
 sv_status sv_linattn_apply(const void *Q, const sv_tensor_desc *q,
                            int32_t tok_begin, int32_t tok_end,
                            const float *S, const float *z, float eps,
