@@ -216,7 +216,8 @@ inline bool f32_last_folds(int d, int C) { return d == 32 ? C <= 16 : d == 64 &&
 //   per head        15 600 266 / 271.  (Of 112 and with factored tables the line could lie further out: 128 heads, 4 680 111 / 98, factored 119 / 112, 7 800
 //                   196 / 175; 87 heads, factored, 7 800 154 / 149, 9 360 163 / 168.)
 //   full table      20 heads, 4 680 38.6 / 35.9, 9 360 53 / 52; 64 heads, 3 000 55 / 53; 100 heads of 128, 2 048 69 / 66; few heads of 128, all spread: 8, 4 680
-//                   26.4 / 30.0, 6 240 28.9 / 32.6, 7 800 33.0 / 32.9, 10, 3 120 24.7 / 27.5, 15, 3 120 27.6 / 29.0, 4 680 39.0 / 35.2
+//                   26.4 / 30.0, 6 240 28.9 / 32.6, 7 800 33.0 / 32.9, 10, 3 120 24.7 / 27.5, 15, 3 120 27.6 / 29.0, 4 680 39.0 / 35.2; 16, 2 070 25.5 / 27.5, 3 120 30.3 / 31.7, 3 780 33.9 / 32.5; 18, 2 756
+//                   30.4 / 31.9, 3 120 33.2 / 32.5; 20, 2 340 28.6 / 30.6, 2 756 32.5 / 31.1; 22, 2 070 32.9 / 28.3
 //   shared lines    plain 20 heads, 4 680 36 / 34, 7 800 45.5 / 45.8, 9 360 52 / 53, 40 heads, 3 120 42 / 41, 4 680 52 / 53, 16 heads, 9 360 44.7 / 44.7; factored tables 40 heads,
 //                   4 680 58 / 56, 20 heads, 9 360 58 / 56
 //   few heads       a head on all dies.  Of 112: 5 heads, 2 028 tokens 19.7 / 18.0, 6, 1 560 18.1 / 17.9, 2 028 18.4 / 18.7, 7, 1 560 18.2 / 19.0, factored tables 20.8 / 21.1, full
@@ -242,7 +243,7 @@ inline bool wide_step_serves(const TokenLayout &t, int n_tokens, int C, bool ful
             if (t.d == 112) return n_tokens <= 2048 && (full_table || t.shares_lines() || head_tokens <= 10240);
             return n_tokens <= 2048 && head_tokens <= (plain ? 5200 : factored_tables ? 8192 : 10240);
         }
-        if (full_table && t.d == 128 && t.BH < 16 && n_tokens > 2048 && n_tokens < 7000) return false;
+        if (full_table && t.d == 128 && n_tokens > 2048 && (t.BH < 16 ? n_tokens < 7000 : t.BH <= 20 && head_tokens < 54000)) return false;
         if (full_table || t.shares_lines()) return head_tokens <= (plain ? 150000 : 200000);
         if (plain && t.d == 128 && t.BH > 8 && t.BH < 16 && n_tokens > 1250 && n_tokens < 5000) return false;
         if (C == 2 && (t.d == 112 || factored_tables)) return n_tokens <= 3072;

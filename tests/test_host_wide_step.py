@@ -67,7 +67,8 @@ def test_lines_end_where_two_launches_were_measured_ahead(exe):
                                      (128, "none", 84, 23400, 32760), (112, "none", 20, 75600, 131040), (112, "none", 7, 1040, 1560), (112, "axes", 7, 1040, 2028),
                                      (112, "table", 7, 2028, 4680), (128, "none", 3, 1560, 2028), (128, "none", 5, 1040, 1560), (128, "axes", 5, 1560, 2028),
                                      (128, "table", 7, 1040, 1560), (128, "none", 13, 1040, 1560), (128, "none", 10, 6240, 3120), (128, "none", 16, 3120, 500000),
-                                     (128, "table", 8, 1560, 4680), (128, "table", 10, 9360, 3120), (128, "axes", 13, 3120, 200000)):
+                                     (128, "table", 8, 1560, 4680), (128, "table", 10, 9360, 3120), (128, "table", 16, 3780, 2070), (128, "table", 17, 3780, 3120), (128, "table", 18, 3120, 2756),
+                                     (128, "table", 20, 2756, 2340), (128, "table", 20, 1560, 2070), (128, "table", 22, 2070, 20000), (128, "axes", 13, 3120, 200000)):
         calls[(d, 1, BH, serves, rope, "bhnd")], calls[(d, 1, BH, two, rope, "bhnd")] = 1, 0
     for H, n, serves in ((20, 4680, 1), (20, 9360, 0), (40, 3120, 1), (40, 4680, 0), (7, 2028, 1)):
         calls[(112, 1, H, n, "none", "bnhd")] = serves
